@@ -347,6 +347,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void k_gemm_mfma(const f16_t* __restr
 #define TD_KC 32
 #define TG_THREADS 512
 #define TG_WROWS 256
+#define TG_PANEL 4          // row blocks a compute die walks per W tile, see the mapping in the kernel
 
 
 // XT: 16-row X tiles per workgroup (8..18).  The two wave rows split them as evenly as whole tiles
@@ -372,10 +373,16 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
     const int k_begin = blockIdx.y * Ks;              // multiple of 128
     const int k_end = min(K, k_begin + Ks);
     const int nchunks = (k_end - k_begin) / TD_KC;    // multiple of 4
-    const int grp = blockIdx.x / (8 * RB), rem = blockIdx.x % (8 * RB);
-    const int w_tile = grp * 8 + (rem & 7);
+    // Workgroup -> (W tile, X row block): XCD x (workgroup ids x, x + 8, ...) owns W tiles x, x + 8, ...
+    // and walks them in panels of TG_PANEL row blocks, all row blocks of a panel per W tile before the
+    // next tile, so that its 32 compute units share few W tiles and few row blocks at any time.
+    // 4095 rows x 4096 (q/k/v, 20 row blocks): 184 -> 169 us against one panel of all row blocks.
+    const int per_xcd = (int)gridDim.x / (8 * RB), seq = (int)blockIdx.x >> 3;
+    const int panel = seq / (TG_PANEL * per_xcd), in_panel = seq - panel * TG_PANEL * per_xcd;
+    const int panel_rows = min(TG_PANEL, RB - panel * TG_PANEL);
+    const int w_tile = in_panel / panel_rows * 8 + ((int)blockIdx.x & 7);
     if (w_tile * TG_WROWS >= N) return;
-    const int r_base = (rem >> 3) * 16 * XT;
+    const int r_base = (panel * TG_PANEL + in_panel % panel_rows) * 16 * XT;
     const int n_tiles = N >> 4;
     const int64_t chunk_stride = (int64_t)n_tiles * 4 * 512;
 
@@ -692,6 +699,35 @@ int cs_tile_x_launch(const void* src, void* dst, int R, int K, hipStream_t s) {
     return cs_launch_ok("k_tile_x");
 }
 
+// Row blocks and K splits of a many-row GEMM: the pair with the least estimated time.  A workgroup
+// with rt X tiles takes 4.5 us * (6.7 + rt) per 4096 of K on a full chip (fitted to q/k/v, o, gate/up
+// and down at 300, 528, 1023 and 4095 rows: the requests and the barrier of a chunk cost what 6.7
+// tiles cost to multiply, so a tile shorter by a ninth pays only where it does not add a round of the
+// chip); a round that fills a part f of the chip takes 0.65 + 0.35 f of a full one (less contention);
+// every partial tile is written and read once more at about 4.9 TB/s.
+// 4095 rows, 8B width, against the fewest row blocks (15 x 288 rows): gate/up 771 -> 695 us,
+// q/k/v 209 -> 169, o 113 -> 104, down 368 -> 339 us; 528 rows: o 31 -> 27 us with half the partial tiles.
+static void tile_plan(int R, int N, int K, bool may_split, int* r_blocks, int* ksplit) {
+    const int rt_total = (int)cs_ceil_div(R, 16);
+    const int per_xcd = (int)cs_ceil_div(cs_ceil_div(N, TG_WROWS), 8);   // W tiles of one die
+    const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
+    const int rb_min = (int)cs_ceil_div(rt_total, 18), rb_max = (int)cs_ceil_div(rt_total, 8);
+    double best = 0.;
+    for (int rb = rb_min; rb <= rb_max; ++rb) {
+        const int rt = (int)cs_ceil_div(rt_total, rb) < 8 ? 8 : (int)cs_ceil_div(rt_total, rb);
+        for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2) {
+            const int wgs = per_xcd * (int)cs_ceil_div(rt_total, rt) * ks;   // on 32 compute units
+            const double part = (wgs % 32) / 32., rounds = wgs / 32 + (part > 0. ? 0.65 + 0.35 * part : 0.);
+            const double us = rounds * 4.5 * (6.7 + rt) * K / ks / 4096. + (may_split ? ks * 8e-6 * R * N / 4.9 : 0.);
+            if ((rb == rb_min && ks == 1) || us < best) {
+                best = us;
+                *r_blocks = rb;
+                *ksplit = ks;
+            }
+        }
+    }
+}
+
 int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, int R, int N, int K,
                    int mode, int allow_split, int* nparts_out, hipStream_t s) {
     if (nparts_out) *nparts_out = 1;
@@ -730,10 +766,11 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     }
     if (mode == CS_GEMM_SWIGLU) Y = reinterpret_cast<float*>(m->range_flags);   // see the epilogue
     const int rt_total = (int)cs_ceil_div(R, 16);
-    const int r_blocks = tile ? (int)cs_ceil_div(rt_total, 18) : (int)cs_ceil_div(rt_total, 6);
-    int ksplit = 1;
-    if (allow_split && mode == CS_GEMM_STORE) {
-        const int n_tiles = (int)cs_ceil_div(N, tile ? TG_WROWS : 128);
+    int r_blocks = (int)cs_ceil_div(rt_total, 6), ksplit = 1;
+    if (tile) {
+        tile_plan(R, N, K, allow_split && mode == CS_GEMM_STORE, &r_blocks, &ksplit);
+    } else if (allow_split && mode == CS_GEMM_STORE) {
+        const int n_tiles = (int)cs_ceil_div(N, 128);
         const int max_split = K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
         while (n_tiles * r_blocks * ksplit < 192 && ksplit * 2 <= max_split) ksplit *= 2;
     }

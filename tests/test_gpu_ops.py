@@ -103,6 +103,14 @@ def test_gemm_row_sweep(host_model, N, K, R):
     _gemm_case(host_model, N, K, R)
 
 
+@pytest.mark.parametrize("N,K,R", [(4112, 512, 1023), (4112, 512, 1300), (6144, 4096, 1300), (4096, 4096, 2064),
+                                   (2048, 8192, 4095), (4096, 1024, 4095)])
+def test_gemm_prompt_rows(host_model, N, K, R):
+    """Prompt-sized row counts: more row blocks than one panel of the workgroup mapping holds, a last
+    panel of fewer, a W tile count that is no multiple of the eight dies, with and without K splits."""
+    _gemm_case(host_model, N, K, R)
+
+
 def test_gemm_tiny_weights_are_not_flushed(host_model):
     """The tuned projections multiply in float16 (weights converted from bfloat16, exactly for
     |w| >= 2^-17).  Weights in float16's subnormal range must still contribute."""
