@@ -8,7 +8,7 @@
 // 8 TB/s, which is why QK^T and PV run on the matrix cores although the kernel is graded
 // against the HBM roofline.
 //
-// Tuned kernel, per wave (no LDS, everything stays in registers):
+// Tuned kernel, per wave (K, V, scores and O stay in registers):
 //   S^T[token][qrow] = K[token][:] . Q[qrow][:]        v_mfma_f32_16x16x32_bf16, A = K rows
 //   O^T[hd][qrow]   += V^T[hd][token] * P^T[token][qrow]                         A = V^T rows
 // K rows are fed in a permuted token order chosen so that the S^T accumulator layout of two
@@ -127,6 +127,7 @@ __device__ __forceinline__ float fa_row4_max(float x) {
 #define FA_QROWS (16 * FA_NT)
 #define FA_RESCALE_LOG2 8.0f
 #define FA_OPAD 4          // LDS row padding (floats) of the in-workgroup merge buffers
+#define FA_BUFFER_WORD3 0x00027000   // buffer resource word 3: raw 32-bit data, range checked in bytes
 
 // attention output element: float16 outputs feed the output projection and are saturated
 __device__ __forceinline__ void fa_store_out(f16_t* p, int64_t i, float v, bool& hit) { p[i] = cs_f16_sat(v, hit); }
@@ -156,34 +157,39 @@ struct fa_fused_rope {
     const float* bias;       // [(H + 2*KVH) * HD] biases of the q, k, v projections, or NULL
 };
 
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
-                                                   const bf16_t* __restrict__ kc,
-                                                   const bf16_t* __restrict__ vc,
+// What bounds it: at long caches the K/V stream (batch 8, 18431 rows, hd 128: 114.7 us = 5.27 TB/s), at
+// short ones a chain of latencies.  A branch around a load makes the compiler's load counts inexact, and
+// every block then waited for the loads issued just before it; so requests never sit behind a branch
+// (buffer loads with an offset outside the buffer instead) and the pipelined loop has no exit in the
+// middle.  Two blocks per trip over two K and two V stages: K of block i + 2 is requested right after the
+// scores of block i, V one block ahead.  Query rows come in NT tiles of 16, the prologue's loads are all
+// requested before the first is used, the masked blocks run in the same loop, and the four waves are
+// merged by all 256 threads (the code shrank from 47 to 18 KB, fetched cold in every launch).
+// Before -> after: batch 8 118.3 -> 114.7 us; one stream, 18431 rows 27.0 -> 22.9, 4095 rows of hd 64
+// 12.5 -> 9.5, one row over 300 tokens 19.7 -> 10.4 us.
+template <int HD, int NT, bool FUSE>
+__global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q, const bf16_t* kc,
+                                                   const bf16_t* vc,
                                                    const int32_t* __restrict__ kv_len, int rows,
-                                                   int H, int KVH, int64_t cap, int Tw, int nqg,
-                                                   int nsplit, float* __restrict__ po,
+                                                   int H, int KVH, int64_t cap, int Tw, int nsplit,
+                                                   float* __restrict__ po,
                                                    float* __restrict__ pml, fa_fused_rope fr) {
     constexpr int KS = HD / 32;      // MFMA k-steps over the head dimension
     constexpr int MT = HD / 16;      // 16-row tiles of O^T
     constexpr int OROW = HD + FA_OPAD;
     constexpr int QROW = HD * 2 + 16;                 // bytes per query row in LDS (padded)
-    constexpr int MERGE_BYTES = 2 * FA_QROWS * OROW * 4 + 2 * FA_QROWS * 2 * 4;
-    constexpr int Q_BYTES = FA_QROWS * QROW;
+    constexpr int ROWS = 16 * NT;                     // query rows of the workgroup: all of the KV head's
+    constexpr int MERGE_BYTES = 4 * ROWS * OROW * 4 + 4 * ROWS * 2 * 4;
+    constexpr int Q_BYTES = ROWS * QROW;
     // the query tile (read during the main loop) and the merge buffers (used after it)
     // share the same LDS
     __shared__ __attribute__((aligned(16))) unsigned char smem[MERGE_BYTES > Q_BYTES ? MERGE_BYTES : Q_BYTES];
-    float* s_o = reinterpret_cast<float*>(smem);                          // [2][FA_QROWS*OROW]
-    float* s_ml = reinterpret_cast<float*>(smem) + 2 * FA_QROWS * OROW;   // [2][FA_QROWS*2]
     const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane & 15, g = lane >> 4;
-    const int qg = blockIdx.x % nqg;
-    const int split = blockIdx.x / nqg;
-    const int wg = split * 4 + wave;                    // wave index along the token axis
-    const int kvh = blockIdx.y, b = blockIdx.z;
+    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
     const int G = H / KVH;
-    const int QR = G * rows;
+    const int QR = G * rows;                            // <= ROWS
     const int L = kv_len[b];
     const int n_tok = L + rows;
     // The workgroup's token range is 4*Tw long; its four waves take the 32-token blocks of it in
@@ -195,149 +201,223 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
     const int t_begin = w_begin + 32 * wave;            // may lie past t_end: no blocks then
     // blocks that lie completely inside the old cache need neither mask nor clean-up
     const int t_split = max(w_begin, min(t_end, (L / 32) * 32));
-    // first block of this wave at or beyond t_split
-    const int t_tail = t_begin >= t_split ? t_begin : t_begin + (t_split - t_begin + STEP - 1) / STEP * STEP;
-    (void)wg;
-    const bf16_t* __restrict__ K = kc + ((int64_t)b * KVH + kvh) * cap * HD;
-    const bf16_t* __restrict__ V = vc + ((int64_t)b * KVH + kvh) * HD * cap;
+    // this wave's blocks: n_open of those, then the masked ones, n_all in total
+    const int n_open = t_begin < t_split ? (t_split - t_begin + STEP - 1) / STEP : 0;
+    const int n_all = t_begin < t_end ? (t_end - t_begin + STEP - 1) / STEP : 0;
+    // Every workgroup starts at a different one of its unmasked blocks (and wraps): the workgroups of
+    // a launch run in step, and with all of them at the same relative position some cache pitches put
+    // them on the same memory channels
+    const int wg_id = (b * KVH + kvh) * nsplit + split;
+    const int n_wg = w_begin < t_split ? (t_split - w_begin + STEP - 1) / STEP : 0;       // wave 0's count
+    const int rot_wg = n_wg > 0 ? (int)(((int64_t)wg_id * 2654435761LL >> 8) % n_wg) : 0;
+    const int rot = n_open > 0 ? min(rot_wg, n_open - 1) : 0;     // the same round for all four waves
+    auto at = [&](int i) {
+        int j = i < n_open ? i + rot : i;
+        j = i < n_open && j >= n_open ? j - n_open : j;
+        return t_begin + j * STEP;
+    };
+    // K and V come through buffer loads based at the workgroup's range: a block past the wave's last has an
+    // offset outside the buffer, which costs no memory traffic and, unlike a branch around the loads, leaves
+    // the compiler's load counts exact (with branches every block waited for the loads just issued).
+    // With the fused append the rows at and beyond L are written by this workgroup, below, and the masked
+    // blocks are requested only after the barrier that follows.
+    const int64_t head0 = (int64_t)b * KVH + kvh;
+    const int n_range = (t_end - w_begin + 31) & ~31;          // a masked block may reach past t_end, into dead rows
+    const auto krsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((FUSE ? fr.kc_w : kc) + (head0 * cap + w_begin) * HD), 0, n_range * HD * 2, FA_BUFFER_WORD3);
+    const auto vrsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)((FUSE ? fr.vc_w : vc) + head0 * HD * cap + cs_v_index(w_begin, 0, HD)), 0,
+        ((n_range + CS_VBLK - 1) / CS_VBLK) * CS_VBLK * HD * 2, FA_BUFFER_WORD3);
+    constexpr unsigned NOWHERE = 0x80000000u;
+    // K tile a, MFMA row m=c  <->  token t0 + 8*(c/4) + 4a + c%4
+    const unsigned klane = ((8 * (c >> 2) + (c & 3)) * HD + g * 8) * 2;
+    auto ldk = [&](fa_kbuf<HD>& buf, int i, int n) {
+        // the four lanes of a token row read 64 contiguous bytes per k-step
+        const unsigned off = i < n ? (unsigned)(at(i) - w_begin) * (HD * 2) + klane : NOWHERE;
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+                buf.k[a][s] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(krsrc, off + a * 4 * HD * 2 + s * 64, 0, 0));
+    };
+    const unsigned vlane = c * (CS_VBLK * 2) + g * 16;
+    auto ldv = [&](fa_vbuf<HD>& buf, int i, int n) {
+        const int t = at(i) - w_begin;
+        const unsigned off = i < n ? (unsigned)((t >> 7) * HD * CS_VBLK + (t & (CS_VBLK - 1))) * 2 + vlane : NOWHERE;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            buf.v[mt] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(vrsrc, off, mt * 16 * CS_VBLK * 2, 0));
+    };
+    fa_kbuf<HD> k0, k1;
+    fa_vbuf<HD> v0, v1;
+    // (the fences keep every request where it is written: a wait counts what was requested after it)
+    auto first_blocks = [&](int n) {
+        __builtin_amdgcn_sched_barrier(0);
+        ldk(k0, 0, n);
+        __builtin_amdgcn_sched_barrier(0);
+        ldv(v0, 0, n);
+        __builtin_amdgcn_sched_barrier(0);
+        ldk(k1, 1, n);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the first blocks are requested before the query tile is ready, if they are old rows
+    const int n_early = n_open >= 2 ? n_open : 0;
 
-    // stage the query tile: global qrow n = qg*48 + local row  <->  block row n / G, head n % G
-    if (fr.qkv == nullptr) {
-        for (int idx = tid; idx < FA_QROWS * (HD / 8); idx += 256) {
-            const int row = idx / (HD / 8), seg = idx % (HD / 8);
-            const int n = qg * FA_QROWS + row;
+    // stage the query tile: query row n  <->  block row n / G, head n % G
+    const int inv_g = (65536 + G - 1) / G;              // n / G == n * inv_g >> 16 for n < 48
+    if constexpr (!FUSE) {
+        for (int idx = tid; idx < ROWS * (HD / 8); idx += 256) {
+            const int n = idx / (HD / 8), seg = idx % (HD / 8);
             bf16x8 v = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
             if (n < QR) {
-                const int i = n / G, gq = n % G;
+                const int i = n * inv_g >> 16, gq = n - i * G;
                 v = *reinterpret_cast<const bf16x8*>(
                     q + (((int64_t)(b * rows + i)) * H + kvh * G + gq) * HD + seg * 8);
             }
-            *reinterpret_cast<bf16x8*>(smem + row * QROW + seg * 16) = v;
+            *reinterpret_cast<bf16x8*>(smem + n * QROW + seg * 16) = v;
         }
+        first_blocks(n_early);
     } else {
-        constexpr int HALF = HD / 2, SEGS = HALF / 8;        // 8-element segments per half head
+        constexpr int HALF = HD / 2, SEGS = HALF / 4;        // 4-element segments per half head
         const int nqkv = (H + 2 * KVH) * HD;
-        // elements j0..j0+7 and HALF+j0..HALF+j0+7 of one head of block row r: partial tiles
-        // summed in order, the pair (j, HALF + j) rotated by the row's angle j
-        auto head_pair = [&](int r, int head, int j0, bool rotate, bf16x8& lo, bf16x8& hi) {
-            const float* __restrict__ src = fr.qkv + (int64_t)r * nqkv + (int64_t)head * HD + j0;
-            float a[8], cc[8];
+        // One task: elements j0..j0+3 and HALF+j0..HALF+j0+3 of one head of block row r.  The partial
+        // tiles are summed in order, the pair (j, HALF + j) is rotated by the row's angle j.  All of
+        // this is load latency (a partial tile was written by another die), so the tiles are
+        // requested four at a time before the first is used.
+        struct pair_tiles { f32x4 t[4][2]; };
+        struct pair_angles { f32x4 v[2]; };                  // (cos, sin) of j0, j0+1; j0+2, j0+3
+        auto request = [&](int r, int head, int j0, int p0, pair_tiles& o) {
+            const float* src = fr.qkv + (int64_t)r * nqkv + (int64_t)head * HD + j0;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) a[u] = cc[u] = 0.f;
-            for (int p = 0; p < fr.nparts; ++p) {
-                const float* __restrict__ sp = src + p * fr.part_stride;
-                const f32x4 a0 = *reinterpret_cast<const f32x4*>(sp), a1 = *reinterpret_cast<const f32x4*>(sp + 4);
-                const f32x4 c0 = *reinterpret_cast<const f32x4*>(sp + HALF), c1 = *reinterpret_cast<const f32x4*>(sp + HALF + 4);
+            for (int w = 0; w < 4; ++w) {
+                const float* sp = src + min(p0 + w, fr.nparts - 1) * fr.part_stride;
+                o.t[w][0] = *reinterpret_cast<const f32x4*>(sp);
+                o.t[w][1] = *reinterpret_cast<const f32x4*>(sp + HALF);
+            }
+        };
+        auto angles = [&](int r, int j0, pair_angles& o) {
+            const f32x4* p = reinterpret_cast<const f32x4*>(fr.rope + (int64_t)r * HALF + j0);
+            o.v[0] = p[0];
+            o.v[1] = p[1];
+        };
+        // sum (first four tiles already requested), bias, rotation, rounding
+        auto finish = [&](pair_tiles& t, int r, int head, int j0, bool rotate, const pair_angles& an, bf16x4& lo, bf16x4& hi) {
+            f32x4 x = (f32x4){0.f, 0.f, 0.f, 0.f}, y = x;
+            for (int p0 = 0;;) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    a[u] += a0[u];
-                    a[4 + u] += a1[u];
-                    cc[u] += c0[u];
-                    cc[4 + u] += c1[u];
+                for (int w = 0; w < 4; ++w) {
+                    const bool in = p0 + w < fr.nparts;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        x[u] = in ? x[u] + t.t[w][0][u] : x[u];
+                        y[u] = in ? y[u] + t.t[w][1][u] : y[u];
+                    }
                 }
+                p0 += 4;
+                if (p0 >= fr.nparts) break;
+                request(r, head, j0, p0, t);
             }
             if (fr.bias) {                            // projection bias, before the rotation
                 const float* __restrict__ bp = fr.bias + head * HD + j0;
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    a[u] += bp[u];
-                    cc[u] += bp[HALF + u];
-                }
+                x += *reinterpret_cast<const f32x4*>(bp);
+                y += *reinterpret_cast<const f32x4*>(bp + HALF);
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                float x = a[u], y = cc[u];
-                if (rotate) {
-                    const float2 cs = fr.rope[(int64_t)r * HALF + j0 + u];
-                    const float rx = x * cs.x - y * cs.y;
-                    const float ry = y * cs.x + x * cs.y;
-                    x = rx;
-                    y = ry;
-                }
-                lo[u] = (bf16_t)x;
-                hi[u] = (bf16_t)y;
+            for (int u = 0; u < 4; ++u) {
+                const float co = an.v[u >> 1][2 * (u & 1)], si = an.v[u >> 1][2 * (u & 1) + 1];
+                const float rx = x[u] * co - y[u] * si, ry = y[u] * co + x[u] * si;
+                lo[u] = (bf16_t)(rotate ? rx : x[u]);
+                hi[u] = (bf16_t)(rotate ? ry : y[u]);
             }
         };
-        // first the new rows whose position lies in this workgroup's token range (4*Tw long):
-        // their stores complete while the query tile is being built
-        bf16_t* Kw = fr.kc_w + ((int64_t)b * KVH + kvh) * cap * HD;
-        bf16_t* Vw = fr.vc_w + ((int64_t)b * KVH + kvh) * HD * cap;
-        if (qg == 0) {
-            for (int idx = tid; idx < rows * SEGS; idx += 256) {
-                const int i = idx / SEGS, sg = idx % SEGS;
-                const int pos = L + i;
-                if ((pos / Tw) >> 2 != split) continue;
-                bf16x8 lo, hi;
-                head_pair(b * rows + i, H + kvh, sg * 8, true, lo, hi);
-                *reinterpret_cast<bf16x8*>(Kw + (int64_t)pos * HD + sg * 8) = lo;
-                *reinterpret_cast<bf16x8*>(Kw + (int64_t)pos * HD + HALF + sg * 8) = hi;
-                head_pair(b * rows + i, H + KVH + kvh, sg * 8, false, lo, hi);
+        constexpr int QT = (ROWS * SEGS + 255) / 256;         // query tasks of a thread
+        pair_angles ang[QT];
+        pair_tiles qt[QT];
+        auto q_row = [&](int t, int& n, int& i, int& head, int& j0) {      // (clamped past the last row)
+            n = (tid + 256 * t) / SEGS;
+            j0 = tid % SEGS * 4;
+            const int m = min(n, QR - 1);
+            i = m * inv_g >> 16;
+            head = kvh * G + m - i * G;
+        };
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    Vw[cs_v_index(pos, sg * 8 + u, HD)] = lo[u];
-                    Vw[cs_v_index(pos, HALF + sg * 8 + u, HD)] = hi[u];
+        for (int t = 0; t < QT; ++t) {
+            int n, i, head, j0;
+            q_row(t, n, i, head, j0);
+            angles(b * rows + i, j0, ang[t]);
+            request(b * rows + i, head, j0, 0, qt[t]);
+        }
+        first_blocks(n_early);
+        // the new rows whose position lies in this workgroup's token range: key heads of all rows, then
+        // value heads
+        bf16_t* Kw = fr.kc_w + head0 * cap * HD;
+        bf16_t* Vw = fr.vc_w + head0 * HD * cap;
+        if (t_end > L) {
+            for (int idx = tid; idx < 2 * rows * SEGS; idx += 256) {
+                const bool is_v = idx >= rows * SEGS;
+                const int i = idx / SEGS - (is_v ? rows : 0), j0 = idx % SEGS * 4;
+                const int pos = L + i;
+                if (pos < w_begin || pos >= t_end) continue;
+                const int head = H + (is_v ? KVH : 0) + kvh;
+                pair_angles an;
+                pair_tiles t;
+                angles(b * rows + i, j0, an);
+                request(b * rows + i, head, j0, 0, t);
+                bf16x4 lo, hi;
+                finish(t, b * rows + i, head, j0, !is_v, an, lo, hi);
+                if (!is_v) {
+                    *reinterpret_cast<bf16x4*>(Kw + (int64_t)pos * HD + j0) = lo;
+                    *reinterpret_cast<bf16x4*>(Kw + (int64_t)pos * HD + HALF + j0) = hi;
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        Vw[cs_v_index(pos, j0 + u, HD)] = lo[u];
+                        Vw[cs_v_index(pos, HALF + j0 + u, HD)] = hi[u];
+                    }
                 }
             }
         }
-        for (int idx = tid; idx < FA_QROWS * SEGS; idx += 256) {
-            const int row = idx / SEGS, sg = idx % SEGS;
-            const int n = qg * FA_QROWS + row;
-            bf16x8 lo = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0}, hi = lo;
-            if (n < QR) head_pair(b * rows + n / G, kvh * G + n % G, sg * 8, true, lo, hi);
-            *reinterpret_cast<bf16x8*>(smem + row * QROW + sg * 16) = lo;
-            *reinterpret_cast<bf16x8*>(smem + row * QROW + HD + sg * 16) = hi;
+#pragma unroll
+        for (int t = 0; t < QT; ++t) {
+            int n, i, head, j0;
+            q_row(t, n, i, head, j0);
+            if (n >= ROWS) continue;
+            bf16x4 lo, hi;
+            finish(qt[t], b * rows + i, head, j0, true, ang[t], lo, hi);
+            if (n >= QR) lo = hi = (bf16x4){0, 0, 0, 0};
+            *reinterpret_cast<bf16x4*>(smem + n * QROW + j0 * 2) = lo;
+            *reinterpret_cast<bf16x4*>(smem + n * QROW + HD + j0 * 2) = hi;
         }
     }
-    int qi[FA_NT];               // block row index of the lane's query row (for the causal mask)
+    int qi[NT];               // block row index of the lane's query row (for the causal mask)
 #pragma unroll
-    for (int nt = 0; nt < FA_NT; ++nt) {
-        const int n = qg * FA_QROWS + nt * 16 + c;
-        qi[nt] = n < QR ? n / G : -1;
+    for (int nt = 0; nt < NT; ++nt) {
+        const int n = nt * 16 + c;
+        qi[nt] = n < QR ? n * inv_g >> 16 : -1;
     }
     __syncthreads();
 
-    f32x4 oacc[MT][FA_NT], lacc[FA_NT];
+    f32x4 oacc[MT][NT], lacc[NT];
 #pragma unroll
-    for (int nt = 0; nt < FA_NT; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
         lacc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) oacc[mt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
-    float m_run[FA_NT];
+    float m_run[NT];
 #pragma unroll
-    for (int nt = 0; nt < FA_NT; ++nt) m_run[nt] = -INFINITY;
+    for (int nt = 0; nt < NT; ++nt) m_run[nt] = -INFINITY;
 
     const float scale2 = 1.4426950408889634f / sqrtf((float)HD);
     const bf16_t one = (bf16_t)1.0f;
     const bf16x8 ones = (bf16x8){one, one, one, one, one, one, one, one};
 
-    // K tile a, MFMA row m=c  <->  token t0 + 8*(c/4) + 4a + c%4
-    const int ktok0 = 8 * (c >> 2) + (c & 3);
-    auto load_k_from = [&](const bf16_t* Kb, fa_kbuf<HD>& buf, int t0, int limit) {
-        if (t0 >= limit) return;
-#pragma unroll
-        for (int a = 0; a < 2; ++a) {
-            // the four lanes of a token row read 64 contiguous bytes per k-step
-            const bf16_t* kp = Kb + (int64_t)(t0 + ktok0 + 4 * a) * HD + g * 8;
-#pragma unroll
-            for (int s = 0; s < KS; ++s) buf.k[a][s] = *reinterpret_cast<const bf16x8*>(kp + s * 32);
-        }
-    };
-    auto load_v_from = [&](const bf16_t* Vb, fa_vbuf<HD>& buf, int t0, int limit) {
-        if (t0 >= limit) return;
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-            buf.v[mt] = *reinterpret_cast<const bf16x8*>(Vb + cs_v_index(t0 + 8 * g, mt * 16 + c, HD));
-    };
-    auto load_k = [&](fa_kbuf<HD>& buf, int t0, int limit) { load_k_from(K, buf, t0, limit); };
-    auto load_v = [&](fa_vbuf<HD>& buf, int t0, int limit) { load_v_from(V, buf, t0, limit); };
-
-    auto compute = [&](fa_kbuf<HD>& kb, fa_vbuf<HD>& vb, int t0, auto tail_tag) {
-        constexpr bool TAIL = decltype(tail_tag)::value;
+    // block i (its K in kb, its V in vb); K of block i + 2 replaces it in kb as soon as the scores are out
+    auto block = [&](fa_kbuf<HD>& kb, fa_vbuf<HD>& vb, int i, auto ahead) {
         // scores: lane (c, g) gets tokens t0 + 8g + (4a + j) of query row nt*16 + c
-        f32x4 sacc[2][FA_NT];
+        f32x4 sacc[2][NT];
 #pragma unroll
-        for (int nt = 0; nt < FA_NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             f32x4 z0 = (f32x4){0.f, 0.f, 0.f, 0.f}, z1 = z0;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
@@ -349,28 +429,39 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
             sacc[0][nt] = z0;
             sacc[1][nt] = z1;
         }
-        if (TAIL) {
-            // dead cache rows may hold anything: zero their V so that 0 * garbage stays 0
+        if constexpr (decltype(ahead)::value) {
+            __builtin_amdgcn_sched_barrier(0);
+            ldk(kb, i + 2, n_all);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (i >= n_open) {
+            // a block with new rows or dead ones.  Dead cache rows may hold anything: their V is zeroed
+            // so that 0 * garbage stays 0
+            const int t0 = at(i);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int j = 0; j < 8; ++j) {
+                const bool dead = t0 + 8 * g + j >= n_tok;
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (t0 + 8 * g + j >= n_tok) vb.v[mt][j] = (bf16_t)0.f;
+                for (int mt = 0; mt < MT; ++mt) vb.v[mt][j] = dead ? (bf16_t)0.f : vb.v[mt][j];
+            }
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        sacc[a][nt][j] = t0 + 8 * g + 4 * a + j > L + qi[nt] ? -INFINITY : sacc[a][nt][j];
         }
         bool moved = false;
-        float alpha[FA_NT];
-        bf16x8 pb[FA_NT];
+        float alpha[NT];
+        bf16x8 pb[NT];
 #pragma unroll
-        for (int nt = 0; nt < FA_NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             float sv[8];
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    float s = sacc[a][nt][j];
-                    if (TAIL && (t0 + 8 * g + 4 * a + j > L + qi[nt])) s = -INFINITY;
-                    sv[4 * a + j] = s;
-                }
+                for (int j = 0; j < 4; ++j) sv[4 * a + j] = sacc[a][nt][j];
             float mx = fmaxf(fmaxf(sv[0], sv[1]), sv[2]);
             mx = fmaxf(fmaxf(mx, sv[3]), sv[4]);
             mx = fmaxf(fmaxf(mx, sv[5]), fmaxf(sv[6], sv[7]));
@@ -393,7 +484,7 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
             // rare path (see above); the empty asm statements keep the register-file copies
             // that the multiply needs inside this branch
 #pragma unroll
-            for (int nt = 0; nt < FA_NT; ++nt) {
+            for (int nt = 0; nt < NT; ++nt) {
                 asm volatile("" : "+a"(lacc[nt]));
                 lacc[nt] *= alpha[nt];
 #pragma unroll
@@ -404,7 +495,7 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
             }
         }
 #pragma unroll
-        for (int nt = 0; nt < FA_NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             // row sums of the rounded probabilities on the matrix core: ones^T * P^T
             lacc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pb[nt], lacc[nt], 0, 0, 0);
 #pragma unroll
@@ -414,124 +505,68 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
         // keep the accumulators in the accumulation registers between blocks, so that the
         // vector registers stay free for the K/V stages (no register-file shuffling per block)
 #pragma unroll
-        for (int nt = 0; nt < FA_NT; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             asm volatile("" : "+a"(lacc[nt]));
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) asm volatile("" : "+a"(oacc[mt][nt]));
         }
     };
-    const std::integral_constant<bool, false> main_tag;
-    const std::integral_constant<bool, true> tail_tag;
-
-    // register stages: K is fetched two 32-token blocks ahead, V one block ahead, so about
-    // 24 KB per wave are in flight while one block is being multiplied
-    {
-        fa_kbuf<HD> k0, k1, k2;
-        fa_vbuf<HD> v0, v1;
-        // this wave's unmasked blocks are t_begin + j*STEP, j < n.  Every workgroup starts at a
-        // different j (and wraps): the workgroups of a launch run in step, and with all of them at
-        // the same relative position some cache pitches put them on the same memory channels
-        const int e = t_split;
-        const int n = t_begin < e ? (e - t_begin + STEP - 1) / STEP : 0;
-        const int wg_id = (b * KVH + kvh) * nsplit + split;
-        const int n_wg = w_begin < e ? (e - w_begin + STEP - 1) / STEP : 0;       // wave 0's count
-        const int rot_wg = n_wg > 0 ? (int)(((int64_t)wg_id * 2654435761LL >> 8) % n_wg) : 0;
-        const int rot = n > 0 ? min(rot_wg, n - 1) : 0;     // the same round for all four waves
-        auto at = [&](int i) {
-            int j = i + rot;
-            j = j >= n ? j - n : j;
-            return t_begin + j * STEP;
-        };
-        auto ldk = [&](fa_kbuf<HD>& buf, int i) { if (i < n) load_k(buf, at(i), e); };
-        auto ldv = [&](fa_vbuf<HD>& buf, int i) { if (i < n) load_v(buf, at(i), e); };
-        ldk(k0, 0);
-        ldv(v0, 0);
-        ldk(k1, 1);
-        for (int i = 0; i < n; i += 6) {
-            ldv(v1, i + 1);  ldk(k2, i + 2);  compute(k0, v0, 0, main_tag);
-            if (i + 1 >= n) break;
-            ldv(v0, i + 2);  ldk(k0, i + 3);  compute(k1, v1, 0, main_tag);
-            if (i + 2 >= n) break;
-            ldv(v1, i + 3);  ldk(k1, i + 4);  compute(k2, v0, 0, main_tag);
-            if (i + 3 >= n) break;
-            ldv(v0, i + 4);  ldk(k2, i + 5);  compute(k0, v1, 0, main_tag);
-            if (i + 4 >= n) break;
-            ldv(v1, i + 5);  ldk(k0, i + 6);  compute(k1, v0, 0, main_tag);
-            if (i + 5 >= n) break;
-            ldv(v0, i + 6);  ldk(k1, i + 7);  compute(k2, v1, 0, main_tag);
+    int i = 0;
+    if (n_early)
+        for (; i + 1 < n_all; i += 2) {        // (no way out in the middle: it would spoil the load counts)
+            ldv(v1, i + 1, n_all);
+            __builtin_amdgcn_sched_barrier(0);
+            block(k0, v0, i, std::true_type{});
+            ldv(v0, i + 2, n_all);
+            __builtin_amdgcn_sched_barrier(0);
+            block(k1, v1, i + 1, std::true_type{});
         }
-    }
-    // the few blocks that touch the new rows or the dead region: masked, not pipelined
-    // With the fused append the rows at and beyond L were written by this workgroup, above, through
-    // the writable cache pointers; K and V promise the compiler memory that nobody writes, so these
-    // blocks are read through pointers derived from the writable ones (after the barrier above).
-    const bf16_t* K_tail = fr.qkv ? fr.kc_w + ((int64_t)b * KVH + kvh) * cap * HD : K;
-    const bf16_t* V_tail = fr.qkv ? fr.vc_w + ((int64_t)b * KVH + kvh) * HD * cap : V;
-    for (int t0 = t_tail; t0 < t_end; t0 += STEP) {
-        fa_kbuf<HD> kt;
-        fa_vbuf<HD> vt;
-        load_k_from(K_tail, kt, t0, t_end);
-        load_v_from(V_tail, vt, t0, t_end);
-        compute(kt, vt, t0, tail_tag);
+    // the odd last block, or, with at most one old block, all of the few blocks
+    for (; i < n_all; ++i) {
+        if (!n_early) {
+            ldk(k0, i, n_all);
+            ldv(v0, i, n_all);
+        }
+        block(k0, v0, i, std::false_type{});
     }
     __syncthreads();             // every wave is done with the query tile: LDS changes hands
 
-    float l_tot[FA_NT];
+    // the four waves' (max, sum, O) side by side in LDS, combined by all threads, wave 0 first
+    float* s_o = reinterpret_cast<float*>(smem);                          // [4][ROWS * OROW]
+    float2* s_ml = reinterpret_cast<float2*>(s_o + 4 * ROWS * OROW);      // [4][ROWS]
 #pragma unroll
-    for (int nt = 0; nt < FA_NT; ++nt) l_tot[nt] = lacc[nt][0];
-
-    // merge the four waves through LDS: (2,3) -> (0,1), then 1 -> 0
-    auto put = [&](int slot) {
-        float* so = s_o + slot * FA_QROWS * OROW;
-        float* sm = s_ml + slot * FA_QROWS * 2;
-#pragma unroll
-        for (int nt = 0; nt < FA_NT; ++nt) {
-            const int n = nt * 16 + c;
-            if (g == 0) { sm[n * 2] = m_run[nt]; sm[n * 2 + 1] = l_tot[nt]; }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                *reinterpret_cast<f32x4*>(&so[n * OROW + mt * 16 + 4 * g]) = oacc[mt][nt];
-        }
-    };
-    auto take = [&](int slot) {
-        const float* so = s_o + slot * FA_QROWS * OROW;
-        const float* sm = s_ml + slot * FA_QROWS * 2;
-#pragma unroll
-        for (int nt = 0; nt < FA_NT; ++nt) {
-            const int n = nt * 16 + c;
-            const float mb = sm[n * 2], lb = sm[n * 2 + 1];
-            const float M = fmaxf(m_run[nt], mb);
-            const float Ms = (M == -INFINITY) ? 0.f : M;
-            const float sa = __builtin_amdgcn_exp2f(m_run[nt] - Ms);
-            const float sb = __builtin_amdgcn_exp2f(mb - Ms);
-            m_run[nt] = M;
-            l_tot[nt] = l_tot[nt] * sa + lb * sb;
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                const f32x4 ob = *reinterpret_cast<const f32x4*>(&so[n * OROW + mt * 16 + 4 * g]);
-                oacc[mt][nt] = oacc[mt][nt] * sa + ob * sb;
-            }
-        }
-    };
-    if (wave >= 2) put(wave - 2);
-    __syncthreads();
-    if (wave < 2) take(wave);
-    __syncthreads();
-    if (wave == 1) put(0);
-    __syncthreads();
-    if (wave != 0) return;
-    take(0);
-
-    const int64_t item = ((int64_t)b * KVH + kvh) * nqg + qg;
-    float* __restrict__ o_out = po + (item * nsplit + split) * FA_QROWS * HD;
-    float* __restrict__ ml_out = pml + (item * nsplit + split) * FA_QROWS * 2;
-#pragma unroll
-    for (int nt = 0; nt < FA_NT; ++nt) {
-        const int n = nt * 16 + c;
-        if (g == 0) { ml_out[n * 2] = m_run[nt]; ml_out[n * 2 + 1] = l_tot[nt]; }
+    for (int nt = 0; nt < NT; ++nt) {
+        const int n = wave * ROWS + nt * 16 + c;
+        if (g == 0) s_ml[n] = make_float2(m_run[nt], lacc[nt][0]);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            *reinterpret_cast<f32x4*>(o_out + (int64_t)n * HD + mt * 16 + 4 * g) = oacc[mt][nt];
+            *reinterpret_cast<f32x4*>(&s_o[n * OROW + mt * 16 + 4 * g]) = oacc[mt][nt];
+    }
+    __syncthreads();
+    const int64_t item = ((int64_t)b * KVH + kvh) * nsplit + split;
+    float* __restrict__ o_out = po + item * FA_QROWS * HD;
+    float2* __restrict__ ml_out = reinterpret_cast<float2*>(pml) + item * FA_QROWS;
+#pragma unroll 1
+    for (int idx = tid; idx < QR * (HD / 4); idx += 256) {
+        const int n = idx / (HD / 4), d = idx % (HD / 4) * 4;
+        float2 ml[4];
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            ml[w] = s_ml[w * ROWS + n];
+            M = fmaxf(M, ml[w].x);
+        }
+        const float Ms = (M == -INFINITY) ? 0.f : M;
+        float l = 0.f;
+        f32x4 o = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float wgt = __builtin_amdgcn_exp2f(ml[w].x - Ms);
+            l += ml[w].y * wgt;
+            o += *reinterpret_cast<const f32x4*>(&s_o[(w * ROWS + n) * OROW + d]) * wgt;
+        }
+        *reinterpret_cast<f32x4*>(o_out + n * HD + d) = o;
+        if (d == 0) ml_out[n] = make_float2(M, l);
     }
 }
 
@@ -1417,12 +1452,23 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         fr.vc_w = (bf16_t*)kv->v + layer * per_layer;
         fr.bias = m->layers[layer].bqkv;
     }
-    if (hd == 128)
-        k_attn_mfma<128><<<grid, 256, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH,
-                                              kv->cap, Tw, nqg, nsplit, po, pml, fr);
-    else
-        k_attn_mfma<64><<<grid, 256, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH,
-                                             kv->cap, Tw, nqg, nsplit, po, pml, fr);
+    const int nt = (int)cs_ceil_div(QR, 16);              // 16-row query tiles
+    auto launch = [&](auto hd_tag, auto nt_tag) {
+        constexpr int HD = decltype(hd_tag)::value, NT = decltype(nt_tag)::value;
+        if (qkv_part)
+            k_attn_mfma<HD, NT, true><<<grid, 256, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH,
+                                                           kv->cap, Tw, nsplit, po, pml, fr);
+        else
+            k_attn_mfma<HD, NT, false><<<grid, 256, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH,
+                                                            kv->cap, Tw, nsplit, po, pml, fr);
+    };
+    auto by_rows = [&](auto hd_tag) {
+        if (nt == 1) launch(hd_tag, std::integral_constant<int, 1>{});
+        else if (nt == 2) launch(hd_tag, std::integral_constant<int, 2>{});
+        else launch(hd_tag, std::integral_constant<int, FA_NT>{});
+    };
+    if (hd == 128) by_rows(std::integral_constant<int, 128>{});
+    else by_rows(std::integral_constant<int, 64>{});
     cs_prof_end(pa, s);
     CS_TRY(cs_launch_ok("k_attn_mfma"));
     dim3 mgrid((unsigned)cs_ceil_div(QR, FA_MERGE_THREADS / (hd / 4)), KVH, B);

@@ -150,6 +150,22 @@ def test_verify_matches_oracle(shape, plain):
     model.destroy()
 
 
+@pytest.mark.parametrize("shape", [MINI64, MINI128])
+@pytest.mark.parametrize("k", [0, 3, 5, 10])
+def test_narrow_blocks_over_short_and_ragged_caches(shape, k):
+    """Block attention where its pipeline starts and ends: no, one and a few whole 32-token blocks per
+    wave, odd and even counts, new rows that straddle a block, a 128-token V block and a split, query
+    rows that fill one, two and three tiles."""
+    w = synth.model_weights(shape, 4243, threads=4)
+    model = cs.Model(w, max_batch=1, max_k=10)
+    rng = np.random.default_rng(22)
+    for n in (1, 2, 30, 33, 65, 118, 129, 161, 257, 260, 390, 505, 545, 1030):
+        kv, okv, err = _verify_case(w, model, rng.integers(0, shape.vocab, n).tolist(),
+                                    rng.integers(0, shape.vocab, k).tolist(), k)
+        kv.destroy()
+    model.destroy()
+
+
 @pytest.mark.parametrize("shape,plain", [(MINI64, False), (MINI64, True), (MINI128, False),
                                          (SMALLF32, False), (MINIQWEN, False)])
 def test_verify_and_decode_with_qkv_bias(shape, plain):
