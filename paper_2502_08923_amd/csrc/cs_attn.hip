@@ -1426,9 +1426,12 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         return cs_launch_ok("k_attn_merge");
     }
     // The kernel keeps one wave per SIMD (register budget), so one workgroup fills a compute
-    // unit: aim at one workgroup per compute unit, at least 128 tokens per wave.
+    // unit: aim at one workgroup per compute unit, at least 128 tokens per wave; up to eight splits, which
+    // the merge reads in one batch, also of 32 tokens per wave (one row, 300 tokens, hd 128: 1, 2, 3 splits
+    // 10.4, 7.6, 7.0 us; 4106 tokens of hd 64 in 9, 17 splits: 9.6, 9.1 us, but the merge 4.0, 5.1).
     nsplit = (int)cs_ceil_div(256, (int64_t)B * KVH * nqg);
-    const int max_split = (int)cs_ceil_div(n_tok_ub, 4 * 128);
+    const int few = (int)cs_ceil_div(n_tok_ub, 4 * 32) < 8 ? (int)cs_ceil_div(n_tok_ub, 4 * 32) : 8;
+    const int max_split = (int)cs_ceil_div(n_tok_ub, 4 * 128) > few ? (int)cs_ceil_div(n_tok_ub, 4 * 128) : few;
     if (nsplit > max_split) nsplit = max_split;
     if (nsplit > FA_MAX_SPLIT) nsplit = FA_MAX_SPLIT;
     if (nsplit < 1) nsplit = 1;

@@ -51,23 +51,22 @@ __global__ __launch_bounds__(256) void k_gemm_plain(const XT* __restrict__ X,
 #define GEMM_KC 128                       // K elements per pipeline stage
 #define GEMM_LDS_ROW (GEMM_KC * 2 + 16)   // bytes per X row in LDS (padded)
 #define GEMM_RING_TILES 8                 // W tile-chunks (4 KB each) in flight per consumer wave
-#define GEMM_THREADS 384                  // 4 consumer waves + 2 producer waves
 
-// The workgroup is specialised by wave.  Waves 0..3 (consumers) stream W: each owns MT
-// 16-row tiles, keeps 8/MT K-chunks of them (32 KB) in flight in registers and multiplies.
-// Waves 4 and 5 (producers) stage the X block of every chunk (half of its rows each)
+// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 5, see mfma_waves) stream W:
+// each owns MT 16-row tiles, keeps 8/MT K-chunks of them (32 KB) in flight in registers and multiplies.
+// Two more waves (producers) stage the X block of every chunk (half of its rows each)
 // through registers into a double-buffered LDS tile.  The hardware counts outstanding loads per wave and retires
 // them in order, so a wave that waits for a near X load would also drain its far W loads;
 // giving X its own wave keeps the W stream deep.  One barrier per chunk hands the LDS
 // buffers over.
 // MT: 16-row W tiles per consumer wave.  NT: 16-row X tiles per workgroup.
-// grid.x: (W row tile of 64*MT, X row block of 16*NT) pairs, see the mapping below;
+// grid.x: (W row tile of 16*MT*CW, X row block of 16*NT) pairs, see the mapping below;
 // grid.y: K splits.
 // act_tiled by mode: SWIGLU - the output goes out in fragment order; ARGMAX - tiles per row of the
 // pair buffer.
 #define GEMM_STORE_STREAM 3   // CS_GEMM_STORE whose partial tiles leave through streaming stores
-template <int MT, int NT, int MODE>
-__global__ __launch_bounds__(GEMM_THREADS) void k_gemm_mfma(const f16_t* __restrict__ X,
+template <int MT, int NT, int MODE, int CW>
+__global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __restrict__ X,
                                                             const f16_t* __restrict__ W,
                                                             float* __restrict__ Y,
                                                             f16_t* __restrict__ act, int R, int N,
@@ -84,15 +83,15 @@ __global__ __launch_bounds__(GEMM_THREADS) void k_gemm_mfma(const f16_t* __restr
     // W from that L2 instead of HBM.
     const int grp = blockIdx.x / (8 * RB), rem = blockIdx.x % (8 * RB);
     const int w_tile = grp * 8 + (rem & 7);
-    if (w_tile * 64 * MT >= N) return;                    // whole workgroup, before any barrier
+    if (w_tile * 16 * MT * CW >= N) return;               // whole workgroup, before any barrier
     const int r_base = (rem >> 3) * 16 * NT;
 
-    if (wave >= 4) {
+    if (wave >= CW) {
         // ---------------- producers: X chunks -> LDS ----------------
         // lane -> 16-byte segment (lane & 15) of rows row0 + 4*i, i < ROWS4; the two producer
         // waves split the 16*NT rows in halves
         constexpr int ROWS4 = 2 * NT;
-        const int seg = lane & 15, row0 = (lane >> 4) + (wave - 4) * 8 * NT;
+        const int seg = lane & 15, row0 = (lane >> 4) + (wave - CW) * 8 * NT;
         const f16_t* xbase = X + (int64_t)(r_base + row0) * K + k_begin + seg * 8;
         const int64_t xstep = (int64_t)4 * K;
         const int rows_left = R - r_base - row0;          // row 4*i is valid iff 4*i < rows_left
@@ -140,7 +139,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void k_gemm_mfma(const f16_t* __restr
 
     // ---------------- consumers: W stream + MFMA ----------------
     const int lrow = lane & 15, g = lane >> 4;
-    const int n_wave = (w_tile * 4 + wave) * MT * 16;           // first W row of this wave
+    const int n_wave = (w_tile * CW + wave) * MT * 16;           // first W row of this wave
     // W is stored in MFMA fragment order, K-chunk major: W_t[k/128][n/16][(k%128)/32][lane][8].
     // The 16-byte piece `lane` of a 1 KB block is exactly that lane's A operand, so every wave
     // load reads 8 whole cache lines, and all workgroups working on the same K chunk read one
@@ -248,14 +247,14 @@ __global__ __launch_bounds__(GEMM_THREADS) void k_gemm_mfma(const f16_t* __restr
             }
         }
     } else if (MODE == CS_GEMM_ARGMAX) {
-        // Per row, the largest of this workgroup's 64*MT columns and its column (the lowest on
+        // Per row, the largest of this workgroup's 16*MT*CW columns and its column (the lowest on
         // ties): over the lane's own columns in increasing order, over the four lanes that share
-        // a row, then over the four waves through LDS (the X buffers are free).  Y carries the
+        // a row, then over the waves through LDS (the X buffers are free).  Y carries the
         // pair buffer [R][tiles][2], act_tiled the number of tiles per row.
         int32_t* __restrict__ am = reinterpret_cast<int32_t*>(Y);
         const int nch = act_tiled;
-        float* rv = reinterpret_cast<float*>(&xs[0][0]);                 // [4 waves][16*NT rows]
-        int* ri = reinterpret_cast<int*>(&xs[0][0]) + 4 * 16 * NT;
+        float* rv = reinterpret_cast<float*>(&xs[0][0]);                 // [CW waves][16*NT rows]
+        int* ri = reinterpret_cast<int*>(&xs[0][0]) + CW * 16 * NT;
         __syncthreads();                                    // every wave is past its last X fragment
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -286,7 +285,7 @@ __global__ __launch_bounds__(GEMM_THREADS) void k_gemm_mfma(const f16_t* __restr
             float bv = rv[tid];
             int bi = ri[tid];
 #pragma unroll
-            for (int w = 1; w < 4; ++w) cs_am_take(bv, bi, rv[w * 16 * NT + tid], ri[w * 16 * NT + tid]);
+            for (int w = 1; w < CW; ++w) cs_am_take(bv, bi, rv[w * 16 * NT + tid], ri[w * 16 * NT + tid]);
             const int64_t o = ((int64_t)(r_base + tid) * nch + w_tile) * 2;
             am[o] = __float_as_int(bv);
             am[o + 1] = bi;
@@ -601,27 +600,75 @@ static int launch_tile(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     return cs_launch_ok("k_gemm_dma");
 }
 
+// Launch shape of the weight-streaming kernel.
+struct mfma_shape { int r_blocks, ksplit, waves; };
+
+// Estimated time of a launch, us.  A workgroup fills a compute unit and takes 30 us per 4096 of K while it
+// is bound by its weights, 6.1 us per X tile from five tiles on (8B width, 224 workgroups: 4, 6, 7, 8 X tiles
+// 30, 37, 43 to 48, 49 to 55 us); five consumer waves share four SIMDs, 1.35 of the time for 1.25 of the
+// rows; a partial tile is written and read once more at about 4.9 TB/s.
+static double mfma_us(int R, int N, int K, const mfma_shape& p) {
+    const int nt = (int)cs_ceil_div(cs_ceil_div(R, 16), p.r_blocks);
+    const int64_t wgs = cs_ceil_div(N, 32 * p.waves) * p.r_blocks * p.ksplit;
+    const double per = (6.1 * nt > 30. ? 6.1 * nt : 30.) * (p.waves == 5 ? 1.35 : 1.);
+    return cs_ceil_div(wgs, 256) * per * K / p.ksplit / 4096. + (p.ksplit > 1 ? p.ksplit * 8e-6 * R * N / 4.9 : 0.);
+}
+
+// Up to 96 rows: one row block, and K splits until about 3/4 of the compute units have a workgroup (measured
+// at the 8B shapes, more splits cost more in partial-tile traffic and fixed per-workgroup latency than they
+// gain: q/k/v 4, o 8, down 8).  More rows: row blocks of up to 128 rows and K splits by estimated time (100
+// rows: gate/up 60 -> 48 us in one block instead of two; 256 rows: q/k/v, gate/up, down 40, 109, 58 ->
+// 28, 97, 46 us in two instead of three; the 1B shape keeps two blocks of 64, which fill the chip, 18 us
+// against 23).  Five consumer waves where tiles of 128 W rows need a second, nearly empty round of the chip
+// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 80 -> 56 us).
+static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
+    const int rt_total = (int)cs_ceil_div(R, 16);
+    const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
+    mfma_shape best = {1, 1, 4};
+    if (rt_total <= 6) {
+        const int n_tiles = (int)cs_ceil_div(N, 128);
+        while (n_tiles * best.ksplit < 192 && best.ksplit * 2 <= max_split) best.ksplit *= 2;
+        mfma_shape five = best;
+        five.waves = 5;
+        return mfma_us(R, N, K, five) < mfma_us(R, N, K, best) ? five : best;
+    }
+    double best_us = -1.;
+    for (int rb = (int)cs_ceil_div(rt_total, 8); rb <= (int)cs_ceil_div(rt_total, 4); ++rb)
+        for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2)
+            for (int waves = 4; waves <= 5; ++waves) {
+                const mfma_shape p = {rb, ks, waves};
+                const double us = mfma_us(R, N, K, p);
+                if (best_us < 0. || us < best_us) { best_us = us; best = p; }
+            }
+    return best;
+}
+
+template <int MT, int NT, int CW>
+static void start_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int R, int N, int K, int mode, int Ks,
+                       int act_tiled, hipStream_t s) {
+    const int RB = (int)cs_ceil_div(R, 16 * NT);
+    constexpr int threads = 64 * (CW + 2);
+    dim3 grid((unsigned)(cs_round_up(cs_ceil_div(N, 16 * MT * CW), 8) * RB), (unsigned)cs_ceil_div(K, Ks));
+    // From about 64 rows on the partial tiles are better sent on at once (88 rows: step -1 %,
+    // 168: -0.9 %, 264: -0.3 %); with few rows the readers find them in the caches and a plain
+    // store wins (48 rows +0.4 %, one stream of 11 rows +2.5 to +3.6 %).
+    if (mode == CS_GEMM_STORE && R >= 64)
+        k_gemm_mfma<MT, NT, GEMM_STORE_STREAM, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+    else if (mode == CS_GEMM_STORE)
+        k_gemm_mfma<MT, NT, CS_GEMM_STORE, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+    else if (mode == CS_GEMM_ARGMAX)
+        k_gemm_mfma<MT, NT, CS_GEMM_ARGMAX, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+    else if constexpr (MT % 2 == 0)
+        k_gemm_mfma<MT, NT, CS_GEMM_SWIGLU, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+}
+
 template <int MT, int NT>
 static int launch_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int R, int N, int K,
-                       int mode, int ksplit, int act_tiled, hipStream_t s) {
+                       int mode, int ksplit, int waves, int act_tiled, hipStream_t s) {
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
-    const int RB = (int)cs_ceil_div(R, 16 * NT);
-    dim3 grid((unsigned)(cs_round_up(cs_ceil_div(N, 64 * MT), 8) * RB), (unsigned)cs_ceil_div(K, Ks));
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
-    if (mode == CS_GEMM_STORE) {
-        // From about 64 rows on the partial tiles are better sent on at once (88 rows: step -1 %,
-        // 168: -0.9 %, 264: -0.3 %); with few rows the readers find them in the caches and a plain
-        // store wins (48 rows +0.4 %, one stream of 11 rows +2.5 to +3.6 %).
-        if (R >= 64)
-            k_gemm_mfma<MT, NT, GEMM_STORE_STREAM><<<grid, GEMM_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
-        else
-            k_gemm_mfma<MT, NT, CS_GEMM_STORE><<<grid, GEMM_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
-    } else if (mode == CS_GEMM_ARGMAX) {
-        k_gemm_mfma<MT, NT, CS_GEMM_ARGMAX><<<grid, GEMM_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
-    } else {
-        if constexpr (MT % 2 == 0)
-            k_gemm_mfma<MT, NT, CS_GEMM_SWIGLU><<<grid, GEMM_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
-    }
+    if (waves == 5) start_mfma<MT, NT, 5>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
+    else start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
     cs_prof_end(pg, s);
     return cs_launch_ok("k_gemm_mfma");
 }
@@ -743,15 +790,11 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     }
     CS_REQUIRE(mfma_shape_ok(N, K) && (mode != CS_GEMM_SWIGLU || N % 32 == 0), CS_E_UNSUPPORTED,
                "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
-    // Shape of the launch.  One workgroup (6 waves, ~250 registers) fills a compute unit.  Wide
-    // projections (gate/up, lm_head) have enough 128-row tiles.  Narrow ones (q/k/v, o, down)
-    // are split along K, but only until about 3/4 of the compute units have a workgroup:
-    // measured at the 8B shapes, more splits cost more in partial-tile traffic and fixed
-    // per-workgroup latency than they gain in parallelism (q/k/v 4, o 8, down 8 splits).
-    // Weight-streaming kernel: a workgroup takes up to 96 block rows; more rows are split into
+    // Shape of the launch.
+    // Weight-streaming kernel: a workgroup takes up to 128 block rows; more rows are split into
     // equal row blocks whose workgroups share each W tile through one XCD's L2 (see the mapping
-    // in the kernel).  Many-row kernel: 256 W rows x up to 288 block rows per workgroup.  It needs
-    // enough 256-row W tiles, or two row blocks of them, to fill the chip: measured inside whole
+    // in the kernel and mfma_plan).  Many-row kernel: 256 W rows x up to 288 block rows per workgroup.
+    // It needs enough 256-row W tiles, or two row blocks of them, to fill the chip: measured inside whole
     // steps at the 8B shapes it wins from 97 rows on for the lm_head (501 tiles) and from 289
     // rows on for every projection (at 168 and 264 rows the q/k/v and gate/up projections,
     // 24 and 112 tiles, are still faster through the weight-streaming kernel).
@@ -761,24 +804,26 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     if (mode == CS_GEMM_ARGMAX) {
         // one (value, column) pair per row and workgroup column tile, in place of Y
         CS_REQUIRE(!allow_split && nparts_out, CS_E_STATE, "argmax epilogue: no K split, tile count wanted");
-        act_tiled = (int)cs_ceil_div(N, tile ? TG_WROWS : 128);
         Y = reinterpret_cast<float*>(m->am_val_idx);
     }
     if (mode == CS_GEMM_SWIGLU) Y = reinterpret_cast<float*>(m->range_flags);   // see the epilogue
     const int rt_total = (int)cs_ceil_div(R, 16);
-    int r_blocks = (int)cs_ceil_div(rt_total, 6), ksplit = 1;
+    int r_blocks, ksplit, waves = 0;
+    const bool may_split = allow_split && mode == CS_GEMM_STORE;
     if (tile) {
-        tile_plan(R, N, K, allow_split && mode == CS_GEMM_STORE, &r_blocks, &ksplit);
-    } else if (allow_split && mode == CS_GEMM_STORE) {
-        const int n_tiles = (int)cs_ceil_div(N, 128);
-        const int max_split = K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
-        while (n_tiles * r_blocks * ksplit < 192 && ksplit * 2 <= max_split) ksplit *= 2;
+        tile_plan(R, N, K, may_split, &r_blocks, &ksplit);
+    } else {
+        const mfma_shape p = mfma_plan(R, N, K, may_split);
+        r_blocks = p.r_blocks;
+        ksplit = p.ksplit;
+        waves = p.waves;
     }
     // the partial tiles must fit the workspace
     while (ksplit > 1 && (size_t)ksplit * R * N > m->part_floats) ksplit /= 2;
     if (ksplit > 1) CS_REQUIRE(allow_split, CS_E_STATE, "K split without a partial-tile buffer");
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
     const int nparts = (int)cs_ceil_div(K, Ks);
+    if (mode == CS_GEMM_ARGMAX) act_tiled = (int)cs_ceil_div(N, tile ? TG_WROWS : 32 * waves);
     if (nparts_out) *nparts_out = mode == CS_GEMM_ARGMAX ? act_tiled : nparts;
     const int rt = (int)cs_ceil_div(rt_total, r_blocks);
     const f16_t* x = (const f16_t*)X;
@@ -800,12 +845,14 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
         }
     }
     switch (rt) {
-        case 1: return launch_mfma<2, 1>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-        case 2: return launch_mfma<2, 2>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-        case 3: return launch_mfma<2, 3>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-        case 4: return launch_mfma<2, 4>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-        case 5: return launch_mfma<2, 5>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-        default: return launch_mfma<2, 6>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
+        case 1: return launch_mfma<2, 1>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 2: return launch_mfma<2, 2>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 3: return launch_mfma<2, 3>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 4: return launch_mfma<2, 4>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 5: return launch_mfma<2, 5>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 6: return launch_mfma<2, 6>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 7: return launch_mfma<2, 7>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        default: return launch_mfma<2, 8>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
     }
 }
 

@@ -166,6 +166,25 @@ def test_narrow_blocks_over_short_and_ragged_caches(shape, k):
     model.destroy()
 
 
+def test_five_wave_tiles_in_every_epilogue():
+    """A model whose gate/up and lm_head widths send both to 160-row W tiles: SwiGLU and argmax epilogues
+    against the oracle, and the tokens with and without stored logits."""
+    shape = ModelShape("mini-five-waves", 1, 256, 4, 2, 64, 18944, 37872, 10000.0, 1e-5, "bf16")
+    w = synth.model_weights(shape, 4244, threads=8)
+    model = cs.Model(w, max_batch=1, max_k=10)
+    rng = np.random.default_rng(23)
+    prompt, draft = rng.integers(0, shape.vocab, 40).tolist(), rng.integers(0, shape.vocab, 10).tolist()
+    kv, okv, err = _verify_case(w, model, prompt, draft, 10)
+    kv.set_len(0, 39)
+    acc, nx, logits = cs.cs_verify(model, kv, t32([prompt[-1]]), t32([draft]), t32([10]), 10, want_logits=True)
+    kv.set_len(0, 39)
+    acc2, nx2, none = cs.cs_verify(model, kv, t32([prompt[-1]]), t32([draft]), t32([10]), 10)
+    assert (int(acc[0]), int(nx[0])) == (int(acc2[0]), int(nx2[0]))
+    assert int(nx[0]) == int(logits[0, int(acc[0])].argmax())
+    kv.destroy()
+    model.destroy()
+
+
 @pytest.mark.parametrize("shape,plain", [(MINI64, False), (MINI64, True), (MINI128, False),
                                          (SMALLF32, False), (MINIQWEN, False)])
 def test_verify_and_decode_with_qkv_bias(shape, plain):

@@ -111,6 +111,14 @@ def test_gemm_prompt_rows(host_model, N, K, R):
     _gemm_case(host_model, N, K, R)
 
 
+@pytest.mark.parametrize("R", [5, 88, 105, 112, 113, 128, 129, 200, 256, 257])
+@pytest.mark.parametrize("N,K", [(37888, 256), (33040, 128), (4096, 1024)])
+def test_gemm_wide_blocks_and_five_wave_tiles(host_model, N, K, R):
+    """The weight-streaming kernel with seven and eight X tiles in one and two row blocks, and with five
+    consumer waves (more than 256 tiles of 128 W rows, ragged last tile) next to four."""
+    _gemm_case(host_model, N, K, R)
+
+
 def test_gemm_tiny_weights_are_not_flushed(host_model):
     """The tuned projections multiply in float16 (weights converted from bfloat16, exactly for
     |w| >= 2^-17).  Weights in float16's subnormal range must still contribute."""
