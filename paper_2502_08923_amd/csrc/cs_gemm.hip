@@ -432,9 +432,22 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
     auto b_frag = [&](int sb, int nt) { return *reinterpret_cast<const f16x8*>(b_base + sb * STAGE + nt * 1024); };
     const int n_wave = w_tile * TG_WROWS + wn * 64;
 
-    // wait until at most `n` of this wave's loads are outstanding, then meet the other waves.
-    // (A plain s_barrier: the workgroup fence of __syncthreads would drain every load in flight.)
-#define TD_SYNC(n) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(n) : "memory")
+    // wait until at most `n` chunks of this wave's requests are outstanding, then meet the other waves.
+    // (A plain s_barrier: the workgroup fence of __syncthreads would drain every load in flight.)  With XT
+    // no multiple of 8 the first XT % 8 waves request one block more per chunk and count their own number:
+    // with the smaller count of the others they waited for part of the newest chunk, and everybody with
+    // them.  (One asm statement: a branch the compiler sees splits the accumulators' live ranges.)
+    int extra = __builtin_amdgcn_readfirstlane(wave < XT % 8 ? 1 : 0);
+    asm volatile("" : "+s"(extra));                  // stays a scalar register
+#define TD_SYNC(n)                                                                                    \
+    do {                                                                                              \
+        if constexpr (XT % 8 == 0)                                                                    \
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((n) * LDMIN) : "memory");           \
+        else                                                                                          \
+            asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 .Lfew%=\n\ts_waitcnt vmcnt(%1)\n"      \
+                         "\ts_branch .Lmet%=\n.Lfew%=:\n\ts_waitcnt vmcnt(%2)\n.Lmet%=:\n\ts_barrier" \
+                         ::"s"(extra), "n"((n) * (LDMIN + 1)), "n"((n) * LDMIN) : "memory", "scc");   \
+    } while (0)
 
     // Everything a wave does with its NT X tiles: the multiply loop and the epilogue.  Both wave rows
     // run it with their own NT; the requests, the waits and the barriers are the same in both, so
@@ -452,7 +465,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
         issue(0, 0);
         issue(1, 1);
         issue(2, 2);
-        TD_SYNC(2 * LDMIN);                                        // chunk 0 has landed everywhere
+        TD_SYNC(2);                                                // chunk 0 has landed everywhere
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) a[mt] = a_frag(0, mt);
         bq[0] = b_frag(0, 0);
@@ -467,7 +480,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
                 // chunk c+1 (requested two iterations ago) must be in LDS before its first fragments
                 // are read at the end of this iteration; only chunk c+2 may still be in flight
                 if (TAIL && u >= 2) TD_SYNC(0);
-                else TD_SYNC(LDMIN);
+                else TD_SYNC(1);
                 // chunk c+3 goes to the stage of chunk c-1, free since the barrier.  Its requests are
                 // spread over the iteration, one after every few MFMA groups: a wave issues in order,
                 // so a burst of requests that the memory pipeline takes one at a time would hold
