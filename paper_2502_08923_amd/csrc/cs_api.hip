@@ -676,7 +676,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, int rows, hipStream_t s) {
     const bool fuse_rope = cs_attention_fuses_rope(m, rows);
     for (int l = 0; l < c.n_layers; ++l) {
         const cs_layer_dev& L = m->layers[l];
-        CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, nqkv, s));
+        CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, nqkv, true, s));
         CS_TRY(cs_gemm_launch(m, m->xn, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, 1, &np, s));
         if (fuse_rope) {
             CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, m->part, np, s));
@@ -685,7 +685,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, int rows, hipStream_t s) {
             CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, nullptr, 0, s));
         }
         CS_TRY(cs_gemm_launch(m, m->xn, L.wo, m->part, R, d, nq, CS_GEMM_STORE, 1, &np, s));
-        CS_TRY(cs_addnorm_launch(m, m->part, np, L.norm2, m->xn, R, 2 * c.d_ff, s));
+        CS_TRY(cs_addnorm_launch(m, m->part, np, L.norm2, m->xn, R, 2 * c.d_ff, false, s));
         if (m->fast) {
             CS_TRY(cs_gemm_launch(m, m->xn, L.wgu, nullptr, R, 2 * c.d_ff, d, CS_GEMM_SWIGLU, 0,
                                   nullptr, s));
@@ -696,7 +696,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, int rows, hipStream_t s) {
         CS_TRY(cs_gemm_launch(m, m->act, L.wd, m->part, R, d, c.d_ff, CS_GEMM_STORE, 1, &np_prev, s));
     }
     // the final norm feeds the lm_head (callers that only fill the cache never read it)
-    return cs_addnorm_launch(m, m->part, np_prev, m->final_norm, m->xn, R, c.vocab, s);
+    return cs_addnorm_launch(m, m->part, np_prev, m->final_norm, m->xn, R, c.vocab, false, s);
 }
 
 static int verify_impl(cs_model* m, cs_kv* kv, const int32_t* d_pending, const int32_t* d_draft,
@@ -1208,7 +1208,7 @@ extern "C" int cs_op_gemm(cs_model* m, int32_t dtype, const void* X, const void*
     int rc = cs_tile_weights_launch(W, nullptr, N, K, 0, N, 0, wt, nullptr, s);
     if (rc == CS_OK) rc = cs_convert_launch(X, CS_T_BF16, xt, CS_T_F16, (int64_t)R * K, s);
     X = xt;
-    if (rc == CS_OK && cs_gemm_x_tiled(R, N)) {            // the many-row kernel reads fragment order
+    if (rc == CS_OK && cs_gemm_x_tiled(R, N, K, (size_t)R * N <= m->part_floats)) {   // the many-row kernel reads fragment order
         void* xt2 = (char*)xt + x_bytes;
         rc = cs_tile_x_launch(xt, xt2, R, K, s);
         X = xt2;

@@ -144,9 +144,10 @@ int cs_scan_stream_keys(size_t need, hipStream_t s, int64_t** out);
 int cs_embed_launch(const cs_model* m, const int32_t* tok, int R, hipStream_t s);
 int cs_rope_table_launch(const cs_model* m, const int32_t* kv_len, int B, int rows, hipStream_t s);
 // x[r] += sum of nparts partial tiles (part[p][r][:]) and, if xn_out, xn_out[r] = rmsnorm(x[r])*gain
-// (next_N: output width of the GEMM that reads xn_out; it decides the layout of xn_out)
+// (next_N, next_split: output width of the GEMM that reads xn_out and whether it may split K; they decide
+// the layout of xn_out)
 int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
-                      const float* gain, void* xn_out, int R, int next_N, hipStream_t s);
+                      const float* gain, void* xn_out, int R, int next_N, bool next_split, hipStream_t s);
 int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* qkv, int nparts,
                           int rows, hipStream_t s);
 int cs_swiglu_launch(const cs_model* m, int R, hipStream_t s);
@@ -178,10 +179,11 @@ int cs_gemm_plain_launch(int dtype, const float* X, const void* W, float* Y, int
 // The many-row GEMM kernel reads its activations in MFMA fragment order as well:
 // X_t[r/16][k/32][lane = r%16 + 16*((k%32)/8)][k%8] (K = row length, row tiles padded to 16
 // rows), so that one direct-to-LDS request is 1 KB of contiguous memory, like a request for W.
-// cs_gemm_x_tiled says whether the GEMM of R rows by N outputs runs that kernel; the producer
+// cs_gemm_x_tiled says whether the GEMM of R rows by N outputs over K inputs, with or without leave to
+// split K (as in cs_gemm_launch), runs that kernel; the producer
 // of its X (norm, attention merge, SwiGLU epilogue) then writes this layout.  Four consecutive
 // k (k % 4 == 0) stay contiguous.
-bool cs_gemm_x_tiled(int R, int N);
+bool cs_gemm_x_tiled(int R, int N, int K, bool may_split);
 __host__ __device__ __forceinline__ int64_t cs_xt_index(int r, int k, int K) {
     return ((int64_t)(r >> 4) * (K >> 5) + (k >> 5)) * 512 + (((r & 15) + 16 * ((k & 31) >> 3)) << 3) + (k & 7);
 }

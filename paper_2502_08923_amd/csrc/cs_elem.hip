@@ -441,12 +441,12 @@ int cs_embed_launch(const cs_model* m, const int32_t* tok, int R, hipStream_t s)
 }
 
 int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
-                      const float* gain, void* xn_out, int R, int next_N, hipStream_t s) {
+                      const float* gain, void* xn_out, int R, int next_N, bool next_split, hipStream_t s) {
     const int d = m->cfg.d_model;
     const int64_t ps = (int64_t)R * d;
     if (xn_out && m->fast) {
         k_addnorm<f16_t><<<R, NORM_THREADS, 0, s>>>(m->x, part, nparts, ps, d, m->cfg.rms_eps, gain,
-                                                    (f16_t*)xn_out, cs_gemm_x_tiled(R, next_N) ? 1 : 0,
+                                                    (f16_t*)xn_out, cs_gemm_x_tiled(R, next_N, d, next_split) ? 1 : 0,
                                                     m->range_flags);
     } else
         k_addnorm<float><<<R, NORM_THREADS, 0, s>>>(m->x, part, nparts, ps, d, m->cfg.rms_eps, gain,

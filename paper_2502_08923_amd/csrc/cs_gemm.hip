@@ -346,10 +346,11 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
 #define TD_KC 32
 #define TG_THREADS 512
 #define TG_WROWS 256
+#define TG_XT_MIN 6        // fewest X tiles of a workgroup (a wave reads its X fragments three tiles ahead)
 #define TG_PANEL 4          // row blocks a compute die walks per W tile, see the mapping in the kernel
 
 
-// XT: 16-row X tiles per workgroup (8..18).  The two wave rows split them as evenly as whole tiles
+// XT: 16-row X tiles per workgroup (TG_XT_MIN..18).  The two wave rows split them as evenly as whole tiles
 // allow: wave row 0 takes the first NT0 = ceil(XT/2), wave row 1 the other NT1 = floor(XT/2); with
 // XT odd (528 rows in two blocks: 17 tiles) the two waves of a SIMD, one of each row, then multiply
 // 4*17 tile pairs per chunk where an even split rounded up would make it 4*18.
@@ -633,7 +634,8 @@ static double mfma_us(int R, int N, int K, const mfma_shape& p) {
 // rows: gate/up 60 -> 48 us in one block instead of two; 256 rows: q/k/v, gate/up, down 40, 109, 58 ->
 // 28, 97, 46 us in two instead of three; the 1B shape keeps two blocks of 64, which fill the chip, 18 us
 // against 23).  Five consumer waves where tiles of 128 W rows need a second, nearly empty round of the chip
-// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 80 -> 56 us).
+// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 80 -> 56 us), not for the few
+// chunks of a K split (1B q/k/v at 200 rows: 19 us against 12).
 static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
     const int rt_total = (int)cs_ceil_div(R, 16);
     const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
@@ -643,12 +645,12 @@ static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
         while (n_tiles * best.ksplit < 192 && best.ksplit * 2 <= max_split) best.ksplit *= 2;
         mfma_shape five = best;
         five.waves = 5;
-        return mfma_us(R, N, K, five) < mfma_us(R, N, K, best) ? five : best;
+        return best.ksplit == 1 && mfma_us(R, N, K, five) < mfma_us(R, N, K, best) ? five : best;
     }
     double best_us = -1.;
     for (int rb = (int)cs_ceil_div(rt_total, 8); rb <= (int)cs_ceil_div(rt_total, 4); ++rb)
         for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2)
-            for (int waves = 4; waves <= 5; ++waves) {
+            for (int waves = 4; waves <= (ks == 1 ? 5 : 4); ++waves) {
                 const mfma_shape p = {rb, ks, waves};
                 const double us = mfma_us(R, N, K, p);
                 if (best_us < 0. || us < best_us) { best_us = us; best = p; }
@@ -737,8 +739,6 @@ int cs_tile_weights_launch(const void* src, const void* src2, int N, int K, int 
     return cs_launch_ok("k_tile_w");
 }
 
-bool cs_gemm_x_tiled(int R, int N) { return R > 96 && (cs_ceil_div(N, TG_WROWS) >= 192 || R > 288); }
-
 // f16 [R][K] row-major -> fragment order (cs_xt_index); rows of the last tile beyond R are zero
 __global__ void k_tile_x(const f16_t* __restrict__ src, f16_t* __restrict__ dst, int R, int K, int rt_tiles) {
     // (one thread per 8 consecutive k of one row)
@@ -767,26 +767,45 @@ int cs_tile_x_launch(const void* src, void* dst, int R, int K, hipStream_t s) {
 // every partial tile is written and read once more at about 4.9 TB/s.
 // 4095 rows, 8B width, against the fewest row blocks (15 x 288 rows): gate/up 771 -> 695 us,
 // q/k/v 209 -> 169, o 113 -> 104, down 368 -> 339 us; 528 rows: o 31 -> 27 us with half the partial tiles.
-static void tile_plan(int R, int N, int K, bool may_split, int* r_blocks, int* ksplit) {
+// (returns the time; a launch of its own costs about 4 us on top)
+static double tile_plan(int R, int N, int K, bool may_split, int* r_blocks, int* ksplit) {
     const int rt_total = (int)cs_ceil_div(R, 16);
     const int per_xcd = (int)cs_ceil_div(cs_ceil_div(N, TG_WROWS), 8);   // W tiles of one die
     const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
-    const int rb_min = (int)cs_ceil_div(rt_total, 18), rb_max = (int)cs_ceil_div(rt_total, 8);
-    double best = 0.;
+    const int rb_min = (int)cs_ceil_div(rt_total, 18), rb_max = (int)cs_ceil_div(rt_total, TG_XT_MIN);
+    double best = -1.;
     for (int rb = rb_min; rb <= rb_max; ++rb) {
-        const int rt = (int)cs_ceil_div(rt_total, rb) < 8 ? 8 : (int)cs_ceil_div(rt_total, rb);
+        const int rt = (int)cs_ceil_div(rt_total, rb) < TG_XT_MIN ? TG_XT_MIN : (int)cs_ceil_div(rt_total, rb);
         for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2) {
             const int wgs = per_xcd * (int)cs_ceil_div(rt_total, rt) * ks;   // on 32 compute units
             const double part = (wgs % 32) / 32., rounds = wgs / 32 + (part > 0. ? 0.65 + 0.35 * part : 0.);
             const double us = rounds * 4.5 * (6.7 + rt) * K / ks / 4096. + (may_split ? ks * 8e-6 * R * N / 4.9 : 0.);
-            if ((rb == rb_min && ks == 1) || us < best) {
+            if (best < 0. || us < best) {
                 best = us;
                 *r_blocks = rb;
                 *ksplit = ks;
             }
         }
     }
+    return best + 4.;
 }
+
+// Which kernel a projection of R rows takes, and its launch shape (waves 0: the many-row kernel, 256 W rows
+// x up to 288 block rows per workgroup).  Measured at the 8B, Qwen2.5-7B and 1B widths: from 97 rows on the
+// many-row kernel wins where its 256-row W tiles alone fill most of the chip (lm_head), from 289 on
+// everywhere, between 129 and 288 rows where the two estimates say so (250 rows, 8B: gate/up 89 -> 68,
+// down 43 -> 38 us; 1B gate/up stays, 27 against 29 us), up to 128 rows nowhere else (128 rows, 8B
+// gate/up: 55 against 65 us).
+static mfma_shape gemm_plan(int R, int N, int K, bool may_split) {
+    mfma_shape t = {1, 1, 0};
+    if (R <= 96) return mfma_plan(R, N, K, may_split);
+    const double tile_us = tile_plan(R, N, K, may_split, &t.r_blocks, &t.ksplit);
+    if (R > 288 || cs_ceil_div(N, TG_WROWS) >= 192) return t;
+    const mfma_shape p = mfma_plan(R, N, K, may_split);
+    return R > 128 && tile_us < mfma_us(R, N, K, p) ? t : p;
+}
+
+bool cs_gemm_x_tiled(int R, int N, int K, bool may_split) { return gemm_plan(R, N, K, may_split).waves == 0; }
 
 int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, int R, int N, int K,
                    int mode, int allow_split, int* nparts_out, hipStream_t s) {
@@ -806,14 +825,12 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     // Shape of the launch.
     // Weight-streaming kernel: a workgroup takes up to 128 block rows; more rows are split into
     // equal row blocks whose workgroups share each W tile through one XCD's L2 (see the mapping
-    // in the kernel and mfma_plan).  Many-row kernel: 256 W rows x up to 288 block rows per workgroup.
-    // It needs enough 256-row W tiles, or two row blocks of them, to fill the chip: measured inside whole
-    // steps at the 8B shapes it wins from 97 rows on for the lm_head (501 tiles) and from 289
-    // rows on for every projection (at 168 and 264 rows the q/k/v and gate/up projections,
-    // 24 and 112 tiles, are still faster through the weight-streaming kernel).
-    const bool tile = cs_gemm_x_tiled(R, N);
+    // in the kernel and mfma_plan).
+    const bool may_split = allow_split && mode == CS_GEMM_STORE;
+    const mfma_shape plan = gemm_plan(R, N, K, may_split);
+    const bool tile = plan.waves == 0;
     // the SwiGLU epilogue writes the input of the down projection (d_model outputs, same rows)
-    int act_tiled = mode == CS_GEMM_SWIGLU && cs_gemm_x_tiled(R, m->cfg.d_model) ? 1 : 0;
+    int act_tiled = mode == CS_GEMM_SWIGLU && cs_gemm_x_tiled(R, m->cfg.d_model, m->cfg.d_ff, true) ? 1 : 0;
     if (mode == CS_GEMM_ARGMAX) {
         // one (value, column) pair per row and workgroup column tile, in place of Y
         CS_REQUIRE(!allow_split && nparts_out, CS_E_STATE, "argmax epilogue: no K split, tile count wanted");
@@ -821,16 +838,8 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     }
     if (mode == CS_GEMM_SWIGLU) Y = reinterpret_cast<float*>(m->range_flags);   // see the epilogue
     const int rt_total = (int)cs_ceil_div(R, 16);
-    int r_blocks, ksplit, waves = 0;
-    const bool may_split = allow_split && mode == CS_GEMM_STORE;
-    if (tile) {
-        tile_plan(R, N, K, may_split, &r_blocks, &ksplit);
-    } else {
-        const mfma_shape p = mfma_plan(R, N, K, may_split);
-        r_blocks = p.r_blocks;
-        ksplit = p.ksplit;
-        waves = p.waves;
-    }
+    const int r_blocks = plan.r_blocks, waves = plan.waves;
+    int ksplit = plan.ksplit;
     // the partial tiles must fit the workspace
     while (ksplit > 1 && (size_t)ksplit * R * N > m->part_floats) ksplit /= 2;
     if (ksplit > 1) CS_REQUIRE(allow_split, CS_E_STATE, "K split without a partial-tile buffer");
@@ -844,6 +853,8 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     f16_t* act = (f16_t*)m->act;
     if (tile) {
         switch (rt) {                                // 16-row X tiles per workgroup
+            case 7: return launch_tile<7>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
+            case 8: return launch_tile<8>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
             case 9: return launch_tile<9>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
             case 10: return launch_tile<10>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
             case 11: return launch_tile<11>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
@@ -854,7 +865,7 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
             case 16: return launch_tile<16>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
             case 17: return launch_tile<17>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
             case 18: return launch_tile<18>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            default: return launch_tile<8>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);   // up to 128 rows
+            default: return launch_tile<TG_XT_MIN>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
         }
     }
     switch (rt) {
