@@ -47,6 +47,14 @@ __device__ __forceinline__ float block_sum(float v, float* wred) {
     return r;
 }
 
+__device__ __forceinline__ f32x4 pa_ld4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 pa_ld4(const bf16_t* p) {
+    const bf16x4 t = *reinterpret_cast<const bf16x4*>(p);
+    return (f32x4){(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
+}
+
+// Latency bound: 44 workgroups over 512 tokens of hd 64 took 41 us with one element per load, 20 us
+// with four.
 template <typename WT, typename QT, typename OT>
 __global__ __launch_bounds__(PA_THREADS) void k_attn_plain(const QT* __restrict__ q,
                                                            const WT* __restrict__ kc,
@@ -76,7 +84,19 @@ __global__ __launch_bounds__(PA_THREADS) void k_attn_plain(const QT* __restrict_
         for (int t = tid; t < cn; t += PA_THREADS) {
             const WT* __restrict__ kr = K + (int64_t)(c0 + t) * hd;
             float s = 0.f;
-            for (int e = 0; e < hd; ++e) s += sq[e] * cs_ld(kr, e);
+            if (hd % 16 == 0) {                    // rows of whole 16-element pieces: wide loads, four in flight
+                for (int e = 0; e < hd; e += 16) {
+                    f32x4 kv[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) kv[u] = pa_ld4(kr + e + 4 * u);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) s += sq[e + 4 * u + j] * kv[u][j];
+                }
+            } else {
+                for (int e = 0; e < hd; ++e) s += sq[e] * cs_ld(kr, e);
+            }
             s *= scale;
             sc[t] = s;
             lmax = fmaxf(lmax, s);
@@ -93,7 +113,13 @@ __global__ __launch_bounds__(PA_THREADS) void k_attn_plain(const QT* __restrict_
         const float lc = block_sum(lsum, wred);   // its barriers also publish sc[]
         l_run = l_run * alpha + lc;
         float acc = 0.f;
-        for (int t = part; t < cn; t += nparts) acc += sc[t] * cs_ld(V, cs_v_index(c0 + t, d, hd));
+        // four tokens at a time (contiguous in the cache); rows past the context may hold anything
+#pragma unroll 4
+        for (int t = 4 * part; t < cn; t += 4 * nparts) {
+            const f32x4 v = pa_ld4(V + cs_v_index(c0 + t, d, hd));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc += t + j < cn ? sc[t + j] * v[j] : 0.f;
+        }
         o = o * alpha + acc;
         m_run = m_new;
         __syncthreads();

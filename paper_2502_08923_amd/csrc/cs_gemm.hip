@@ -17,32 +17,106 @@
 #include <type_traits>
 
 // -------------------------------------------------------------------------------------
-// plain reference kernel: one wave per W row, float32 accumulation
+// float32 kernel (float32 models, and any model on the plain kernels)
+//
+// Small models: launch and load latency bound it, not the matrix rate (o and down of a 256-wide model, 11 rows:
+// 87 us with a wave per W row that walked K 64 scalars at a time, 5 us now).  A workgroup owns 16 W rows
+// by 16*NT block rows; its eight waves take the 16-wide pieces of K in turn, four pieces of loads in
+// flight each, straight into the operands of v_mfma_f32_16x16x4_f32 (float32 products and sums; lane l
+// holds row l % 16, and element j of its four is k = 4 * (l / 16) + j in both operands), and the eight
+// partial sums are added through LDS in wave order.  VEC: K % 4 == 0 and both operands aligned to four
+// elements; otherwise the same kernel loads single elements.
 // -------------------------------------------------------------------------------------
-template <typename XT, typename WT>
-__global__ __launch_bounds__(256) void k_gemm_plain(const XT* __restrict__ X,
-                                                    const WT* __restrict__ W, float* __restrict__ Y,
-                                                    int R, int N, int K) {
-    const int lane = threadIdx.x & 63;
-    const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (n >= N) return;
-    const WT* __restrict__ w = W + (int64_t)n * K;
-    for (int r0 = 0; r0 < R; r0 += 8) {
-        float acc[8];
+#define GF_WAVES 8
+template <bool VEC, typename T>
+__device__ __forceinline__ f32x4 gf_load4(const T* __restrict__ row, int k, int K, bool live) {
+    f32x4 v = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if constexpr (VEC) {
+        if (live && k < K) {
+            if constexpr (sizeof(T) == 4) {
+                v = *reinterpret_cast<const f32x4*>(row + k);
+            } else {
+                const bf16x4 t = *reinterpret_cast<const bf16x4*>(row + k);
 #pragma unroll
-        for (int u = 0; u < 8; ++u) acc[u] = 0.f;
-        for (int k = lane; k < K; k += 64) {
-            const float wv = cs_ld(w, k);
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (r0 + u < R) acc[u] += wv * cs_ld(X, (int64_t)(r0 + u) * K + k);
+                for (int j = 0; j < 4; ++j) v[j] = (float)t[j];
+            }
         }
+    } else {
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float t = cs_wave_sum(acc[u]);
-            if (lane == 0 && r0 + u < R) Y[(int64_t)(r0 + u) * N + n] = t;
-        }
+        for (int j = 0; j < 4; ++j)
+            if (live && k + j < K) v[j] = cs_ld(row, k + j);
     }
+    return v;
+}
+
+template <typename WT, int NT, bool VEC>
+__global__ __launch_bounds__(64 * GF_WAVES) void k_gemm_f32(const float* __restrict__ X,
+                                                            const WT* __restrict__ W, float* __restrict__ Y,
+                                                            int R, int N, int K) {
+    constexpr int AHEAD = 4;                      // pieces of K in flight per wave
+    __shared__ __attribute__((aligned(16))) f32x4 red[GF_WAVES][NT][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lrow = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16 * NT;
+    const bool w_live = n0 + lrow < N;
+    const WT* __restrict__ w = W + (int64_t)(w_live ? n0 + lrow : 0) * K;
+    bool x_live[NT];
+    const float* x[NT];
+    f32x4 acc[NT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+        const int r = r0 + nt * 16 + lrow;
+        x_live[nt] = r < R;
+        x[nt] = X + (int64_t)(x_live[nt] ? r : 0) * K;
+        acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    for (int k0 = 16 * wave; k0 < K; k0 += AHEAD * 16 * GF_WAVES) {
+        f32x4 a[AHEAD], b[AHEAD][NT];
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u) {
+            const int k = k0 + u * 16 * GF_WAVES + 4 * g;          // (pieces past K are zeros)
+            a[u] = gf_load4<VEC>(w, k, K, w_live);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) b[u][nt] = gf_load4<VEC>(x[nt], k, K, x_live[nt]);
+        }
+#pragma unroll
+        for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][nt][j], acc[nt], 0, 0, 0);
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) red[wave][nt][lane] = acc[nt];
+    __syncthreads();
+    if (wave >= NT) return;
+    // wave nt sums row tile nt: y[j] = Y[row r0 + nt*16 + lrow][col n0 + 4g + j]
+    f32x4 y = red[0][wave][lane];
+#pragma unroll
+    for (int u = 1; u < GF_WAVES; ++u) y += red[u][wave][lane];
+    const int r = r0 + wave * 16 + lrow;
+    if (r >= R) return;
+    float* __restrict__ out = Y + (int64_t)r * N + n0 + 4 * g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if (n0 + 4 * g + j < N) out[j] = y[j];
+}
+
+template <typename WT>
+static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K, hipStream_t s) {
+    const bool vec = K % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % (4 * sizeof(WT)) == 0;
+    const int nt = R <= 16 ? 1 : R <= 32 ? 2 : 4;
+    dim3 grid((unsigned)cs_ceil_div(N, 16), (unsigned)cs_ceil_div(R, 16 * nt));
+    auto start = [&](auto nt_tag) {
+        constexpr int NT = decltype(nt_tag)::value;
+        if (vec) k_gemm_f32<WT, NT, true><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K);
+        else k_gemm_f32<WT, NT, false><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K);
+    };
+    if (nt == 1) start(std::integral_constant<int, 1>{});
+    else if (nt == 2) start(std::integral_constant<int, 2>{});
+    else start(std::integral_constant<int, 4>{});
+    return cs_launch_ok("k_gemm_f32");
 }
 
 // -------------------------------------------------------------------------------------
@@ -811,15 +885,7 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
                    int mode, int allow_split, int* nparts_out, hipStream_t s) {
     if (nparts_out) *nparts_out = 1;
     if (R <= 0) return CS_OK;
-    if (!m->fast) {
-        if (m->cfg.dtype == CS_BF16)
-            k_gemm_plain<float, bf16_t><<<(unsigned)cs_ceil_div(N, 4), 256, 0, s>>>(
-                (const float*)X, (const bf16_t*)W, Y, R, N, K);
-        else
-            k_gemm_plain<float, float><<<(unsigned)cs_ceil_div(N, 4), 256, 0, s>>>(
-                (const float*)X, (const float*)W, Y, R, N, K);
-        return cs_launch_ok("k_gemm_plain");
-    }
+    if (!m->fast) return cs_gemm_plain_launch(m->cfg.dtype, (const float*)X, W, Y, R, N, K, s);
     CS_REQUIRE(mfma_shape_ok(N, K) && (mode != CS_GEMM_SWIGLU || N % 32 == 0), CS_E_UNSUPPORTED,
                "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
     // Shape of the launch.
@@ -883,11 +949,6 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
 int cs_gemm_plain_launch(int dtype, const float* X, const void* W, float* Y, int R, int N, int K,
                          hipStream_t s) {
     if (R <= 0) return CS_OK;
-    if (dtype == CS_BF16)
-        k_gemm_plain<float, bf16_t><<<(unsigned)cs_ceil_div(N, 4), 256, 0, s>>>(X, (const bf16_t*)W, Y,
-                                                                              R, N, K);
-    else
-        k_gemm_plain<float, float><<<(unsigned)cs_ceil_div(N, 4), 256, 0, s>>>(X, (const float*)W, Y,
-                                                                             R, N, K);
-    return cs_launch_ok("k_gemm_plain");
+    return dtype == CS_BF16 ? launch_f32(X, (const bf16_t*)W, Y, R, N, K, s)
+                            : launch_f32(X, (const float*)W, Y, R, N, K, s);
 }

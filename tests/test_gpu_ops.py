@@ -143,6 +143,28 @@ def test_gemm_f32_plain(host_model):
     assert np.abs(Y.cpu().numpy() - ref).max() < 1e-4
 
 
+@pytest.mark.parametrize("R,N,K", [(1, 97, 64), (11, 777, 256), (16, 16, 4), (17, 250, 1030), (33, 64, 7), (70, 33, 516),
+                                   (511, 256, 1024), (5, 31, 1)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_gemm_f32_edges(host_model, R, N, K, shift):
+    """The float32 kernel at the edges of its tiles: one, two and four row tiles, ragged last rows and
+    columns, K below one piece and no multiple of four, operands that are not 16-byte aligned (shift).
+    Bound: a sum of K float32 products in any order is within K roundings of sum |x||w|."""
+    rng = np.random.default_rng(R * 1000 + N + K)
+    X = rng.standard_normal((R, K)).astype(np.float32)
+    W = rng.standard_normal((N, K)).astype(np.float32)
+
+    def dev(a):
+        buf = torch.empty(a.size + shift, dtype=torch.float32, device=DEV)
+        buf[shift:].copy_(torch.from_numpy(a.ravel()))
+        return buf[shift:].view(a.shape)
+
+    Y = cs.cs_op_gemm(host_model, dev(X), dev(W)).cpu().numpy()
+    ref = X.astype(np.float64) @ W.astype(np.float64).T
+    bound = (K + 16) * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(W).astype(np.float64).T)
+    assert (np.abs(Y - ref) <= bound).all()
+
+
 # ----------------------------------------------------------------------------------------
 # block attention
 # ----------------------------------------------------------------------------------------
