@@ -738,20 +738,30 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
         load(1, 4);
         __syncthreads();                                   // stages 0, 1 and the query tiles are ready
         static_assert(FA_STAGES == 3, "block j: register slot j % 3, LDS stage j % 3");
-        for (int i = 0; i < nblocks_wg; i += 3) {
-            // consumer iteration i reads stages i and i+1: block i+2 goes to stage (i+2)%3, which
-            // held block i-1; its register slot is refilled with block i+5, so blocks i+3, i+4
-            // and i+5 (48 KB) are in flight while block i is being multiplied
+        // Consumer iteration i reads stages i and i+1: block i+2 goes to stage (i+2)%3, which
+        // held block i-1; its register slot is refilled with block i+5, so blocks i+3, i+4
+        // and i+5 (48 KB) are in flight while block i is being multiplied.  The loop has no way out in
+        // the middle (the last one or two iterations follow it): with one, the compiler could not tell at
+        // the loop's head which loads were the newest and drained them all once per trip (16 streams,
+        // 16384 rows, 132 query rows: 243.8 -> 237.5 us; 16000 rows 220.9 -> 214.1).
+        int i = 0;
+        for (; i + 3 <= nblocks_wg; i += 3) {
             store(2, 2, i + 2);
             load(2, i + 5);
             __syncthreads();
-            if (i + 1 >= nblocks_wg) break;
             store(0, 0, i + 3);
             load(0, i + 6);
             __syncthreads();
-            if (i + 2 >= nblocks_wg) break;
             store(1, 1, i + 4);
             load(1, i + 7);
+            __syncthreads();
+        }
+        if (i < nblocks_wg) {
+            store(2, 2, i + 2);
+            __syncthreads();
+        }
+        if (i + 1 < nblocks_wg) {
+            store(0, 0, i + 3);
             __syncthreads();
         }
         return;
