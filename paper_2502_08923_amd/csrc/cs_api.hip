@@ -660,8 +660,8 @@ static int kv_check_room(cs_kv* kv, int rows) {
     return CS_OK;
 }
 
-// m->tok holds the block tokens; runs all layers; leaves the final-normed rows in m->xn
-static int forward_layers(cs_model* m, cs_kv* kv, int rows, hipStream_t s) {
+// runs all layers over the block tokens of `src`; leaves the final-normed rows in m->xn
+static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int rows, hipStream_t s) {
     const cs_model_cfg& c = m->cfg;
     const int B = kv->B, R = B * rows;
     const int d = c.d_model, nq = c.n_heads * c.head_dim, nqkv = nq + 2 * c.n_kv_heads * c.head_dim;
@@ -669,8 +669,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, int rows, hipStream_t s) {
     CS_REQUIRE(m->head_loaded && m->layers_loaded == c.n_layers, CS_E_STATE,
                "the model is not complete: %d of %d layers loaded, embedding and lm_head %s", m->layers_loaded,
                c.n_layers, m->head_loaded ? "loaded" : "missing");
-    CS_TRY(cs_rope_table_launch(m, kv->d_len, B, rows, s));
-    CS_TRY(cs_embed_launch(m, m->tok, R, s));
+    CS_TRY(cs_block_start_launch(m, src, kv->d_len, B, rows, s));
     int np_prev = 0, np = 1;
     // narrow blocks: the attention kernel rotates q and k and appends k, v itself
     const bool fuse_rope = cs_attention_fuses_rope(m, rows);
@@ -699,14 +698,17 @@ static int forward_layers(cs_model* m, cs_kv* kv, int rows, hipStream_t s) {
     return cs_addnorm_launch(m, m->part, np_prev, m->final_norm, m->xn, R, c.vocab, false, s);
 }
 
+// the block tokens are in m->tok
+static cs_block_src prompt_src(const cs_model* m) { return {m->tok, nullptr, nullptr, 0, nullptr, nullptr, nullptr}; }
+
 static int verify_impl(cs_model* m, cs_kv* kv, const int32_t* d_pending, const int32_t* d_draft,
                        const int32_t* d_draft_len, int k, int32_t* d_accepted, int32_t* d_next,
                        float* d_logits_out, int32_t* hist, int64_t hist_stride, int32_t* hist_len,
                        int32_t* room, hipStream_t s) {
     const int rows = k + 1, B = kv->B, R = B * rows, V = m->cfg.vocab;
     CS_TRY(kv_check_room(kv, rows));
-    CS_TRY(cs_tokens_launch(m, d_pending, d_draft, d_draft_len, B, k, s));
-    CS_TRY(forward_layers(m, kv, rows, s));
+    const cs_block_src src = {nullptr, d_pending, hist, hist_stride, hist_len, d_draft, d_draft_len};
+    CS_TRY(forward_layers(m, kv, src, rows, s));
     const int pl = cs_prof_begin(CS_PROF_LMHEAD, s);
     if (m->fast && !d_logits_out) {
         // nobody wants the logits: the lm_head keeps them in its accumulators and hands over the
@@ -767,11 +769,10 @@ extern "C" int cs_step(cs_model* m, cs_kv* kv, int32_t* d_hist, int64_t stride, 
     } else {
         CS_TRY(cs_fill_i32_launch(m->draft_len, 0, B, s));
     }
-    k_pending<<<(unsigned)cs_ceil_div(B, 64), 64, 0, s>>>(d_hist, stride, d_hist_len, B, m->pending);
-    CS_TRY(cs_launch_ok("k_pending"));
     if (d_draft_len_out)
         CS_HIP(hipMemcpyAsync(d_draft_len_out, m->draft_len, (size_t)B * 4, hipMemcpyDeviceToDevice, s));
-    return verify_impl(m, kv, m->pending, m->draft, m->draft_len, k, d_accepted_len, d_next_token,
+    // (no pending array: the last token of each history)
+    return verify_impl(m, kv, nullptr, m->draft, m->draft_len, k, d_accepted_len, d_next_token,
                        nullptr, d_hist, stride, d_hist_len, d_room, s);
 }
 
@@ -795,7 +796,7 @@ extern "C" int cs_prefill(cs_model* m, cs_kv* kv, int32_t stream_idx, const int3
     for (int64_t c0 = 0; c0 < body; c0 += chunk) {
         const int rows = (int)(body - c0 < chunk ? body - c0 : chunk);
         CS_HIP(hipMemcpyAsync(m->tok, prompt + c0, (size_t)rows * 4, hipMemcpyHostToDevice, nullptr));
-        CS_TRY(forward_layers(m, kv, rows, nullptr));
+        CS_TRY(forward_layers(m, kv, prompt_src(m), rows, nullptr));
         k_add_i32<<<1, 64, 0, nullptr>>>(kv->d_len, rows, 1);
         CS_TRY(cs_launch_ok("k_add_i32"));
         kv->h_len_ub[0] += rows;
@@ -1007,7 +1008,7 @@ extern "C" int cs_prefill_batch(cs_model* m, cs_kv* kv, const int32_t* prompts, 
             rc = CS_E_DEVICE;
             break;
         }
-        rc = forward_layers(m, kv, rows, nullptr);
+        rc = forward_layers(m, kv, prompt_src(m), rows, nullptr);
         if (rc != CS_OK) break;
         k_add_i32_vec<<<(unsigned)cs_ceil_div(B, 64), 64, 0, nullptr>>>(kv->d_len, d_inc, B);
         rc = cs_launch_ok("k_add_i32_vec");
@@ -1134,7 +1135,7 @@ extern "C" int cs_decode_merged(cs_model* m, cs_kv* kv, cs_model* dm, cs_kv* dkv
                 const int64_t left = n - 1 - draft_rows;
                 const int rows = (int)(left < dm->prefill_rows ? left : dm->prefill_rows);
                 CS_HIP(hipMemcpyAsync(dm->tok, d + draft_rows, (size_t)rows * 4, hipMemcpyDeviceToDevice, s));
-                CS_TRY(forward_layers(dm, dkv, rows, s));
+                CS_TRY(forward_layers(dm, dkv, prompt_src(dm), rows, s));
                 k_add_i32<<<1, 64, 0, s>>>(dkv->d_len, rows, 1);
                 CS_TRY(cs_launch_ok("k_add_i32"));
                 dkv->h_len_ub[0] += rows;

@@ -102,7 +102,7 @@ struct cs_model {
     size_t attn_part_floats;
     float2* rope;       // [R][hd/2] (cos, sin) of every block row's position
     double* rope_inv_freq;   // [hd/2] rotary frequencies of the model's own (device), or NULL
-    int32_t* tok;       // [R] token of every block row
+    int32_t* tok;       // [R] tokens of a prompt block
     int32_t* am_val_idx;// argmax partials: [R][chunks] (float bits, idx) pairs
     int32_t* row_argmax;// [R]
     int32_t* draft;     // [B][max_k]   (cs_step scratch)
@@ -141,8 +141,20 @@ int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, 
 int cs_scan_stream_keys(size_t need, hipStream_t s, int64_t** out);
 
 // elementwise / small
-int cs_embed_launch(const cs_model* m, const int32_t* tok, int R, hipStream_t s);
-int cs_rope_table_launch(const cs_model* m, const int32_t* kv_len, int B, int rows, hipStream_t s);
+// Where the tokens of a block come from: `tok` [B*rows] if given (prompts); else row 0 of stream b is
+// pending[b], or the last token of its history where `pending` is NULL, and row i is draft[b][i-1].
+struct cs_block_src {
+    const int32_t* tok;
+    const int32_t* pending;
+    const int32_t* hist;        // [B][hist_stride]
+    int64_t hist_stride;
+    const int32_t* hist_len;
+    const int32_t* draft;       // [B][rows - 1]
+    const int32_t* draft_len;
+};
+// block tokens -> m->x (embeddings), m->rope (angles of every row's position)
+int cs_block_start_launch(const cs_model* m, const cs_block_src& src, const int32_t* kv_len, int B, int rows,
+                          hipStream_t s);
 // x[r] += sum of nparts partial tiles (part[p][r][:]) and, if xn_out, xn_out[r] = rmsnorm(x[r])*gain
 // (next_N, next_split: output width of the GEMM that reads xn_out and whether it may split K; they decide
 // the layout of xn_out)
@@ -151,8 +163,6 @@ int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
 int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* qkv, int nparts,
                           int rows, hipStream_t s);
 int cs_swiglu_launch(const cs_model* m, int R, hipStream_t s);
-int cs_tokens_launch(const cs_model* m, const int32_t* pending, const int32_t* draft,
-                     const int32_t* draft_len, int B, int k, hipStream_t s);
 // accept rule, state update from the argmax partials m->am_val_idx[row][nch]
 int cs_accept_launch(const cs_model* m, int nch, int B, int k, const int32_t* draft,
                      const int32_t* draft_len, int32_t* accepted, int32_t* next_tok,

@@ -1,51 +1,54 @@
-// Small kernels of the verify pass: block tokens + rotary table, embedding gather,
+// Small kernels of the verify pass: block start (tokens, embedding gather, rotary table),
 // residual-add + RMSNorm, rotary + KV append, SwiGLU, greedy argmax + accept rule + KV
 // length update + history append (Sec. 3.2, App. B.2, App. B.3 step 2).
 #include "cs_common.h"
 #include <type_traits>
 
 // -------------------------------------------------------------------------------------
-// block tokens and rotary table
-//   row r = b*(k+1) + i : token = pending[b] (i == 0) or draft[b][i-1] (i <= draft_len[b])
+// start of a forward pass, one workgroup per block row r = b*rows + i:
+//   token: given, or pending[b] (the last token of the history, i == 0) / draft[b][i-1] (i <= draft_len[b])
+//   x[r][:] = embed[token][:]
 //   rope[r][j] = (cos, sin)(pos * theta^(-2j/hd)),  pos = kv_len[b] + i, in float64
+// All of it is launch and load latency (a few KB per row), so it is one launch, not four (11 rows, 8B width:
+// 4.4 + 4.1 + 4.5 + 9.2 us and the gaps between them -> 5.7 us), and a row is copied four elements at a
+// time.
 // -------------------------------------------------------------------------------------
-__global__ void k_tokens(const int32_t* __restrict__ pending, const int32_t* __restrict__ draft,
-                         const int32_t* __restrict__ draft_len, int k, int V,
-                         int32_t* __restrict__ tok) {
-    const int b = blockIdx.x;
-    const int rows = k + 1;
-    for (int i = threadIdx.x; i < rows; i += blockDim.x) {
-        int t = 0;
-        if (i == 0) t = pending[b];
-        else if (i - 1 < draft_len[b]) t = draft[(int64_t)b * k + i - 1];
-        if (t < 0 || t >= V) t = 0;   // an out-of-vocabulary draft can never be accepted
-        tok[b * rows + i] = t;
-    }
+#define START_THREADS 256
+__device__ __forceinline__ float4 start_load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 start_load4(const bf16_t* p) {
+    const bf16x4 t = *reinterpret_cast<const bf16x4*>(p);
+    return make_float4((float)t[0], (float)t[1], (float)t[2], (float)t[3]);
 }
-
-__global__ void k_rope_table(const int32_t* __restrict__ kv_len, int rows, int half, int hd,
-                             double theta, const double* __restrict__ inv_freq,
-                             float2* __restrict__ rope) {
+template <typename WT>
+__global__ __launch_bounds__(START_THREADS) void k_block_start(cs_block_src src, int rows, int V,
+                                                               const WT* __restrict__ embed, int d,
+                                                               float* __restrict__ x,
+                                                               const int32_t* __restrict__ kv_len, int half,
+                                                               double theta, const double* __restrict__ inv_freq,
+                                                               float2* __restrict__ rope) {
     const int r = blockIdx.x;
     const int b = r / rows, i = r % rows;
+    int t = 0;
+    if (src.tok) {
+        t = src.tok[r];
+    } else if (i == 0) {
+        // (an empty history has no pending token: token 0 keeps the block well-formed)
+        if (src.pending) t = src.pending[b];
+        else if (src.hist_len[b] >= 1) t = src.hist[(int64_t)b * src.hist_stride + src.hist_len[b] - 1];
+    } else if (i - 1 < src.draft_len[b]) {
+        t = src.draft[(int64_t)b * (rows - 1) + i - 1];
+    }
+    if (t < 0 || t >= V) t = 0;   // an out-of-vocabulary draft can never be accepted
+    const WT* __restrict__ e = embed + (int64_t)t * d;
+    for (int c = 4 * threadIdx.x; c < d; c += 4 * START_THREADS)      // d is a multiple of 4 (checked on the host)
+        *reinterpret_cast<float4*>(x + (int64_t)r * d + c) = start_load4(e + c);
     const double pos = (double)(kv_len[b] + i);
-    for (int j = threadIdx.x; j < half; j += blockDim.x) {
-        const double inv = inv_freq ? inv_freq[j] : pow(theta, -2.0 * (double)j / (double)hd);
+    for (int j = threadIdx.x; j < half; j += START_THREADS) {
+        const double inv = inv_freq ? inv_freq[j] : pow(theta, -2.0 * (double)j / (double)(2 * half));
         double sn, cs;
         sincos(pos * inv, &sn, &cs);
         rope[(int64_t)r * half + j] = make_float2((float)cs, (float)sn);
     }
-}
-
-// -------------------------------------------------------------------------------------
-// embedding gather: x[r][:] = embed[tok[r]][:]
-// -------------------------------------------------------------------------------------
-template <typename WT>
-__global__ void k_embed(const WT* __restrict__ embed, const int32_t* __restrict__ tok, int d,
-                        float* __restrict__ x) {
-    const int r = blockIdx.x;
-    const WT* __restrict__ e = embed + (int64_t)tok[r] * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) x[(int64_t)r * d + c] = cs_ld(e, c);
 }
 
 // -------------------------------------------------------------------------------------
@@ -420,24 +423,18 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
 // -------------------------------------------------------------------------------------
 // host launchers
 // -------------------------------------------------------------------------------------
-int cs_tokens_launch(const cs_model* m, const int32_t* pending, const int32_t* draft,
-                     const int32_t* draft_len, int B, int k, hipStream_t s) {
-    k_tokens<<<B, 64, 0, s>>>(pending, draft, draft_len, k, m->cfg.vocab, m->tok);
-    return cs_launch_ok("k_tokens");
-}
-
-int cs_rope_table_launch(const cs_model* m, const int32_t* kv_len, int B, int rows, hipStream_t s) {
-    k_rope_table<<<B * rows, 64, 0, s>>>(kv_len, rows, m->cfg.head_dim / 2, m->cfg.head_dim,
-                                         (double)m->cfg.rope_theta, m->rope_inv_freq, m->rope);
-    return cs_launch_ok("k_rope_table");
-}
-
-int cs_embed_launch(const cs_model* m, const int32_t* tok, int R, hipStream_t s) {
-    if (m->cfg.dtype == CS_BF16)
-        k_embed<bf16_t><<<R, 256, 0, s>>>((const bf16_t*)m->embed, tok, m->cfg.d_model, m->x);
+int cs_block_start_launch(const cs_model* m, const cs_block_src& src, const int32_t* kv_len, int B, int rows,
+                          hipStream_t s) {
+    const cs_model_cfg& c = m->cfg;
+    if (c.dtype == CS_BF16)
+        k_block_start<bf16_t><<<B * rows, START_THREADS, 0, s>>>(src, rows, c.vocab, (const bf16_t*)m->embed, c.d_model,
+                                                                 m->x, kv_len, c.head_dim / 2, (double)c.rope_theta,
+                                                                 m->rope_inv_freq, m->rope);
     else
-        k_embed<float><<<R, 256, 0, s>>>((const float*)m->embed, tok, m->cfg.d_model, m->x);
-    return cs_launch_ok("k_embed");
+        k_block_start<float><<<B * rows, START_THREADS, 0, s>>>(src, rows, c.vocab, (const float*)m->embed, c.d_model,
+                                                                m->x, kv_len, c.head_dim / 2, (double)c.rope_theta,
+                                                                m->rope_inv_freq, m->rope);
+    return cs_launch_ok("k_block_start");
 }
 
 int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
