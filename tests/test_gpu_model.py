@@ -166,6 +166,32 @@ def test_narrow_blocks_over_short_and_ragged_caches(shape, k):
     model.destroy()
 
 
+@pytest.mark.parametrize("shape", [MINI64, SMALLF32])
+def test_logits_into_an_unaligned_buffer(shape):
+    """The logits of a verify call whose output buffer is only 4-byte aligned equal those of an aligned one."""
+    w = synth.model_weights(shape, 4245, threads=4)
+    model = cs.Model(w, max_batch=1, max_k=3)
+    kv = cs.KV(model, 1, 128)
+    prompt = np.random.default_rng(24).integers(0, shape.vocab, 40).tolist()
+    cs.cs_prefill(model, kv, 0, prompt)
+    pending, draft, dlen = t32([prompt[-1]]), t32([[1, 2, 3]]), t32([3])
+    out = []
+    for shift in (0, 1):
+        kv.set_len(0, 39)
+        buf = torch.full((4 * shape.vocab + 8,), float("nan"), dtype=torch.float32, device=DEV)
+        acc, nxt = t32([0]), t32([0])
+        rc = cs.load_library().cs_verify(model.handle, kv.handle, pending.data_ptr(), draft.data_ptr(), dlen.data_ptr(), 3,
+                                         acc.data_ptr(), nxt.data_ptr(), buf[shift:].data_ptr(), None)
+        torch.cuda.synchronize()
+        assert rc == 0
+        view = buf[shift:shift + 4 * shape.vocab]
+        assert torch.isfinite(view).all() and torch.isnan(buf[shift + 4 * shape.vocab:]).all()
+        out.append((int(acc[0]), int(nxt[0]), view.clone()))
+    assert out[0][:2] == out[1][:2] and torch.equal(out[0][2], out[1][2])
+    kv.destroy()
+    model.destroy()
+
+
 def test_five_wave_tiles_in_every_epilogue():
     """A model whose gate/up and lm_head widths send both to 160-row W tiles: SwiGLU and argmax epilogues
     against the oracle, and the tokens with and without stored logits."""
