@@ -99,7 +99,7 @@ def test_gemm_row_sweep(host_model, N, K, R):
     """Row counts between the two regimes.  The 193 W tiles of the 49168-row matrix send every
     row count above 96 to the many-row kernel (each of its row-tile counts, one and two row
     blocks, ragged last tiles in both dimensions, K of one and of four pipeline trips); the
-    q/k/v shape switches kernels at 289 rows and is split along K."""
+    q/k/v shape switches kernels by estimated time below 289 rows and is split along K."""
     _gemm_case(host_model, N, K, R)
 
 
