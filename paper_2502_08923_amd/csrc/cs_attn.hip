@@ -1470,6 +1470,8 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const int max_split = (int)cs_ceil_div(n_tok_ub, 4 * 128) > few ? (int)cs_ceil_div(n_tok_ub, 4 * 128) : few;
     if (nsplit > max_split) nsplit = max_split;
     if (nsplit > FA_MAX_SPLIT) nsplit = FA_MAX_SPLIT;
+    // a workgroup's range is addressed with 31-bit byte offsets: at most 2^22 tokens of 256 bytes
+    if (nsplit < cs_ceil_div(n_tok_ub, (int64_t)1 << 22)) nsplit = (int)cs_ceil_div(n_tok_ub, (int64_t)1 << 22);
     if (nsplit < 1) nsplit = 1;
     const int Tw = (int)cs_round_up(cs_ceil_div(n_tok_ub, (int64_t)nsplit * 4), 32);
     nsplit = (int)cs_ceil_div(n_tok_ub, (int64_t)Tw * 4);
