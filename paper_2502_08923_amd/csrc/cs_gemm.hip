@@ -21,11 +21,16 @@
 //
 // Small models: launch and load latency bound it, not the matrix rate (o and down of a 256-wide model, 11 rows:
 // 87 us with a wave per W row that walked K 64 scalars at a time, 5 us now).  A workgroup owns 16 W rows
-// by 16*NT block rows; its eight waves take the 16-wide pieces of K in turn, four pieces of loads in
+// by 16*NT block rows; its eight waves take the 16-wide pieces of K in turn, two pieces of loads in
 // flight each, straight into the operands of v_mfma_f32_16x16x4_f32 (float32 products and sums; lane l
-// holds row l % 16, and element j of its four is k = 4 * (l / 16) + j in both operands), and the eight
-// partial sums are added through LDS in wave order.  VEC: K % 4 == 0 and both operands aligned to four
-// elements; otherwise the same kernel loads single elements.
+// holds row l % 16, and element j of its four is k = 4 * (l / 16) + j in both operands).  The instruction
+// rounds after each of its four products, so an accumulator is one chain of them: a wave keeps eight, for
+// chains of K / 64 products, and all partial sums are added in pairs, those of the waves through LDS.
+// Error against float64, N(0, 1) operands: 7.7e-8 at K = 256, 1.6e-7 at 4096, as with 64 lanes of K / 64 products
+// each (one chain of K / 8 per wave: 1.2e-7, 4.1e-7).  Two row tiles and two pieces ahead leave room for two
+// workgroups on a compute unit, four and four for one (4096 x 4096, 300 rows: 214 us, as much with four and
+// four; 128256 x 256, 65 rows: 158 against 279).  VEC: K % 4 == 0 and both operands aligned to four elements;
+// otherwise the same kernel loads single elements.
 // -------------------------------------------------------------------------------------
 #define GF_WAVES 8
 template <bool VEC, typename T>
@@ -53,22 +58,24 @@ template <typename WT, int NT, bool VEC>
 __global__ __launch_bounds__(64 * GF_WAVES) void k_gemm_f32(const float* __restrict__ X,
                                                             const WT* __restrict__ W, float* __restrict__ Y,
                                                             int R, int N, int K) {
-    constexpr int AHEAD = 4;                      // pieces of K in flight per wave
+    constexpr int AHEAD = 2;                      // pieces of K in flight per wave
     __shared__ __attribute__((aligned(16))) f32x4 red[GF_WAVES][NT][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lrow = lane & 15, g = lane >> 4;
     const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16 * NT;
     const bool w_live = n0 + lrow < N;
     const WT* __restrict__ w = W + (int64_t)(w_live ? n0 + lrow : 0) * K;
+    constexpr int CHAINS = 4 * AHEAD;             // accumulators of a wave per row tile
     bool x_live[NT];
     const float* x[NT];
-    f32x4 acc[NT];
+    f32x4 acc[CHAINS][NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int r = r0 + nt * 16 + lrow;
         x_live[nt] = r < R;
         x[nt] = X + (int64_t)(x_live[nt] ? r : 0) * K;
-        acc[nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < CHAINS; ++c) acc[c][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
     }
     for (int k0 = 16 * wave; k0 < K; k0 += AHEAD * 16 * GF_WAVES) {
         f32x4 a[AHEAD], b[AHEAD][NT];
@@ -84,17 +91,30 @@ __global__ __launch_bounds__(64 * GF_WAVES) void k_gemm_f32(const float* __restr
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    acc[nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][nt][j], acc[nt], 0, 0, 0);
+                for (int nt = 0; nt < NT; ++nt) {
+                    f32x4& o = acc[4 * u + j][nt];
+                    o = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][nt][j], o, 0, 0, 0);
+                }
     }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) red[wave][nt][lane] = acc[nt];
+    for (int nt = 0; nt < NT; ++nt) {
+#pragma unroll
+        for (int h = CHAINS / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int c = 0; c < h; ++c) acc[c][nt] += acc[c + h][nt];
+        red[wave][nt][lane] = acc[0][nt];
+    }
     __syncthreads();
     if (wave >= NT) return;
     // wave nt sums row tile nt: y[j] = Y[row r0 + nt*16 + lrow][col n0 + 4g + j]
-    f32x4 y = red[0][wave][lane];
+    f32x4 part[GF_WAVES];
 #pragma unroll
-    for (int u = 1; u < GF_WAVES; ++u) y += red[u][wave][lane];
+    for (int u = 0; u < GF_WAVES; ++u) part[u] = red[u][wave][lane];
+#pragma unroll
+    for (int h = GF_WAVES / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int u = 0; u < h; ++u) part[u] += part[u + h];
+    const f32x4 y = part[0];
     const int r = r0 + wave * 16 + lrow;
     if (r >= R) return;
     float* __restrict__ out = Y + (int64_t)r * N + n0 + 4 * g;
@@ -106,7 +126,7 @@ __global__ __launch_bounds__(64 * GF_WAVES) void k_gemm_f32(const float* __restr
 template <typename WT>
 static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K, hipStream_t s) {
     const bool vec = K % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % (4 * sizeof(WT)) == 0;
-    const int nt = R <= 16 ? 1 : R <= 32 ? 2 : 4;
+    const int nt = R <= 16 ? 1 : 2;
     dim3 grid((unsigned)cs_ceil_div(N, 16), (unsigned)cs_ceil_div(R, 16 * nt));
     auto start = [&](auto nt_tag) {
         constexpr int NT = decltype(nt_tag)::value;
@@ -114,8 +134,7 @@ static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K
         else k_gemm_f32<WT, NT, false><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K);
     };
     if (nt == 1) start(std::integral_constant<int, 1>{});
-    else if (nt == 2) start(std::integral_constant<int, 2>{});
-    else start(std::integral_constant<int, 4>{});
+    else start(std::integral_constant<int, 2>{});
     return cs_launch_ok("k_gemm_f32");
 }
 

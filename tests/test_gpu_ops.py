@@ -147,7 +147,7 @@ def test_gemm_f32_plain(host_model):
                                    (511, 256, 1024), (5, 31, 1)])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_gemm_f32_edges(host_model, R, N, K, shift):
-    """The float32 kernel at the edges of its tiles: one, two and four row tiles, ragged last rows and
+    """The float32 kernel at the edges of its tiles: one row tile, two and more, ragged last rows and
     columns, K below one piece and no multiple of four, operands that are not 16-byte aligned (shift).
     Bound: a sum of K float32 products in any order is within K roundings of sum |x||w|."""
     rng = np.random.default_rng(R * 1000 + N + K)
@@ -163,6 +163,29 @@ def test_gemm_f32_edges(host_model, R, N, K, shift):
     ref = X.astype(np.float64) @ W.astype(np.float64).T
     bound = (K + 16) * 2.0 ** -24 * (np.abs(X).astype(np.float64) @ np.abs(W).astype(np.float64).T)
     assert (np.abs(Y - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("R,N,K", [(5, 300, 64), (11, 256, 256), (40, 512, 1024), (100, 256, 4096), (16, 640, 1030)])
+def test_gemm_f32_error_of_short_chains(host_model, R, N, K):
+    """The rounding error of the float32 kernel against float64 is no larger than that of a sum over 64 interleaved
+    chains of K / 64 fused multiply-adds, added in pairs (root mean square over at least 1500 outputs, so 10 % is
+    about four times its sampling error)."""
+    rng = np.random.default_rng(R + N + K)
+    X = rng.standard_normal((R, K)).astype(np.float32)
+    W = rng.standard_normal((N, K)).astype(np.float32)
+    Y = cs.cs_op_gemm(host_model, torch.from_numpy(X).to(DEV), torch.from_numpy(W).to(DEV)).cpu().numpy()
+    x64, w64 = X.astype(np.float64), W.astype(np.float64)
+    ref = x64 @ w64.T
+    acc = np.zeros((64, R, N), dtype=np.float32)
+    for k0 in range(0, K, 64):              # (a product of two float32 is exact in float64)
+        for lane in range(min(64, K - k0)):
+            acc[lane] = acc[lane].astype(np.float64) + np.outer(x64[:, k0 + lane], w64[:, k0 + lane])
+    half = 32
+    while half:
+        acc[:half] += acc[half:2 * half]
+        half //= 2
+    rms = lambda e: float(np.sqrt(np.mean(np.square(e))))
+    assert rms(Y - ref) <= 1.1 * rms(acc[0] - ref), (rms(Y - ref), rms(acc[0] - ref))
 
 
 # ----------------------------------------------------------------------------------------
