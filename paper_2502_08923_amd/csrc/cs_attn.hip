@@ -249,11 +249,16 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
     // blocks are requested only after the barrier that follows.
     const int64_t head0 = (int64_t)b * KVH + kvh;
     const int n_range = (t_end - w_begin + 31) & ~31;          // a masked block may reach past t_end, into dead rows
+    // V's buffer counts at least one 128-token block, also for an empty range (a split past the end of a short
+    // stream): the range check compares the offset with the size minus the scalar offset, which must not be
+    // negative.  Nothing is read there, every offset of an empty range is NOWHERE.
+    const int v_blocks = max(1, (n_range + CS_VBLK - 1) / CS_VBLK);
+    static_assert((MT - 1) * 16 * CS_VBLK < HD * CS_VBLK, "scalar offsets of a V block stay inside it");
     const auto krsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)((FUSE ? fr.kc_w : kc) + (head0 * cap + w_begin) * HD), 0, n_range * HD * 2, FA_BUFFER_WORD3);
     const auto vrsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)((FUSE ? fr.vc_w : vc) + head0 * HD * cap + cs_v_index(w_begin, 0, HD)), 0,
-        ((n_range + CS_VBLK - 1) / CS_VBLK) * CS_VBLK * HD * 2, FA_BUFFER_WORD3);
+        v_blocks * CS_VBLK * HD * 2, FA_BUFFER_WORD3);
     constexpr unsigned NOWHERE = 0x80000000u;
     // K tile a, MFMA row m=c  <->  token t0 + 8*(c/4) + 4a + c%4
     const unsigned klane = ((8 * (c >> 2) + (c & 3)) * HD + g * 8) * 2;

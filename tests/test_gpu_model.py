@@ -166,6 +166,43 @@ def test_narrow_blocks_over_short_and_ragged_caches(shape, k):
     model.destroy()
 
 
+def _ragged_verify(shape, lens, k, check, seed):
+    """One block of every stream over caches of the given lengths; the streams in `check` against the oracle."""
+    w = synth.model_weights(shape, seed, threads=4)
+    model = cs.Model(w, max_batch=len(lens), max_k=k)
+    kv = cs.KV(model, len(lens), max(lens) + k + 8)
+    rng = np.random.default_rng(seed + k)
+    pending = rng.integers(0, shape.vocab, len(lens))
+    draft = rng.integers(0, shape.vocab, (len(lens), k))
+    rows = {}
+    for b, n in enumerate(lens):
+        for layer in range(shape.n_layers):
+            if n:
+                rows[b, layer] = synth.random_kv(shape, n, seed, layer, b)
+                kv.load(layer, b, 0, *rows[b, layer])
+        kv.set_len(b, n)
+    acc, nxt, logits = cs.cs_verify(model, kv, t32(pending), t32(draft), t32([k] * len(lens)), k, want_logits=True)
+    torch.cuda.synchronize()
+    for b in check:
+        okv = orc.KVCache(shape, lens[b] + k + 8)
+        for layer in range(shape.n_layers):
+            if lens[b]:
+                okv.load(layer, *rows[b, layer])
+        okv.truncate(lens[b])
+        _, _, ologits = orc.verify(w, okv, int(pending[b]), draft[b].tolist())
+        assert np.abs(logits[b].cpu().numpy() - ologits).max() <= tol_for(shape), b
+    kv.destroy()
+    model.destroy()
+
+
+@pytest.mark.parametrize("shape", [MINI64, MINI128])
+@pytest.mark.parametrize("k", [0, 5, 10])
+def test_short_streams_beside_a_long_one(shape, k):
+    """Token ranges past the end of a stream: the long stream's splits leave the short and the empty one with ranges
+    that hold no token, or new rows alone."""
+    _ragged_verify(shape, (1500, 0, 3, 190), k, range(4), seed=4246)
+
+
 @pytest.mark.parametrize("shape", [MINI64, SMALLF32])
 def test_logits_into_an_unaligned_buffer(shape):
     """The logits of a verify call whose output buffer is only 4-byte aligned equal those of an aligned one."""
