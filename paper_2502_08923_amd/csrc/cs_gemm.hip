@@ -895,7 +895,8 @@ static mfma_shape gemm_plan(int R, int N, int K, bool may_split) {
     const double tile_us = tile_plan(R, N, K, may_split, &t.r_blocks, &t.ksplit);
     if (R > 288 || cs_ceil_div(N, TG_WROWS) >= 192) return t;
     const mfma_shape p = mfma_plan(R, N, K, may_split);
-    return R > 128 && tile_us < mfma_us(R, N, K, p) ? t : p;
+    const bool tile_fits = ((int64_t)R + 15) * K < ((int64_t)1 << 31);      // (launch_tile refuses more)
+    return R > 128 && tile_fits && tile_us < mfma_us(R, N, K, p) ? t : p;
 }
 
 bool cs_gemm_x_tiled(int R, int N, int K, bool may_split) { return gemm_plan(R, N, K, may_split).waves == 0; }

@@ -69,3 +69,13 @@ def test_product_path_does_not_import_the_oracle():
         if f.endswith(".py"):
             text = open(os.path.join(ROOT, "oracle", f)).read()
             assert "paper_2502_08923_amd" not in text and "libcopyspec" not in text
+
+
+@pytest.mark.parametrize("R,N,K", [(129, 1152, 16_000_000), (200, 2048, 10_000_128), (288, 8192, 8_000_000)])
+def test_rows_too_long_for_the_many_row_gemm_go_to_the_other_kernel(lib, R, N, K):
+    """Up to 288 rows a projection has two kernels; the one that refuses operands of 2^31 elements is not chosen for
+    them, however its estimated time compares."""
+    tiled = lib._Z15cs_gemm_x_tilediiib
+    tiled.restype = ctypes.c_bool
+    assert (R + 15) * K >= 2**31
+    assert not tiled(R, N, K, True) and not tiled(R, N, K, False)
