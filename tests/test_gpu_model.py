@@ -153,9 +153,9 @@ def test_verify_matches_oracle(shape, plain):
 @pytest.mark.parametrize("shape", [MINI64, MINI128])
 @pytest.mark.parametrize("k", [0, 3, 5, 10])
 def test_narrow_blocks_over_short_and_ragged_caches(shape, k):
-    """Block attention where its pipeline starts and ends: no, one and a few whole 32-token blocks per
-    wave, odd and even counts, new rows that straddle a block, a 128-token V block and a split, query
-    rows that fill one, two and three tiles."""
+    """Block attention before its pipeline runs more than one trip: waves with no 32-token block, one and two (masked ones, old
+    ones and old ones alone), new rows that straddle a block, a 128-token V block and a split, query rows that
+    fill one, two and three tiles."""
     w = synth.model_weights(shape, 4243, threads=4)
     model = cs.Model(w, max_batch=1, max_k=10)
     rng = np.random.default_rng(22)
@@ -201,6 +201,15 @@ def test_short_streams_beside_a_long_one(shape, k):
     """Token ranges past the end of a stream: the long stream's splits leave the short and the empty one with ranges
     that hold no token, or new rows alone."""
     _ragged_verify(shape, (1500, 0, 3, 190), k, range(4), seed=4246)
+
+
+@pytest.mark.parametrize("shape,k", [(MINI64, 3), (MINI64, 10), (MINI64, 20), (MINI128, 3), (MINI128, 7), (MINI128, 10)])
+@pytest.mark.parametrize("streams,n", [(1, 2100), (1, 2590), (1, 3500), (1, 4107), (16, 5000), (16, 5330)])
+def test_narrow_blocks_through_the_pipelined_loop(shape, k, streams, n):
+    """Block attention with one, two and three query tiles at both head sizes and two to six 32-token blocks per wave,
+    even and odd counts, old ones alone and followed by a masked one: refills of both K stages and both V stages, the
+    block left over after the loop.  (Sixteen streams leave eight splits for the long one, which is the one checked.)"""
+    _ragged_verify(shape, (n,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4247)
 
 
 @pytest.mark.parametrize("shape", [MINI64, SMALLF32])

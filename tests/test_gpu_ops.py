@@ -97,8 +97,7 @@ def test_gemm_bf16_full_shapes(host_model, N, K, R):
 @pytest.mark.parametrize("N,K", [(49168, 512), (49168, 128), (6144, 4096)])
 def test_gemm_row_sweep(host_model, N, K, R):
     """Row counts between the two regimes.  The 193 W tiles of the 49168-row matrix send every
-    row count above 96 to the many-row kernel (each of its row-tile counts, one and two row
-    blocks, ragged last tiles in both dimensions, K of one and of four pipeline trips); the
+    row count above 96 to the many-row kernel (7 to 17 X tiles, one and two row blocks, ragged last tiles in both dimensions, K of one and of four pipeline trips); the
     q/k/v shape switches kernels by estimated time below 289 rows and is split along K."""
     _gemm_case(host_model, N, K, R)
 
@@ -114,8 +113,23 @@ def test_gemm_prompt_rows(host_model, N, K, R):
 @pytest.mark.parametrize("R", [5, 88, 105, 112, 113, 128, 129, 200, 256, 257])
 @pytest.mark.parametrize("N,K", [(37888, 256), (33040, 128), (4096, 1024)])
 def test_gemm_wide_blocks_and_five_wave_tiles(host_model, N, K, R):
-    """The weight-streaming kernel with seven and eight X tiles in one and two row blocks, and with five
-    consumer waves (more than 256 tiles of 128 W rows, ragged last tile) next to four."""
+    """The weight-streaming kernel with five consumer waves (more than 256 tiles of 128 W rows, ragged last tile) and one to
+    eight X tiles over the one or two K chunks of its remainder loop, and with four waves and K splits."""
+    _gemm_case(host_model, N, K, R)
+
+
+@pytest.mark.parametrize("R", [190, 215, 235, 280])
+def test_gemm_row_tile_counts_between(host_model, R):
+    """The row-tile counts of the many-row kernel that the sweep above leaves out (12, 14, 15 and 18), which differ in
+    how many requests a wave counts per chunk; four pipeline trips."""
+    _gemm_case(host_model, 49168, 512, R)
+
+
+@pytest.mark.parametrize("R,N,K", [(R, N, K) for N, K in ((37888, 512), (33040, 640), (33040, 1408)) for R in (5, 88, 105, 128, 200, 256)]
+                         + [(105, 37888, 3584)])
+def test_gemm_five_wave_tiles_over_long_rows(host_model, R, N, K):
+    """Five consumer waves with 1, 6, 7 and 8 X tiles through the pipelined loop (four K chunks per trip): one trip, one and a
+    remainder of one, two and a remainder of three, and the 28 chunks of a 3584-wide model's gate/up."""
     _gemm_case(host_model, N, K, R)
 
 
@@ -445,6 +459,13 @@ def test_verify_qwen7b_width(B, k, L):
     (seven per KV head, so 11 block rows already need two 48-row query groups), d_model 3584,
     d_ff 18944, 152064-token vocabulary, q/k/v biases; 88 and 528 block rows and one stream."""
     worst = _deep_verify(QWEN_7B, B, L, k, [B - 1], seed=synth.seed_for(5) + 300 + k + B)
+    assert worst <= 2e-2, worst
+
+
+def test_verify_qwen7b_width_105_rows():
+    """105 block rows at the Qwen2.5-7B width: gate/up (with its SwiGLU epilogue) in one block of seven X tiles by five
+    consumer waves, lm_head with and without stored logits."""
+    worst = _deep_verify(QWEN_7B, 5, 300, 20, [4], seed=synth.seed_for(5) + 325)
     assert worst <= 2e-2, worst
 
 
