@@ -748,7 +748,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
         // and i+5 (48 KB) are in flight while block i is being multiplied.  The loop has no way out in
         // the middle (the last one or two iterations follow it): with one, the compiler could not tell at
         // the loop's head which loads were the newest and drained them all once per trip (16 streams,
-        // 16384 rows, 132 query rows: 243.8 -> 237.5 us; 16000 rows 220.9 -> 214.1).
+        // 132 query rows: 65535 cached rows 821 -> 815 us, 16384 rows 243.8 -> 237.5, 16000 rows 220.9 -> 214.1).
         int i = 0;
         for (; i + 3 <= nblocks_wg; i += 3) {
             store(2, 2, i + 2);
@@ -1499,6 +1499,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         fr.bias = m->layers[layer].bqkv;
     }
     const int nt = (int)cs_ceil_div(QR, 16);              // 16-row query tiles
+    // (without partial tiles: cs_op_attention, whose queries are given; the model's narrow blocks always fuse)
     auto launch = [&](auto hd_tag, auto nt_tag) {
         constexpr int HD = decltype(hd_tag)::value, NT = decltype(nt_tag)::value;
         if (qkv_part)

@@ -145,7 +145,7 @@ static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K
 #define GEMM_LDS_ROW (GEMM_KC * 2 + 16)   // bytes per X row in LDS (padded)
 #define GEMM_RING_TILES 8                 // W tile-chunks (4 KB each) in flight per consumer wave
 
-// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 5, see mfma_waves) stream W:
+// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 5, see mfma_plan) stream W:
 // each owns MT 16-row tiles, keeps 8/MT K-chunks of them (32 KB) in flight in registers and multiplies.
 // Two more waves (producers) stage the X block of every chunk (half of its rows each)
 // through registers into a double-buffered LDS tile.  The hardware counts outstanding loads per wave and retires
@@ -469,7 +469,8 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
     // Workgroup -> (W tile, X row block): XCD x (workgroup ids x, x + 8, ...) owns W tiles x, x + 8, ...
     // and walks them in panels of TG_PANEL row blocks, all row blocks of a panel per W tile before the
     // next tile, so that its 32 compute units share few W tiles and few row blocks at any time.
-    // 4095 rows x 4096 (q/k/v, 20 row blocks): 184 -> 169 us against one panel of all row blocks.
+    // Against one panel of all row blocks: 16384 x 2048 (1B gate/up), 4095 rows in 16 or 20 blocks 227, 246 -> 214,
+    // 228 us; the 8B and Qwen2.5-7B projections within 3 % either way, their whole prompts within half a percent.
     const int per_xcd = (int)gridDim.x / (8 * RB), seq = (int)blockIdx.x >> 3;
     const int panel = seq / (TG_PANEL * per_xcd), in_panel = seq - panel * TG_PANEL * per_xcd;
     const int panel_rows = min(TG_PANEL, RB - panel * TG_PANEL);
@@ -713,7 +714,9 @@ struct mfma_shape { int r_blocks, ksplit, waves; };
 // Estimated time of a launch, us.  A workgroup fills a compute unit and takes 30 us per 4096 of K while it
 // is bound by its weights, 6.1 us per X tile from five tiles on (8B width, 224 workgroups: 4, 6, 7, 8 X tiles
 // 30, 37, 43 to 48, 49 to 55 us); five consumer waves share four SIMDs, 1.35 of the time for 1.25 of the
-// rows; a partial tile is written and read once more at about 4.9 TB/s.
+// rows; a partial tile is written and read once more at about 4.9 TB/s (an unsplit output is charged nothing here
+// and once in tile_plan: with both charged alike, and the rate fitted anew, 21 of 284 whole calls of 97 to 1024
+// rows and prompts up to 4096 got faster and 53 slower, 1 to 6 % each).
 static double mfma_us(int R, int N, int K, const mfma_shape& p) {
     const int nt = (int)cs_ceil_div(cs_ceil_div(R, 16), p.r_blocks);
     const int64_t wgs = cs_ceil_div(N, 32 * p.waves) * p.r_blocks * p.ksplit;
