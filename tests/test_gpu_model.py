@@ -166,11 +166,14 @@ def test_narrow_blocks_over_short_and_ragged_caches(shape, k):
     model.destroy()
 
 
-def _ragged_verify(shape, lens, k, check, seed):
-    """One block of every stream over caches of the given lengths; the streams in `check` against the oracle."""
+def _ragged_verify(shape, lens, k, check, seed, plain=False):
+    """One block of every stream over caches of the given lengths, NaN in the rows past the block; the streams in
+    `check` against the oracle."""
     w = synth.model_weights(shape, seed, threads=4)
-    model = cs.Model(w, max_batch=len(lens), max_k=k)
+    model = cs.Model(w, max_batch=len(lens), max_k=k, plain=plain)
     kv = cs.KV(model, len(lens), max(lens) + k + 8)
+    nan = torch.full((shape.n_kv_heads, 5, shape.head_dim), float("nan"), device=DEV,
+                     dtype=torch.float32 if shape.dtype == "f32" else torch.bfloat16)
     rng = np.random.default_rng(seed + k)
     pending = rng.integers(0, shape.vocab, len(lens))
     draft = rng.integers(0, shape.vocab, (len(lens), k))
@@ -180,6 +183,7 @@ def _ragged_verify(shape, lens, k, check, seed):
             if n:
                 rows[b, layer] = synth.random_kv(shape, n, seed, layer, b)
                 kv.load(layer, b, 0, *rows[b, layer])
+            kv.load(layer, b, n + k + 1, nan, nan)
         kv.set_len(b, n)
     acc, nxt, logits = cs.cs_verify(model, kv, t32(pending), t32(draft), t32([k] * len(lens)), k, want_logits=True)
     torch.cuda.synchronize()
@@ -210,6 +214,15 @@ def test_narrow_blocks_through_the_pipelined_loop(shape, k, streams, n):
     even and odd counts, old ones alone and followed by a masked one: refills of both K stages and both V stages, the
     block left over after the loop.  (Sixteen streams leave eight splits for the long one, which is the one checked.)"""
     _ragged_verify(shape, (n,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4247)
+
+
+@pytest.mark.parametrize("hd,heads,kv_heads", [(2, 4, 2), (8, 4, 4), (16, 6, 2), (256, 2, 1)])
+@pytest.mark.parametrize("dtype,k", [("f32", 0), ("f32", 6), ("bf16", 6)])
+def test_plain_attention_head_sizes_and_chunk_edges(hd, heads, kv_heads, dtype, k):
+    """The plain attention kernel: head sizes below and from 16 on (single and wide loads of K), contexts around its
+    2048-token chunk and with every remainder of the four tokens that a load of V takes."""
+    shape = ModelShape(f"plain-hd{hd}", 1, 64, heads, kv_heads, hd, 96, 97, 10000.0, 1e-5, dtype)
+    _ragged_verify(shape, (2046, 2047, 2049, 4100, 1, 0, 129), k, range(7), seed=4248, plain=True)
 
 
 @pytest.mark.parametrize("shape", [MINI64, SMALLF32])
