@@ -25,25 +25,26 @@
 // -------------------------------------------------------------------------------------
 // plain reference kernel: one workgroup per (block row, query head, stream)
 // -------------------------------------------------------------------------------------
-#define PA_THREADS 256
 #define PA_CHUNK 2048
 
+template <int THREADS>
 __device__ __forceinline__ float block_max(float v, float* wred) {
     v = cs_wave_max(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) wred[threadIdx.x >> 6] = v;
     __syncthreads();
     float r = wred[0];
-    for (int w = 1; w < PA_THREADS / CS_WAVE; ++w) r = fmaxf(r, wred[w]);
+    for (int w = 1; w < THREADS / CS_WAVE; ++w) r = fmaxf(r, wred[w]);
     return r;
 }
+template <int THREADS>
 __device__ __forceinline__ float block_sum(float v, float* wred) {
     v = cs_wave_sum(v);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) wred[threadIdx.x >> 6] = v;
     __syncthreads();
     float r = 0.f;
-    for (int w = 0; w < PA_THREADS / CS_WAVE; ++w) r += wred[w];
+    for (int w = 0; w < THREADS / CS_WAVE; ++w) r += wred[w];
     return r;
 }
 
@@ -53,19 +54,21 @@ __device__ __forceinline__ f32x4 pa_ld4(const bf16_t* p) {
     return (f32x4){(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
 }
 
-// Latency bound: 44 workgroups over 512 tokens of hd 64 took 41 us with one element per load, 20 us
-// with four.
-template <typename WT, typename QT, typename OT>
-__global__ __launch_bounds__(PA_THREADS) void k_attn_plain(const QT* __restrict__ q,
-                                                           const WT* __restrict__ kc,
-                                                           const WT* __restrict__ vc,
-                                                           const int32_t* __restrict__ kv_len,
-                                                           int rows, int H, int KVH, int hd,
-                                                           int64_t cap, OT* __restrict__ out) {
-    __shared__ float sq[256];
+// A verify block of a small model (44 workgroups over 512 tokens of hd 64) leaves most of the chip idle: what counts
+// is how fast one compute unit gets its K and V.  So neighbouring lanes read neighbouring memory, with four to
+// eight independent loads in flight per thread: hd/4 lanes share a token's key row (four elements each, their
+// products added by shuffles), and 32 lanes take the 128 consecutive tokens of one feature of V (cs_v_index), whose
+// sums meet by shuffles as well.  19.2 us with a key row per thread and four waves, 12.1 us now with 16.
+template <typename WT, typename QT, typename OT, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_attn_plain(const QT* __restrict__ q,
+                                                        const WT* __restrict__ kc,
+                                                        const WT* __restrict__ vc,
+                                                        const int32_t* __restrict__ kv_len,
+                                                        int rows, int H, int KVH, int hd,
+                                                        int64_t cap, OT* __restrict__ out) {
     __shared__ float sc[PA_CHUNK];
-    __shared__ float red[PA_THREADS];
-    __shared__ float wred[PA_THREADS / CS_WAVE];
+    __shared__ float so[256];                      // running output of every feature
+    __shared__ float wred[THREADS / CS_WAVE];
     const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
     const int tid = threadIdx.x;
     const int r = b * rows + i;
@@ -73,64 +76,84 @@ __global__ __launch_bounds__(PA_THREADS) void k_attn_plain(const QT* __restrict_
     const int n_ctx = kv_len[b] + i + 1;
     const WT* __restrict__ K = kc + ((int64_t)b * KVH + g) * cap * hd;
     const WT* __restrict__ V = vc + ((int64_t)b * KVH + g) * hd * cap;
-    if (tid < hd) sq[tid] = cs_ld(q, ((int64_t)r * H + h) * hd + tid);
-    __syncthreads();
     const float scale = 1.0f / sqrtf((float)hd);
-    const int d = tid % hd, part = tid / hd, nparts = PA_THREADS / hd;
-    float m_run = -INFINITY, l_run = 0.f, o = 0.f;
+    // (hd is a power of two in 2..256)
+    const int lpt = hd >= 4 ? hd >> 2 : 1;         // lanes per token, 1..64
+    const int lpt_log = 31 - __clz(lpt);
+    const int e0 = (tid & (lpt - 1)) * 4, tok0 = tid >> lpt_log, tpp = THREADS >> lpt_log;
+    const QT* __restrict__ qrow = q + ((int64_t)r * H + h) * hd;
+    f32x4 q4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 4; ++j)
+        if (e0 + j < hd) q4[j] = cs_ld(qrow, e0 + j);
+    for (int d = tid; d < hd; d += THREADS) so[d] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
     for (int c0 = 0; c0 < n_ctx; c0 += PA_CHUNK) {
         const int cn = min(PA_CHUNK, n_ctx - c0);
         float lmax = -INFINITY;
-        for (int t = tid; t < cn; t += PA_THREADS) {
-            const WT* __restrict__ kr = K + (int64_t)(c0 + t) * hd;
-            float s = 0.f;
-            if (hd % 16 == 0) {                    // rows of whole 16-element pieces: wide loads, four in flight
-                for (int e = 0; e < hd; e += 16) {
-                    f32x4 kv[4];
+        for (int base = 0; base < cn; base += 4 * tpp) {
+            f32x4 kv[4];
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) kv[u] = pa_ld4(kr + e + 4 * u);
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) s += sq[e + 4 * u + j] * kv[u][j];
-                }
-            } else {
-                for (int e = 0; e < hd; ++e) s += sq[e] * cs_ld(kr, e);
+            for (int u = 0; u < 4; ++u) {          // (tokens past the last are read at the last)
+                const WT* __restrict__ kr = K + (int64_t)(c0 + min(base + u * tpp + tok0, cn - 1)) * hd;
+                kv[u] = hd >= 4 ? pa_ld4(kr + e0) : (f32x4){cs_ld(kr, 0), cs_ld(kr, 1), 0.f, 0.f};
             }
-            s *= scale;
-            sc[t] = s;
-            lmax = fmaxf(lmax, s);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                float s = (q4[0] * kv[u][0] + q4[1] * kv[u][1]) + (q4[2] * kv[u][2] + q4[3] * kv[u][3]);
+                for (int o = 1; o < lpt; o <<= 1) s += __shfl_xor(s, o, 64);
+                s *= scale;
+                const int t = base + u * tpp + tok0;
+                if (t < cn) {
+                    if (e0 == 0) sc[t] = s;
+                    lmax = fmaxf(lmax, s);
+                }
+            }
         }
-        const float mc = block_max(lmax, wred);
+        const float mc = block_max<THREADS>(lmax, wred);          // its barriers also publish sc[]
         const float m_new = fmaxf(m_run, mc);
         const float alpha = expf(m_run - m_new);
         float lsum = 0.f;
-        for (int t = tid; t < cn; t += PA_THREADS) {
+        for (int t = tid; t < cn; t += THREADS) {
             const float p = expf(sc[t] - m_new);
             sc[t] = p;
             lsum += p;
         }
-        const float lc = block_sum(lsum, wred);   // its barriers also publish sc[]
+        const float lc = block_sum<THREADS>(lsum, wred);          // likewise
         l_run = l_run * alpha + lc;
-        float acc = 0.f;
-        // four tokens at a time (contiguous in the cache); rows past the context may hold anything
+        // rows past the context may hold anything (they are inside the allocation: cap % 128 == 0)
+        const int tq = (tid & 31) * 4;
+        for (int d = tid >> 5; d < hd; d += 2 * (THREADS / 32)) {
+            const bool two = d + THREADS / 32 < hd;
+            const int d1 = two ? d + THREADS / 32 : d;
+            float a0 = 0.f, a1 = 0.f;
 #pragma unroll 4
-        for (int t = 4 * part; t < cn; t += 4 * nparts) {
-            const f32x4 v = pa_ld4(V + cs_v_index(c0 + t, d, hd));
+            for (int t = tq; t - tq < cn; t += CS_VBLK) {
+                const f32x4 v0 = pa_ld4(V + cs_v_index(c0 + t, d, hd)), v1 = pa_ld4(V + cs_v_index(c0 + t, d1, hd));
+                float p0 = 0.f, p1 = 0.f;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc += t + j < cn ? sc[t + j] * v[j] : 0.f;
+                for (int j = 0; j < 4; ++j) {
+                    const bool in = t + j < cn;
+                    const float p = in ? sc[t + j] : 0.f;
+                    p0 += in ? p * v0[j] : 0.f;
+                    p1 += in ? p * v1[j] : 0.f;
+                }
+                a0 += p0;
+                a1 += p1;
+            }
+#pragma unroll
+            for (int o = 16; o > 0; o >>= 1) {
+                a0 += __shfl_xor(a0, o, 64);
+                a1 += __shfl_xor(a1, o, 64);
+            }
+            if (tq == 0) {
+                so[d] = so[d] * alpha + a0;
+                if (two) so[d1] = so[d1] * alpha + a1;
+            }
         }
-        o = o * alpha + acc;
         m_run = m_new;
         __syncthreads();
     }
-    red[tid] = o;
-    __syncthreads();
-    if (part == 0) {
-        float tot = 0.f;
-        for (int p = 0; p < nparts; ++p) tot += red[p * hd + d];
-        cs_st(out, ((int64_t)r * H + h) * hd + d, tot / l_run);
-    }
+    for (int d = tid; d < hd; d += THREADS) cs_st(out, ((int64_t)r * H + h) * hd + d, so[d] / l_run);
 }
 
 // -------------------------------------------------------------------------------------
@@ -1389,16 +1412,22 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const int64_t per_layer = (int64_t)B * KVH * kv->cap * hd;
     if (!m->fast) {
         dim3 grid(rows, H, B);
-        if (c.dtype == CS_BF16)
-            k_attn_plain<bf16_t, float, float><<<grid, PA_THREADS, 0, s>>>(
-                (const float*)m->q, (const bf16_t*)kv->k + layer * per_layer,
-                (const bf16_t*)kv->v + layer * per_layer, kv->d_len, rows, H, KVH, hd, kv->cap,
-                (float*)m->xn);
-        else
-            k_attn_plain<float, float, float><<<grid, PA_THREADS, 0, s>>>(
-                (const float*)m->q, (const float*)kv->k + layer * per_layer,
-                (const float*)kv->v + layer * per_layer, kv->d_len, rows, H, KVH, hd, kv->cap,
-                (float*)m->xn);
+        auto start = [&](auto* k, auto threads) {
+            typedef std::remove_pointer_t<decltype(k)> WT;
+            constexpr int THREADS = decltype(threads)::value;
+            k_attn_plain<WT, float, float, THREADS><<<grid, THREADS, 0, s>>>(
+                (const float*)m->q, (const WT*)kv->k + layer * per_layer, (const WT*)kv->v + layer * per_layer, kv->d_len,
+                rows, H, KVH, hd, kv->cap, (float*)m->xn);
+        };
+        // up to two workgroups per compute unit: 16 waves each instead of four (44 workgroups 23 -> 12 us; 2044 workgroups
+        // of a prompt 43 -> 60 us)
+        const bool few = (int64_t)rows * H * B <= 512;
+        auto by_type = [&](auto threads) {
+            if (c.dtype == CS_BF16) start((bf16_t*)nullptr, threads);
+            else start((float*)nullptr, threads);
+        };
+        if (few) by_type(std::integral_constant<int, 1024>{});
+        else by_type(std::integral_constant<int, 256>{});
         return cs_launch_ok("k_attn_plain");
     }
     const int G = H / KVH;

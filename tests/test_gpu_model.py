@@ -225,6 +225,13 @@ def test_plain_attention_head_sizes_and_chunk_edges(hd, heads, kv_heads, dtype, 
     _ragged_verify(shape, (2046, 2047, 2049, 4100, 1, 0, 129), k, range(7), seed=4248, plain=True)
 
 
+@pytest.mark.parametrize("hd,heads,kv_heads", [(2, 4, 2), (16, 6, 2), (256, 2, 1)])
+def test_plain_attention_with_many_workgroups(hd, heads, kv_heads):
+    """The same kernel where the launch has more than two workgroups per compute unit and takes four waves per workgroup."""
+    shape = ModelShape(f"plain-hd{hd}", 1, 64, heads, kv_heads, hd, 96, 97, 10000.0, 1e-5, "f32")
+    _ragged_verify(shape, (2046, 2047, 2049, 4100, 1, 0, 129) * 6, 6, (0, 1, 2, 3, 39, 40, 41), seed=4249, plain=True)
+
+
 @pytest.mark.parametrize("shape", [MINI64, SMALLF32])
 def test_logits_into_an_unaligned_buffer(shape):
     """The logits of a verify call whose output buffer is only 4-byte aligned equal those of an aligned one."""
