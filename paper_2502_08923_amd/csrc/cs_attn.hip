@@ -644,7 +644,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
                                                               const bf16_t* __restrict__ vc,
                                                               const int32_t* __restrict__ kv_len,
                                                               int rows, int H, int KVH, int64_t cap,
-                                                              int Tw, int nqg, int nqgw, int nsplit,
+                                                              int Tw, int nqg, int nqgw, int gpw, int nsplit,
                                                               int ranges, float* __restrict__ po,
                                                               float* __restrict__ pml) {
     constexpr int KS = HD / 32, MT = HD / 16;
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int range = (slot / nqgw) * 8 + xcd;
     if (range >= ranges) return;                        // whole workgroup, before any barrier
-    // which group of FA_QG query groups: the last rows of a block see the most tokens (see n_lim
+    // which gpw (<= FA_QG) of the query groups: the last rows of a block see the most tokens (see n_lim
     // below), so they are dispatched first and the short ones fill the tail of the launch
     const int qgw = nqgw - 1 - slot % nqgw;
     // Roles of the eight waves (hardware waves go to the four SIMDs in turn: wave w runs on SIMD
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     // the four live consumers get a SIMD each: waves 0-3 = (team 0, group 0), (0, 1), (1, 0), (1, 1),
     // waves 4 and 5 the producers, waves 6 and 7 the dead third groups.
     const int hw = tid >> 6;
-    const int live_groups = min(FA_QG, nqg - qgw * FA_QG);
+    const int live_groups = min(gpw, nqg - qgw * gpw);
     const bool spread = live_groups <= 2;
     const int team = spread ? (hw < 4 ? hw >> 1 : (hw & 1)) : hw / (FA_QG + 1);
     const int wave = spread ? (hw < 4 ? (hw & 1) : (hw < 6 ? FA_QG : 2)) : hw % (FA_QG + 1);
@@ -687,7 +687,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     const int n_tok = L + rows;
     // Causality: block row i sees the tokens up to L + i, so nothing beyond the last row of this
     // workgroup's query groups is walked (long prompt blocks: the upper triangle of the block).
-    const int last_row = min(rows - 1, ((qgw + 1) * FA_QG * FA_QROWS - 1) / G);
+    const int last_row = min(rows - 1, ((qgw + 1) * gpw * FA_QROWS - 1) / G);
     const int n_lim = L + last_row + 1;
     // The two teams share the workgroup's token range of FA_TEAMS*Tw and take its 32-token blocks
     // in turn (team t: blocks t, t+2, ...), so the workgroup reads neighbouring blocks together.
@@ -707,9 +707,9 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
         const int grp = idx / (FA_QROWS * (HD / 8));
         const int rem = idx % (FA_QROWS * (HD / 8));
         const int row = rem / (HD / 8), seg = rem % (HD / 8);
-        const int n = (qgw * FA_QG + grp) * FA_QROWS + row;
+        const int n = (qgw * gpw + grp) * FA_QROWS + row;
         bf16x8 v = (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
-        if (n < QR) {
+        if (grp < gpw && n < QR) {
             const int i = n / G, gq = n % G;
             v = *reinterpret_cast<const bf16x8*>(
                 q + (((int64_t)(b * rows + i)) * H + kvh * G + gq) * HD + seg * 8);
@@ -796,8 +796,8 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     }
 
     // ---------------- consumers: one 48-row query group each ----------------
-    const int qg = qgw * FA_QG + wave;
-    const bool live = qg < nqg;
+    const int qg = qgw * gpw + wave;
+    const bool live = wave < gpw && qg < nqg;
     const unsigned char* myq = qs[wave];
     int qi[FA_NT];
 #pragma unroll
@@ -1464,7 +1464,19 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     if (nqg > 1) {
         // wide block: consumers share the K/V stream of one producer wave through LDS
         const int nqgw = (int)cs_ceil_div(nqg, FA_QG);
-        nsplit = FA_TEAMS * (int)cs_ceil_div(256, (int64_t)B * KVH * nqgw);
+        // query groups evenly over the workgroups of a range (147 rows: 2 + 2, which spread over the SIMDs, not 3 + 1)
+        const int gpw = (int)cs_ceil_div(nqg, nqgw);
+        // A workgroup fills a compute unit and takes its share of the tokens plus the time of about 512 more
+        // (16 streams: 26 us per 1000 tokens and 12 us): as many ranges as one round of the chip holds rather
+        // than a few workgroups more (5 streams of 6001 rows, 147 query rows per KV head: 288 workgroups 38.1 us,
+        // 240 29.8 us; with 3 + 1 groups 43.1 and 35.6).
+        int nsp = 1;
+        double best_t = 0.;
+        for (int n = 1; n <= (int)cs_ceil_div(256, (int64_t)B * KVH * nqgw); ++n) {
+            const double t = (double)cs_ceil_div(cs_round_up((int64_t)B * KVH * n, 8) * nqgw, 256) * (512. + (double)n_tok_ub / n);
+            if (n == 1 || t < best_t) { best_t = t; nsp = n; }
+        }
+        nsplit = FA_TEAMS * nsp;
         const int max_split = (int)cs_ceil_div(n_tok_ub, 256);
         if (nsplit > max_split) nsplit = max_split;
         if (nsplit > FA_MAX_SPLIT) nsplit = FA_MAX_SPLIT;
@@ -1482,10 +1494,10 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         const int pa = cs_prof_begin(CS_PROF_ATTN, s);
         if (hd == 128)
             k_attn_lds<128><<<grid, FA_LDS_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows,
-                                                             H, KVH, kv->cap, Tw, nqg, nqgw, nsplit, ranges, po, pml);
+                                                             H, KVH, kv->cap, Tw, nqg, nqgw, gpw, nsplit, ranges, po, pml);
         else
             k_attn_lds<64><<<grid, FA_LDS_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows,
-                                                            H, KVH, kv->cap, Tw, nqg, nqgw, nsplit, ranges, po, pml);
+                                                            H, KVH, kv->cap, Tw, nqg, nqgw, gpw, nsplit, ranges, po, pml);
         cs_prof_end(pa, s);
         CS_TRY(cs_launch_ok("k_attn_lds"));
         dim3 mgrid((unsigned)cs_ceil_div(QR, FA_MERGE_THREADS / (hd / 4)), KVH, B);

@@ -334,6 +334,20 @@ def test_attention_block_size_sweep(rows):
     assert worst < 1e-2, worst
 
 
+@pytest.mark.parametrize("H,KVH,B,rows", [(28, 4, 5, 21), (28, 4, 3, 7), (32, 8, 3, 37), (32, 8, 1, 60)])
+def test_attention_even_query_groups_and_one_round(H, KVH, B, rows):
+    """Wide blocks whose query groups are shared out evenly over the workgroups of a token range: 4 groups (of 147 rows)
+    as 2 + 2, 49 rows in two groups, 4 groups (148 rows) as 2 + 2, 5 (240 rows) as 3 + 2; stream counts for which the
+    token ranges stop at one round of the chip."""
+    shape = ModelShape("groups", 1, 256, H, KVH, 128, 256, 512, 10000.0, 1e-5, "bf16")
+    m = cs.Model(synth.model_weights(shape, 98, threads=8), max_batch=B, max_k=rows - 1)
+    lens = [2500, 777, 40, 0, 4100][-B:]
+    sample = [(b, h) for b in range(B) for h in (0, H // 2, H - 1)]
+    worst = _attention_case(m, shape, lens, rows, sample, seed=70 + rows, poison=True)
+    m.destroy()
+    assert worst < 1e-2, worst
+
+
 def test_attention_hd64():
     shape = ModelShape("w-hd64", 1, 2048, 32, 8, 64, 8192, 1024, 10000.0, 1e-5, "bf16")
     w = synth.model_weights(shape, 5, threads=16)
