@@ -1401,6 +1401,22 @@ __global__ __launch_bounds__(FA_MERGE_THREADS) void k_attn_merge(const float* __
     cs_range_report(flags, hit, CS_RANGE_ATTN);
 }
 
+// Into how many token ranges the `items` (stream, KV head) pairs are split, `wgs` workgroups per range.  A workgroup
+// fills a compute unit and takes its share of the tokens plus the time of about 512 more (wide blocks of 16 streams:
+// 26 us per 1000 tokens and 12 us): as many ranges as one round of the chip holds rather than a few workgroups
+// more.  Wide, 5 streams of 6001 rows, 147 query rows per KV head: 288 workgroups 38.1 us, 240 29.8 us (with groups of
+// 3 + 1 43.1 and 35.6); narrow, 18431 rows, batch 3 / 5 / 6 / 7: 51 / 107 / 130 / 149 -> 41 / 77 / 90 / 105 us, batches that
+// divide 256 as before.
+static int fit_ranges(int64_t items, int wgs, int64_t n_tok) {
+    int best = 1;
+    double best_t = 0.;
+    for (int n = 1; n <= (int)cs_ceil_div(256, items * wgs); ++n) {
+        const double t = (double)cs_ceil_div(cs_round_up(items * n, 8) * wgs, 256) * (512. + (double)n_tok / n);
+        if (n == 1 || t < best_t) { best_t = t; best = n; }
+    }
+    return best;
+}
+
 bool cs_attention_fuses_rope(const cs_model* m, int rows) {
     return m->fast && (m->cfg.n_heads / m->cfg.n_kv_heads) * rows <= FA_QROWS;
 }
@@ -1466,17 +1482,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         const int nqgw = (int)cs_ceil_div(nqg, FA_QG);
         // query groups evenly over the workgroups of a range (147 rows: 2 + 2, which spread over the SIMDs, not 3 + 1)
         const int gpw = (int)cs_ceil_div(nqg, nqgw);
-        // A workgroup fills a compute unit and takes its share of the tokens plus the time of about 512 more
-        // (16 streams: 26 us per 1000 tokens and 12 us): as many ranges as one round of the chip holds rather
-        // than a few workgroups more (5 streams of 6001 rows, 147 query rows per KV head: 288 workgroups 38.1 us,
-        // 240 29.8 us; with 3 + 1 groups 43.1 and 35.6).
-        int nsp = 1;
-        double best_t = 0.;
-        for (int n = 1; n <= (int)cs_ceil_div(256, (int64_t)B * KVH * nqgw); ++n) {
-            const double t = (double)cs_ceil_div(cs_round_up((int64_t)B * KVH * n, 8) * nqgw, 256) * (512. + (double)n_tok_ub / n);
-            if (n == 1 || t < best_t) { best_t = t; nsp = n; }
-        }
-        nsplit = FA_TEAMS * nsp;
+        nsplit = FA_TEAMS * fit_ranges((int64_t)B * KVH, nqgw, n_tok_ub);
         const int max_split = (int)cs_ceil_div(n_tok_ub, 256);
         if (nsplit > max_split) nsplit = max_split;
         if (nsplit > FA_MAX_SPLIT) nsplit = FA_MAX_SPLIT;
@@ -1508,10 +1514,10 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         return cs_launch_ok("k_attn_merge");
     }
     // The kernel keeps one wave per SIMD (register budget), so one workgroup fills a compute
-    // unit: aim at one workgroup per compute unit, at least 128 tokens per wave; up to eight splits, which
+    // unit: aim at one round of the chip, at least 128 tokens per wave; up to eight splits, which
     // the merge reads in one batch, also of 32 tokens per wave (one row, 300 tokens, hd 128: 1, 2, 3 splits
     // 10.4, 7.6, 7.0 us; 4106 tokens of hd 64 in 9, 17 splits: 9.6, 9.1 us, but the merge 4.0, 5.1).
-    nsplit = (int)cs_ceil_div(256, (int64_t)B * KVH * nqg);
+    nsplit = fit_ranges((int64_t)B * KVH, 1, n_tok_ub);
     const int few = (int)cs_ceil_div(n_tok_ub, 4 * 32) < 8 ? (int)cs_ceil_div(n_tok_ub, 4 * 32) : 8;
     const int max_split = (int)cs_ceil_div(n_tok_ub, 4 * 128) > few ? (int)cs_ceil_div(n_tok_ub, 4 * 128) : few;
     if (nsplit > max_split) nsplit = max_split;

@@ -334,11 +334,12 @@ def test_attention_block_size_sweep(rows):
     assert worst < 1e-2, worst
 
 
-@pytest.mark.parametrize("H,KVH,B,rows", [(28, 4, 5, 21), (28, 4, 3, 7), (32, 8, 3, 37), (32, 8, 1, 60)])
+@pytest.mark.parametrize("H,KVH,B,rows", [(28, 4, 5, 21), (28, 4, 3, 7), (32, 8, 3, 37), (32, 8, 1, 60),
+                                          (32, 8, 5, 11), (32, 8, 3, 4)])
 def test_attention_even_query_groups_and_one_round(H, KVH, B, rows):
     """Wide blocks whose query groups are shared out evenly over the workgroups of a token range: 4 groups (of 147 rows)
     as 2 + 2, 49 rows in two groups, 4 groups (148 rows) as 2 + 2, 5 (240 rows) as 3 + 2; stream counts for which the
-    token ranges stop at one round of the chip."""
+    token ranges stop at one round of the chip, also in narrow blocks (44 and 16 rows)."""
     shape = ModelShape("groups", 1, 256, H, KVH, 128, 256, 512, 10000.0, 1e-5, "bf16")
     m = cs.Model(synth.model_weights(shape, 98, threads=8), max_batch=B, max_k=rows - 1)
     lens = [2500, 777, 40, 0, 4100][-B:]
