@@ -303,8 +303,8 @@ static int model_alloc(cs_model* m) {
     DEV_ALLOC(m->rope, R * (hd / 2) * sizeof(float2));
     DEV_ALLOC(m->tok, R * 4);
     m->am_chunks = 64;                                   // column chunks of the stand-alone argmax
-    // ... or one pair per 128-column tile when the lm_head reduces its own tiles
-    const size_t am_tiles = cs_ceil_div(V, 128) > m->am_chunks ? (size_t)cs_ceil_div(V, 128) : (size_t)m->am_chunks;
+    // ... or one pair per column tile (64 columns at least) when the lm_head reduces its own tiles
+    const size_t am_tiles = cs_ceil_div(V, 64) > m->am_chunks ? (size_t)cs_ceil_div(V, 64) : (size_t)m->am_chunks;
     DEV_ALLOC(m->am_val_idx, (size_t)m->R_max * am_tiles * 2 * 4);
     DEV_ALLOC(m->row_argmax, (size_t)m->R_max * 4);
     DEV_ALLOC(m->draft, (size_t)c.max_batch * (c.max_k > 0 ? c.max_k : 1) * 4);

@@ -145,7 +145,7 @@ static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K
 #define GEMM_LDS_ROW (GEMM_KC * 2 + 16)   // bytes per X row in LDS (padded)
 #define GEMM_RING_TILES 8                 // W tile-chunks (4 KB each) in flight per consumer wave
 
-// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 5, see mfma_plan) stream W:
+// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 2 or 5, see mfma_plan) stream W:
 // each owns MT 16-row tiles, keeps 8/MT K-chunks of them (32 KB) in flight in registers and multiplies.
 // Two more waves (producers) stage the X block of every chunk (half of its rows each)
 // through registers into a double-buffered LDS tile.  The hardware counts outstanding loads per wave and retires
@@ -731,7 +731,9 @@ static double mfma_us(int R, int N, int K, const mfma_shape& p) {
 // 28, 97, 46 us in two instead of three; the 1B shape keeps two blocks of 64, which fill the chip, 18 us
 // against 23).  Five consumer waves where tiles of 128 W rows need a second, nearly empty round of the chip
 // (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 80 -> 56 us), not for the few
-// chunks of a K split (1B q/k/v at 200 rows: 19 us against 12).
+// chunks of a K split (1B q/k/v at 200 rows: 19 us against 12).  Two consumer waves where a projection that may not
+// split K has tiles of 128 W rows for half of the chip at most (1B gate/up, 16384 rows: 16, 48, 88 rows 16.2, 18.8,
+// 23.5 -> 13.5, 15.9, 19.9 us); with twice as many tiles as compute units they lose (8B gate/up, 88 rows: 46 -> 53).
 static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
     const int rt_total = (int)cs_ceil_div(R, 16);
     const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
@@ -739,9 +741,12 @@ static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
     if (rt_total <= 6) {
         const int n_tiles = (int)cs_ceil_div(N, 128);
         while (n_tiles * best.ksplit < 192 && best.ksplit * 2 <= max_split) best.ksplit *= 2;
+        if (best.ksplit > 1) return best;
         mfma_shape five = best;
         five.waves = 5;
-        return best.ksplit == 1 && mfma_us(R, N, K, five) < mfma_us(R, N, K, best) ? five : best;
+        if (mfma_us(R, N, K, five) < mfma_us(R, N, K, best)) return five;
+        if (!may_split && cs_ceil_div(N, 64) <= 256) best.waves = 2;
+        return best;
     }
     double best_us = -1.;
     for (int rb = (int)cs_ceil_div(rt_total, 8); rb <= (int)cs_ceil_div(rt_total, 4); ++rb)
@@ -779,6 +784,7 @@ static int launch_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
     if (waves == 5) start_mfma<MT, NT, 5>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
+    else if (waves == 2) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
     else start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
     cs_prof_end(pg, s);
     return cs_launch_ok("k_gemm_mfma");

@@ -277,6 +277,28 @@ def test_five_wave_tiles_in_every_epilogue():
     model.destroy()
 
 
+@pytest.mark.parametrize("d_ff,vocab", [(8192, 16368), (8320, 16400)])
+@pytest.mark.parametrize("rows", [1, 17, 96])
+def test_two_and_four_wave_tiles_in_every_epilogue(d_ff, vocab, rows):
+    """Gate/up and lm_head widths on both sides of 256 tiles of 64 W rows, the last tile ragged: SwiGLU and argmax
+    epilogues against the oracle, and the tokens with and without stored logits."""
+    shape = ModelShape("mini-two-waves", 1, 256, 4, 2, 64, d_ff, vocab, 10000.0, 1e-5, "bf16")
+    w = synth.model_weights(shape, 4250, threads=8)
+    model = cs.Model(w, max_batch=1, max_k=95)
+    rng = np.random.default_rng(25)
+    prompt, draft = rng.integers(0, vocab, 40).tolist(), rng.integers(0, vocab, rows - 1).tolist()
+    kv, okv, err = _verify_case(w, model, prompt, draft, rows - 1, cap=160)
+    d, n = t32([draft]) if rows > 1 else None, t32([rows - 1])
+    kv.set_len(0, 39)
+    acc, nx, logits = cs.cs_verify(model, kv, t32([prompt[-1]]), d, n, rows - 1, want_logits=True)
+    kv.set_len(0, 39)
+    acc2, nx2, none = cs.cs_verify(model, kv, t32([prompt[-1]]), d, n, rows - 1)
+    assert (int(acc[0]), int(nx[0])) == (int(acc2[0]), int(nx2[0]))
+    assert int(nx[0]) == int(logits[0, int(acc[0])].argmax())
+    kv.destroy()
+    model.destroy()
+
+
 @pytest.mark.parametrize("shape,plain", [(MINI64, False), (MINI64, True), (MINI128, False),
                                          (SMALLF32, False), (MINIQWEN, False)])
 def test_verify_and_decode_with_qkv_bias(shape, plain):
