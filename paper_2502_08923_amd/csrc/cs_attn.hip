@@ -1033,34 +1033,34 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
 // token axis is not split at all: a workgroup of eight waves owns 256 query rows (32 each: with
 // 48, the register tile of the kernels above, a 2048-row block gives 176 workgroups for 256
 // compute units and is slower), walks the tokens its rows can see once, and writes the
-// normalised result itself (no partial results, no merge).  All eight waves multiply; nobody
+// normalised result itself (no partial results, no merge).  Short blocks are a serial walk over few
+// workgroups instead: there four waves of 16 rows each, with a SIMD for themselves, take a 32-token block in
+// 0.6 us where the 256-row tile takes 1.2 (see the launcher).  All waves multiply; nobody
 // is set aside to load: each wave requests its share (1 KB fragment blocks) of every 32-token
-// block with direct-to-LDS loads into a ring of six stages, so four blocks are in flight while
+// block with direct-to-LDS loads into a ring of six (four) stages, so four (two) blocks are in flight while
 // one is multiplied, and the loads cost no registers.  The loads and the waits on them are
 // inline assembly with exact counts, as in the many-row GEMM: after the query fragments have
 // arrived the kernel issues no other vector memory load until its final stores.  Per block a
 // wave runs scores -> softmax -> PV in sequence (the other wave of its SIMD fills the gaps);
 // interleaving them inside the wave, or across the two waves of a SIMD, was slower or spilled.
-// Workgroups of one KV head get ids 8 apart (one XCD, one L2); the last rows of a block see the
-// most tokens and are dispatched first.
+// The last rows of a block see the most tokens and are dispatched first, those of all KV heads and streams in
+// turn (8 streams of 512 rows: 55.5 -> 45 us against one group of 8 heads after the other); with 8 of them or a
+// multiple each stays on one XCD and its L2, with fewer all XCDs work (Qwen2.5-7B's 4 heads, 700 rows: 42 -> 27 us).
 // -------------------------------------------------------------------------------------
-#define PF_WAVES 8
-#define PF_THREADS (64 * PF_WAVES)
-#define PF_STAGES 6
-#define PF_NT 2             // 16-row query tiles per wave
-
-template <int HD, int NT, typename OT>
-__global__ __launch_bounds__(PF_THREADS) void k_attn_prefill(const bf16_t* __restrict__ q,
+// NT: 16-row query tiles per wave.  PF_WAVES: 8, or 4.
+template <int HD, int NT, int PF_WAVES, typename OT>
+__global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __restrict__ q,
                                                              const bf16_t* __restrict__ kc,
                                                              const bf16_t* __restrict__ vc,
                                                              const int32_t* __restrict__ kv_len,
                                                              int rows, int H, int KVH, int64_t cap,
-                                                             int nqt, int ranges, int g_shift,
+                                                             int nqt, int ranges, unsigned inv_g,
                                                              OT* __restrict__ out, int tiled,
                                                              int32_t* __restrict__ flags) {
     constexpr int KS = HD / 32, MT = HD / 16;
     constexpr int WQROWS = 16 * NT;                     // query rows per wave
     constexpr int PF_QROWS = PF_WAVES * WQROWS;         // ... per workgroup
+    constexpr int PF_STAGES = PF_WAVES == 4 ? 4 : 6;    // four: two small workgroups share a compute unit's LDS
     constexpr int K_BYTES = 2 * KS * 1024, V_BYTES = MT * 1024;
     constexpr int STAGE_BYTES = K_BYTES + V_BYTES;
     constexpr int NLOAD = 2 * KS + MT;                  // 1 KB requests per 32-token block
@@ -1072,10 +1072,8 @@ __global__ __launch_bounds__(PF_THREADS) void k_attn_prefill(const bf16_t* __res
     const int wave = tid >> 6;
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);   // uniform copy for the request addresses
     const int c = lane & 15, g = lane >> 4;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int range = (slot / nqt) * 8 + xcd;           // (stream, KV head)
-    if (range >= ranges) return;                        // whole workgroup, before any barrier
-    const int qt = nqt - 1 - slot % nqt;                // heaviest first
+    const int range = (int)(blockIdx.x % ranges);       // (stream, KV head)
+    const int qt = nqt - 1 - (int)(blockIdx.x / ranges);          // heaviest first
     const int kvh = range % KVH, b = range / KVH;
     const int G = H / KVH;
     const int QR = G * rows;
@@ -1089,14 +1087,16 @@ __global__ __launch_bounds__(PF_THREADS) void k_attn_prefill(const bf16_t* __res
     const bf16_t* __restrict__ V = vc + ((int64_t)b * KVH + kvh) * HD * cap;
 
     // query fragments: straight from memory into registers, once
-    // query row nt*16 + c of this wave is row n0 + nt*16 of the KV head: block row n >> g_shift,
-    // head n & (G - 1) of the group (G is a power of two here)
+    // query row nt*16 + c of this wave is row n0 + nt*16 of the KV head: block row n / G, head n % G of the group
+    // (inv_g = 2^32 / G rounded up, exact while n * G < 2^32; 0 for G = 1)
+    auto block_row = [&](int n) { return inv_g ? (int)__umulhi((unsigned)n, inv_g) : n; };
     const int n0 = qt * PF_QROWS + wave * WQROWS + c;
     bf16x8 qreg[NT][KS];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int n = n0 + nt * 16;
-        const bf16_t* qp = q + (((int64_t)(b * rows + (n < QR ? n >> g_shift : 0))) * H + kvh * G + (n < QR ? n & (G - 1) : 0)) * HD + g * 8;
+        const int i = n < QR ? block_row(n) : 0;
+        const bf16_t* qp = q + ((int64_t)(b * rows + i) * H + kvh * G + (n < QR ? n - i * G : 0)) * HD + g * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
             qreg[nt][s] = n < QR ? *reinterpret_cast<const bf16x8*>(qp + s * 32) : (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
@@ -1181,10 +1181,13 @@ __global__ __launch_bounds__(PF_THREADS) void k_attn_prefill(const bf16_t* __res
             k1 = n1;
         }
     };
+    int last_tok[NT];                                   // the last token the lane's query row sees
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) last_tok[nt] = L + block_row(n0 + nt * 16);
     auto score_of = [&](const f32x4 (&sacc)[2][NT], int nt, int e, int t0, auto tail_tag) {   // e = 4a + j
         constexpr bool TAIL = decltype(tail_tag)::value;
         const float sc = sacc[e >> 2][nt][e & 3];
-        return (TAIL && (t0 + 8 * g + e > L + ((n0 + nt * 16) >> g_shift))) ? -INFINITY : sc;
+        return (TAIL && (t0 + 8 * g + e > last_tok[nt])) ? -INFINITY : sc;
     };
     auto reference = [&](const f32x4 (&sacc)[2][NT], int t0, auto tail_tag) {
         constexpr bool TAIL = decltype(tail_tag)::value;
@@ -1291,8 +1294,8 @@ __global__ __launch_bounds__(PF_THREADS) void k_attn_prefill(const bf16_t* __res
     const int nblocks_v = nblocks + vzero, L_v = L + vzero;
     // this wave's rows see the tokens up to L + row_lo .. L + row_hi: a block entirely below
     // needs no mask (and holds no dead token), a block entirely above is not computed
-    const int row_lo = (n0 - c) >> g_shift;
-    const int row_hi = min(rows - 1, (n0 - c + WQROWS - 1) >> g_shift);
+    const int row_lo = block_row(n0 - c);
+    const int row_hi = min(rows - 1, block_row(n0 - c + WQROWS - 1));
     f32x4 sa[2][NT];
     for (int i = 0; i < nblocks_v; ++i) {
         issue(i + PF_STAGES - 1, st_req);
@@ -1316,8 +1319,8 @@ __global__ __launch_bounds__(PF_THREADS) void k_attn_prefill(const bf16_t* __res
     for (int nt = 0; nt < NT; ++nt) {
         const int n = n0 + nt * 16;
         if (n >= QR) continue;
-        const int r = b * rows + (n >> g_shift);
-        const int col0 = (kvh * G + (n & (G - 1))) * HD + 4 * g;
+        const int i = block_row(n), r = b * rows + i;
+        const int col0 = (kvh * G + n - i * G) * HD + 4 * g;
         const float inv = 1.0f / lacc[nt][0];
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
@@ -1457,23 +1460,36 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const bf16_t* vc = (const bf16_t*)kv->v + layer * per_layer;
     CS_REQUIRE(!qkv_part || nqg == 1, CS_E_STATE, "fused rotary embedding needs a narrow block");
     int nsplit;
-    // prompt blocks: enough query rows per KV head that a workgroup's 256 rows are all used and
-    // the token axis need not be split to fill the chip
-    const int pf_qrows = PF_WAVES * 16 * PF_NT;
-    const int nqt = (int)cs_ceil_div(QR, pf_qrows);
-    int g_shift = 0;
-    while ((1 << g_shift) < G) ++g_shift;
-    if (QR >= 2 * pf_qrows && (1 << g_shift) == G && (int64_t)B * KVH * nqt >= 40 &&
-        (int64_t)hd * kv->cap * 2 < ((int64_t)1 << 32)) {
-        const int ranges = B * KVH;
-        dim3 grid((unsigned)(cs_round_up(ranges, 8) * nqt));
+    // Blocks whose query rows fill the chip without splitting the token axis: prompt blocks of at least two tiles
+    // of 256 query rows per KV head and 40 workgroups, and, while the context is short, wide blocks that a round
+    // of 64-row tiles covers.  (Attention and merge, or this kernel alone, one stream of the 8B shape, prompts of 24, 64,
+    // 128, 256 rows: 18.3, 20.7, 24.0, 29.7 us split, 9.4, 9.8, 11.7, 15.4 unsplit; a 32-token block costs a workgroup
+    // 0.6 us, so that from about 900 tokens on the split kernel's 22 to 27 us are fewer.)
+    const int64_t ranges = (int64_t)B * KVH;
+    const int64_t wgs_many = ranges * cs_ceil_div(QR, 256), wgs_few = ranges * cs_ceil_div(QR, 64);
+    const bool many = QR >= 512 && wgs_many >= 40, brief = nqg > 1 && wgs_few <= 256 && n_tok_ub <= 768;
+    if ((many || brief) && (int64_t)hd * kv->cap * 2 < ((int64_t)1 << 32)) {
+        // 64 query rows in four waves while that gives at most two workgroups per compute unit, or three of a prompt's
+        // first block, whose early rows see few tokens (300, 512, 700, 1024, 1500 rows of the 8B shape: 21.1, 27.3, 33.4,
+        // 42.6, 57.0 us with 256-row tiles, 15.8, 20.0, 27.5, 38.0, 54.0 with 64; 8 streams of 300 rows, 1216 workgroups: 31
+        // against 34 us; 400 rows behind 4096, 200 workgroups: 134 against 95)
+        const bool small = wgs_few <= (len_ub < rows ? 768 : 512);
+        const int nqt = (int)cs_ceil_div(QR, small ? 64 : 256);
+        const unsigned inv_g = G > 1 ? (unsigned)(((1ull << 32) + G - 1) / G) : 0;
+        dim3 grid((unsigned)(ranges * nqt));
         const int pa = cs_prof_begin(CS_PROF_ATTN, s);
-        if (hd == 128)
-            k_attn_prefill<128, PF_NT, f16_t><<<grid, PF_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH,
-                                                                  kv->cap, nqt, ranges, g_shift, (f16_t*)m->xn, tiled, m->range_flags);
-        else
-            k_attn_prefill<64, PF_NT, f16_t><<<grid, PF_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH,
-                                                                 kv->cap, nqt, ranges, g_shift, (f16_t*)m->xn, tiled, m->range_flags);
+        auto start = [&](auto hd_tag, auto nt_tag, auto wave_tag) {
+            constexpr int HD = decltype(hd_tag)::value, NT = decltype(nt_tag)::value, WAVES = decltype(wave_tag)::value;
+            k_attn_prefill<HD, NT, WAVES, f16_t><<<grid, 64 * WAVES, 0, s>>>(
+                (const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH, kv->cap, nqt, (int)ranges, inv_g, (f16_t*)m->xn, tiled,
+                m->range_flags);
+        };
+        auto by_tile = [&](auto hd_tag) {
+            if (small) start(hd_tag, std::integral_constant<int, 1>{}, std::integral_constant<int, 4>{});
+            else start(hd_tag, std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+        };
+        if (hd == 128) by_tile(std::integral_constant<int, 128>{});
+        else by_tile(std::integral_constant<int, 64>{});
         cs_prof_end(pa, s);
         return cs_launch_ok("k_attn_prefill");
     }

@@ -321,6 +321,22 @@ def test_attention_prompt_block(k_ramp):
     assert worst < 1e-2, worst
 
 
+@pytest.mark.parametrize("H,KVH,hd,lens,rows,k_ramp", [
+    (28, 4, 128, [0], 7, None), (28, 4, 128, [0, 700], 65, (0.05, 6.0)), (28, 4, 128, [300, 0, 17], 257, None),
+    (8, 8, 64, [0, 33, 400], 49, None), (8, 8, 64, [31, 600], 257, (6.0, 0.05)), (64, 8, 128, [250, 0], 17, None),
+    (6, 2, 64, [100, 0, 3, 64], 128, None), (6, 2, 64, [0] * 30, 256, None), (28, 4, 128, [0, 1] * 5, 257, None)])
+def test_attention_unsplit_short_contexts(H, KVH, hd, lens, rows, k_ramp):
+    """Wide blocks over short contexts, which the prompt kernel takes without splitting the tokens: 64-row tiles (most)
+    and 256-row tiles (the last two), one, three, seven and eight query heads per KV head, 2 to 60 (stream, KV head)
+    pairs, ragged last tiles, poisoned rows past the block."""
+    shape = ModelShape("brief", 1, 256, H, KVH, hd, 256, 512, 10000.0, 1e-5, "bf16")
+    m = cs.Model(synth.model_weights(shape, 97, threads=8), max_batch=len(lens), max_k=256)
+    sample = [(b, h) for b in sorted({0, len(lens) // 2, len(lens) - 1}) for h in (0, H // 2, H - 1)]
+    worst = _attention_case(m, shape, lens, rows, sample, seed=80 + rows, poison=True, k_ramp=k_ramp)
+    m.destroy()
+    assert worst < 1e-2, worst
+
+
 @pytest.mark.parametrize("rows", [6, 21, 51, 101])
 def test_attention_block_size_sweep(rows):
     """Block sizes of the paper's sweep (Sec. 5.3, Table 4: 5, 10, 50, 100 draft tokens; 20 added):
