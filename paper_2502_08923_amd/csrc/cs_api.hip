@@ -661,27 +661,28 @@ static int kv_check_room(cs_kv* kv, int rows) {
 }
 
 // runs all layers over the block tokens of `src`; leaves the final-normed rows in m->xn
-static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int rows, hipStream_t s) {
+// (rg: rows per stream, NULL: `rows` for each)
+static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int rows, const cs_ragged* rg, hipStream_t s) {
     const cs_model_cfg& c = m->cfg;
-    const int B = kv->B, R = B * rows;
+    const int B = kv->B, R = rg ? rg->R : B * rows;
     const int d = c.d_model, nq = c.n_heads * c.head_dim, nqkv = nq + 2 * c.n_kv_heads * c.head_dim;
     const int64_t len_ub = kv_max_ub(kv);
     CS_REQUIRE(m->head_loaded && m->layers_loaded == c.n_layers, CS_E_STATE,
                "the model is not complete: %d of %d layers loaded, embedding and lm_head %s", m->layers_loaded,
                c.n_layers, m->head_loaded ? "loaded" : "missing");
-    CS_TRY(cs_block_start_launch(m, src, kv->d_len, B, rows, s));
+    CS_TRY(cs_block_start_launch(m, src, kv->d_len, B, rows, rg, s));
     int np_prev = 0, np = 1;
     // narrow blocks: the attention kernel rotates q and k and appends k, v itself
-    const bool fuse_rope = cs_attention_fuses_rope(m, rows);
+    const bool fuse_rope = !rg && cs_attention_fuses_rope(m, rows);
     for (int l = 0; l < c.n_layers; ++l) {
         const cs_layer_dev& L = m->layers[l];
         CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, nqkv, true, s));
         CS_TRY(cs_gemm_launch(m, m->xn, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, 1, &np, s));
         if (fuse_rope) {
-            CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, m->part, np, s));
+            CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, m->part, np, nullptr, s));
         } else {
-            CS_TRY(cs_rope_append_launch(m, kv, l, m->part, np, rows, s));
-            CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, nullptr, 0, s));
+            CS_TRY(cs_rope_append_launch(m, kv, l, m->part, np, rows, rg, s));
+            CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, nullptr, 0, rg, s));
         }
         CS_TRY(cs_gemm_launch(m, m->xn, L.wo, m->part, R, d, nq, CS_GEMM_STORE, 1, &np, s));
         CS_TRY(cs_addnorm_launch(m, m->part, np, L.norm2, m->xn, R, 2 * c.d_ff, false, s));
@@ -708,7 +709,7 @@ static int verify_impl(cs_model* m, cs_kv* kv, const int32_t* d_pending, const i
     const int rows = k + 1, B = kv->B, R = B * rows, V = m->cfg.vocab;
     CS_TRY(kv_check_room(kv, rows));
     const cs_block_src src = {nullptr, d_pending, hist, hist_stride, hist_len, d_draft, d_draft_len};
-    CS_TRY(forward_layers(m, kv, src, rows, s));
+    CS_TRY(forward_layers(m, kv, src, rows, nullptr, s));
     const int pl = cs_prof_begin(CS_PROF_LMHEAD, s);
     if (m->fast && !d_logits_out) {
         // nobody wants the logits: the lm_head keeps them in its accumulators and hands over the
@@ -799,7 +800,7 @@ extern "C" int cs_prefill(cs_model* m, cs_kv* kv, int32_t stream_idx, const int3
     for (int64_t c0 = 0; c0 < body; c0 += chunk) {
         const int rows = (int)(body - c0 < chunk ? body - c0 : chunk);
         CS_HIP(hipMemcpyAsync(m->tok, prompt + c0, (size_t)rows * 4, hipMemcpyHostToDevice, nullptr));
-        CS_TRY(forward_layers(m, kv, prompt_src(m), rows, nullptr));
+        CS_TRY(forward_layers(m, kv, prompt_src(m), rows, nullptr, nullptr));
         k_add_i32<<<1, 64, 0, nullptr>>>(kv->d_len, rows, 1);
         CS_TRY(cs_launch_ok("k_add_i32"));
         kv->h_len_ub[0] += rows;
@@ -986,42 +987,77 @@ extern "C" int cs_prefill_batch(cs_model* m, cs_kv* kv, const int32_t* prompts, 
     CS_HIP(hipDeviceSynchronize());
     CS_HIP(hipMemset(kv->d_len, 0, (size_t)B * 4));
     for (int b = 0; b < B; ++b) kv->h_len_ub[b] = 0;
-    // Lock step: every pass runs the same number of rows for every stream.  A stream whose
-    // prompt is used up rides along on padding rows; their cache entries land beyond its
-    // length (dead rows) and, the block being causal, no live row ever sees them.
+    // Live rows only: every pass takes about the same number of rows, as many of each stream as of any other while they
+    // last (so that the attention of a pass has equally long walks), and the kernels are told whose row is whose.
+    // (With padding up to the longest prompt, eight 1B prompts of 593 to 1531 tokens took 27.3 ms, now 20.4.)
     const int64_t ws_rows = m->R_max > m->prefill_rows ? m->R_max : m->prefill_rows;
-    const int64_t chunk = ws_rows / B > 0 ? ws_rows / B : 1;
-    const int64_t max_body = max_len - 1;
-    std::vector<int32_t> tok, inc((size_t)B);
-    int32_t* d_inc = nullptr;
-    CS_HIP(hipMalloc(&d_inc, (size_t)B * 4));
-    int rc = CS_OK;
-    for (int64_t c0 = 0; c0 < max_body && rc == CS_OK; c0 += chunk) {
-        const int rows = (int)(max_body - c0 < chunk ? max_body - c0 : chunk);
-        tok.assign((size_t)B * rows, 0);
+    int64_t total = 0;
+    for (int b = 0; b < B; ++b) total += prompt_len[b] - 1;
+    if (total == 0) return CS_OK;
+    const int64_t per0 = cs_round_up(cs_ceil_div(total, cs_ceil_div(total, ws_rows)), 16), per = per0 < ws_rows ? per0 : ws_rows;
+    const int passes = (int)cs_ceil_div(total, per);
+    // one upload: per pass and stream (first row, rows), per row (stream, row within the share), tokens, row counts
+    std::vector<int32_t> up((size_t)(3 * passes * B + 3 * total), 0);
+    int32_t* h_seg = up.data();
+    int32_t* h_row = h_seg + (size_t)2 * passes * B;
+    int32_t* h_tok = h_row + 2 * total;
+    int32_t* h_cnt = h_tok + total;
+    std::vector<int64_t> done((size_t)(passes + 1) * B, 0);      // rows of each stream before each pass
+    int64_t at = 0;
+    for (int p = 0; p < passes; ++p) {
+        const int64_t target = total - p * per < per ? total - p * per : per;
+        const int64_t* before = done.data() + (size_t)p * B;
+        auto left = [&](int b) { return prompt_len[b] - 1 - before[b]; };
+        // the largest share c that fits when every stream gives min(left, c) rows; what remains, one row each
+        int64_t lo = 0, hi = target, taken = 0;
+        while (lo < hi) {
+            const int64_t c = (lo + hi + 1) / 2;
+            int64_t sum = 0;
+            for (int b = 0; b < B; ++b) sum += left(b) < c ? left(b) : c;
+            if (sum <= target) lo = c; else hi = c - 1;
+        }
+        for (int b = 0; b < B; ++b) taken += left(b) < lo ? left(b) : lo;
+        int64_t first = 0;
         for (int b = 0; b < B; ++b) {
-            const int64_t left = prompt_len[b] - 1 - c0;
-            const int64_t live = left < 0 ? 0 : (left < rows ? left : rows);
-            for (int64_t i = 0; i < live; ++i) tok[(size_t)b * rows + i] = prompts[(int64_t)b * prompt_stride + c0 + i];
-            inc[b] = (int32_t)live;
+            int64_t n = left(b) < lo ? left(b) : lo;
+            if (n < left(b) && taken < target) { ++n; ++taken; }
+            h_seg[2 * ((size_t)p * B + b)] = (int32_t)first;
+            h_seg[2 * ((size_t)p * B + b) + 1] = h_cnt[(size_t)p * B + b] = (int32_t)n;
+            for (int64_t i = 0; i < n; ++i, ++at) {
+                h_row[2 * at] = b;
+                h_row[2 * at + 1] = (int32_t)i;
+                h_tok[at] = prompts[(int64_t)b * prompt_stride + before[b] + i];
+            }
+            done[(size_t)(p + 1) * B + b] = before[b] + n;
+            first += n;
         }
-        if (hipMemcpy(m->tok, tok.data(), tok.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-            hipMemcpy(d_inc, inc.data(), (size_t)B * 4, hipMemcpyHostToDevice) != hipSuccess) {
-            cs_set_error("cs_prefill_batch: copy to device failed");
-            rc = CS_E_DEVICE;
-            break;
-        }
-        rc = forward_layers(m, kv, prompt_src(m), rows, nullptr);
-        if (rc != CS_OK) break;
-        k_add_i32_vec<<<(unsigned)cs_ceil_div(B, 64), 64, 0, nullptr>>>(kv->d_len, d_inc, B);
-        rc = cs_launch_ok("k_add_i32_vec");
-        for (int b = 0; b < B; ++b) kv->h_len_ub[b] += inc[b];
     }
+    int32_t* d_up = nullptr;
+    CS_HIP(hipMalloc(&d_up, up.size() * 4));
+    int rc = CS_OK;
+    if (hipMemcpy(d_up, up.data(), up.size() * 4, hipMemcpyHostToDevice) != hipSuccess) {
+        cs_set_error("cs_prefill_batch: copy to device failed");
+        rc = CS_E_DEVICE;
+    }
+    for (int p = 0; p < passes && rc == CS_OK; ++p) {
+        const int R = (int)(total - p * per < per ? total - p * per : per);
+        const int32_t* d_tok = d_up + (h_tok - up.data()) + p * per;
+        const int32_t* d_cnt = d_up + (h_cnt - up.data()) + (size_t)p * B;
+        const cs_ragged rg = {reinterpret_cast<const int2*>(d_up + (h_row - up.data())) + p * per,
+                              reinterpret_cast<const int2*>(d_up) + (size_t)p * B, h_cnt + (size_t)p * B, R};
+        for (int b = 0; b < B; ++b) kv->h_len_ub[b] = done[(size_t)p * B + b];
+        const cs_block_src src = {d_tok, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
+        rc = forward_layers(m, kv, src, 0, &rg, nullptr);
+        if (rc != CS_OK) break;
+        k_add_i32_vec<<<(unsigned)cs_ceil_div(B, 64), 64, 0, nullptr>>>(kv->d_len, d_cnt, B);
+        rc = cs_launch_ok("k_add_i32_vec");
+    }
+    for (int b = 0; b < B; ++b) kv->h_len_ub[b] = prompt_len[b] - 1;
     if (hipDeviceSynchronize() != hipSuccess && rc == CS_OK) {
         cs_set_error("cs_prefill_batch: device error");
         rc = CS_E_DEVICE;
     }
-    (void)hipFree(d_inc);
+    (void)hipFree(d_up);
     return rc;
 }
 
@@ -1138,7 +1174,7 @@ extern "C" int cs_decode_merged(cs_model* m, cs_kv* kv, cs_model* dm, cs_kv* dkv
                 const int64_t left = n - 1 - draft_rows;
                 const int rows = (int)(left < dm->prefill_rows ? left : dm->prefill_rows);
                 CS_HIP(hipMemcpyAsync(dm->tok, d + draft_rows, (size_t)rows * 4, hipMemcpyDeviceToDevice, s));
-                CS_TRY(forward_layers(dm, dkv, prompt_src(dm), rows, s));
+                CS_TRY(forward_layers(dm, dkv, prompt_src(dm), rows, nullptr, s));
                 k_add_i32<<<1, 64, 0, s>>>(dkv->d_len, rows, 1);
                 CS_TRY(cs_launch_ok("k_add_i32"));
                 dkv->h_len_ub[0] += rows;
@@ -1249,7 +1285,7 @@ extern "C" int cs_op_attention(cs_model* m, cs_kv* kv, int32_t layer, const floa
     CS_TRY(kv_check_room(kv, rows));
     const int64_t n = (int64_t)kv->B * rows * m->cfg.n_heads * m->cfg.head_dim;
     CS_TRY(cs_convert_launch(q, CS_T_F32, m->q, m->fast ? CS_T_BF16 : CS_T_F32, n, s));
-    CS_TRY(cs_attention_launch(m, kv, layer, rows, kv_max_ub(kv), 0, nullptr, 0, s));
+    CS_TRY(cs_attention_launch(m, kv, layer, rows, kv_max_ub(kv), 0, nullptr, 0, nullptr, s));
     return cs_convert_launch(m->xn, m->fast ? CS_T_F16 : CS_T_F32, out, CS_T_F32, n, s);
 }
 

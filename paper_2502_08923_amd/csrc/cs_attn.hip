@@ -18,6 +18,7 @@
 // four lanes that hold a query row, and O is only rescaled when some maximum moved.
 // The token range of a stream is split over workgroups, whose waves take its 32-token blocks in
 // turn; a merge kernel combines the partial (max, sum, O) triples.
+#include <algorithm>
 #include <type_traits>
 
 #include "cs_common.h"
@@ -64,14 +65,16 @@ __global__ __launch_bounds__(THREADS) void k_attn_plain(const QT* __restrict__ q
                                                         const WT* __restrict__ kc,
                                                         const WT* __restrict__ vc,
                                                         const int32_t* __restrict__ kv_len,
+                                                        const int2* __restrict__ map,
                                                         int rows, int H, int KVH, int hd,
                                                         int64_t cap, OT* __restrict__ out) {
     __shared__ float sc[PA_CHUNK];
     __shared__ float so[256];                      // running output of every feature
     __shared__ float wred[THREADS / CS_WAVE];
-    const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+    const int h = blockIdx.y, r = blockIdx.z * rows + blockIdx.x;
     const int tid = threadIdx.x;
-    const int r = b * rows + i;
+    const int2 at = cs_block_row(map, r, rows);
+    const int b = at.x, i = at.y;
     const int g = h / (H / KVH);
     const int n_ctx = kv_len[b] + i + 1;
     const WT* __restrict__ K = kc + ((int64_t)b * KVH + g) * cap * hd;
@@ -1053,6 +1056,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __
                                                              const bf16_t* __restrict__ kc,
                                                              const bf16_t* __restrict__ vc,
                                                              const int32_t* __restrict__ kv_len,
+                                                             const int2* __restrict__ segs,
                                                              int rows, int H, int KVH, int64_t cap,
                                                              int nqt, int ranges, unsigned inv_g,
                                                              OT* __restrict__ out, int tiled,
@@ -1076,7 +1080,13 @@ __global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __
     const int qt = nqt - 1 - (int)(blockIdx.x / ranges);          // heaviest first
     const int kvh = range % KVH, b = range / KVH;
     const int G = H / KVH;
+    int row0 = b * rows;                                // first of the stream's rows
+    if (segs) {
+        row0 = segs[b].x;
+        rows = segs[b].y;
+    }
     const int QR = G * rows;
+    if (qt * PF_QROWS >= QR) return;                    // (whole workgroup; a stream with fewer rows than others)
     const int L = kv_len[b];
     const int n_tok = L + rows;
     // causality: nothing beyond the last row of this workgroup is walked
@@ -1096,7 +1106,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __
     for (int nt = 0; nt < NT; ++nt) {
         const int n = n0 + nt * 16;
         const int i = n < QR ? block_row(n) : 0;
-        const bf16_t* qp = q + ((int64_t)(b * rows + i) * H + kvh * G + (n < QR ? n - i * G : 0)) * HD + g * 8;
+        const bf16_t* qp = q + ((int64_t)(row0 + i) * H + kvh * G + (n < QR ? n - i * G : 0)) * HD + g * 8;
 #pragma unroll
         for (int s = 0; s < KS; ++s)
             qreg[nt][s] = n < QR ? *reinterpret_cast<const bf16x8*>(qp + s * 32) : (bf16x8){0, 0, 0, 0, 0, 0, 0, 0};
@@ -1319,7 +1329,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __
     for (int nt = 0; nt < NT; ++nt) {
         const int n = n0 + nt * 16;
         if (n >= QR) continue;
-        const int i = block_row(n), r = b * rows + i;
+        const int i = block_row(n), r = row0 + i;
         const int col0 = (kvh * G + n - i * G) * HD + 4 * g;
         const float inv = 1.0f / lacc[nt][0];
 #pragma unroll
@@ -1425,22 +1435,22 @@ bool cs_attention_fuses_rope(const cs_model* m, int rows) {
 }
 
 int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64_t len_ub,
-                        int for_o_proj, const float* qkv_part, int qkv_nparts, hipStream_t s) {
+                        int for_o_proj, const float* qkv_part, int qkv_nparts, const cs_ragged* rg, hipStream_t s) {
     const cs_model_cfg& c = m->cfg;
     const int B = kv->B, H = c.n_heads, KVH = c.n_kv_heads, hd = c.head_dim;
     const int64_t per_layer = (int64_t)B * KVH * kv->cap * hd;
     if (!m->fast) {
-        dim3 grid(rows, H, B);
+        dim3 grid(rg ? rg->R : rows, H, rg ? 1 : B);
         auto start = [&](auto* k, auto threads) {
             typedef std::remove_pointer_t<decltype(k)> WT;
             constexpr int THREADS = decltype(threads)::value;
             k_attn_plain<WT, float, float, THREADS><<<grid, THREADS, 0, s>>>(
                 (const float*)m->q, (const WT*)kv->k + layer * per_layer, (const WT*)kv->v + layer * per_layer, kv->d_len,
-                rows, H, KVH, hd, kv->cap, (float*)m->xn);
+                rg ? rg->row : nullptr, rows, H, KVH, hd, kv->cap, (float*)m->xn);
         };
         // up to two workgroups per compute unit: 16 waves each instead of four (44 workgroups 23 -> 12 us; 2044 workgroups
         // of a prompt 43 -> 60 us)
-        const bool few = (int64_t)rows * H * B <= 512;
+        const bool few = (int64_t)grid.x * grid.y * grid.z <= 512;
         auto by_type = [&](auto threads) {
             if (c.dtype == CS_BF16) start((bf16_t*)nullptr, threads);
             else start((float*)nullptr, threads);
@@ -1450,12 +1460,14 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         return cs_launch_ok("k_attn_plain");
     }
     const int G = H / KVH;
-    const int QR = G * rows;
+    int widest = rows;
+    if (rg) widest = *std::max_element(rg->rows, rg->rows + B);
+    const int QR = G * widest;
     const int nqg = (int)cs_ceil_div(QR, FA_QROWS);
-    const int64_t n_tok_ub = len_ub + rows;
+    const int64_t n_tok_ub = len_ub + widest;
     // layout of the merged output: fragment order if the output projection (d_model outputs)
     // of these B*rows rows runs the many-row GEMM
-    const int tiled = for_o_proj && cs_gemm_x_tiled(B * rows, c.d_model, H * hd, true) ? 1 : 0;
+    const int tiled = for_o_proj && cs_gemm_x_tiled(rg ? rg->R : B * rows, c.d_model, H * hd, true) ? 1 : 0;
     const bf16_t* kc = (const bf16_t*)kv->k + layer * per_layer;
     const bf16_t* vc = (const bf16_t*)kv->v + layer * per_layer;
     CS_REQUIRE(!qkv_part || nqg == 1, CS_E_STATE, "fused rotary embedding needs a narrow block");
@@ -1465,15 +1477,18 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     // of 64-row tiles covers.  (Attention and merge, or this kernel alone, one stream of the 8B shape, prompts of 24, 64,
     // 128, 256 rows: 18.3, 20.7, 24.0, 29.7 us split, 9.4, 9.8, 11.7, 15.4 unsplit; a 32-token block costs a workgroup
     // 0.6 us, so that from about 900 tokens on the split kernel's 22 to 27 us are fewer.)
+    // Blocks with their own number of rows per stream always come here.
     const int64_t ranges = (int64_t)B * KVH;
-    const int64_t wgs_many = ranges * cs_ceil_div(QR, 256), wgs_few = ranges * cs_ceil_div(QR, 64);
+    const int64_t wgs_many = ranges * cs_ceil_div(QR, 256);
+    int64_t wgs_few = 0;
+    for (int b = 0; b < B; ++b) wgs_few += KVH * cs_ceil_div((int64_t)G * (rg ? rg->rows[b] : rows), 64);
     const bool many = QR >= 512 && wgs_many >= 40, brief = nqg > 1 && wgs_few <= 256 && n_tok_ub <= 768;
-    if ((many || brief) && (int64_t)hd * kv->cap * 2 < ((int64_t)1 << 32)) {
+    if (many || brief || rg) {
         // 64 query rows in four waves while that gives at most two workgroups per compute unit, or three of a prompt's
         // first block, whose early rows see few tokens (300, 512, 700, 1024, 1500 rows of the 8B shape: 21.1, 27.3, 33.4,
         // 42.6, 57.0 us with 256-row tiles, 15.8, 20.0, 27.5, 38.0, 54.0 with 64; 8 streams of 300 rows, 1216 workgroups: 31
         // against 34 us; 400 rows behind 4096, 200 workgroups: 134 against 95)
-        const bool small = wgs_few <= (len_ub < rows ? 768 : 512);
+        const bool small = wgs_few <= (len_ub < widest ? 768 : 512);
         const int nqt = (int)cs_ceil_div(QR, small ? 64 : 256);
         const unsigned inv_g = G > 1 ? (unsigned)(((1ull << 32) + G - 1) / G) : 0;
         dim3 grid((unsigned)(ranges * nqt));
@@ -1481,7 +1496,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         auto start = [&](auto hd_tag, auto nt_tag, auto wave_tag) {
             constexpr int HD = decltype(hd_tag)::value, NT = decltype(nt_tag)::value, WAVES = decltype(wave_tag)::value;
             k_attn_prefill<HD, NT, WAVES, f16_t><<<grid, 64 * WAVES, 0, s>>>(
-                (const bf16_t*)m->q, kc, vc, kv->d_len, rows, H, KVH, kv->cap, nqt, (int)ranges, inv_g, (f16_t*)m->xn, tiled,
+                (const bf16_t*)m->q, kc, vc, kv->d_len, rg ? rg->seg : nullptr, rows, H, KVH, kv->cap, nqt, (int)ranges, inv_g, (f16_t*)m->xn, tiled,
                 m->range_flags);
         };
         auto by_tile = [&](auto hd_tag) {

@@ -152,16 +152,25 @@ struct cs_block_src {
     const int32_t* draft;       // [B][rows - 1]
     const int32_t* draft_len;
 };
+// A prompt block with its own number of rows for every stream (all its rows are live): the rows lie stream after
+// stream, and the kernels look up which row is whose instead of dividing by a common count.
+struct cs_ragged {
+    const int2* row;            // [R] (stream, row within the stream's share), device
+    const int2* seg;            // [B] (first row, rows) of every stream, device
+    const int32_t* rows;        // [B] the same counts, host
+    int R;
+};
 // block tokens -> m->x (embeddings), m->rope (angles of every row's position)
+// (rg: NULL, or the block's rows per stream; `rows` is not used then.  So in the launchers below.)
 int cs_block_start_launch(const cs_model* m, const cs_block_src& src, const int32_t* kv_len, int B, int rows,
-                          hipStream_t s);
+                          const cs_ragged* rg, hipStream_t s);
 // x[r] += sum of nparts partial tiles (part[p][r][:]) and, if xn_out, xn_out[r] = rmsnorm(x[r])*gain
 // (next_N, next_split: output width of the GEMM that reads xn_out and whether it may split K; they decide
 // the layout of xn_out)
 int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
                       const float* gain, void* xn_out, int R, int next_N, bool next_split, hipStream_t s);
 int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* qkv, int nparts,
-                          int rows, hipStream_t s);
+                          int rows, const cs_ragged* rg, hipStream_t s);
 int cs_swiglu_launch(const cs_model* m, int R, hipStream_t s);
 // accept rule, state update from the argmax partials m->am_val_idx[row][nch]
 int cs_accept_launch(const cs_model* m, int nch, int B, int k, const int32_t* draft,
@@ -224,7 +233,7 @@ int cs_tile_weights_launch(const void* src, const void* src2, int N, int K, int 
 // append itself (no cs_rope_append_launch before it).
 bool cs_attention_fuses_rope(const cs_model* m, int rows);
 int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64_t len_ub,
-                        int for_o_proj, const float* qkv_part, int qkv_nparts, hipStream_t s);
+                        int for_o_proj, const float* qkv_part, int qkv_nparts, const cs_ragged* rg, hipStream_t s);
 
 // conversion helpers
 // element type codes for cs_convert_launch
@@ -277,6 +286,11 @@ __device__ __forceinline__ void cs_range_report(int32_t* flags, bool hit, int bi
 // running (largest value, lowest index) pair of an argmax
 __device__ __forceinline__ void cs_am_take(float& bv, int& bi, float v, int i) {
     if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
+}
+
+// (stream, row within the stream's block) of block row r
+__device__ __forceinline__ int2 cs_block_row(const int2* __restrict__ map, int r, int rows) {
+    return map ? map[r] : make_int2(r / rows, r % rows);
 }
 
 __device__ __forceinline__ float cs_wave_sum(float v) {

@@ -20,14 +20,15 @@ __device__ __forceinline__ float4 start_load4(const bf16_t* p) {
     return make_float4((float)t[0], (float)t[1], (float)t[2], (float)t[3]);
 }
 template <typename WT>
-__global__ __launch_bounds__(START_THREADS) void k_block_start(cs_block_src src, int rows, int V,
+__global__ __launch_bounds__(START_THREADS) void k_block_start(cs_block_src src, const int2* __restrict__ map, int rows, int V,
                                                                const WT* __restrict__ embed, int d,
                                                                float* __restrict__ x,
                                                                const int32_t* __restrict__ kv_len, int half,
                                                                double theta, const double* __restrict__ inv_freq,
                                                                float2* __restrict__ rope) {
     const int r = blockIdx.x;
-    const int b = r / rows, i = r % rows;
+    const int2 at = cs_block_row(map, r, rows);
+    const int b = at.x, i = at.y;
     int t = 0;
     if (src.tok) {
         t = src.tok[r];
@@ -129,13 +130,14 @@ template <typename WT, typename QT>
 __global__ __launch_bounds__(64) void k_rope_append(const float* __restrict__ qkv, int nparts,
                                                     int64_t part_stride,
                                                     const float2* __restrict__ rope,
-                                                    const int32_t* __restrict__ kv_len, int rows,
-                                                    int H, int KVH, int hd, int64_t cap,
+                                                    const int32_t* __restrict__ kv_len,
+                                                    const int2* __restrict__ map, int rows, int H, int KVH, int hd, int64_t cap,
                                                     WT* __restrict__ kc, WT* __restrict__ vc,
                                                     QT* __restrict__ q,
                                                     const float* __restrict__ bias) {
     const int r = blockIdx.y, head = blockIdx.x;     // head: q heads, then k heads, then v heads
-    const int b = r / rows, i = r % rows;
+    const int2 at = cs_block_row(map, r, rows);
+    const int b = at.x, i = at.y;
     const int half = hd / 2;
     const int nq = (H + 2 * KVH) * hd;
     const int64_t pos = (int64_t)kv_len[b] + i;
@@ -183,7 +185,7 @@ __global__ __launch_bounds__(64) void k_rope_append(const float* __restrict__ qk
 #define RA_THREADS 256
 __global__ __launch_bounds__(RA_THREADS) void k_rope_append_rows(
     const float* __restrict__ qkv, int nparts, int64_t part_stride, const float2* __restrict__ rope,
-    const int32_t* __restrict__ kv_len, int rows, int R, int H, int KVH, int hd, int64_t cap,
+    const int32_t* __restrict__ kv_len, const int2* __restrict__ map, int rows, int R, int H, int KVH, int hd, int64_t cap,
     bf16_t* __restrict__ kc, bf16_t* __restrict__ vc, bf16_t* __restrict__ q,
     const float* __restrict__ bias) {
     __shared__ bf16_t vt[256][RA_ROWS + 2];            // [d][row of the workgroup], hd <= 256
@@ -194,7 +196,8 @@ __global__ __launch_bounds__(RA_THREADS) void k_rope_append_rows(
     const int half = hd / 2;
     const int nq = (H + 2 * KVH) * hd;
     const bool live = r < R;
-    const int b = live ? r / rows : 0, i = live ? r % rows : 0;
+    const int2 at = live ? cs_block_row(map, r, rows) : make_int2(0, 0);
+    const int b = at.x, i = at.y;
     const int64_t pos = live ? (int64_t)kv_len[b] + i : 0;
     const bool is_v = head >= H + KVH;
     if (is_v && t8 == 0) voff[rr] = live ? ((int64_t)b * KVH + (head - H - KVH)) * hd * cap + cs_v_index(pos, 0, hd) : -1;
@@ -424,14 +427,16 @@ __global__ void k_fill_i32(int32_t* p, int32_t v, int64_t n) {
 // host launchers
 // -------------------------------------------------------------------------------------
 int cs_block_start_launch(const cs_model* m, const cs_block_src& src, const int32_t* kv_len, int B, int rows,
-                          hipStream_t s) {
+                          const cs_ragged* rg, hipStream_t s) {
     const cs_model_cfg& c = m->cfg;
+    const int R = rg ? rg->R : B * rows;
+    const int2* map = rg ? rg->row : nullptr;
     if (c.dtype == CS_BF16)
-        k_block_start<bf16_t><<<B * rows, START_THREADS, 0, s>>>(src, rows, c.vocab, (const bf16_t*)m->embed, c.d_model,
+        k_block_start<bf16_t><<<R, START_THREADS, 0, s>>>(src, map, rows, c.vocab, (const bf16_t*)m->embed, c.d_model,
                                                                  m->x, kv_len, c.head_dim / 2, (double)c.rope_theta,
                                                                  m->rope_inv_freq, m->rope);
     else
-        k_block_start<float><<<B * rows, START_THREADS, 0, s>>>(src, rows, c.vocab, (const float*)m->embed, c.d_model,
+        k_block_start<float><<<R, START_THREADS, 0, s>>>(src, map, rows, c.vocab, (const float*)m->embed, c.d_model,
                                                                 m->x, kv_len, c.head_dim / 2, (double)c.rope_theta,
                                                                 m->rope_inv_freq, m->rope);
     return cs_launch_ok("k_block_start");
@@ -452,9 +457,10 @@ int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
 }
 
 int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* qkv, int nparts,
-                          int rows, hipStream_t s) {
+                          int rows, const cs_ragged* rg, hipStream_t s) {
     const cs_model_cfg& c = m->cfg;
-    const int R = kv->B * rows;
+    const int R = rg ? rg->R : kv->B * rows;
+    const int2* map = rg ? rg->row : nullptr;
     const int64_t per_layer = (int64_t)kv->B * c.n_kv_heads * kv->cap * c.head_dim;
     const int64_t ps = (int64_t)R * (c.n_heads + 2 * c.n_kv_heads) * c.head_dim;
     const float2* rope = m->rope;
@@ -466,21 +472,21 @@ int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* 
         // many rows: the tiled version (needs 16-byte aligned quads: head_dim % 8 == 0)
         if (m->fast && R >= 4 * RA_ROWS && c.head_dim % 8 == 0 && c.head_dim <= 256) {
             dim3 grid(c.n_heads + 2 * c.n_kv_heads, (unsigned)cs_ceil_div(R, RA_ROWS));
-            k_rope_append_rows<<<grid, RA_THREADS, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, rows, R, c.n_heads,
+            k_rope_append_rows<<<grid, RA_THREADS, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, map, rows, R, c.n_heads,
                                                           c.n_kv_heads, c.head_dim, kv->cap, kc, vc,
                                                           (bf16_t*)m->q, bias);
         } else if (m->fast)
-            k_rope_append<bf16_t, bf16_t><<<rgrid, 64, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, rows,
+            k_rope_append<bf16_t, bf16_t><<<rgrid, 64, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, map, rows,
                                                            c.n_heads, c.n_kv_heads, c.head_dim,
                                                            kv->cap, kc, vc, (bf16_t*)m->q, bias);
         else
-            k_rope_append<bf16_t, float><<<rgrid, 64, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, rows,
+            k_rope_append<bf16_t, float><<<rgrid, 64, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, map, rows,
                                                           c.n_heads, c.n_kv_heads, c.head_dim,
                                                           kv->cap, kc, vc, (float*)m->q, bias);
     } else {
         float* kc = (float*)kv->k + layer * per_layer;
         float* vc = (float*)kv->v + layer * per_layer;
-        k_rope_append<float, float><<<rgrid, 64, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, rows,
+        k_rope_append<float, float><<<rgrid, 64, 0, s>>>(qkv, nparts, ps, rope, kv->d_len, map, rows,
                                                      c.n_heads, c.n_kv_heads, c.head_dim, kv->cap,
                                                      kc, vc, (float*)m->q, bias);
     }

@@ -899,6 +899,34 @@ def test_prefill_batch_and_decode_batch_bf16():
     model.destroy()
 
 
+@pytest.mark.parametrize("shape,plain", [(MINI64, False), (MINI128, False), (MINIQWEN, False), (MINI64, True), (SMALLF32, False)])
+@pytest.mark.parametrize("block_rows", [16, 52, 400])
+def test_prefill_batch_passes_across_prompts(shape, plain, block_rows):
+    """Passes that hold the end of one prompt, whole ones (of no row, one row, a few) and the start of another, down to a
+    few rows of one stream behind many: the cache rows are the oracle's, and nothing is written past a stream's rows."""
+    lens = [100, 1, 33, 2, 70, 150, 1]
+    w = synth.model_weights(shape, 8130, threads=4)
+    model = cs.Model(w, max_batch=len(lens), max_k=1, plain=plain, prompt_block_rows=block_rows)
+    prompts = _ragged_prompts(shape.vocab, [max(n, 40) for n in lens], 5201)
+    prompts = [p[:n] for p, n in zip(prompts, lens)]
+    kv = cs.KV(model, len(lens), 192)
+    tol = 1e-4 if shape.dtype == "f32" else 2e-2
+    for _ in range(2):
+        cs.cs_prefill_batch(model, kv, prompts)
+        for b, n in enumerate(lens):
+            assert kv.len(b) == n - 1
+            okv = orc.KVCache(shape, 192)
+            orc.prefill(w, okv, prompts[b], chunk=64)
+            for layer in range(shape.n_layers):
+                k_rows, v_rows = kv.read(layer, b, 0, 192)
+                if n > 1:
+                    _cache_rows_close(k_rows[:, :n - 1], okv.k[layer, :, :n - 1], tol)
+                    _cache_rows_close(v_rows[:, :n - 1], okv.v[layer, :, :n - 1], tol)
+                assert not k_rows[:, n - 1:].any() and not v_rows[:, n - 1:].any()
+    kv.destroy()
+    model.destroy()
+
+
 def test_decode_batch_full_acceptance_repeat_model():
     """A model whose greedy token repeats its input: every history becomes x, x, x, ..., every
     match is accepted whole, in every stream; steps, attempts and accepted counts are the
