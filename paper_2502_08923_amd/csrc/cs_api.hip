@@ -162,7 +162,7 @@ static int dev_alloc(void** p, size_t bytes) {
 
 static void model_free(cs_model* m) {
     if (!m) return;
-    void* ptrs[] = {m->embed, m->lm_head, m->final_norm, m->x, m->xn, m->q, m->gu, m->act,
+    void* ptrs[] = {m->embed, m->lm_head, m->final_norm, m->x, m->ss, m->xn, m->q, m->gu, m->act,
                     m->logits, m->part, m->attn_part, m->rope, m->tok, m->am_val_idx,
                     m->row_argmax, m->draft, m->draft_len, m->match_pos, m->pending, m->range_flags,
                     m->rope_inv_freq};
@@ -284,6 +284,7 @@ static int model_alloc(cs_model* m) {
     const size_t a = m->asz;
     const int wide = d > nq ? d : nq;
     DEV_ALLOC(m->x, R * d * 4);
+    DEV_ALLOC(m->ss, (size_t)cs_ceil_div(d, 16) * 16 * 4);
     DEV_ALLOC(m->xn, R * wide * 4 > cs_xt_bytes(R, wide) ? R * wide * 4 : cs_xt_bytes(R, wide));
     DEV_ALLOC(m->q, R * nq * 4);
     if (!m->fast) DEV_ALLOC(m->gu, R * 2 * F * 4);
@@ -674,15 +675,28 @@ static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int r
     int np_prev = 0, np = 1;
     // narrow blocks: the attention kernel rotates q and k and appends k, v itself
     const bool fuse_rope = !rg && cs_attention_fuses_rope(m, rows);
+    // up to 16 rows: no norm kernels, the projections read and write the residual stream (see cs_gemm_norm_launch)
+    const bool few = cs_gemm_few_rows(m, R);
+    int nss = 1;
     for (int l = 0; l < c.n_layers; ++l) {
         const cs_layer_dev& L = m->layers[l];
-        CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, nqkv, true, s));
-        CS_TRY(cs_gemm_launch(m, m->xn, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, 1, &np, s));
+        if (few) {
+            CS_TRY(cs_gemm_norm_launch(m, L.norm1, nss, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, &np, s));
+        } else {
+            CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, nqkv, true, s));
+            CS_TRY(cs_gemm_launch(m, m->xn, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, 1, &np, s));
+        }
         if (fuse_rope) {
             CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, m->part, np, nullptr, s));
         } else {
             CS_TRY(cs_rope_append_launch(m, kv, l, m->part, np, rows, rg, s));
             CS_TRY(cs_attention_launch(m, kv, l, rows, len_ub, 1, nullptr, 0, rg, s));
+        }
+        if (few) {
+            CS_TRY(cs_gemm_residual_launch(m, m->xn, L.wo, R, d, nq, &nss, s));
+            CS_TRY(cs_gemm_norm_launch(m, L.norm2, nss, L.wgu, nullptr, R, 2 * c.d_ff, d, CS_GEMM_SWIGLU, nullptr, s));
+            CS_TRY(cs_gemm_residual_launch(m, m->act, L.wd, R, d, c.d_ff, &nss, s));
+            continue;
         }
         CS_TRY(cs_gemm_launch(m, m->xn, L.wo, m->part, R, d, nq, CS_GEMM_STORE, 1, &np, s));
         CS_TRY(cs_addnorm_launch(m, m->part, np, L.norm2, m->xn, R, 2 * c.d_ff, false, s));

@@ -1466,8 +1466,9 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const int nqg = (int)cs_ceil_div(QR, FA_QROWS);
     const int64_t n_tok_ub = len_ub + widest;
     // layout of the merged output: fragment order if the output projection (d_model outputs)
-    // of these B*rows rows runs the many-row GEMM
-    const int tiled = for_o_proj && cs_gemm_x_tiled(rg ? rg->R : B * rows, c.d_model, H * hd, true) ? 1 : 0;
+    // of these rows runs the many-row GEMM or the one for few rows
+    const int R = rg ? rg->R : B * rows;
+    const int tiled = for_o_proj && (cs_gemm_few_rows(m, R) || cs_gemm_x_tiled(R, c.d_model, H * hd, true)) ? 1 : 0;
     const bf16_t* kc = (const bf16_t*)kv->k + layer * per_layer;
     const bf16_t* vc = (const bf16_t*)kv->v + layer * per_layer;
     CS_REQUIRE(!qkv_part || nqg == 1, CS_E_STATE, "fused rotary embedding needs a narrow block");

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(START_THREADS) void k_block_start(cs_block_src src,
                                                                float* __restrict__ x,
                                                                const int32_t* __restrict__ kv_len, int half,
                                                                double theta, const double* __restrict__ inv_freq,
-                                                               float2* __restrict__ rope) {
+                                                               float2* __restrict__ rope, float* __restrict__ ss) {
     const int r = blockIdx.x;
     const int2 at = cs_block_row(map, r, rows);
     const int b = at.x, i = at.y;
@@ -41,8 +41,20 @@ __global__ __launch_bounds__(START_THREADS) void k_block_start(cs_block_src src,
     }
     if (t < 0 || t >= V) t = 0;   // an out-of-vocabulary draft can never be accepted
     const WT* __restrict__ e = embed + (int64_t)t * d;
-    for (int c = 4 * threadIdx.x; c < d; c += 4 * START_THREADS)      // d is a multiple of 4 (checked on the host)
-        *reinterpret_cast<float4*>(x + (int64_t)r * d + c) = start_load4(e + c);
+    float q = 0.f;
+    for (int c = 4 * threadIdx.x; c < d; c += 4 * START_THREADS) {    // d is a multiple of 4 (checked on the host)
+        const float4 v = start_load4(e + c);
+        *reinterpret_cast<float4*>(x + (int64_t)r * d + c) = v;
+        q += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+    }
+    if (ss) {                                          // blocks of up to 16 rows: the sum of squares, in one piece
+        __shared__ float wsum[START_THREADS / CS_WAVE];
+        q = cs_wave_sum(q);
+        if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = q;
+        __syncthreads();
+        if (threadIdx.x == 0) ss[r] = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+        static_assert(START_THREADS == 4 * CS_WAVE, "four wave sums");
+    }
     const double pos = (double)(kv_len[b] + i);
     for (int j = threadIdx.x; j < half; j += START_THREADS) {
         const double inv = inv_freq ? inv_freq[j] : pow(theta, -2.0 * (double)j / (double)(2 * half));
@@ -431,14 +443,15 @@ int cs_block_start_launch(const cs_model* m, const cs_block_src& src, const int3
     const cs_model_cfg& c = m->cfg;
     const int R = rg ? rg->R : B * rows;
     const int2* map = rg ? rg->row : nullptr;
+    float* ss = cs_gemm_few_rows(m, R) ? m->ss : nullptr;
     if (c.dtype == CS_BF16)
         k_block_start<bf16_t><<<R, START_THREADS, 0, s>>>(src, map, rows, c.vocab, (const bf16_t*)m->embed, c.d_model,
                                                                  m->x, kv_len, c.head_dim / 2, (double)c.rope_theta,
-                                                                 m->rope_inv_freq, m->rope);
+                                                                 m->rope_inv_freq, m->rope, ss);
     else
         k_block_start<float><<<R, START_THREADS, 0, s>>>(src, map, rows, c.vocab, (const float*)m->embed, c.d_model,
                                                                 m->x, kv_len, c.head_dim / 2, (double)c.rope_theta,
-                                                                m->rope_inv_freq, m->rope);
+                                                                m->rope_inv_freq, m->rope, ss);
     return cs_launch_ok("k_block_start");
 }
 

@@ -157,13 +157,23 @@ static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K
 // grid.y: K splits.
 // act_tiled by mode: SWIGLU - the output goes out in fragment order; ARGMAX - tiles per row of the
 // pair buffer.
+// XN: X is not given; the producers normalise the float32 residual stream themselves (few rows, see cs_norm_in).
+struct cs_norm_in {
+    const float* x;         // [R][K] residual stream
+    const float* gain;      // [K]
+    const float* ss;        // [nss][16] pieces of every row's sum of squares
+    int nss;
+    float eps;
+    int32_t* flags;
+};
 #define GEMM_STORE_STREAM 3   // CS_GEMM_STORE whose partial tiles leave through streaming stores
-template <int MT, int NT, int MODE, int CW>
+template <int MT, int NT, int MODE, int CW, bool XN = false>
 __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __restrict__ X,
                                                             const f16_t* __restrict__ W,
                                                             float* __restrict__ Y,
                                                             f16_t* __restrict__ act, int R, int N,
-                                                            int K, int Ks, int RB, int act_tiled) {
+                                                            int K, int Ks, int RB, int act_tiled,
+                                                            cs_norm_in nrm) {
     __shared__ __attribute__((aligned(16))) unsigned char xs[2][16 * NT * GEMM_LDS_ROW];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
@@ -179,7 +189,93 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
     if (w_tile * 16 * MT * CW >= N) return;               // whole workgroup, before any barrier
     const int r_base = (rem >> 3) * 16 * NT;
 
-    if (wave >= CW) {
+    // XN: the rows' sums of squares come in nss pieces [nss][16], one per column tile of the kernel that wrote the
+    // stream.  All waves take a share, requested before anything else (loads return in order).
+    constexpr int SQ = XN ? 4 : 1;
+    f32x4 sq[SQ];
+    auto sq_request = [&]() {
+#pragma unroll
+        for (int u = 0; u < SQ; ++u) {
+            const int i = tid + u * 64 * (CW + 2);
+            sq[u] = i < 4 * nrm.nss ? *reinterpret_cast<const f32x4*>(nrm.ss + 4 * i) : (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+    };
+    __shared__ __attribute__((aligned(16))) float sq_part[XN ? CW + 2 : 1][16];
+    auto sq_reduce = [&]() {
+        f32x4 a = sq[0];
+#pragma unroll
+        for (int u = 1; u < SQ; ++u) a += sq[u];
+        for (int i = tid + SQ * 64 * (CW + 2); i < 4 * nrm.nss; i += 64 * (CW + 2)) a += *reinterpret_cast<const f32x4*>(nrm.ss + 4 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int o = 4; o < 64; o <<= 1) a[j] += __shfl_xor(a[j], o, 64);
+        if (lane < 4) *reinterpret_cast<f32x4*>(&sq_part[wave][4 * lane]) = a;
+        __syncthreads();
+    };
+    if constexpr (XN) sq_request();
+
+    if constexpr (XN) {
+        if (wave >= CW) {
+            // ---------------- producers, X the residual stream: RMSNorm on the way to LDS ----------------
+            static_assert(NT == 1, "few rows only");
+            constexpr int ROWS4 = 2;                   // rows of a lane, four apart
+            const int seg = lane & 15, row0 = (lane >> 4) + (wave - CW) * 8;
+            const int dst0 = row0 * GEMM_LDS_ROW + seg * 16;
+            const float* xrow[ROWS4];
+#pragma unroll
+            for (int i = 0; i < ROWS4; ++i) xrow[i] = nrm.x + (int64_t)min(row0 + 4 * i, R - 1) * K + k_begin + seg * 8;
+            const float* grow = nrm.gain + k_begin + seg * 8;
+            f32x4 xr[2][ROWS4][2], gr[2][2];
+            const int last = nchunks - 1;
+            auto load_x = [&](int slot, int c) {
+                c = c < last ? c : last;               // clamped, see below
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    gr[slot][h] = *reinterpret_cast<const f32x4*>(grow + c * GEMM_KC + 4 * h);
+#pragma unroll
+                    for (int i = 0; i < ROWS4; ++i) xr[slot][i][h] = *reinterpret_cast<const f32x4*>(xrow[i] + c * GEMM_KC + 4 * h);
+                }
+            };
+            load_x(0, 0);
+            load_x(1, 1);
+            sq_reduce();
+            float scale[ROWS4];
+#pragma unroll
+            for (int i = 0; i < ROWS4; ++i) {
+                float q = 0.f;
+#pragma unroll
+                for (int w = 0; w < CW + 2; ++w) q += sq_part[w][row0 + 4 * i];
+                scale[i] = row0 + 4 * i < R ? 1.0f / sqrtf(q / (float)K + nrm.eps) : 0.f;      // rows past R: zeros
+            }
+            bool hit = false;
+            auto store_x = [&](int slot, int buf) {
+#pragma unroll
+                for (int i = 0; i < ROWS4; ++i) {
+                    f16x8 o;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] = cs_f16_sat(xr[slot][i][e >> 2][e & 3] * scale[i] * gr[slot][e >> 2][e & 3], hit);
+                    *reinterpret_cast<f16x8*>(&xs[buf][dst0 + i * 4 * GEMM_LDS_ROW]) = o;
+                }
+            };
+            store_x(0, 0);
+            load_x(0, 2);
+            __syncthreads();
+            int c = 0;
+            for (; c + 1 < nchunks; c += 2) {          // as below
+                store_x(1, 1);
+                load_x(1, c + 3);
+                __syncthreads();
+                store_x(0, 0);
+                load_x(0, c + 4);
+                __syncthreads();
+            }
+            if (c < nchunks) __syncthreads();
+            cs_range_report(nrm.flags, hit, CS_RANGE_NORM);
+            return;
+        }
+    }
+    if (!XN && wave >= CW) {
         // ---------------- producers: X chunks -> LDS ----------------
         // lane -> 16-byte segment (lane & 15) of rows row0 + 4*i, i < ROWS4; the two producer
         // waves split the 16*NT rows in halves
@@ -281,6 +377,7 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
     };
 #pragma unroll
     for (int u = 0; u < GEMM_DEPTH; ++u) load_w(a[u], u);
+    if constexpr (XN) sq_reduce();
     __syncthreads();
     int c = 0;
     for (; c + GEMM_DEPTH <= nchunks; c += GEMM_DEPTH) {      // branch-free groups of DEPTH chunks
@@ -769,13 +866,29 @@ static void start_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     // 168: -0.9 %, 264: -0.3 %); with few rows the readers find them in the caches and a plain
     // store wins (48 rows +0.4 %, one stream of 11 rows +2.5 to +3.6 %).
     if (mode == CS_GEMM_STORE && R >= 64)
-        k_gemm_mfma<MT, NT, GEMM_STORE_STREAM, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+        k_gemm_mfma<MT, NT, GEMM_STORE_STREAM, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
     else if (mode == CS_GEMM_STORE)
-        k_gemm_mfma<MT, NT, CS_GEMM_STORE, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+        k_gemm_mfma<MT, NT, CS_GEMM_STORE, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
     else if (mode == CS_GEMM_ARGMAX)
-        k_gemm_mfma<MT, NT, CS_GEMM_ARGMAX, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+        k_gemm_mfma<MT, NT, CS_GEMM_ARGMAX, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
     else if constexpr (MT % 2 == 0)
-        k_gemm_mfma<MT, NT, CS_GEMM_SWIGLU, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+        k_gemm_mfma<MT, NT, CS_GEMM_SWIGLU, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
+}
+
+// few rows, normalised by the producers
+static void start_norm(const cs_norm_in& nrm, const f16_t* W, float* Y, f16_t* act, int R, int N, int K, int mode, int Ks,
+                       int waves, hipStream_t s) {
+    dim3 grid((unsigned)cs_round_up(cs_ceil_div(N, 32 * waves), 8), (unsigned)cs_ceil_div(K, Ks));
+    auto start = [&](auto cw_tag) {
+        constexpr int CW = decltype(cw_tag)::value;
+        if (mode == CS_GEMM_STORE)
+            k_gemm_mfma<2, 1, CS_GEMM_STORE, CW, true><<<grid, 64 * (CW + 2), 0, s>>>(nullptr, W, Y, act, R, N, K, Ks, 1, 0, nrm);
+        else
+            k_gemm_mfma<2, 1, CS_GEMM_SWIGLU, CW, true><<<grid, 64 * (CW + 2), 0, s>>>(nullptr, W, Y, act, R, N, K, Ks, 1, 1, nrm);
+    };
+    if (waves == 5) start(std::integral_constant<int, 5>{});
+    else if (waves == 2) start(std::integral_constant<int, 2>{});
+    else start(std::integral_constant<int, 4>{});
 }
 
 template <int MT, int NT>
@@ -973,6 +1086,110 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
         case 7: return launch_mfma<2, 7>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
         default: return launch_mfma<2, 8>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
     }
+}
+
+// -------------------------------------------------------------------------------------
+// output and down projections of few rows (up to 16): x += X * W^T, all of K in one workgroup
+//
+// A step of one stream is a chain of short launches, and what the partial tiles of a K split cost there is the kernel
+// that adds them to the residual stream and normalises it (4 to 5 us, twice per layer).  Here a workgroup owns 16 W
+// rows and all of K: its eight waves take the 128-wide chunks of K in turn, W and X fragments (both stored in that
+// order; X row-major, 64 bytes per row and load, 9.4 against 8.6 us) straight into registers, four chunks (16 KB of W
+// each wave) in flight, and are summed through LDS.  It then adds its columns to the residual stream and leaves their
+// sums of squares per row, from which the next projection's producers normalise the stream (cs_norm_in).
+// 11 rows, a layer's norms, q/k/v, o, gate/up, down: 1B shape 45 -> 40 us, 8B 94 -> 84 us.  Tiles of 8 W rows on twice
+// the compute units: no faster at 1B, 24 against 15 us at 8B.  17 to 32 rows the same way (two row tiles): no gain,
+// the float32 rows that every workgroup reads and its 32 rows of X cost what the norm kernels did.
+// -------------------------------------------------------------------------------------
+#define GR_WAVES 8
+#define GR_DEPTH 4            // chunks in flight per wave
+__global__ __launch_bounds__(64 * GR_WAVES) void k_gemm_residual(const f16_t* __restrict__ X, const f16_t* __restrict__ W,
+                                                                 float* __restrict__ x, float* __restrict__ ss, int R,
+                                                                 int N, int K) {
+    __shared__ f32x4 red[GR_WAVES][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lrow = lane & 15, g = lane >> 4;
+    const int64_t chunk_stride = (int64_t)(N >> 4) * 2048;
+    const f16_t* __restrict__ w = W + (int64_t)blockIdx.x * 2048 + lane * 8;
+    const f16_t* __restrict__ xr = X + (min(lrow, R - 1) + 16 * g) * 8;         // (rows past R: the last row again)
+    const int nch = K / GEMM_KC, mine = (nch - wave + GR_WAVES - 1) / GR_WAVES;
+    // wave 0 adds to the residual stream: row lrow, columns n .. n + 3
+    const int n = blockIdx.x * 16 + 4 * g;
+    const bool out = wave == 0 && lrow < R;
+    float* __restrict__ dst = x + (int64_t)(out ? lrow : 0) * N + n;
+    f32x4 res = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if (out) res = *reinterpret_cast<const f32x4*>(dst);
+    f16x8 a[GR_DEPTH][4], b[GR_DEPTH][4];
+    auto load = [&](int u, int i) {                    // (clamped: a surplus load re-reads the last chunk)
+        const int c = min(wave + GR_WAVES * i, nch - 1);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            a[u][s] = *reinterpret_cast<const f16x8*>(w + c * chunk_stride + s * 512);
+            b[u][s] = *reinterpret_cast<const f16x8*>(xr + c * 2048 + s * 512);
+        }
+    };
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    auto multiply = [&](int u) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[s & 1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[u][s], b[u][s], acc[s & 1], 0, 0, 0);
+    };
+#pragma unroll
+    for (int u = 0; u < GR_DEPTH; ++u) load(u, u);
+    int i = 0;
+    for (; i + GR_DEPTH <= mine; i += GR_DEPTH) {
+#pragma unroll
+        for (int u = 0; u < GR_DEPTH; ++u) {
+            multiply(u);
+            load(u, i + u + GR_DEPTH);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < GR_DEPTH - 1; ++u)
+        if (i + u < mine) multiply(u);
+    red[wave][lane] = acc[0] + acc[1];
+    __syncthreads();
+    if (wave > 0) return;
+    f32x4 part[GR_WAVES];
+#pragma unroll
+    for (int u = 0; u < GR_WAVES; ++u) part[u] = red[u][lane];
+#pragma unroll
+    for (int h = GR_WAVES / 2; h > 0; h /= 2)
+#pragma unroll
+        for (int u = 0; u < h; ++u) part[u] += part[u + h];
+    const f32x4 v = res + part[0];
+    if (out) *reinterpret_cast<f32x4*>(dst) = v;
+    float q = out ? v[0] * v[0] + v[1] * v[1] + v[2] * v[2] + v[3] * v[3] : 0.f;
+    q += __shfl_xor(q, 16, 64);
+    q += __shfl_xor(q, 32, 64);
+    if (g == 0) ss[blockIdx.x * 16 + lrow] = q;
+}
+
+// Blocks that take the normalising projections and the ones that write the residual stream.
+bool cs_gemm_few_rows(const cs_model* m, int R) { return m->fast && R <= 16; }
+
+int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const void* W, float* Y, int R, int N, int K, int mode,
+                        int* nparts_out, hipStream_t s) {
+    CS_REQUIRE(mfma_shape_ok(N, K) && (mode == CS_GEMM_STORE || N % 32 == 0), CS_E_UNSUPPORTED,
+               "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
+    mfma_shape plan = mfma_plan(R, N, K, mode == CS_GEMM_STORE);
+    while (plan.ksplit > 1 && (size_t)plan.ksplit * R * N > m->part_floats) plan.ksplit /= 2;
+    const int Ks = (int)cs_round_up(cs_ceil_div(K, plan.ksplit), GEMM_KC);
+    if (nparts_out) *nparts_out = (int)cs_ceil_div(K, Ks);
+    if (mode == CS_GEMM_SWIGLU) Y = reinterpret_cast<float*>(m->range_flags);   // see the epilogue
+    const cs_norm_in nrm = {m->x, gain, m->ss, nss, m->cfg.rms_eps, m->range_flags};
+    const int pg = cs_prof_begin(CS_PROF_GEMM, s);
+    start_norm(nrm, (const f16_t*)W, Y, (f16_t*)m->act, R, N, K, mode, Ks, plan.waves, s);
+    cs_prof_end(pg, s);
+    return cs_launch_ok("k_gemm_mfma (normalising)");
+}
+
+int cs_gemm_residual_launch(const cs_model* m, const void* X, const void* W, int R, int N, int K, int* nss, hipStream_t s) {
+    CS_REQUIRE(mfma_shape_ok(N, K), CS_E_UNSUPPORTED, "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
+    *nss = N / 16;
+    const int pg = cs_prof_begin(CS_PROF_GEMM, s);
+    k_gemm_residual<<<*nss, 64 * GR_WAVES, 0, s>>>((const f16_t*)X, (const f16_t*)W, m->x, m->ss, R, N, K);
+    cs_prof_end(pg, s);
+    return cs_launch_ok("k_gemm_residual");
 }
 
 int cs_gemm_plain_launch(int dtype, const float* X, const void* W, float* Y, int R, int N, int K,

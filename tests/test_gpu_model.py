@@ -216,6 +216,17 @@ def test_narrow_blocks_through_the_pipelined_loop(shape, k, streams, n):
     _ragged_verify(shape, (n,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4247)
 
 
+FEW = ModelShape("few-rows", 2, 1280, 10, 2, 128, 2944, 512, 10000.0, 1e-5, "bf16")
+
+
+@pytest.mark.parametrize("shape", [MINI64, FEW])
+@pytest.mark.parametrize("streams,k", [(1, 0), (1, 7), (1, 14), (1, 15), (1, 16), (2, 7), (2, 8), (16, 0), (17, 0)])
+def test_blocks_around_sixteen_rows(shape, streams, k):
+    """1 to 18 block rows: up to 16 the projections read and write the residual stream (2, 4, 10 and 23 chunks of K for
+    the eight waves, four in flight each), from 17 on the norm kernels stand between them."""
+    _ragged_verify(shape, (150,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4251)
+
+
 @pytest.mark.parametrize("hd,heads,kv_heads", [(2, 4, 2), (8, 4, 4), (16, 6, 2), (256, 2, 1)])
 @pytest.mark.parametrize("dtype,k", [("f32", 0), ("f32", 6), ("bf16", 6)])
 def test_plain_attention_head_sizes_and_chunk_edges(hd, heads, kv_heads, dtype, k):
