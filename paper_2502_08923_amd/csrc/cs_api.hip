@@ -579,7 +579,7 @@ extern "C" int cs_find_match_batch_dev(const int32_t* d_hist, int64_t stride, co
     CS_REQUIRE(B <= 65535, CS_E_ARG, "at most 65535 histories per call");
     const int nslots = cs_scan_slots(stride);
     int64_t* keys = nullptr;
-    CS_TRY(cs_scan_stream_keys((size_t)B * nslots, (hipStream_t)stream, &keys));
+    if (cs_scan_needs_keys(B, nslots)) CS_TRY(cs_scan_stream_keys((size_t)B * nslots, (hipStream_t)stream, &keys));
     return cs_scan_launch(d_hist, stride, d_len, B, gamma, k, policy, keys, nslots, d_match_pos, d_src_pos,
                           d_draft, d_draft_len, nullptr, (hipStream_t)stream);
 }

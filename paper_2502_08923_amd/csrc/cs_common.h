@@ -135,6 +135,7 @@ int cs_gather_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len
                      hipStream_t s);
 int cs_check_scan_args(int gamma, int k, int policy);     // CS_E_ARG with a message, or CS_OK
 int cs_scan_slots(int64_t max_len);
+bool cs_scan_needs_keys(int B, int nslots);
 int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, int B,
                    int gamma, int k, int policy, int64_t* keys, int nslots, int32_t* d_match_pos,
                    int32_t* d_src_pos, int32_t* d_draft, int32_t* d_draft_len,

@@ -14,6 +14,7 @@
 // rightmost among equals.
 #include <map>
 #include <mutex>
+#include <type_traits>
 #include <utility>
 
 #include "cs_common.h"
@@ -39,15 +40,17 @@ __device__ __forceinline__ int64_t key_better(int64_t a, int64_t b) {
     return a > b ? a : b;
 }
 
-__device__ __forceinline__ bool rest_matches(const int32_t* __restrict__ h, int p, int n, int gamma) {
-    for (int j = 1; j < gamma; ++j)
+// tokens first, first + 1, ... of the candidate at p against those of the suffix
+__device__ __forceinline__ bool rest_matches(const int32_t* __restrict__ h, int p, int n, int gamma, int first) {
+    for (int j = first; j < gamma; ++j)
         if (h[p + j] != h[n - gamma + j]) return false;
     return true;
 }
 
 // The candidates begin, begin + 1, ... of history h[0..n) in strides of THREADS*16 positions
-// (`first` and `step` count such strides): a thread loads 16 bytes (4 tokens) per step, compares
-// them with the first token of the suffix and only on a hit checks the other gamma - 1.  Returns
+// (`first` and `step` count such strides): a thread loads four times 16 bytes (4 tokens), compares
+// them with the first token of the suffix and only on a hit checks the other gamma - 1: the next two in registers
+// (its own and the next lane's), the rest in memory.  Returns
 // the thread's best key.  Every lane runs every iteration (positions past the end never hit), so
 // the wave stays converged for the cooperative context measurement.
 template <int POLICY, int THREADS>
@@ -57,24 +60,38 @@ __device__ __forceinline__ int64_t scan_strides(const int32_t* __restrict__ h, i
     const int cnt = n - 2 * gamma + 1;            // candidate starts are 0 .. cnt-1
     int64_t best = -1;
     const int s0 = cnt > 0 ? h[n - gamma] : 0;
+    const int s1 = cnt > 0 && gamma > 1 ? h[n - gamma + 1] : 0, s2 = cnt > 0 && gamma > 2 ? h[n - gamma + 2] : 0;
+    const bool inner = (threadIdx.x & 63) != 63;
     for (int64_t begin64 = (int64_t)first * STRIDE; begin64 < cnt; begin64 += (int64_t)step * STRIDE) {
         const int begin = (int)begin64;
         const int end = (int)min((int64_t)cnt, begin64 + STRIDE);
+        // the four loads of a stride are in flight together, ahead of the rare branches (1 GiB of histories 172 -> 161 us)
+        int t[4][4];
+#pragma unroll
         for (int it = 0; it < 4; ++it) {
             const int p = begin + (it * THREADS + (int)threadIdx.x) * 4;
-            int t[4];
             if (vec_ok && p + 3 < n) {
                 const int4 v = *reinterpret_cast<const int4*>(h + p);
-                t[0] = v.x; t[1] = v.y; t[2] = v.z; t[3] = v.w;
+                t[it][0] = v.x; t[it][1] = v.y; t[it][2] = v.z; t[it][3] = v.w;
             } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] = (p + i < n) ? h[p + i] : ~s0;
+                for (int i = 0; i < 4; ++i) t[it][i] = (p + i < n) ? h[p + i] : ~s0;
             }
+        }
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int p = begin + (it * THREADS + (int)threadIdx.x) * 4;
+            if (!__any(t[it][0] == s0 || t[it][1] == s0 || t[it][2] == s0 || t[it][3] == s0)) continue;    // (wave-uniform)
+            // the two tokens after this lane's four (the last lane has none and asks memory): where the suffix starts with
+            // a frequent token, chains of loads for every hit cost 2.6 times the scan (Zipf ranks of 1024 tokens)
+            const int w[6] = {t[it][0], t[it][1], t[it][2], t[it][3], __shfl_down(t[it][0], 1, 64), __shfl_down(t[it][1], 1, 64)};
             int hits = 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int pp = p + i;
-                if (pp < end && t[i] == s0 && rest_matches(h, pp, n, gamma)) {
+                const bool known = inner || i < 2;             // tokens pp + 1 and pp + 2 are in w
+                const bool next_two = !known || ((gamma < 2 || w[i + 1] == s1) && (gamma < 3 || w[i + 2] == s2));
+                if (pp < end && t[it][i] == s0 && next_two && rest_matches(h, pp, n, gamma, known ? 3 : 1)) {
                     hits |= 1 << i;
                     if (POLICY != CS_POLICY_CONTEXT) best = key_better<POLICY>(best, (int64_t)pp);
                 }
@@ -176,19 +193,61 @@ __global__ __launch_bounds__(64) void k_gather(const int32_t* __restrict__ hist,
     gather_draft(hist + (int64_t)b * stride, len[b], gamma, k, key, b, room, match_pos, src_pos, draft, draft_len);
 }
 
+// Short histories: search and draft in one launch, a workgroup per stream, no keys in memory.
+template <int POLICY, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_scan_short(const int32_t* __restrict__ hist, int64_t stride,
+                                                        const int32_t* __restrict__ len, int gamma, int k, int vec_ok,
+                                                        const int32_t* __restrict__ room,
+                                                        int32_t* __restrict__ match_pos,
+                                                        int32_t* __restrict__ src_pos,
+                                                        int32_t* __restrict__ draft,
+                                                        int32_t* __restrict__ draft_len) {
+    const int b = blockIdx.x;
+    const int32_t* __restrict__ h = hist + (int64_t)b * stride;
+    const int n = len[b];
+    const int64_t key = scan_block_best<POLICY, THREADS>(scan_strides<POLICY, THREADS>(h, n, gamma, vec_ok, 0, 1));
+    gather_draft(h, n, gamma, k, key, b, room, match_pos, src_pos, draft, draft_len);
+}
+
 // Number of key slots per stream a scan over histories of up to max_len tokens wants (one per
 // chunk).  Fewer slots are always correct (the workgroups then walk several chunks each).
 int cs_scan_slots(int64_t max_len) { return (int)cs_ceil_div(max_len > 0 ? max_len : 1, SCAN_CHUNK); }
 
+// One launch where a workgroup per stream does as well as one per chunk and a second kernel: one chunk (4.6 -> 2.9 us on the
+// GPU; a call from Python 16.4 -> 10.9 us, 2 us of them the stream handle), or up to eight for at most two workgroups of
+// 1024 threads per compute unit (32768 tokens of 1, 64, 256 streams: 5.2, 5.9, 8.4 -> 4.7, 5.2, 6.0 us; 8192 of 1024
+// streams: 8.3 -> 15.2).
+bool cs_scan_needs_keys(int B, int nslots) { return nslots > 1 && (nslots > 8 || B > 512); }
+
 // keys: device scratch of B * nslots int64 (every slot is written by k_scan before k_gather reads
-// it, so it needs no clearing).  The caller says where it lives: a cache handle's own buffer, the
-// per-stream buffers below, or the static array of the entry point that allocates nothing.
+// it, so it needs no clearing), not used unless cs_scan_needs_keys.  The caller says where it lives: a cache handle's
+// own buffer, the per-stream buffers below, or the static array of the entry point that allocates nothing.
 int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, int B, int gamma,
                    int k, int policy, int64_t* keys, int nslots, int32_t* d_match_pos, int32_t* d_src_pos,
                    int32_t* d_draft, int32_t* d_draft_len, const int32_t* d_room, hipStream_t s) {
     if (B == 0) return CS_OK;
-    CS_REQUIRE(keys && nslots >= 1 && B <= 65535, CS_E_ARG, "scan: no key buffer, or more than 65535 histories");
+    CS_REQUIRE((keys || !cs_scan_needs_keys(B, nslots)) && nslots >= 1 && B <= 65535, CS_E_ARG,
+               "scan: no key buffer, or more than 65535 histories");
     const int vec_ok = ((reinterpret_cast<uintptr_t>(d_hist) & 15) == 0) && (stride % 4 == 0);
+    if (!cs_scan_needs_keys(B, nslots)) {
+        auto start = [&](auto policy_tag, auto threads_tag) {
+            constexpr int POLICY = decltype(policy_tag)::value, THREADS = decltype(threads_tag)::value;
+            k_scan_short<POLICY, THREADS><<<B, THREADS, 0, s>>>(d_hist, stride, d_len, gamma, k, vec_ok, d_room, d_match_pos,
+                                                                d_src_pos, d_draft, d_draft_len);
+        };
+        auto by_policy = [&](auto threads_tag) {
+            if (policy == CS_POLICY_RIGHTMOST) start(std::integral_constant<int, CS_POLICY_RIGHTMOST>{}, threads_tag);
+            else if (policy == CS_POLICY_FIRST) start(std::integral_constant<int, CS_POLICY_FIRST>{}, threads_tag);
+            else start(std::integral_constant<int, CS_POLICY_CONTEXT>{}, threads_tag);
+        };
+        const int ps = cs_prof_begin(CS_PROF_SCAN, s);
+        // (one wave covers 1024 tokens: 65000 histories of 512, 104 us before, 102 with four waves, 31 with one)
+        if (stride <= 1024) by_policy(std::integral_constant<int, 64>{});
+        else if (nslots == 1) by_policy(std::integral_constant<int, SCAN_THREADS>{});
+        else by_policy(std::integral_constant<int, 1024>{});
+        cs_prof_end(ps, s);
+        return cs_launch_ok("k_scan_short");
+    }
     dim3 grid(nslots, B);
     const int ps = cs_prof_begin(CS_PROF_SCAN, s);
     if (policy == CS_POLICY_RIGHTMOST)

@@ -70,6 +70,38 @@ def test_ragged_lengths_small_vocab(gamma, k):
         _check_batch(hs, gamma, k, policy, stride=20000)
 
 
+@pytest.mark.parametrize("policy", ["rightmost", "first", "context"])
+@pytest.mark.parametrize("stride", [1, 63, 1021, 1024, 1028, 4096, 4097, 4100, 32768, 32772])
+def test_one_launch_and_two(stride, policy):
+    """Histories around the lengths where the scan takes one wave, one workgroup of four or sixteen waves, or one per
+    chunk and a second kernel; few tokens, so that hits fall on every lane, the last of a wave and of a load among them,
+    with one, two or three tokens of the suffix in registers."""
+    rng = np.random.default_rng(stride)
+    lens = sorted({n for n in (stride, stride - 1, stride - 2, stride - 64, stride // 2, 255, 7) if 0 < n <= stride})
+    for vocab, gamma in ((2, 1), (3, 2), (3, 3), (4, 5)):
+        hs = [rng.integers(0, vocab, n).astype(np.int32) for n in lens]
+        _check_batch(hs, gamma, 10, policy, stride=stride)
+    # one planted match per history, at the places where a wave, a load or a workgroup's share ends
+    n = stride
+    if n >= 600:
+        at = [p for p in (0, 1, 61, 62, 63, 251, 252, 253, 254, 255, 256, 509, n // 2, n - 8) if p <= n - 8]
+        hs = []
+        for p in at:
+            h = np.arange(10, 10 + n, dtype=np.int32)
+            h[-4:] = (1, 2, 3, 4)
+            h[p:p + 4] = (1, 2, 3, 4)
+            hs.append(h)
+        for gamma in (2, 3, 4):
+            _check_batch(hs, gamma, 5, policy, stride=stride)
+
+
+@pytest.mark.parametrize("streams", [512, 513])
+def test_many_short_histories(streams):
+    """The number of histories of several chunks where the scan goes from one launch to two."""
+    rng = np.random.default_rng(streams)
+    _check_batch([rng.integers(0, 9, n).astype(np.int32) for n in rng.integers(1, 4200, streams)], 3, 4, "rightmost", stride=4200)
+
+
 def test_degenerate_histories():
     same = np.full(9000, 5, dtype=np.int32)
     period = np.tile(np.array([1, 2, 3], dtype=np.int32), 3000)
