@@ -284,7 +284,7 @@ static int model_alloc(cs_model* m) {
     const size_t a = m->asz;
     const int wide = d > nq ? d : nq;
     DEV_ALLOC(m->x, R * d * 4);
-    DEV_ALLOC(m->ss, (size_t)cs_ceil_div(d, 16) * 16 * 4);
+    DEV_ALLOC(m->ss, (size_t)cs_ceil_div(d, 16) * (m->fast ? 16 : 32) * 4);
     DEV_ALLOC(m->xn, R * wide * 4 > cs_xt_bytes(R, wide) ? R * wide * 4 : cs_xt_bytes(R, wide));
     DEV_ALLOC(m->q, R * nq * 4);
     if (!m->fast) DEV_ALLOC(m->gu, R * 2 * F * 4);
@@ -675,7 +675,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int r
     int np_prev = 0, np = 1;
     // narrow blocks: the attention kernel rotates q and k and appends k, v itself
     const bool fuse_rope = !rg && cs_attention_fuses_rope(m, rows);
-    // up to 16 rows: no norm kernels, the projections read and write the residual stream (see cs_gemm_norm_launch)
+    // few rows: no norm kernels, the projections read and write the residual stream (see cs_gemm_norm_launch)
     const bool few = cs_gemm_few_rows(m, R);
     int nss = 1;
     for (int l = 0; l < c.n_layers; ++l) {

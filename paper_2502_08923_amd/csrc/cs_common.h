@@ -91,7 +91,7 @@ struct cs_model {
     int layers_loaded, head_loaded;
     // workspace (device)
     float* x;           // [R][d] residual stream
-    float* ss;          // [d/16][16] pieces of the rows' sums of squares (blocks of up to 16 rows)
+    float* ss;          // [d/16][16 or 32] pieces of the rows' sums of squares (blocks of few rows, see cs_gemm_few_rows)
     void* xn;           // [R][max(d, H*hd)] GEMM input (normed rows / attention output)
     void* q;            // [R][H][hd] rotated queries
     float* gu;          // [R][2F]  (plain path only)
@@ -196,9 +196,10 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
                    int mode, int allow_split, int* nparts_out, hipStream_t s);
 int cs_gemm_plain_launch(int dtype, const float* X, const void* W, float* Y, int R, int N, int K,
                          hipStream_t s);
-// Blocks of up to 16 rows (cs_gemm_few_rows) need no norm kernel of their own: cs_gemm_residual_launch adds X * W^T (X in
-// fragment order, see cs_xt_index) to the residual stream m->x and leaves nss pieces of every row's sum of squares in m->ss, and cs_gemm_norm_launch
-// is Y = rmsnorm(m->x) * W^T from those (modes and partial tiles as in cs_gemm_launch).
+// Blocks of few rows (cs_gemm_few_rows: up to 16 with the tuned kernels, 32 with the float32 one) need no norm kernel of
+// their own: cs_gemm_residual_launch adds X * W^T (tuned kernels: X in fragment order, see cs_xt_index) to the
+// residual stream m->x and leaves nss pieces of every row's sum of squares in m->ss, and cs_gemm_norm_launch is
+// Y = rmsnorm(m->x) * W^T from those (modes and partial tiles as in cs_gemm_launch; SwiGLU into m->act).
 bool cs_gemm_few_rows(const cs_model* m, int R);
 int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const void* W, float* Y, int R, int N, int K, int mode,
                         int* nparts_out, hipStream_t s);

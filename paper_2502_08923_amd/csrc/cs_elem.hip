@@ -47,7 +47,7 @@ __global__ __launch_bounds__(START_THREADS) void k_block_start(cs_block_src src,
         *reinterpret_cast<float4*>(x + (int64_t)r * d + c) = v;
         q += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     }
-    if (ss) {                                          // blocks of up to 16 rows: the sum of squares, in one piece
+    if (ss) {                                          // blocks of few rows: the sum of squares, in one piece
         __shared__ float wsum[START_THREADS / CS_WAVE];
         q = cs_wave_sum(q);
         if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = q;

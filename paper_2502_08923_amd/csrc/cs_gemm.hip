@@ -32,6 +32,16 @@
 // four; 128256 x 256, 65 rows: 158 against 279).  VEC: K % 4 == 0 and both operands aligned to four elements;
 // otherwise the same kernel loads single elements.
 // -------------------------------------------------------------------------------------
+// X given as the residual stream and what its RMSNorm needs (blocks of few rows, see cs_gemm_few_rows).
+struct cs_norm_in {
+    const float* x;         // [R][K] residual stream
+    const float* gain;      // [K]
+    const float* ss;        // [nss][row tiles of 16] pieces of every row's sum of squares
+    int nss;
+    float eps;
+    int32_t* flags;
+};
+
 #define GF_WAVES 8
 template <bool VEC, typename T>
 __device__ __forceinline__ f32x4 gf_load4(const T* __restrict__ row, int k, int K, bool live) {
@@ -54,88 +64,166 @@ __device__ __forceinline__ f32x4 gf_load4(const T* __restrict__ row, int k, int 
     return v;
 }
 
-template <typename WT, int NT, bool VEC>
+// Few rows (see cs_gemm_few_rows) have modes of their own, so that a layer of a small model is six launches, not nine:
+// GF_NORM reads X through the RMSNorm of the residual stream (GF_SWIGLU as well, with a gate and an up tile per
+// workgroup and SwiGLU of both as the result), GF_RESIDUAL adds to the residual stream and leaves the sums of squares.
+enum { GF_STORE = 0, GF_NORM = 1, GF_SWIGLU = 2, GF_RESIDUAL = 3 };
+template <typename WT, int NT, bool VEC, int MODE>
 __global__ __launch_bounds__(64 * GF_WAVES) void k_gemm_f32(const float* __restrict__ X,
                                                             const WT* __restrict__ W, float* __restrict__ Y,
-                                                            int R, int N, int K) {
+                                                            int R, int N, int K, cs_norm_in nrm, float* __restrict__ ss) {
     constexpr int AHEAD = 2;                      // pieces of K in flight per wave
-    __shared__ __attribute__((aligned(16))) f32x4 red[GF_WAVES][NT][64];
+    constexpr bool XN = MODE == GF_NORM || MODE == GF_SWIGLU;
+    constexpr int MT = MODE == GF_SWIGLU ? 2 : 1; // 16-row W tiles
+    __shared__ __attribute__((aligned(16))) f32x4 red[GF_WAVES][MT][NT][64];
+    __shared__ __attribute__((aligned(16))) float sq[XN ? GF_WAVES : 1][16 * NT];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lrow = lane & 15, g = lane >> 4;
-    const int n0 = blockIdx.x * 16, r0 = blockIdx.y * 16 * NT;
-    const bool w_live = n0 + lrow < N;
-    const WT* __restrict__ w = W + (int64_t)(w_live ? n0 + lrow : 0) * K;
-    constexpr int CHAINS = 4 * AHEAD;             // accumulators of a wave per row tile
+    const int n0 = blockIdx.x * 16 * MT, r0 = blockIdx.y * 16 * NT;
+    bool w_live[MT];
+    const WT* __restrict__ w[MT];
+    constexpr int CHAINS = 4 * AHEAD;             // accumulators of a wave per tile pair
     bool x_live[NT];
     const float* x[NT];
-    f32x4 acc[CHAINS][NT];
+    f32x4 acc[CHAINS][MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int n = n0 + mt * 16 + lrow;
+        w_live[mt] = n < N;
+        w[mt] = W + (int64_t)(w_live[mt] ? n : 0) * K;
+    }
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
         const int r = r0 + nt * 16 + lrow;
         x_live[nt] = r < R;
         x[nt] = X + (int64_t)(x_live[nt] ? r : 0) * K;
 #pragma unroll
-        for (int c = 0; c < CHAINS; ++c) acc[c][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int c = 0; c < CHAINS; ++c)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[c][mt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    }
+    float scale[NT];
+    if constexpr (XN) {
+        f32x4 q = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int i = threadIdx.x; i < 4 * NT * nrm.nss; i += 64 * GF_WAVES) q += *reinterpret_cast<const f32x4*>(nrm.ss + 4 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int o = 4 * NT; o < 64; o <<= 1) q[j] += __shfl_xor(q[j], o, 64);
+        if (lane < 4 * NT) *reinterpret_cast<f32x4*>(&sq[wave][4 * lane]) = q;
+        __syncthreads();
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            float t = 0.f;
+#pragma unroll
+            for (int u = 0; u < GF_WAVES; ++u) t += sq[u][nt * 16 + lrow];
+            scale[nt] = x_live[nt] ? 1.0f / sqrtf(t / (float)K + nrm.eps) : 0.f;
+        }
     }
     for (int k0 = 16 * wave; k0 < K; k0 += AHEAD * 16 * GF_WAVES) {
-        f32x4 a[AHEAD], b[AHEAD][NT];
+        f32x4 a[AHEAD][MT], b[AHEAD][NT], gn[AHEAD];
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u) {
             const int k = k0 + u * 16 * GF_WAVES + 4 * g;          // (pieces past K are zeros)
-            a[u] = gf_load4<VEC>(w, k, K, w_live);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) a[u][mt] = gf_load4<VEC>(w[mt], k, K, w_live[mt]);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) b[u][nt] = gf_load4<VEC>(x[nt], k, K, x_live[nt]);
+            if constexpr (XN) gn[u] = gf_load4<VEC>(nrm.gain, k, K, true);
+        }
+        if constexpr (XN) {
+#pragma unroll
+            for (int u = 0; u < AHEAD; ++u)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) b[u][nt] = b[u][nt] * scale[nt] * gn[u];
         }
 #pragma unroll
         for (int u = 0; u < AHEAD; ++u)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    f32x4& o = acc[4 * u + j][nt];
-                    o = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][j], b[u][nt][j], o, 0, 0, 0);
-                }
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) {
+                        f32x4& o = acc[4 * u + j][mt][nt];
+                        o = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][mt][j], b[u][nt][j], o, 0, 0, 0);
+                    }
     }
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int h = CHAINS / 2; h > 0; h /= 2)
+        for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-            for (int c = 0; c < h; ++c) acc[c][nt] += acc[c + h][nt];
-        red[wave][nt][lane] = acc[0][nt];
-    }
+            for (int h = CHAINS / 2; h > 0; h /= 2)
+#pragma unroll
+                for (int c = 0; c < h; ++c) acc[c][mt][nt] += acc[c + h][mt][nt];
+            red[wave][mt][nt][lane] = acc[0][mt][nt];
+        }
     __syncthreads();
     if (wave >= NT) return;
-    // wave nt sums row tile nt: y[j] = Y[row r0 + nt*16 + lrow][col n0 + 4g + j]
-    f32x4 part[GF_WAVES];
+    // wave nt sums row tile nt: y[mt][j] = Y[row r0 + nt*16 + lrow][col n0 + mt*16 + 4g + j]
+    f32x4 y[MT];
 #pragma unroll
-    for (int u = 0; u < GF_WAVES; ++u) part[u] = red[u][wave][lane];
+    for (int mt = 0; mt < MT; ++mt) {
+        f32x4 part[GF_WAVES];
 #pragma unroll
-    for (int h = GF_WAVES / 2; h > 0; h /= 2)
+        for (int u = 0; u < GF_WAVES; ++u) part[u] = red[u][mt][wave][lane];
 #pragma unroll
-        for (int u = 0; u < h; ++u) part[u] += part[u + h];
-    const f32x4 y = part[0];
+        for (int h = GF_WAVES / 2; h > 0; h /= 2)
+#pragma unroll
+            for (int u = 0; u < h; ++u) part[u] += part[u + h];
+        y[mt] = part[0];
+    }
     const int r = r0 + wave * 16 + lrow;
-    if (r >= R) return;
-    float* __restrict__ out = Y + (int64_t)r * N + n0 + 4 * g;
+    if constexpr (MODE == GF_SWIGLU) {
+        if (r >= R) return;
+        const int F = N / 2, f = n0 / 2 + 4 * g;  // 16 gate rows, then the 16 up rows of the same channels
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (n0 + 4 * g + j < N) out[j] = y[j];
+        for (int j = 0; j < 4; ++j) Y[(int64_t)r * F + f + j] = y[0][j] / (1.0f + expf(-y[0][j])) * y[1][j];
+    } else if constexpr (MODE == GF_RESIDUAL) {
+        float q = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (r < R && n0 + 4 * g + j < N) {
+                float* __restrict__ o = Y + (int64_t)r * N + n0 + 4 * g + j;
+                const float v = *o + y[0][j];
+                *o = v;
+                q += v * v;
+            }
+        q += __shfl_xor(q, 16, 64);
+        q += __shfl_xor(q, 32, 64);
+        if (g == 0) ss[blockIdx.x * 16 * NT + wave * 16 + lrow] = q;
+    } else {
+        if (r >= R) return;
+        float* __restrict__ out = Y + (int64_t)r * N + n0 + 4 * g;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (n0 + 4 * g + j < N) out[j] = y[0][j];
+    }
 }
 
-template <typename WT>
-static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K, hipStream_t s) {
+template <typename WT, int MODE>
+static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K, const cs_norm_in& nrm, float* ss,
+                      hipStream_t s) {
     const bool vec = K % 4 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % (4 * sizeof(WT)) == 0;
     const int nt = R <= 16 ? 1 : 2;
-    dim3 grid((unsigned)cs_ceil_div(N, 16), (unsigned)cs_ceil_div(R, 16 * nt));
+    dim3 grid((unsigned)cs_ceil_div(N, MODE == GF_SWIGLU ? 32 : 16), (unsigned)cs_ceil_div(R, 16 * nt));
     auto start = [&](auto nt_tag) {
         constexpr int NT = decltype(nt_tag)::value;
-        if (vec) k_gemm_f32<WT, NT, true><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K);
-        else k_gemm_f32<WT, NT, false><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K);
+        if (vec) k_gemm_f32<WT, NT, true, MODE><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K, nrm, ss);
+        else k_gemm_f32<WT, NT, false, MODE><<<grid, 64 * GF_WAVES, 0, s>>>(X, W, Y, R, N, K, nrm, ss);
     };
     if (nt == 1) start(std::integral_constant<int, 1>{});
     else start(std::integral_constant<int, 2>{});
     return cs_launch_ok("k_gemm_f32");
+}
+
+// by the weights' type
+template <int MODE>
+static int launch_plain(int dtype, const float* X, const void* W, float* Y, int R, int N, int K, const cs_norm_in& nrm,
+                        float* ss, hipStream_t s) {
+    return dtype == CS_BF16 ? launch_f32<bf16_t, MODE>(X, (const bf16_t*)W, Y, R, N, K, nrm, ss, s)
+                            : launch_f32<float, MODE>(X, (const float*)W, Y, R, N, K, nrm, ss, s);
 }
 
 // -------------------------------------------------------------------------------------
@@ -158,14 +246,6 @@ static int launch_f32(const float* X, const WT* W, float* Y, int R, int N, int K
 // act_tiled by mode: SWIGLU - the output goes out in fragment order; ARGMAX - tiles per row of the
 // pair buffer.
 // XN: X is not given; the producers normalise the float32 residual stream themselves (few rows, see cs_norm_in).
-struct cs_norm_in {
-    const float* x;         // [R][K] residual stream
-    const float* gain;      // [K]
-    const float* ss;        // [nss][16] pieces of every row's sum of squares
-    int nss;
-    float eps;
-    int32_t* flags;
-};
 #define GEMM_STORE_STREAM 3   // CS_GEMM_STORE whose partial tiles leave through streaming stores
 template <int MT, int NT, int MODE, int CW, bool XN = false>
 __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __restrict__ X,
@@ -1164,11 +1244,17 @@ __global__ __launch_bounds__(64 * GR_WAVES) void k_gemm_residual(const f16_t* __
     if (g == 0) ss[blockIdx.x * 16 + lrow] = q;
 }
 
-// Blocks that take the normalising projections and the ones that write the residual stream.
-bool cs_gemm_few_rows(const cs_model* m, int R) { return m->fast && R <= 16; }
+// Blocks that take the normalising projections and the ones that write the residual stream (float32 kernel: one row block).
+bool cs_gemm_few_rows(const cs_model* m, int R) { return R <= (m->fast ? 16 : 32); }
 
 int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const void* W, float* Y, int R, int N, int K, int mode,
                         int* nparts_out, hipStream_t s) {
+    const cs_norm_in nrm = {m->x, gain, m->ss, nss, m->cfg.rms_eps, m->range_flags};
+    if (!m->fast) {
+        if (nparts_out) *nparts_out = 1;
+        if (mode == CS_GEMM_SWIGLU) return launch_plain<GF_SWIGLU>(m->cfg.dtype, m->x, W, (float*)m->act, R, N, K, nrm, nullptr, s);
+        return launch_plain<GF_NORM>(m->cfg.dtype, m->x, W, Y, R, N, K, nrm, nullptr, s);
+    }
     CS_REQUIRE(mfma_shape_ok(N, K) && (mode == CS_GEMM_STORE || N % 32 == 0), CS_E_UNSUPPORTED,
                "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
     mfma_shape plan = mfma_plan(R, N, K, mode == CS_GEMM_STORE);
@@ -1176,7 +1262,6 @@ int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const voi
     const int Ks = (int)cs_round_up(cs_ceil_div(K, plan.ksplit), GEMM_KC);
     if (nparts_out) *nparts_out = (int)cs_ceil_div(K, Ks);
     if (mode == CS_GEMM_SWIGLU) Y = reinterpret_cast<float*>(m->range_flags);   // see the epilogue
-    const cs_norm_in nrm = {m->x, gain, m->ss, nss, m->cfg.rms_eps, m->range_flags};
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
     start_norm(nrm, (const f16_t*)W, Y, (f16_t*)m->act, R, N, K, mode, Ks, plan.waves, s);
     cs_prof_end(pg, s);
@@ -1184,6 +1269,10 @@ int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const voi
 }
 
 int cs_gemm_residual_launch(const cs_model* m, const void* X, const void* W, int R, int N, int K, int* nss, hipStream_t s) {
+    if (!m->fast) {
+        *nss = (int)cs_ceil_div(N, 16);
+        return launch_plain<GF_RESIDUAL>(m->cfg.dtype, (const float*)X, W, m->x, R, N, K, cs_norm_in{}, m->ss, s);
+    }
     CS_REQUIRE(mfma_shape_ok(N, K), CS_E_UNSUPPORTED, "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
     *nss = N / 16;
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
@@ -1195,6 +1284,5 @@ int cs_gemm_residual_launch(const cs_model* m, const void* X, const void* W, int
 int cs_gemm_plain_launch(int dtype, const float* X, const void* W, float* Y, int R, int N, int K,
                          hipStream_t s) {
     if (R <= 0) return CS_OK;
-    return dtype == CS_BF16 ? launch_f32(X, (const bf16_t*)W, Y, R, N, K, s)
-                            : launch_f32(X, (const float*)W, Y, R, N, K, s);
+    return launch_plain<GF_STORE>(dtype, X, W, Y, R, N, K, cs_norm_in{}, nullptr, s);
 }

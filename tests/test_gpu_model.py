@@ -227,6 +227,17 @@ def test_blocks_around_sixteen_rows(shape, streams, k):
     _ragged_verify(shape, (150,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4251)
 
 
+ODDF32 = ModelShape("odd-f32", 2, 68, 3, 1, 16, 48, 97, 10000.0, 1e-5, "f32")
+
+
+@pytest.mark.parametrize("shape,plain", [(SMALLF32, False), (ODDF32, False), (MINI64, True), (MINIQWEN, True)])
+@pytest.mark.parametrize("streams,k", [(1, 0), (1, 15), (1, 16), (1, 31), (1, 32), (3, 9), (3, 10), (33, 0)])
+def test_float32_kernel_around_sixteen_and_thirty_two_rows(shape, plain, streams, k):
+    """The same of the float32 kernel (one row tile up to 16 rows, two up to 32, the norm and SwiGLU kernels from 33 on):
+    widths that end inside a 16-row tile of W, float32 and bfloat16 weights."""
+    _ragged_verify(shape, (150,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4252, plain=plain)
+
+
 @pytest.mark.parametrize("hd,heads,kv_heads", [(2, 4, 2), (8, 4, 4), (16, 6, 2), (256, 2, 1)])
 @pytest.mark.parametrize("dtype,k", [("f32", 0), ("f32", 6), ("bf16", 6)])
 def test_plain_attention_head_sizes_and_chunk_edges(hd, heads, kv_heads, dtype, k):
