@@ -130,16 +130,6 @@ __global__ void k_add_i32_vec(int32_t* p, const int32_t* __restrict__ v, int n) 
     if (i < n) p[i] += v[i];
 }
 
-// the tokens a step appended to each history: out[b][0 .. accepted[b]] (k+1 slots per stream)
-__global__ void k_emitted(const int32_t* __restrict__ hist, int64_t stride,
-                          const int32_t* __restrict__ hist_len, const int32_t* __restrict__ accepted,
-                          int k, int32_t* __restrict__ out) {
-    const int b = blockIdx.x;
-    const int got = accepted[b] + 1;
-    const int32_t* __restrict__ h = hist + (int64_t)b * stride + hist_len[b] - got;
-    for (int i = threadIdx.x; i < got; i += blockDim.x) out[b * (k + 1) + i] = h[i];
-}
-
 __global__ void k_sum_parts(const float* __restrict__ part, int nparts, int64_t n,
                             float* __restrict__ y) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
@@ -581,7 +571,7 @@ extern "C" int cs_find_match_batch_dev(const int32_t* d_hist, int64_t stride, co
     int64_t* keys = nullptr;
     if (cs_scan_needs_keys(B, nslots)) CS_TRY(cs_scan_stream_keys((size_t)B * nslots, (hipStream_t)stream, &keys));
     return cs_scan_launch(d_hist, stride, d_len, B, gamma, k, policy, keys, nslots, d_match_pos, d_src_pos,
-                          d_draft, d_draft_len, nullptr, (hipStream_t)stream);
+                          d_draft, d_draft_len, nullptr, nullptr, (hipStream_t)stream);
 }
 
 extern "C" int cs_find_match_ex(const int32_t* history, int64_t len, int32_t gamma, int32_t k,
@@ -612,7 +602,7 @@ extern "C" int cs_find_match_ex(const int32_t* history, int64_t len, int32_t gam
         }
         if (rc == CS_OK)
             rc = cs_scan_launch(d, stride, d_len, 1, gamma, k, policy, d_keys, nslots, d_out, d_out + 1,
-                                d_draft, d_out + 2, nullptr, nullptr);
+                                d_draft, d_out + 2, nullptr, nullptr, nullptr);
         if (rc == CS_OK && (hipMemcpy(out, d_out, 12, hipMemcpyDeviceToHost) != hipSuccess ||
                             (k > 0 && hipMemcpy(hdraft.data(), d_draft, (size_t)k * 4,
                                                 hipMemcpyDeviceToHost) != hipSuccess))) {
@@ -719,7 +709,7 @@ static cs_block_src prompt_src(const cs_model* m) { return {m->tok, nullptr, nul
 static int verify_impl(cs_model* m, cs_kv* kv, const int32_t* d_pending, const int32_t* d_draft,
                        const int32_t* d_draft_len, int k, int32_t* d_accepted, int32_t* d_next,
                        float* d_logits_out, int32_t* hist, int64_t hist_stride, int32_t* hist_len,
-                       int32_t* room, hipStream_t s) {
+                       int32_t* room, int32_t* emitted, hipStream_t s) {
     const int rows = k + 1, B = kv->B, R = B * rows, V = m->cfg.vocab;
     CS_TRY(kv_check_room(kv, rows));
     const cs_block_src src = {nullptr, d_pending, hist, hist_stride, hist_len, d_draft, d_draft_len};
@@ -733,7 +723,7 @@ static int verify_impl(cs_model* m, cs_kv* kv, const int32_t* d_pending, const i
                               &nch, s));
         cs_prof_end(pl, s);
         CS_TRY(cs_accept_launch(m, nch, B, k, d_draft, d_draft_len, d_accepted, d_next, nullptr,
-                                kv->d_len, hist, hist_stride, hist_len, room, s));
+                                kv->d_len, hist, hist_stride, hist_len, room, emitted, s));
     } else {
         // straight into the caller's buffer where its alignment allows the lm_head's 16-byte stores (105 rows of
         // 152064 logits: the copy from a buffer of the model's own took 19 us)
@@ -742,7 +732,7 @@ static int verify_impl(cs_model* m, cs_kv* kv, const int32_t* d_pending, const i
                               nullptr, s));
         cs_prof_end(pl, s);
         CS_TRY(cs_argmax_accept_launch(m, logits, B, k, V, d_draft, d_draft_len, d_accepted, d_next,
-                                       nullptr, kv->d_len, hist, hist_stride, hist_len, room, s));
+                                       nullptr, kv->d_len, hist, hist_stride, hist_len, room, emitted, s));
         if (d_logits_out && logits != d_logits_out)
             CS_HIP(hipMemcpyAsync(d_logits_out, logits, (size_t)R * V * 4, hipMemcpyDeviceToDevice, s));
     }
@@ -764,18 +754,17 @@ extern "C" int cs_verify(cs_model* m, cs_kv* kv, const int32_t* d_pending, const
     CS_REQUIRE(d_pending && d_draft_len && d_accepted_len && d_next_token && (d_draft || k == 0),
                CS_E_ARG, "cs_verify: NULL pointer");
     return verify_impl(m, kv, d_pending, d_draft, d_draft_len, k, d_accepted_len, d_next_token,
-                       d_logits_out, nullptr, 0, nullptr, nullptr, (hipStream_t)stream);
+                       d_logits_out, nullptr, 0, nullptr, nullptr, nullptr, (hipStream_t)stream);
 }
 
-extern "C" int cs_step(cs_model* m, cs_kv* kv, int32_t* d_hist, int64_t stride, int32_t* d_hist_len,
-                       int32_t* d_room, int32_t gamma, int32_t k, int32_t policy,
-                       int32_t* d_accepted_len, int32_t* d_next_token, int32_t* d_draft_len_out,
-                       void* stream) {
+// cs_step; `emitted`: [B][k+1] for the tokens every history grows by, or NULL
+static int step_impl(cs_model* m, cs_kv* kv, int32_t* d_hist, int64_t stride, int32_t* d_hist_len,
+                     int32_t* d_room, int gamma, int k, int policy, int32_t* d_accepted_len, int32_t* d_next_token,
+                     int32_t* d_draft_len_out, int32_t* emitted, hipStream_t s) {
     CS_TRY(check_verify_args(m, kv, k));
     CS_TRY(cs_check_scan_args(gamma, k, policy));
     CS_REQUIRE(d_hist && d_hist_len && d_accepted_len && d_next_token, CS_E_ARG, "cs_step: NULL pointer");
     CS_REQUIRE(stride >= 1 && stride <= CS_MAX_STRIDE, CS_E_ARG, "stride out of range");
-    hipStream_t s = (hipStream_t)stream;
     const int B = kv->B;
     CS_TRY(kv_check_room(kv, k + 1));
     // the history may grow by k+1 tokens: same bound as the cache (length = kv length + 1)
@@ -783,15 +772,22 @@ extern "C" int cs_step(cs_model* m, cs_kv* kv, int32_t* d_hist, int64_t stride, 
                "history buffer (stride %lld) may overflow", (long long)stride);
     if (k > 0) {
         CS_TRY(cs_scan_launch(d_hist, stride, d_hist_len, B, gamma, k, policy, kv->scan_keys,
-                              kv_scan_slots(kv), m->match_pos, nullptr, m->draft, m->draft_len, d_room, s));
+                              kv_scan_slots(kv), m->match_pos, nullptr, m->draft, m->draft_len, d_room, d_draft_len_out, s));
     } else {
         CS_TRY(cs_fill_i32_launch(m->draft_len, 0, B, s));
+        if (d_draft_len_out) CS_TRY(cs_fill_i32_launch(d_draft_len_out, 0, B, s));
     }
-    if (d_draft_len_out)
-        CS_HIP(hipMemcpyAsync(d_draft_len_out, m->draft_len, (size_t)B * 4, hipMemcpyDeviceToDevice, s));
     // (no pending array: the last token of each history)
     return verify_impl(m, kv, nullptr, m->draft, m->draft_len, k, d_accepted_len, d_next_token,
-                       nullptr, d_hist, stride, d_hist_len, d_room, s);
+                       nullptr, d_hist, stride, d_hist_len, d_room, emitted, s);
+}
+
+extern "C" int cs_step(cs_model* m, cs_kv* kv, int32_t* d_hist, int64_t stride, int32_t* d_hist_len,
+                       int32_t* d_room, int32_t gamma, int32_t k, int32_t policy,
+                       int32_t* d_accepted_len, int32_t* d_next_token, int32_t* d_draft_len_out,
+                       void* stream) {
+    return step_impl(m, kv, d_hist, stride, d_hist_len, d_room, gamma, k, policy, d_accepted_len, d_next_token,
+                     d_draft_len_out, nullptr, (hipStream_t)stream);
 }
 
 // -------------------------------------------------------------------------------------
@@ -871,11 +867,8 @@ static int decode_loop(cs_model* m, cs_kv* kv, int32_t* d_hist, int64_t stride,
         const int burst = (int)(need < DECODE_BURST ? need : DECODE_BURST);
         for (int j = 0; j < burst && rc == CS_OK; ++j) {
             int32_t* sl = d_state + 2 * B + (size_t)j * n_slice;
-            rc = cs_step(m, kv, d_hist, stride, d_state, d_state + B, gamma, k, policy, sl, sl + B,
-                         sl + 2 * B, nullptr);
-            if (rc != CS_OK) break;
-            k_emitted<<<B, 64, 0, nullptr>>>(d_hist, stride, d_state, sl, k, sl + 3 * B);
-            rc = cs_launch_ok("k_emitted");
+            rc = step_impl(m, kv, d_hist, stride, d_state, d_state + B, gamma, k, policy, sl, sl + B, sl + 2 * B, sl + 3 * B,
+                           nullptr);
         }
         if (rc != CS_OK) break;
         if (hipMemcpy(h.data(), d_state, ((size_t)2 * B + (size_t)burst * n_slice) * 4,
@@ -1171,7 +1164,7 @@ extern "C" int cs_decode_merged(cs_model* m, cs_kv* kv, cs_model* dm, cs_kv* dkv
         // step 1: copy opportunity
         if (k > 0) {
             CS_TRY(cs_scan_launch(d, stride, d_len, 1, gamma, k, policy, kv->scan_keys, kv_scan_slots(kv),
-                                  m->match_pos, nullptr, m->draft, m->draft_len, d_len + 1, s));
+                                  m->match_pos, nullptr, m->draft, m->draft_len, d_len + 1, nullptr, s));
             CS_HIP(hipMemcpy(&dl, m->draft_len, 4, hipMemcpyDeviceToHost));
         }
         k_pending<<<1, 64, 0, s>>>(d, stride, d_len, 1, m->pending);
@@ -1198,7 +1191,7 @@ extern "C" int cs_decode_merged(cs_model* m, cs_kv* kv, cs_model* dm, cs_kv* dkv
             for (int i = 0; i < proposed; ++i) {  // one greedy token per forward pass
                 const int32_t* tok = i == 0 ? m->pending : d_proposed + i - 1;
                 CS_TRY(verify_impl(dm, dkv, tok, nullptr, d_len + 6, 0, d_len + 5, d_proposed + i, nullptr,
-                                   nullptr, 0, nullptr, nullptr, s));
+                                   nullptr, 0, nullptr, nullptr, nullptr, s));
                 draft_rows += 1;
                 st.draft_forwards += 1;
             }
@@ -1208,7 +1201,7 @@ extern "C" int cs_decode_merged(cs_model* m, cs_kv* kv, cs_model* dm, cs_kv* dkv
             len_ptr = d_len + 4;
         }
         CS_TRY(verify_impl(m, kv, m->pending, draft_ptr, len_ptr, block, d_len + 2, d_len + 3, nullptr, d,
-                           stride, d_len, d_len + 1, s));
+                           stride, d_len, d_len + 1, nullptr, s));
         int32_t h[4];
         CS_HIP(hipMemcpy(h, d_len, sizeof(h), hipMemcpyDeviceToHost));
         const int tau = h[2], got = tau + 1;
@@ -1312,6 +1305,6 @@ extern "C" int cs_op_argmax_accept(cs_model* m, const float* logits, int32_t B, 
     CS_REQUIRE(B >= 1 && k >= 0 && V >= 1 && B * (k + 1) <= m->R_max, CS_E_ARG,
                "cs_op_argmax_accept: B*(k+1) exceeds the model's max_batch*(max_k+1)");
     return cs_argmax_accept_launch(m, logits, B, k, V, draft, draft_len, accepted_len, next_token,
-                                   row_argmax, nullptr, nullptr, 0, nullptr, nullptr,
+                                   row_argmax, nullptr, nullptr, 0, nullptr, nullptr, nullptr,
                                    (hipStream_t)stream);
 }

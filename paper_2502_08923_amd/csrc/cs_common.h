@@ -136,10 +136,11 @@ int cs_gather_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len
 int cs_check_scan_args(int gamma, int k, int policy);     // CS_E_ARG with a message, or CS_OK
 int cs_scan_slots(int64_t max_len);
 bool cs_scan_needs_keys(int B, int nslots);
+// (d_draft_len2: the draft lengths once more, or NULL)
 int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, int B,
                    int gamma, int k, int policy, int64_t* keys, int nslots, int32_t* d_match_pos,
                    int32_t* d_src_pos, int32_t* d_draft, int32_t* d_draft_len,
-                   const int32_t* d_room, hipStream_t s);
+                   const int32_t* d_room, int32_t* d_draft_len2, hipStream_t s);
 int cs_scan_stream_keys(size_t need, hipStream_t s, int64_t** out);
 
 // elementwise / small
@@ -175,15 +176,16 @@ int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* 
                           int rows, const cs_ragged* rg, hipStream_t s);
 int cs_swiglu_launch(const cs_model* m, int R, hipStream_t s);
 // accept rule, state update from the argmax partials m->am_val_idx[row][nch]
+// (emitted: [B][k+1], the tokens each history grew by, or NULL)
 int cs_accept_launch(const cs_model* m, int nch, int B, int k, const int32_t* draft,
                      const int32_t* draft_len, int32_t* accepted, int32_t* next_tok,
                      int32_t* row_argmax_out, int32_t* kv_len, int32_t* hist, int64_t hist_stride,
-                     int32_t* hist_len, int32_t* room, hipStream_t s);
+                     int32_t* hist_len, int32_t* room, int32_t* emitted, hipStream_t s);
 int cs_argmax_accept_launch(const cs_model* m, const float* logits, int B, int k, int V,
                             const int32_t* draft, const int32_t* draft_len, int32_t* accepted,
                             int32_t* next_tok, int32_t* row_argmax_out, int32_t* kv_len,
                             int32_t* hist, int64_t hist_stride, int32_t* hist_len,
-                            int32_t* room, hipStream_t s);
+                            int32_t* room, int32_t* emitted, hipStream_t s);
 
 // GEMM: Y = X * W^T.  mode 0: float32 result [R][N] written to Y (nparts_out tells how many
 // split-K partial tiles were written, each [R_stride][N]); mode 1: SwiGLU epilogue into

@@ -157,7 +157,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan(const int32_t* __restrict
 __device__ __forceinline__ void gather_draft(const int32_t* __restrict__ h, int n, int gamma, int k, int64_t key,
                                              int b, const int32_t* __restrict__ room,
                                              int32_t* __restrict__ match_pos, int32_t* __restrict__ src_pos,
-                                             int32_t* __restrict__ draft, int32_t* __restrict__ draft_len) {
+                                             int32_t* __restrict__ draft, int32_t* __restrict__ draft_len,
+                                             int32_t* __restrict__ draft_len2) {
     const int best = key < 0 ? -1 : (int)(key & 0x7fffffff);      // low word: the position
     const int src = best < 0 ? -1 : best + gamma;
     int dl = best < 0 ? 0 : min(k, n - src);
@@ -166,6 +167,7 @@ __device__ __forceinline__ void gather_draft(const int32_t* __restrict__ h, int 
         if (match_pos) match_pos[b] = best;
         if (src_pos) src_pos[b] = src;
         draft_len[b] = dl;
+        if (draft_len2) draft_len2[b] = dl;
     }
     for (int i = threadIdx.x; i < k; i += blockDim.x) draft[(int64_t)b * k + i] = i < dl ? h[src + i] : -1;
 }
@@ -178,7 +180,8 @@ __global__ __launch_bounds__(64) void k_gather(const int32_t* __restrict__ hist,
                                                int32_t* __restrict__ match_pos,
                                                int32_t* __restrict__ src_pos,
                                                int32_t* __restrict__ draft,
-                                               int32_t* __restrict__ draft_len) {
+                                               int32_t* __restrict__ draft_len,
+                                               int32_t* __restrict__ draft_len2) {
     const int b = blockIdx.x;
     int64_t key = -1;
     for (int c = threadIdx.x; c < nchunks; c += 64) {
@@ -190,7 +193,7 @@ __global__ __launch_bounds__(64) void k_gather(const int32_t* __restrict__ hist,
         const int64_t other = __shfl_xor(key, o, 64);
         key = policy == CS_POLICY_FIRST ? key_better<CS_POLICY_FIRST>(key, other) : key_better<CS_POLICY_RIGHTMOST>(key, other);
     }
-    gather_draft(hist + (int64_t)b * stride, len[b], gamma, k, key, b, room, match_pos, src_pos, draft, draft_len);
+    gather_draft(hist + (int64_t)b * stride, len[b], gamma, k, key, b, room, match_pos, src_pos, draft, draft_len, draft_len2);
 }
 
 // Short histories: search and draft in one launch, a workgroup per stream, no keys in memory.
@@ -201,12 +204,13 @@ __global__ __launch_bounds__(THREADS) void k_scan_short(const int32_t* __restric
                                                         int32_t* __restrict__ match_pos,
                                                         int32_t* __restrict__ src_pos,
                                                         int32_t* __restrict__ draft,
-                                                        int32_t* __restrict__ draft_len) {
+                                                        int32_t* __restrict__ draft_len,
+                                                        int32_t* __restrict__ draft_len2) {
     const int b = blockIdx.x;
     const int32_t* __restrict__ h = hist + (int64_t)b * stride;
     const int n = len[b];
     const int64_t key = scan_block_best<POLICY, THREADS>(scan_strides<POLICY, THREADS>(h, n, gamma, vec_ok, 0, 1));
-    gather_draft(h, n, gamma, k, key, b, room, match_pos, src_pos, draft, draft_len);
+    gather_draft(h, n, gamma, k, key, b, room, match_pos, src_pos, draft, draft_len, draft_len2);
 }
 
 // Number of key slots per stream a scan over histories of up to max_len tokens wants (one per
@@ -224,7 +228,7 @@ bool cs_scan_needs_keys(int B, int nslots) { return nslots > 1 && (nslots > 8 ||
 // own buffer, the per-stream buffers below, or the static array of the entry point that allocates nothing.
 int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, int B, int gamma,
                    int k, int policy, int64_t* keys, int nslots, int32_t* d_match_pos, int32_t* d_src_pos,
-                   int32_t* d_draft, int32_t* d_draft_len, const int32_t* d_room, hipStream_t s) {
+                   int32_t* d_draft, int32_t* d_draft_len, const int32_t* d_room, int32_t* d_draft_len2, hipStream_t s) {
     if (B == 0) return CS_OK;
     CS_REQUIRE((keys || !cs_scan_needs_keys(B, nslots)) && nslots >= 1 && B <= 65535, CS_E_ARG,
                "scan: no key buffer, or more than 65535 histories");
@@ -233,7 +237,7 @@ int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, 
         auto start = [&](auto policy_tag, auto threads_tag) {
             constexpr int POLICY = decltype(policy_tag)::value, THREADS = decltype(threads_tag)::value;
             k_scan_short<POLICY, THREADS><<<B, THREADS, 0, s>>>(d_hist, stride, d_len, gamma, k, vec_ok, d_room, d_match_pos,
-                                                                d_src_pos, d_draft, d_draft_len);
+                                                                d_src_pos, d_draft, d_draft_len, d_draft_len2);
         };
         auto by_policy = [&](auto threads_tag) {
             if (policy == CS_POLICY_RIGHTMOST) start(std::integral_constant<int, CS_POLICY_RIGHTMOST>{}, threads_tag);
@@ -259,7 +263,7 @@ int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, 
     cs_prof_end(ps, s);
     CS_TRY(cs_launch_ok("k_scan"));
     k_gather<<<B, 64, 0, s>>>(d_hist, stride, d_len, gamma, k, policy, keys, nslots, d_room,
-                              d_match_pos, d_src_pos, d_draft, d_draft_len);
+                              d_match_pos, d_src_pos, d_draft, d_draft_len, d_draft_len2);
     return cs_launch_ok("k_gather");
 }
 
@@ -300,7 +304,7 @@ int cs_gather_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len
                      hipStream_t s) {
     if (B == 0) return CS_OK;
     k_gather<<<B, 64, 0, s>>>(d_hist, stride, d_len, gamma, k, policy, d_keys, nchunks, d_room, d_match_pos,
-                              d_src_pos, d_draft, d_draft_len);
+                              d_src_pos, d_draft, d_draft_len, nullptr);
     return cs_launch_ok("k_gather");
 }
 
@@ -350,5 +354,5 @@ extern "C" int cs_find_match_batch_dev_noalloc(const int32_t* d_hist, int64_t st
     int64_t* keys = nullptr;
     CS_TRY(scan_static_keys(&keys));
     return cs_scan_launch(d_hist, stride, d_len, B, gamma, k, policy, keys, nslots, d_match_pos, d_src_pos,
-                          d_draft, d_draft_len, nullptr, (hipStream_t)stream);
+                          d_draft, d_draft_len, nullptr, nullptr, (hipStream_t)stream);
 }
