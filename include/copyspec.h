@@ -321,9 +321,9 @@ int cs_decode_greedy(cs_model* m, cs_kv* kv, const int32_t* prompt /*host*/, int
  *
  * cs_prefill_batch: prompts is a host array [B][prompt_stride], B = the batch of `kv`,
  * stream b's prompt being its first prompt_len[b] >= 1 tokens.  All lengths are reset; the
- * prompts are run through the model in lock step (every pass takes the same number of rows
- * from every stream, the workspace rows divided by B; a stream whose prompt is used up rides
- * along on padding rows that stay dead), leaving stream b with length prompt_len[b] - 1.
+ * prompts are run through the model together (every pass takes about the same number of rows,
+ * equally many from every stream that has some left), leaving stream b with length
+ * prompt_len[b] - 1.
  * cs_decode_batch: cs_prefill_batch, then cs_step on all streams until every stream has
  * emitted max_new tokens or eos_id (>= 0; its output is cut after it).  A stream that is done
  * takes no further part (its emission budget is 0, see cs_step).  out_tokens: host

@@ -284,8 +284,7 @@ static int model_alloc(cs_model* m) {
     m->part_floats = (size_t)16 * R * widest;
     DEV_ALLOC(m->part, m->part_floats * 4);
     const size_t groups_verify = (size_t)c.max_batch * KVH * cs_ceil_div((H / KVH) * m->rows_max, 48);
-    // prompt blocks: one stream with prefill_rows rows, or all streams in lock step with
-    // their share of the workspace rows each (one more query group per stream from rounding)
+    // prompt blocks: one stream with prefill_rows rows (batched prompts need no attention partials)
     const size_t ws_rows = (size_t)(m->R_max > m->prefill_rows ? m->R_max : m->prefill_rows);
     const size_t groups_prompt = (size_t)KVH * (cs_ceil_div((H / KVH) * ws_rows, 48) + c.max_batch);
     const size_t groups_max = groups_verify > groups_prompt ? groups_verify : groups_prompt;

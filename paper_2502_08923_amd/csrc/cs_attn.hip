@@ -633,8 +633,8 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
 // Up to FA_QG consumer waves each own one 48-row query group and all walk the same token
 // range; one producer wave streams K and V from HBM once per workgroup and lays them into a
 // three-stage LDS ring in MFMA fragment order, so the KV bytes are read once however many
-// query groups share them.  One barrier per 32-token block hands the stages over.  Every
-// consumer writes its own partial (no in-workgroup merge); k_attn_merge combines the splits.
+// query groups share them.  One barrier per 32-token block hands the stages over.  The two teams'
+// results meet in LDS at the end; k_attn_merge combines the workgroups'.
 // -------------------------------------------------------------------------------------
 #define FA_QG 3
 #define FA_STAGES 3
@@ -682,7 +682,6 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     const int team = spread ? (hw < 4 ? hw >> 1 : (hw & 1)) : hw / (FA_QG + 1);
     const int wave = spread ? (hw < 4 ? (hw & 1) : (hw < 6 ? FA_QG : 2)) : hw % (FA_QG + 1);
     unsigned char (*stage)[STAGE_BYTES] = stage_all[team];
-    const int split = (range % nsp) * FA_TEAMS + team;  // number of this team's partial result
     const int kvh = (range / nsp) % KVH, b = range / (nsp * KVH);
     const int G = H / KVH;
     const int QR = G * rows;
@@ -694,9 +693,8 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     const int n_lim = L + last_row + 1;
     // The two teams share the workgroup's token range of FA_TEAMS*Tw and take its 32-token blocks
     // in turn (team t: blocks t, t+2, ...), so the workgroup reads neighbouring blocks together.
-    // `split` still numbers the partial result: (range, team).
     constexpr int TSTEP = 32 * FA_TEAMS;
-    const int w_begin = min((split - team) * Tw, n_lim);
+    const int w_begin = min(range % nsp * FA_TEAMS * Tw, n_lim);
     const int w_blocks = (min(n_lim, w_begin + FA_TEAMS * Tw) - w_begin + 31) / 32;
     const int t_begin = w_begin + 32 * team;
     const int nblocks = (w_blocks - team + FA_TEAMS - 1) / FA_TEAMS;
@@ -795,6 +793,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
             store(0, 0, i + 3);
             __syncthreads();
         }
+        __syncthreads();                                   // the one between the teams' results, below
         return;
     }
 
@@ -1013,18 +1012,39 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
         block(sb, sa, i + 1);
         __syncthreads();
     }
-    if (!live) return;
 
-    const int64_t item = ((int64_t)b * KVH + kvh) * nqg + qg;
-    float* __restrict__ o_out = po + (item * nsplit + split) * FA_QROWS * HD;
-    float* __restrict__ ml_out = pml + (item * nsplit + split) * FA_QROWS * 2;
+    // Team 1 hands its (max, sum, O) over through LDS (the stages are free after the last barrier), team 0 adds its own:
+    // one partial result per workgroup (16 streams of 16384 rows: 35 -> 18 MB written and read again by the merge).
+    constexpr int OROW = HD + FA_OPAD;
+    float* s_o = reinterpret_cast<float*>(&stage_all[0][0][0]);                           // [FA_QG][FA_QROWS][OROW]
+    float2* s_ml = reinterpret_cast<float2*>(s_o + FA_QG * FA_QROWS * OROW);              // [FA_QG][FA_QROWS]
+    static_assert(FA_QG * FA_QROWS * (OROW * 4 + 8) <= FA_TEAMS * FA_STAGES * STAGE_BYTES && FA_TEAMS == 2, "fits the stages");
+    if (live && team == 1) {
+#pragma unroll
+        for (int nt = 0; nt < FA_NT; ++nt) {
+            const int n = wave * FA_QROWS + nt * 16 + c;
+            if (g == 0) s_ml[n] = make_float2(m_run[nt], lacc[nt][0]);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<f32x4*>(&s_o[n * OROW + mt * 16 + 4 * g]) = oacc[mt][nt];
+        }
+    }
+    __syncthreads();
+    if (!live || team == 1) return;
+
+    const int64_t item = (((int64_t)b * KVH + kvh) * nqg + qg) * nsp + range % nsp;
+    float* __restrict__ o_out = po + item * FA_QROWS * HD;
+    float* __restrict__ ml_out = pml + item * FA_QROWS * 2;
 #pragma unroll
     for (int nt = 0; nt < FA_NT; ++nt) {
         const int n = nt * 16 + c;
-        if (g == 0) { ml_out[n * 2] = m_run[nt]; ml_out[n * 2 + 1] = lacc[nt][0]; }
+        const float2 ml = s_ml[wave * FA_QROWS + n];
+        const float M = fmaxf(m_run[nt], ml.x), Ms = (M == -INFINITY) ? 0.f : M;
+        const float w0 = __builtin_amdgcn_exp2f(m_run[nt] - Ms), w1 = __builtin_amdgcn_exp2f(ml.x - Ms);
+        if (g == 0) { ml_out[n * 2] = M; ml_out[n * 2 + 1] = lacc[nt][0] * w0 + ml.y * w1; }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
-            *reinterpret_cast<f32x4*>(o_out + (int64_t)n * HD + mt * 16 + 4 * g) = oacc[mt][nt];
+            *reinterpret_cast<f32x4*>(o_out + (int64_t)n * HD + mt * 16 + 4 * g) =
+                oacc[mt][nt] * w0 + *reinterpret_cast<const f32x4*>(&s_o[(wave * FA_QROWS + n) * OROW + mt * 16 + 4 * g]) * w1;
     }
 }
 
@@ -1521,7 +1541,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         if (nsplit < 1) nsplit = 1;
         const int Tw = (int)cs_round_up(cs_ceil_div(n_tok_ub, nsplit), 32);
         nsplit = (int)cs_round_up(cs_ceil_div(n_tok_ub, Tw), FA_TEAMS);
-        const size_t items = (size_t)B * KVH * nqg * nsplit;
+        const size_t items = (size_t)B * KVH * nqg * (nsplit / FA_TEAMS);
         CS_REQUIRE(items * FA_QROWS * (hd + 2) <= m->attn_part_floats, CS_E_CAPACITY,
                    "attention workspace too small");
         float* po = m->attn_part;
@@ -1540,7 +1560,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         CS_TRY(cs_launch_ok("k_attn_lds"));
         dim3 mgrid((unsigned)cs_ceil_div(QR, FA_MERGE_THREADS / (hd / 4)), KVH, B);
         const int pm = cs_prof_begin(CS_PROF_ATTN_MERGE, s);
-        k_attn_merge<f16_t><<<mgrid, FA_MERGE_THREADS, 0, s>>>(po, pml, rows, H, KVH, hd, nqg, nsplit,
+        k_attn_merge<f16_t><<<mgrid, FA_MERGE_THREADS, 0, s>>>(po, pml, rows, H, KVH, hd, nqg, nsplit / FA_TEAMS,
                                                               (f16_t*)m->xn, tiled, m->range_flags);
         cs_prof_end(pm, s);
         return cs_launch_ok("k_attn_merge");
