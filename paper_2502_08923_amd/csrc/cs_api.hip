@@ -283,12 +283,12 @@ static int model_alloc(cs_model* m) {
     const int widest = nqkv > d ? nqkv : d;
     m->part_floats = (size_t)16 * R * widest;
     DEV_ALLOC(m->part, m->part_floats * 4);
-    const size_t groups_verify = (size_t)c.max_batch * KVH * cs_ceil_div((H / KVH) * m->rows_max, 48);
-    // prompt blocks: one stream with prefill_rows rows (batched prompts need no attention partials)
+    const size_t groups_verify = (size_t)c.max_batch * KVH * cs_ceil_div((H / KVH) * m->rows_max, CS_ATTN_GROUP);
+    // prompt blocks: prefill_rows rows of one stream, or shared out over all (a group more for each from rounding)
     const size_t ws_rows = (size_t)(m->R_max > m->prefill_rows ? m->R_max : m->prefill_rows);
-    const size_t groups_prompt = (size_t)KVH * (cs_ceil_div((H / KVH) * ws_rows, 48) + c.max_batch);
+    const size_t groups_prompt = (size_t)KVH * (cs_ceil_div((H / KVH) * ws_rows, CS_ATTN_GROUP) + c.max_batch);
     const size_t groups_max = groups_verify > groups_prompt ? groups_verify : groups_prompt;
-    m->attn_part_floats = (size_t)(4 * (512 + groups_max) + 64) * 48 * (hd + 2);
+    m->attn_part_floats = (size_t)(4 * (512 + groups_max) + 64) * CS_ATTN_GROUP * (hd + 2);
     if (m->fast) DEV_ALLOC(m->attn_part, m->attn_part_floats * 4);
     DEV_ALLOC(m->rope, R * (hd / 2) * sizeof(float2));
     DEV_ALLOC(m->tok, R * 4);
@@ -1002,10 +1002,11 @@ extern "C" int cs_prefill_batch(cs_model* m, cs_kv* kv, const int32_t* prompts, 
     if (total == 0) return CS_OK;
     const int64_t per0 = cs_round_up(cs_ceil_div(total, cs_ceil_div(total, ws_rows)), 16), per = per0 < ws_rows ? per0 : ws_rows;
     const int passes = (int)cs_ceil_div(total, per);
-    // one upload: per pass and stream (first row, rows), per row (stream, row within the share), tokens, row counts
-    std::vector<int32_t> up((size_t)(3 * passes * B + 3 * total), 0);
+    // one upload: per pass and stream (first row, rows, first query group, -), per row (stream, row within the share),
+    // tokens, row counts
+    std::vector<int32_t> up((size_t)(5 * passes * B + 3 * total), 0);
     int32_t* h_seg = up.data();
-    int32_t* h_row = h_seg + (size_t)2 * passes * B;
+    int32_t* h_row = h_seg + (size_t)4 * passes * B;
     int32_t* h_tok = h_row + 2 * total;
     int32_t* h_cnt = h_tok + total;
     std::vector<int64_t> done((size_t)(passes + 1) * B, 0);      // rows of each stream before each pass
@@ -1023,12 +1024,15 @@ extern "C" int cs_prefill_batch(cs_model* m, cs_kv* kv, const int32_t* prompts, 
             if (sum <= target) lo = c; else hi = c - 1;
         }
         for (int b = 0; b < B; ++b) taken += left(b) < lo ? left(b) : lo;
-        int64_t first = 0;
+        int64_t first = 0, group = 0;
         for (int b = 0; b < B; ++b) {
             int64_t n = left(b) < lo ? left(b) : lo;
             if (n < left(b) && taken < target) { ++n; ++taken; }
-            h_seg[2 * ((size_t)p * B + b)] = (int32_t)first;
-            h_seg[2 * ((size_t)p * B + b) + 1] = h_cnt[(size_t)p * B + b] = (int32_t)n;
+            int32_t* seg = h_seg + 4 * ((size_t)p * B + b);
+            seg[0] = (int32_t)first;
+            seg[1] = h_cnt[(size_t)p * B + b] = (int32_t)n;
+            seg[2] = (int32_t)group;
+            group += cs_ceil_div(m->cfg.n_heads / m->cfg.n_kv_heads * n, CS_ATTN_GROUP);
             for (int64_t i = 0; i < n; ++i, ++at) {
                 h_row[2 * at] = b;
                 h_row[2 * at + 1] = (int32_t)i;
@@ -1050,7 +1054,7 @@ extern "C" int cs_prefill_batch(cs_model* m, cs_kv* kv, const int32_t* prompts, 
         const int32_t* d_tok = d_up + (h_tok - up.data()) + p * per;
         const int32_t* d_cnt = d_up + (h_cnt - up.data()) + (size_t)p * B;
         const cs_ragged rg = {reinterpret_cast<const int2*>(d_up + (h_row - up.data())) + p * per,
-                              reinterpret_cast<const int2*>(d_up) + (size_t)p * B, h_cnt + (size_t)p * B, R};
+                              reinterpret_cast<const int4*>(d_up) + (size_t)p * B, h_cnt + (size_t)p * B, R};
         for (int b = 0; b < B; ++b) kv->h_len_ub[b] = done[(size_t)p * B + b];
         const cs_block_src src = {d_tok, nullptr, nullptr, 0, nullptr, nullptr, nullptr};
         rc = forward_layers(m, kv, src, 0, &rg, nullptr);

@@ -177,6 +177,7 @@ __device__ __forceinline__ float fa_row4_max(float x) {
 }
 
 #define FA_QROWS (16 * FA_NT)
+static_assert(FA_QROWS == CS_ATTN_GROUP, "the host counts query groups in these rows");
 #define FA_RESCALE_LOG2 8.0f
 #define FA_OPAD 4          // LDS row padding (floats) of the in-workgroup merge buffers
 #define FA_BUFFER_WORD3 0x00027000   // buffer resource word 3: raw 32-bit data, range checked in bytes
@@ -646,6 +647,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
                                                               const bf16_t* __restrict__ kc,
                                                               const bf16_t* __restrict__ vc,
                                                               const int32_t* __restrict__ kv_len,
+                                                              const int4* __restrict__ segs,
                                                               int rows, int H, int KVH, int64_t cap,
                                                               int Tw, int nqg, int nqgw, int gpw, int nsplit,
                                                               int ranges, float* __restrict__ po,
@@ -670,6 +672,17 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     // which gpw (<= FA_QG) of the query groups: the last rows of a block see the most tokens (see n_lim
     // below), so they are dispatched first and the short ones fill the tail of the launch
     const int qgw = nqgw - 1 - slot % nqgw;
+    const int kvh = (range / nsp) % KVH, b = range / (nsp * KVH);
+    const int G = H / KVH;
+    int row0 = b * rows, group0 = b * nqg;              // the stream's first block row, its first query group
+    if (segs) {
+        const int4 sg = segs[b];
+        row0 = sg.x;
+        rows = sg.y;
+        group0 = sg.z;
+        nqg = (G * rows + FA_QROWS - 1) / FA_QROWS;
+        if (qgw * gpw >= nqg) return;                   // (whole workgroup; a stream with fewer rows than others)
+    }
     // Roles of the eight waves (hardware waves go to the four SIMDs in turn: wave w runs on SIMD
     // w % 4).  With three live query groups per team: waves 0-2 and 4-6 are the consumers of teams 0
     // and 1, waves 3 and 7 the producers, so every consumer SIMD carries one consumer of each team.
@@ -682,8 +695,6 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     const int team = spread ? (hw < 4 ? hw >> 1 : (hw & 1)) : hw / (FA_QG + 1);
     const int wave = spread ? (hw < 4 ? (hw & 1) : (hw < 6 ? FA_QG : 2)) : hw % (FA_QG + 1);
     unsigned char (*stage)[STAGE_BYTES] = stage_all[team];
-    const int kvh = (range / nsp) % KVH, b = range / (nsp * KVH);
-    const int G = H / KVH;
     const int QR = G * rows;
     const int L = kv_len[b];
     const int n_tok = L + rows;
@@ -713,7 +724,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
         if (grp < gpw && n < QR) {
             const int i = n / G, gq = n % G;
             v = *reinterpret_cast<const bf16x8*>(
-                q + (((int64_t)(b * rows + i)) * H + kvh * G + gq) * HD + seg * 8);
+                q + (((int64_t)(row0 + i)) * H + kvh * G + gq) * HD + seg * 8);
         }
         *reinterpret_cast<bf16x8*>(&qs[grp][row * QROW + seg * 16]) = v;
     }
@@ -1031,7 +1042,7 @@ __global__ __launch_bounds__(FA_LDS_THREADS) void k_attn_lds(const bf16_t* __res
     __syncthreads();
     if (!live || team == 1) return;
 
-    const int64_t item = (((int64_t)b * KVH + kvh) * nqg + qg) * nsp + range % nsp;
+    const int64_t item = ((int64_t)group0 * KVH + kvh * nqg + qg) * nsp + range % nsp;
     float* __restrict__ o_out = po + item * FA_QROWS * HD;
     float* __restrict__ ml_out = pml + item * FA_QROWS * 2;
 #pragma unroll
@@ -1076,7 +1087,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __
                                                              const bf16_t* __restrict__ kc,
                                                              const bf16_t* __restrict__ vc,
                                                              const int32_t* __restrict__ kv_len,
-                                                             const int2* __restrict__ segs,
+                                                             const int4* __restrict__ segs,
                                                              int rows, int H, int KVH, int64_t cap,
                                                              int nqt, int ranges, unsigned inv_g,
                                                              OT* __restrict__ out, int tiled,
@@ -1373,6 +1384,7 @@ __global__ __launch_bounds__(64 * PF_WAVES) void k_attn_prefill(const bf16_t* __
 template <typename OT>
 __global__ __launch_bounds__(FA_MERGE_THREADS) void k_attn_merge(const float* __restrict__ po,
                                                                  const float* __restrict__ pml,
+                                                                 const int4* __restrict__ segs,
                                                                  int rows, int H, int KVH, int HD,
                                                                  int nqg, int nsplit,
                                                                  OT* __restrict__ out, int tiled,
@@ -1382,10 +1394,18 @@ __global__ __launch_bounds__(FA_MERGE_THREADS) void k_attn_merge(const float* __
     const int d = ((int)threadIdx.x % lpr) * 4;
     const int kvh = blockIdx.y, b = blockIdx.z;
     const int G = H / KVH;
+    int row0 = b * rows, group0 = b * nqg;    // the stream's first block row, its first query group
+    if (segs) {
+        const int4 sg = segs[b];
+        row0 = sg.x;
+        rows = sg.y;
+        group0 = sg.z;
+        nqg = (G * rows + FA_QROWS - 1) / FA_QROWS;
+    }
     if (n >= G * rows) return;
     const int i = n / G, gq = n % G;
     const int qg = n / FA_QROWS, nl = n % FA_QROWS;
-    const int64_t item = ((int64_t)b * KVH + kvh) * nqg + qg;
+    const int64_t item = (int64_t)group0 * KVH + kvh * nqg + qg;
     const float2* __restrict__ ml = reinterpret_cast<const float2*>(pml) + (item * nsplit * FA_QROWS + nl);
     const float* __restrict__ o = po + (item * nsplit * FA_QROWS + nl) * HD + d;
     // eight splits at a time, all their loads issued before the first is used: with many splits
@@ -1418,7 +1438,7 @@ __global__ __launch_bounds__(FA_MERGE_THREADS) void k_attn_merge(const float* __
         }
     }
     const float inv = 1.0f / den;
-    const int r = b * rows + i;
+    const int r = row0 + i;
     // tiled: the output projection runs the many-row GEMM, which reads fragment order
     const int col = (kvh * G + gq) * HD + d;
     const int64_t off = tiled ? cs_xt_index(r, col, H * HD) : (int64_t)r * H * HD + col;
@@ -1498,13 +1518,18 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     // of 64-row tiles covers.  (Attention and merge, or this kernel alone, one stream of the 8B shape, prompts of 24, 64,
     // 128, 256 rows: 18.3, 20.7, 24.0, 29.7 us split, 9.4, 9.8, 11.7, 15.4 unsplit; a 32-token block costs a workgroup
     // 0.6 us, so that from about 900 tokens on the split kernel's 22 to 27 us are fewer.)
-    // Blocks with their own number of rows per stream always come here.
+    // Blocks with their own number of rows per stream come here by the same two rules, however narrow; the others of
+    // them go to the wide kernel (64 rows at the end of 8000 tokens are 250 blocks for a workgroup here; prompts of 8000
+    // tokens in 64-row passes through four layers of 8B widths: one 104 ms, two 207, always here; 72 and 145 so).
     const int64_t ranges = (int64_t)B * KVH;
-    const int64_t wgs_many = ranges * cs_ceil_div(QR, 256);
-    int64_t wgs_few = 0;
-    for (int b = 0; b < B; ++b) wgs_few += KVH * cs_ceil_div((int64_t)G * (rg ? rg->rows[b] : rows), 64);
-    const bool many = QR >= 512 && wgs_many >= 40, brief = nqg > 1 && wgs_few <= 256 && n_tok_ub <= 768;
-    if (many || brief || rg) {
+    int64_t wgs_many = 0, wgs_few = 0;
+    for (int b = 0; b < B; ++b) {
+        const int64_t n = (int64_t)G * (rg ? rg->rows[b] : rows);
+        wgs_many += KVH * cs_ceil_div(n, 256);
+        wgs_few += KVH * cs_ceil_div(n, 64);
+    }
+    const bool many = QR >= 512 && wgs_many >= 40, brief = n_tok_ub <= 768 && (rg || (nqg > 1 && wgs_few <= 256));
+    if (many || brief) {
         // 64 query rows in four waves while that gives at most two workgroups per compute unit, or three of a prompt's
         // first block, whose early rows see few tokens (300, 512, 700, 1024, 1500 rows of the 8B shape: 21.1, 27.3, 33.4,
         // 42.6, 57.0 us with 256-row tiles, 15.8, 20.0, 27.5, 38.0, 54.0 with 64; 8 streams of 300 rows, 1216 workgroups: 31
@@ -1529,38 +1554,49 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         cs_prof_end(pa, s);
         return cs_launch_ok("k_attn_prefill");
     }
-    if (nqg > 1) {
+    if (nqg > 1 || rg) {
         // wide block: consumers share the K/V stream of one producer wave through LDS
         const int nqgw = (int)cs_ceil_div(nqg, FA_QG);
         // query groups evenly over the workgroups of a range (147 rows: 2 + 2, which spread over the SIMDs, not 3 + 1)
         const int gpw = (int)cs_ceil_div(nqg, nqgw);
-        nsplit = FA_TEAMS * fit_ranges((int64_t)B * KVH, nqgw, n_tok_ub);
+        // query groups of all streams, and workgroups per token range that have some of them
+        int64_t groups = (int64_t)B * nqg, wgs = (int64_t)B * nqgw;
+        if (rg) {
+            groups = wgs = 0;
+            for (int b = 0; b < B; ++b) {
+                const int64_t g = cs_ceil_div((int64_t)G * rg->rows[b], FA_QROWS);
+                groups += g;
+                wgs += cs_ceil_div(g, gpw);
+            }
+        }
+        nsplit = FA_TEAMS * (rg ? fit_ranges(KVH * wgs, 1, n_tok_ub) : fit_ranges((int64_t)B * KVH, nqgw, n_tok_ub));
         const int max_split = (int)cs_ceil_div(n_tok_ub, 256);
         if (nsplit > max_split) nsplit = max_split;
         if (nsplit > FA_MAX_SPLIT) nsplit = FA_MAX_SPLIT;
         if (nsplit < 1) nsplit = 1;
         const int Tw = (int)cs_round_up(cs_ceil_div(n_tok_ub, nsplit), 32);
         nsplit = (int)cs_round_up(cs_ceil_div(n_tok_ub, Tw), FA_TEAMS);
-        const size_t items = (size_t)B * KVH * nqg * (nsplit / FA_TEAMS);
+        const size_t items = (size_t)groups * KVH * (nsplit / FA_TEAMS);
         CS_REQUIRE(items * FA_QROWS * (hd + 2) <= m->attn_part_floats, CS_E_CAPACITY,
                    "attention workspace too small");
         float* po = m->attn_part;
         float* pml = m->attn_part + items * FA_QROWS * hd;
         // one-dimensional grid, decoded in the kernel (XCD-aware order)
         const int ranges = B * KVH * (nsplit / FA_TEAMS);
+        const int4* segs = rg ? rg->seg : nullptr;
         dim3 grid((unsigned)(cs_round_up(ranges, 8) * nqgw));
         const int pa = cs_prof_begin(CS_PROF_ATTN, s);
         if (hd == 128)
-            k_attn_lds<128><<<grid, FA_LDS_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows,
+            k_attn_lds<128><<<grid, FA_LDS_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, segs, rows,
                                                              H, KVH, kv->cap, Tw, nqg, nqgw, gpw, nsplit, ranges, po, pml);
         else
-            k_attn_lds<64><<<grid, FA_LDS_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, rows,
+            k_attn_lds<64><<<grid, FA_LDS_THREADS, 0, s>>>((const bf16_t*)m->q, kc, vc, kv->d_len, segs, rows,
                                                             H, KVH, kv->cap, Tw, nqg, nqgw, gpw, nsplit, ranges, po, pml);
         cs_prof_end(pa, s);
         CS_TRY(cs_launch_ok("k_attn_lds"));
         dim3 mgrid((unsigned)cs_ceil_div(QR, FA_MERGE_THREADS / (hd / 4)), KVH, B);
         const int pm = cs_prof_begin(CS_PROF_ATTN_MERGE, s);
-        k_attn_merge<f16_t><<<mgrid, FA_MERGE_THREADS, 0, s>>>(po, pml, rows, H, KVH, hd, nqg, nsplit / FA_TEAMS,
+        k_attn_merge<f16_t><<<mgrid, FA_MERGE_THREADS, 0, s>>>(po, pml, segs, rows, H, KVH, hd, nqg, nsplit / FA_TEAMS,
                                                               (f16_t*)m->xn, tiled, m->range_flags);
         cs_prof_end(pm, s);
         return cs_launch_ok("k_attn_merge");
@@ -1619,7 +1655,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     CS_TRY(cs_launch_ok("k_attn_mfma"));
     dim3 mgrid((unsigned)cs_ceil_div(QR, FA_MERGE_THREADS / (hd / 4)), KVH, B);
     const int pm = cs_prof_begin(CS_PROF_ATTN_MERGE, s);
-    k_attn_merge<f16_t><<<mgrid, FA_MERGE_THREADS, 0, s>>>(po, pml, rows, H, KVH, hd, nqg, nsplit,
+    k_attn_merge<f16_t><<<mgrid, FA_MERGE_THREADS, 0, s>>>(po, pml, nullptr, rows, H, KVH, hd, nqg, nsplit,
                                                           (f16_t*)m->xn, tiled, m->range_flags);
     cs_prof_end(pm, s);
     return cs_launch_ok("k_attn_merge");

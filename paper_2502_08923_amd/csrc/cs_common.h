@@ -155,11 +155,13 @@ struct cs_block_src {
     const int32_t* draft;       // [B][rows - 1]
     const int32_t* draft_len;
 };
+#define CS_ATTN_GROUP 48        // query rows per group of the split attention kernels
 // A prompt block with its own number of rows for every stream (all its rows are live): the rows lie stream after
 // stream, and the kernels look up which row is whose instead of dividing by a common count.
 struct cs_ragged {
     const int2* row;            // [R] (stream, row within the stream's share), device
-    const int2* seg;            // [B] (first row, rows) of every stream, device
+    const int4* seg;            // [B] (first row, rows, first query group, -) of every stream, device; a stream has
+                                // as many groups of CS_ATTN_GROUP query rows as its rows of one KV head fill
     const int32_t* rows;        // [B] the same counts, host
     int R;
 };

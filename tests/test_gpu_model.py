@@ -949,6 +949,34 @@ def test_prefill_batch_passes_across_prompts(shape, plain, block_rows):
     model.destroy()
 
 
+@pytest.mark.parametrize("shape", [MINI64, MINI128, MINIQWEN])
+@pytest.mark.parametrize("lens,block_rows", [([1100, 1, 830, 1101], 48), ([1000], 32), ([1200, 900], 160)])
+def test_prefill_batch_few_rows_behind_a_long_context(shape, lens, block_rows):
+    """Passes of few rows (of one stream, of some, uneven) behind up to 1200 tokens: the tokens are split over workgroups,
+    which the merge kernel shows, and the cache rows are the oracle's."""
+    w = synth.model_weights(shape, 8131, threads=4)
+    model = cs.Model(w, max_batch=len(lens), max_k=1, prompt_block_rows=block_rows)
+    prompts = [p[:n] for p, n in zip(_ragged_prompts(shape.vocab, [max(n, 40) for n in lens], 5202), lens)]
+    kv = cs.KV(model, len(lens), max(lens))
+    cs.cs_profile_enable(["attn", "attn_merge"])
+    cs.cs_profile_reset()
+    cs.cs_prefill_batch(model, kv, prompts)
+    merges = cs.cs_profile_read("attn_merge")[1]
+    cs.cs_profile_enable([])
+    assert merges > 0
+    for b, n in enumerate(lens):
+        assert kv.len(b) == n - 1
+        okv = orc.KVCache(shape, max(lens))
+        orc.prefill(w, okv, prompts[b], chunk=64)
+        for layer in range(shape.n_layers):
+            if n > 1:
+                k_rows, v_rows = kv.read(layer, b, 0, n - 1)
+                _cache_rows_close(k_rows, okv.k[layer, :, :n - 1], 2e-2)
+                _cache_rows_close(v_rows, okv.v[layer, :, :n - 1], 2e-2)
+    kv.destroy()
+    model.destroy()
+
+
 def test_decode_batch_full_acceptance_repeat_model():
     """A model whose greedy token repeats its input: every history becomes x, x, x, ..., every
     match is accepted whole, in every stream; steps, attempts and accepted counts are the
