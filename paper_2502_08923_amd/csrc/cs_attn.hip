@@ -1470,6 +1470,40 @@ static int fit_ranges(int64_t items, int wgs, int64_t n_tok) {
     return best;
 }
 
+// How the wide kernel would take a block: query groups per workgroup, token ranges, and what that costs, in tokens' worth
+// of a workgroup's time (about 17 ns at hd 128, 11 at hd 64).
+struct wide_plan {
+    int nqgw, gpw, nsplit, Tw;      // workgroups per token range, query groups of each; team ranges, tokens of one
+    int64_t groups;                 // query groups of one KV head, over all streams
+    double cost;
+};
+static wide_plan plan_wide(int B, int KVH, int G, int nqg, int64_t n_tok, const cs_ragged* rg) {
+    wide_plan p;
+    p.nqgw = (int)cs_ceil_div(nqg, FA_QG);
+    // query groups evenly over the workgroups of a range (147 rows: 2 + 2, which spread over the SIMDs, not 3 + 1)
+    p.gpw = (int)cs_ceil_div(nqg, p.nqgw);
+    int64_t wgs = (int64_t)B * p.nqgw;                   // workgroups per token range that have query groups
+    p.groups = (int64_t)B * nqg;
+    if (rg) {
+        p.groups = wgs = 0;
+        for (int b = 0; b < B; ++b) {
+            const int64_t g = cs_ceil_div((int64_t)G * rg->rows[b], FA_QROWS);
+            p.groups += g;
+            wgs += cs_ceil_div(g, p.gpw);
+        }
+    }
+    p.nsplit = FA_TEAMS * (rg ? fit_ranges(KVH * wgs, 1, n_tok) : fit_ranges((int64_t)B * KVH, p.nqgw, n_tok));
+    const int max_split = (int)cs_ceil_div(n_tok, 256);
+    if (p.nsplit > max_split) p.nsplit = max_split;
+    if (p.nsplit > FA_MAX_SPLIT) p.nsplit = FA_MAX_SPLIT;
+    if (p.nsplit < 1) p.nsplit = 1;
+    p.Tw = (int)cs_round_up(cs_ceil_div(n_tok, p.nsplit), 32);
+    p.nsplit = (int)cs_round_up(cs_ceil_div(n_tok, p.Tw), FA_TEAMS);
+    const int ranges = p.nsplit / FA_TEAMS;
+    p.cost = 400. + (double)cs_ceil_div(KVH * wgs * ranges, 256) * (1000. + (double)n_tok / ranges) + 1.2 * (double)(KVH * p.groups * ranges);
+    return p;
+}
+
 bool cs_attention_fuses_rope(const cs_model* m, int rows) {
     return m->fast && (m->cfg.n_heads / m->cfg.n_kv_heads) * rows <= FA_QROWS;
 }
@@ -1513,14 +1547,15 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const bf16_t* vc = (const bf16_t*)kv->v + layer * per_layer;
     CS_REQUIRE(!qkv_part || nqg == 1, CS_E_STATE, "fused rotary embedding needs a narrow block");
     int nsplit;
-    // Blocks whose query rows fill the chip without splitting the token axis: prompt blocks of at least two tiles
-    // of 256 query rows per KV head and 40 workgroups, and, while the context is short, wide blocks that a round
-    // of 64-row tiles covers.  (Attention and merge, or this kernel alone, one stream of the 8B shape, prompts of 24, 64,
-    // 128, 256 rows: 18.3, 20.7, 24.0, 29.7 us split, 9.4, 9.8, 11.7, 15.4 unsplit; a 32-token block costs a workgroup
-    // 0.6 us, so that from about 900 tokens on the split kernel's 22 to 27 us are fewer.)
-    // Blocks with their own number of rows per stream come here by the same two rules, however narrow; the others of
-    // them go to the wide kernel (64 rows at the end of 8000 tokens are 250 blocks for a workgroup here; prompts of 8000
-    // tokens in 64-row passes through four layers of 8B widths: one 104 ms, two 207, always here; 72 and 145 so).
+    // The prompt kernel, which walks all tokens of a tile in one workgroup, or the token ranges of the wide kernel and
+    // their merge.  Considered for the first: prompt blocks of at least two tiles of 256 query rows per KV head and 40
+    // workgroups, and, while the context is short, wide blocks that a round of 64-row tiles covers and blocks with their
+    // own number of rows per stream, however narrow.  Those of more than two 64-row tiles per compute unit take it; the
+    // others where it is estimated to take less.  (7260 blocks of hd 64 and 128, one to eight query heads per KV head, 1
+    // to 32 streams of 0 to 24000 tokens, all three ways: on average 2 % slower than the fastest.  8B widths, one stream,
+    // 24, 64, 128, 256 rows: 18.3, 20.7, 24.0, 29.7 us split, 9.4, 9.8, 11.7, 15.4 unsplit; Qwen2.5-7B, 4 streams of 80
+    // rows behind 1500, 3000, 24000 tokens: 39, 44, 140 us split, 48, 79, 534 unsplit; a prompt of 8000 tokens in passes of
+    // 64 rows, four layers of 8B widths: 72 ms split, 104 unsplit.)
     const int64_t ranges = (int64_t)B * KVH;
     int64_t wgs_many = 0, wgs_few = 0;
     for (int b = 0; b < B; ++b) {
@@ -1529,12 +1564,20 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         wgs_few += KVH * cs_ceil_div(n, 64);
     }
     const bool many = QR >= 512 && wgs_many >= 40, brief = n_tok_ub <= 768 && (rg || (nqg > 1 && wgs_few <= 256));
-    if (many || brief) {
-        // 64 query rows in four waves while that gives at most two workgroups per compute unit, or three of a prompt's
-        // first block, whose early rows see few tokens (300, 512, 700, 1024, 1500 rows of the 8B shape: 21.1, 27.3, 33.4,
-        // 42.6, 57.0 us with 256-row tiles, 15.8, 20.0, 27.5, 38.0, 54.0 with 64; 8 streams of 300 rows, 1216 workgroups: 31
-        // against 34 us; 400 rows behind 4096, 200 workgroups: 134 against 95)
-        const bool small = wgs_few <= (len_ub < widest ? 768 : 512);
+    wide_plan wide = {};
+    if (nqg > 1 || rg) wide = plan_wide(B, KVH, G, nqg, n_tok_ub, rg);
+    const double reach = (double)len_ub + 0.5 * (widest + 1);        // tokens the rows see on average, at most
+    const double unsplit = wgs_few <= 256 ? (hd == 64 ? 650. : 500.) + 2. * reach : 1400. + 1.2 * reach;
+    if ((many || brief) && (wgs_few > 512 || unsplit <= wide.cost)) {
+        // 64 query rows in four waves while that gives at most two workgroups per compute unit (three, of half the LDS
+        // each, at hd 64 up to 2048 tokens), or three of a long prompt's first block, whose early rows see few tokens
+        // (300, 512, 700, 1024, 1500 rows of the 8B shape: 21.1, 27.3, 33.4, 42.6, 57.0 us with 256-row tiles, 15.8, 20.0,
+        // 27.5, 38.0, 54.0 with 64; 8 streams of 300 rows, 1216 workgroups: 31 against 34 us; 3 streams of 256 rows of
+        // eight query heads, 768 workgroups, behind 0 / 200 tokens: 36 / 43 against 38 / 50; hd 64, 5 streams of 200 rows
+        // of four, 520 workgroups, behind 300 / 2000 tokens: 26 / 62 against 22 / 62)
+        const bool first = len_ub < widest;
+        const bool three = first ? hd == 64 || QR >= 4096 : hd == 64 && n_tok_ub <= 2048;
+        const bool small = wgs_few <= (three ? 768 : 512);
         const int nqt = (int)cs_ceil_div(QR, small ? 64 : 256);
         const unsigned inv_g = G > 1 ? (unsigned)(((1ull << 32) + G - 1) / G) : 0;
         dim3 grid((unsigned)(ranges * nqt));
@@ -1556,27 +1599,9 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     }
     if (nqg > 1 || rg) {
         // wide block: consumers share the K/V stream of one producer wave through LDS
-        const int nqgw = (int)cs_ceil_div(nqg, FA_QG);
-        // query groups evenly over the workgroups of a range (147 rows: 2 + 2, which spread over the SIMDs, not 3 + 1)
-        const int gpw = (int)cs_ceil_div(nqg, nqgw);
-        // query groups of all streams, and workgroups per token range that have some of them
-        int64_t groups = (int64_t)B * nqg, wgs = (int64_t)B * nqgw;
-        if (rg) {
-            groups = wgs = 0;
-            for (int b = 0; b < B; ++b) {
-                const int64_t g = cs_ceil_div((int64_t)G * rg->rows[b], FA_QROWS);
-                groups += g;
-                wgs += cs_ceil_div(g, gpw);
-            }
-        }
-        nsplit = FA_TEAMS * (rg ? fit_ranges(KVH * wgs, 1, n_tok_ub) : fit_ranges((int64_t)B * KVH, nqgw, n_tok_ub));
-        const int max_split = (int)cs_ceil_div(n_tok_ub, 256);
-        if (nsplit > max_split) nsplit = max_split;
-        if (nsplit > FA_MAX_SPLIT) nsplit = FA_MAX_SPLIT;
-        if (nsplit < 1) nsplit = 1;
-        const int Tw = (int)cs_round_up(cs_ceil_div(n_tok_ub, nsplit), 32);
-        nsplit = (int)cs_round_up(cs_ceil_div(n_tok_ub, Tw), FA_TEAMS);
-        const size_t items = (size_t)groups * KVH * (nsplit / FA_TEAMS);
+        const int nqgw = wide.nqgw, gpw = wide.gpw, Tw = wide.Tw;
+        nsplit = wide.nsplit;
+        const size_t items = (size_t)wide.groups * KVH * (nsplit / FA_TEAMS);
         CS_REQUIRE(items * FA_QROWS * (hd + 2) <= m->attn_part_floats, CS_E_CAPACITY,
                    "attention workspace too small");
         float* po = m->attn_part;

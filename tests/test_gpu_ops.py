@@ -337,6 +337,40 @@ def test_attention_unsplit_short_contexts(H, KVH, hd, lens, rows, k_ramp):
     assert worst < 1e-2, worst
 
 
+@pytest.fixture
+def attention_kernels(monkeypatch):
+    """The names of the attention kernels that cs_op_attention starts in the test."""
+    from torch.profiler import ProfilerActivity, profile
+    names, op = [], cs.cs_op_attention
+
+    def traced(*args, **kw):
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            out = op(*args, **kw)
+            torch.cuda.synchronize()
+        names.extend(e.name for e in prof.events() if "k_attn" in e.name)
+        return out
+
+    monkeypatch.setattr(cs, "cs_op_attention", traced)
+    return names
+
+
+@pytest.mark.parametrize("H,KVH,hd,lens,rows,kernel", [
+    (28, 4, 128, [6000, 5999, 3000, 1], 80, "k_attn_lds"), (40, 8, 128, [3000, 2999], 128, "k_attn_lds"),
+    (32, 8, 64, [700], 16, "k_attn_lds"), (32, 8, 128, [3000, 700], 128, "k_attn_lds"),
+    (32, 8, 64, [400], 16, "k_attn_prefillILi64ELi1ELi4E"), (28, 4, 128, [500, 0, 499, 3], 80, "k_attn_prefillILi128ELi1ELi4E")])
+def test_attention_long_contexts_are_split_over_the_tokens(attention_kernels, H, KVH, hd, lens, rows, kernel):
+    """Wide blocks of few tiles behind a long context go to the kernel that splits the tokens, whatever the head group;
+    behind a short one they do not."""
+    shape = ModelShape("split", 1, 256, H, KVH, hd, 256, 512, 10000.0, 1e-5, "bf16")
+    m = cs.Model(synth.model_weights(shape, 96, threads=8), max_batch=len(lens), max_k=rows - 1)
+    sample = [(b, h) for b in range(len(lens)) for h in (0, H // 2, H - 1)]
+    worst = _attention_case(m, shape, lens, rows, sample, seed=60 + rows, poison=True)
+    m.destroy()
+    assert any(kernel in name for name in attention_kernels), attention_kernels
+    assert worst < 1e-2, worst
+
+
 @pytest.mark.parametrize("rows", [6, 21, 51, 101])
 def test_attention_block_size_sweep(rows):
     """Block sizes of the paper's sweep (Sec. 5.3, Table 4: 5, 10, 50, 100 draft tokens; 20 added):
