@@ -337,37 +337,30 @@ def test_attention_unsplit_short_contexts(H, KVH, hd, lens, rows, k_ramp):
     assert worst < 1e-2, worst
 
 
-@pytest.fixture
-def attention_kernels(monkeypatch):
-    """The names of the attention kernels that cs_op_attention starts in the test."""
-    from torch.profiler import ProfilerActivity, profile
-    names, op = [], cs.cs_op_attention
-
-    def traced(*args, **kw):
-        torch.cuda.synchronize()
-        with profile(activities=[ProfilerActivity.CUDA]) as prof:
-            out = op(*args, **kw)
-            torch.cuda.synchronize()
-        names.extend(e.name for e in prof.events() if "k_attn" in e.name)
-        return out
-
-    monkeypatch.setattr(cs, "cs_op_attention", traced)
-    return names
+def _attention_kernels(kernels_of, m, shape, lens, rows):
+    """The attention kernels of a block behind caches of these lengths."""
+    kv = cs.KV(m, len(lens), max(lens) + rows)
+    for b, n in enumerate(lens):
+        kv.set_len(b, n)
+    q = torch.zeros(len(lens), rows, shape.n_heads, shape.head_dim, device=DEV)
+    names = kernels_of(lambda: cs.cs_op_attention(m, kv, 0, q))
+    kv.destroy()
+    return [n for n in names if "k_attn" in n]
 
 
 @pytest.mark.parametrize("H,KVH,hd,lens,rows,kernel", [
     (28, 4, 128, [6000, 5999, 3000, 1], 80, "k_attn_lds"), (40, 8, 128, [3000, 2999], 128, "k_attn_lds"),
     (32, 8, 64, [700], 16, "k_attn_lds"), (32, 8, 128, [3000, 700], 128, "k_attn_lds"),
     (32, 8, 64, [400], 16, "k_attn_prefillILi64ELi1ELi4E"), (28, 4, 128, [500, 0, 499, 3], 80, "k_attn_prefillILi128ELi1ELi4E")])
-def test_attention_long_contexts_are_split_over_the_tokens(attention_kernels, H, KVH, hd, lens, rows, kernel):
+def test_attention_long_contexts_are_split_over_the_tokens(kernels_of, H, KVH, hd, lens, rows, kernel):
     """Wide blocks of few tiles behind a long context go to the kernel that splits the tokens, whatever the head group;
     behind a short one they do not."""
     shape = ModelShape("split", 1, 256, H, KVH, hd, 256, 512, 10000.0, 1e-5, "bf16")
     m = cs.Model(synth.model_weights(shape, 96, threads=8), max_batch=len(lens), max_k=rows - 1)
     sample = [(b, h) for b in range(len(lens)) for h in (0, H // 2, H - 1)]
     worst = _attention_case(m, shape, lens, rows, sample, seed=60 + rows, poison=True)
+    assert kernel in _attention_kernels(kernels_of, m, shape, lens, rows)[0]
     m.destroy()
-    assert any(kernel in name for name in attention_kernels), attention_kernels
     assert worst < 1e-2, worst
 
 
