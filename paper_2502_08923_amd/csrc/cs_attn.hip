@@ -24,9 +24,10 @@
 #include "cs_common.h"
 
 // -------------------------------------------------------------------------------------
-// plain reference kernel: one workgroup per (block row, query head, stream)
+// plain reference kernels: one workgroup per (block row, query head, stream); see the launcher for which of the two
 // -------------------------------------------------------------------------------------
 #define PA_CHUNK 2048
+#define PA_THREADS 256
 
 template <int THREADS>
 __device__ __forceinline__ float block_max(float v, float* wred) {
@@ -55,13 +56,99 @@ __device__ __forceinline__ f32x4 pa_ld4(const bf16_t* p) {
     return (f32x4){(float)t[0], (float)t[1], (float)t[2], (float)t[3]};
 }
 
+// A key row per thread, four tokens of one V feature per thread: every wave's loads touch 64 lines, but a thread needs no
+// other thread's sums, and a workgroup of four waves is done soonest where the context is short or the cache bfloat16.
+template <typename WT, typename QT, typename OT>
+__global__ __launch_bounds__(PA_THREADS) void k_attn_plain(const QT* __restrict__ q,
+                                                           const WT* __restrict__ kc,
+                                                           const WT* __restrict__ vc,
+                                                           const int32_t* __restrict__ kv_len,
+                                                           const int2* __restrict__ map,
+                                                           int rows, int H, int KVH, int hd,
+                                                           int64_t cap, OT* __restrict__ out) {
+    __shared__ float sq[256];
+    __shared__ float sc[PA_CHUNK];
+    __shared__ float red[PA_THREADS];
+    __shared__ float wred[PA_THREADS / CS_WAVE];
+    const int h = blockIdx.y, r = blockIdx.z * rows + blockIdx.x;
+    const int tid = threadIdx.x;
+    const int2 at = map ? map[r] : make_int2(blockIdx.z, blockIdx.x);
+    const int b = at.x, i = at.y;
+    const int g = h / (H / KVH);
+    const int n_ctx = kv_len[b] + i + 1;
+    const WT* __restrict__ K = kc + ((int64_t)b * KVH + g) * cap * hd;
+    const WT* __restrict__ V = vc + ((int64_t)b * KVH + g) * hd * cap;
+    if (tid < hd) sq[tid] = cs_ld(q, ((int64_t)r * H + h) * hd + tid);
+    __syncthreads();
+    const float scale = 1.0f / sqrtf((float)hd);
+    const int d = tid % hd, part = tid / hd, nparts = PA_THREADS / hd;
+    float m_run = -INFINITY, l_run = 0.f, o = 0.f;
+    for (int c0 = 0; c0 < n_ctx; c0 += PA_CHUNK) {
+        const int cn = min(PA_CHUNK, n_ctx - c0);
+        float lmax = -INFINITY;
+        for (int t = tid; t < cn; t += PA_THREADS) {
+            const WT* __restrict__ kr = K + (int64_t)(c0 + t) * hd;
+            float s = 0.f;
+            if (hd % 16 == 0) {                    // rows of whole 16-element pieces: wide loads, four in flight
+                f32x4 s4 = (f32x4){0.f, 0.f, 0.f, 0.f};
+                for (int e = 0; e < hd; e += 16) {
+                    f32x4 kv[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) kv[u] = pa_ld4(kr + e + 4 * u);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) s4[j] += sq[e + 4 * u + j] * kv[u][j];
+                }
+                s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+            } else {
+                for (int e = 0; e < hd; ++e) s += sq[e] * cs_ld(kr, e);
+            }
+            s *= scale;
+            sc[t] = s;
+            lmax = fmaxf(lmax, s);
+        }
+        const float mc = block_max<PA_THREADS>(lmax, wred);
+        const float m_new = fmaxf(m_run, mc);
+        const float alpha = expf(m_run - m_new);
+        float lsum = 0.f;
+        for (int t = tid; t < cn; t += PA_THREADS) {
+            const float p = expf(sc[t] - m_new);
+            sc[t] = p;
+            lsum += p;
+        }
+        const float lc = block_sum<PA_THREADS>(lsum, wred);       // its barriers also publish sc[]
+        l_run = l_run * alpha + lc;
+        float acc = 0.f;
+        // four tokens at a time (contiguous in the cache); rows past the context may hold anything
+#pragma unroll 4
+        for (int t = 4 * part; t < cn; t += 4 * nparts) {
+            const f32x4 v = pa_ld4(V + cs_v_index(c0 + t, d, hd));
+            float p[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) p[j] = t + j < cn ? sc[t + j] * v[j] : 0.f;
+            acc += (p[0] + p[1]) + (p[2] + p[3]);
+        }
+        o = o * alpha + acc;
+        m_run = m_new;
+        __syncthreads();
+    }
+    red[tid] = o;
+    __syncthreads();
+    if (part == 0) {
+        float tot = 0.f;
+        for (int p = 0; p < nparts; ++p) tot += red[p * hd + d];
+        cs_st(out, ((int64_t)r * H + h) * hd + d, tot / l_run);
+    }
+}
+
 // A verify block of a small model (44 workgroups over 512 tokens of hd 64) leaves most of the chip idle: what counts
 // is how fast one compute unit gets its K and V.  So neighbouring lanes read neighbouring memory, with four to
 // eight independent loads in flight per thread: hd/4 lanes share a token's key row (four elements each, their
 // products added by shuffles), and 32 lanes take the 128 consecutive tokens of one feature of V (cs_v_index), whose
-// sums meet by shuffles as well.  19.2 us with a key row per thread and four waves, 12.1 us now with 16.
+// sums meet by shuffles as well.  19.2 us with a key row per thread and four waves, 12.1 us here with 16.
 template <typename WT, typename QT, typename OT, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_attn_plain(const QT* __restrict__ q,
+__global__ __launch_bounds__(THREADS) void k_attn_plain_lanes(const QT* __restrict__ q,
                                                         const WT* __restrict__ kc,
                                                         const WT* __restrict__ vc,
                                                         const int32_t* __restrict__ kv_len,
@@ -73,7 +160,7 @@ __global__ __launch_bounds__(THREADS) void k_attn_plain(const QT* __restrict__ q
     __shared__ float wred[THREADS / CS_WAVE];
     const int h = blockIdx.y, r = blockIdx.z * rows + blockIdx.x;
     const int tid = threadIdx.x;
-    const int2 at = cs_block_row(map, r, rows);
+    const int2 at = map ? map[r] : make_int2(blockIdx.z, blockIdx.x);
     const int b = at.x, i = at.y;
     const int g = h / (H / KVH);
     const int n_ctx = kv_len[b] + i + 1;
@@ -1515,22 +1602,45 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const int64_t per_layer = (int64_t)B * KVH * kv->cap * hd;
     if (!m->fast) {
         dim3 grid(rg ? rg->R : rows, H, rg ? 1 : B);
+        // The kernel whose lanes share a key row does more per token and has more to add up at the end: it is for
+        // contexts that outweigh this, measured by the elements of a head's K that a row sees on average (rows of 4 or 8
+        // elements, which the other kernel reads one by one, count eightfold).  Its workgroups of 16 waves fill a compute
+        // unit each (113 to 127 registers), those of four pay where there are many.
+        // Times against the kernel with a key row per thread, hd 32 / 64 / 128:
+        //   up to 256 workgroups, 16 waves:  200 tokens 1.07 / 0.91 / 0.82, 1000 0.71 / 0.58 / 0.55 (bfloat16 0.90 / 0.71 / 0.72)
+        //   384 workgroups, 16 waves:        500 tokens 1.29 / 1.03 / 0.89, 2000 0.86 / 0.65 / 0.68 (1.30 / 0.99 / 1.00)
+        //   768 workgroups, four:            100 tokens 1.16 / 1.20 / 1.14, 500 0.96 / 0.93 / 0.87 (1.27 / 1.21 / 1.12)
+        //   8192 workgroups, four:           100 tokens 1.33 / 1.21 / 1.01, 500 0.83 / 0.72 / 0.62 (1.29 / 1.15 / 0.84)
+        const int64_t wgs = (int64_t)grid.x * grid.y * grid.z;
+        const bool bf16 = c.dtype == CS_BF16;
+        const bool narrow = hd == 4 || hd == 8;
+        const double seen = (narrow ? 8 : 1) * hd * ((double)len_ub + 0.5 * ((rg ? *std::max_element(rg->rows, rg->rows + B) : rows) + 1));
+        int lanes;                                       // threads of the kernel whose lanes share a row, 0: the other
+        if (wgs <= 256) lanes = seen >= (bf16 ? 12288. : 9216.) ? 1024 : 0;
+        else if (wgs <= 512) lanes = (bf16 ? hd == 256 && wgs >= 384 && seen >= 131072. : (hd >= 32 || narrow) && seen >= 49152.) ? 1024 : 0;
+        else if (wgs < 1024) lanes = (bf16 ? narrow && seen >= 32768. : seen >= (hd <= 32 ? 16384. : 32768.)) ? 256 : 0;
+        else lanes = (bf16 ? (hd >= 64 || narrow) && seen >= (hd == 64 ? 65536. : 32768.) : seen >= 12288.) ? 256 : 0;
         auto start = [&](auto* k, auto threads) {
             typedef std::remove_pointer_t<decltype(k)> WT;
             constexpr int THREADS = decltype(threads)::value;
-            k_attn_plain<WT, float, float, THREADS><<<grid, THREADS, 0, s>>>(
-                (const float*)m->q, (const WT*)kv->k + layer * per_layer, (const WT*)kv->v + layer * per_layer, kv->d_len,
-                rg ? rg->row : nullptr, rows, H, KVH, hd, kv->cap, (float*)m->xn);
+            const float* q = (const float*)m->q;
+            const WT* kc = (const WT*)kv->k + layer * per_layer;
+            const WT* vc = (const WT*)kv->v + layer * per_layer;
+            const int2* map = rg ? rg->row : nullptr;
+            if constexpr (THREADS > 0)
+                k_attn_plain_lanes<WT, float, float, THREADS><<<grid, THREADS, 0, s>>>(q, kc, vc, kv->d_len, map, rows, H, KVH, hd,
+                                                                                       kv->cap, (float*)m->xn);
+            else
+                k_attn_plain<WT, float, float><<<grid, PA_THREADS, 0, s>>>(q, kc, vc, kv->d_len, map, rows, H, KVH, hd, kv->cap,
+                                                                           (float*)m->xn);
         };
-        // up to two workgroups per compute unit: 16 waves each instead of four (44 workgroups 23 -> 12 us; 2044 workgroups
-        // of a prompt 43 -> 60 us)
-        const bool few = (int64_t)grid.x * grid.y * grid.z <= 512;
         auto by_type = [&](auto threads) {
-            if (c.dtype == CS_BF16) start((bf16_t*)nullptr, threads);
+            if (bf16) start((bf16_t*)nullptr, threads);
             else start((float*)nullptr, threads);
         };
-        if (few) by_type(std::integral_constant<int, 1024>{});
-        else by_type(std::integral_constant<int, 256>{});
+        if (lanes == 1024) by_type(std::integral_constant<int, 1024>{});
+        else if (lanes == 256) by_type(std::integral_constant<int, 256>{});
+        else by_type(std::integral_constant<int, 0>{});
         return cs_launch_ok("k_attn_plain");
     }
     const int G = H / KVH;

@@ -254,6 +254,32 @@ def test_plain_attention_with_many_workgroups(hd, heads, kv_heads):
     _ragged_verify(shape, (2046, 2047, 2049, 4100, 1, 0, 129) * 6, 6, (0, 1, 2, 3, 39, 40, 41), seed=4249, plain=True)
 
 
+EDGES = (2046, 2047, 2049, 4100, 1, 0, 129)
+
+
+@pytest.mark.parametrize("dtype,hd,heads,kv_heads,lens,k,kernel", [
+    ("bf16", 16, 6, 2, EDGES, 6, "k_attn_plain"), ("bf16", 64, 6, 2, EDGES, 6, "k_attn_plain"),
+    ("bf16", 256, 6, 3, EDGES, 6, "k_attn_plain"), ("f32", 16, 6, 2, EDGES, 6, "k_attn_plain"),
+    ("f32", 32, 16, 4, (100,), 16, "k_attn_plain"), ("bf16", 128, 16, 4, (700,), 32, "k_attn_plain"),
+    ("f32", 64, 4, 2, (100, 0, 33), 6, "k_attn_plain"), ("f32", 32, 8, 2, (40, 0, 3) * 10, 8, "k_attn_plain"),
+    ("f32", 64, 4, 2, (600, 0, 33), 6, "k_attn_plain_lanes"), ("f32", 64, 6, 2, EDGES, 6, "k_attn_plain_lanes"),
+    ("f32", 32, 8, 2, (1100, 0, 3) * 10, 8, "k_attn_plain_lanes")])
+def test_plain_attention_by_workgroups_and_context(kernels_of, dtype, hd, heads, kv_heads, lens, k, kernel):
+    """Which of the two plain attention kernels a block takes, over launches below and above one round of the chip,
+    contexts of less and more than a chunk, short and long: both against the oracle."""
+    shape = ModelShape(f"plain-hd{hd}", 1, 64, heads, kv_heads, hd, 96, 97, 10000.0, 1e-5, dtype)
+    _ragged_verify(shape, lens, k, range(min(len(lens), 7)), seed=4253, plain=True)
+    model = cs.Model(synth.model_weights(shape, 4253, threads=4), max_batch=len(lens), max_k=k, plain=True)
+    kv = cs.KV(model, len(lens), max(lens) + k + 8)
+    for b, n in enumerate(lens):
+        kv.set_len(b, n)
+    q = torch.zeros(len(lens), k + 1, heads, hd, device=DEV)
+    started = [n for n in kernels_of(lambda: cs.cs_op_attention(model, kv, 0, q)) if "k_attn" in n]
+    assert len(started) == 1 and ("k_attn_plain_lanes" in started[0]) == (kernel == "k_attn_plain_lanes"), started
+    kv.destroy()
+    model.destroy()
+
+
 @pytest.mark.parametrize("shape", [MINI64, SMALLF32])
 def test_logits_into_an_unaligned_buffer(shape):
     """The logits of a verify call whose output buffer is only 4-byte aligned equal those of an aligned one."""
