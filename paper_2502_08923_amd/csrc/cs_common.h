@@ -200,7 +200,7 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
                    int mode, int allow_split, int* nparts_out, hipStream_t s);
 int cs_gemm_plain_launch(int dtype, const float* X, const void* W, float* Y, int R, int N, int K,
                          hipStream_t s);
-// Blocks of few rows (cs_gemm_few_rows: up to 16 with the tuned kernels, 32 with the float32 one) need no norm kernel of
+// Blocks of few rows (cs_gemm_few_rows: at most 16 with the tuned kernels, 32 with the float32 one) need no norm kernel of
 // their own: cs_gemm_residual_launch adds X * W^T (tuned kernels: X in fragment order, see cs_xt_index) to the
 // residual stream m->x and leaves nss pieces of every row's sum of squares in m->ss, and cs_gemm_norm_launch is
 // Y = rmsnorm(m->x) * W^T from those (modes and partial tiles as in cs_gemm_launch; SwiGLU into m->act).

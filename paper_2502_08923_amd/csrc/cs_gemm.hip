@@ -1244,8 +1244,23 @@ __global__ __launch_bounds__(64 * GR_WAVES) void k_gemm_residual(const f16_t* __
     if (g == 0) ss[blockIdx.x * 16 + lrow] = q;
 }
 
-// Blocks that take the normalising projections and the ones that write the residual stream (float32 kernel: one row block).
-bool cs_gemm_few_rows(const cs_model* m, int R) { return R <= (m->fast ? 16 : 32); }
+// Blocks that take the normalising projections and the ones that write the residual stream: up to 16 rows (float32 kernel
+// 32, one row block), while that is the faster way.  Tuned kernels: a residual workgroup per 16 columns is one round of
+// the chip up to d_model 4096; with more they read W at 4.2 TB/s where the K split reads it at 5.1, so that a large down
+// projection costs what the norm kernels did, sooner with more than 8 rows of X.  A layer at 1 / 8 / 11 / 16 rows, against the
+// same with norm kernels (d_model / d_ff): 4096 / 14336 -8, -9, -6, -7 us, 4096 / 38400 -11, -13, -7, -9, 5120 / 13824 -8, -8, -3,
+// -4, 5120 / 27648 -5, -4, +5, +4, 6144 / 16384 -2, -3, +5, +4, 7168 / 20480 -4, -5, +6, +5, 6144 / 24576 +5, +4, +14, +12,
+// 8192 / 28672 +11, +9, +14, +14.  Float32 kernel with bfloat16 weights (3 layers, 1 / 16 / 32 rows): 1024 / 4096 216, 239, 331
+// against 223, 250, 345 us, 3072 / 8192 478, 516, 774 against 479, 541, 766, 4096 / 11008 779, 830, 1154 against 724, 797, 1103;
+// with float32 weights it is ahead or within 5 % at all widths (3072 / 8192 418, 464, 640 against 423, 508, 708).
+bool cs_gemm_few_rows(const cs_model* m, int R) {
+    const int64_t d = m->cfg.d_model, down = d * m->cfg.d_ff;
+    if (!m->fast) {
+        if (m->cfg.dtype == CS_BF16 && d > 1024) return d <= 3072 && R <= 16;
+        return R <= 32;
+    }
+    return R <= 16 && (d <= 4096 || (d <= 7168 && down <= (R <= 8 ? 150000000 : 100000000)));
+}
 
 int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const void* W, float* Y, int R, int N, int K, int mode,
                         int* nparts_out, hipStream_t s) {

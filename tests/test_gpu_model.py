@@ -227,6 +227,30 @@ def test_blocks_around_sixteen_rows(shape, streams, k):
     _ragged_verify(shape, (150,) + (9,) * (streams - 1), k, (0, streams - 1), seed=4251)
 
 
+@pytest.mark.parametrize("d,d_ff,dtype,plain,rows,few", [
+    (4096, 14336, "bf16", False, 16, True), (4096, 14336, "bf16", False, 17, False), (5120, 27648, "bf16", False, 8, True),
+    (5120, 27648, "bf16", False, 9, False), (6144, 24576, "bf16", False, 1, False), (8192, 28672, "bf16", False, 11, False),
+    (1024, 2816, "bf16", True, 32, True), (2048, 5632, "bf16", True, 16, True), (2048, 5632, "bf16", True, 17, False),
+    (4096, 11008, "bf16", True, 1, False), (4096, 11008, "f32", False, 32, True), (4096, 11008, "f32", False, 33, False)])
+def test_widths_that_take_the_few_row_kernels(kernels_of, d, d_ff, dtype, plain, rows, few):
+    """Few rows go without norm kernels where that is the faster way: not through the down projections of wide models."""
+    shape = ModelShape("width", 1, d, d // 128, d // 1024 or 1, 128, d_ff, 512, 10000.0, 1e-5, dtype)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    z = lambda *size: torch.zeros(size, dtype=dt, device=DEV)          # noqa: E731
+    gain, kv_rows = torch.ones(d, device=DEV), shape.n_kv_heads * 128
+    layer = {"wq": z(d, d), "wk": z(kv_rows, d), "wv": z(kv_rows, d), "wo": z(d, d), "wg": z(d_ff, d), "wu": z(d_ff, d),
+             "wd": z(d, d_ff), "norm1": gain, "norm2": gain}
+    head = {"embed": z(512, d), "lm_head": z(512, d), "final_norm": gain}
+    model = cs.Model({"shape": shape, "head": lambda: head, "layers": lambda _: layer}, max_batch=1, max_k=rows, plain=plain)
+    kv = cs.KV(model, 1, 64)
+    tok = torch.zeros(1, dtype=torch.int32, device=DEV)
+    draft = torch.zeros(1, rows - 1, dtype=torch.int32, device=DEV)
+    names = kernels_of(lambda: cs.cs_verify(model, kv, tok, draft, tok, rows - 1))
+    assert sum("k_addnorm" in n for n in names) == (1 if few else 3), names
+    kv.destroy()
+    model.destroy()
+
+
 ODDF32 = ModelShape("odd-f32", 2, 68, 3, 1, 16, 48, 97, 10000.0, 1e-5, "f32")
 
 
