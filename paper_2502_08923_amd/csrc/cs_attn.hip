@@ -1617,7 +1617,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
         const double seen = (narrow ? 8 : 1) * hd * ((double)len_ub + 0.5 * ((rg ? *std::max_element(rg->rows, rg->rows + B) : rows) + 1));
         int lanes;                                       // threads of the kernel whose lanes share a row, 0: the other
         if (wgs <= 256) lanes = seen >= (bf16 ? 12288. : 9216.) ? 1024 : 0;
-        else if (wgs <= 512) lanes = (bf16 ? hd == 256 && wgs >= 384 && seen >= 131072. : (hd >= 32 || narrow) && seen >= 49152.) ? 1024 : 0;
+        else if (wgs <= 512) lanes = (bf16 ? hd == 256 && wgs >= 384 && seen >= 131072. : (hd >= 32 || narrow) && seen >= 30720.) ? 1024 : 0;
         else if (wgs < 1024) lanes = (bf16 ? narrow && seen >= 32768. : seen >= (hd <= 32 ? 16384. : 32768.)) ? 256 : 0;
         else lanes = (bf16 ? (hd >= 64 || narrow) && seen >= (hd == 64 ? 65536. : 32768.) : seen >= 12288.) ? 256 : 0;
         auto start = [&](auto* k, auto threads) {
