@@ -217,11 +217,25 @@ __global__ __launch_bounds__(THREADS) void k_scan_short(const int32_t* __restric
 // chunk).  Fewer slots are always correct (the workgroups then walk several chunks each).
 int cs_scan_slots(int64_t max_len) { return (int)cs_ceil_div(max_len > 0 ? max_len : 1, SCAN_CHUNK); }
 
-// One launch where a workgroup per stream does as well as one per chunk and a second kernel: one chunk (4.6 -> 2.9 us on the
-// GPU; a call from Python 16.4 -> 10.9 us, 2 us of them the stream handle), or up to eight for at most two workgroups of
-// 1024 threads per compute unit (32768 tokens of 1, 64, 256 streams: 5.2, 5.9, 8.4 -> 4.7, 5.2, 6.0 us; 8192 of 1024
-// streams: 8.3 -> 15.2).
+// One launch where a workgroup per stream does as well as one per chunk and a second kernel.  One chunk: 4.6 -> 2.9 us on
+// the GPU, a call from Python 16.4 -> 10.9 us (2 us of them the stream handle); or up to eight for at most 512 histories.
+// Both launches against this one, every call on cold histories of its own:
+//   uniform tokens, rightmost          1 / 64 / 256 streams of 32768: 7.2, 9.1, 15.2 -> 7.0, 8.2, 13.8 us, one of 8192: 7.3 -> 4.9
+//   Zipf ranks of 1024 tokens, context 1 / 64 / 256 of 32768: 7.4, 10.3, 16.8 -> 8.8, 12.2, 18.2, of 16384: 6.9, 9.2, 12.5 -> 6.3,
+//                                      7.9, 11.0
+// A step of eight streams of 18432 tokens, from the kernel before the scan to the one after it: 21.0 -> 19.0 us.
 bool cs_scan_needs_keys(int B, int nslots) { return nslots > 1 && (nslots > 8 || B > 512); }
+
+// Threads of that launch.  One wave covers 1024 tokens (65000 histories of 512: 104 us in two launches, 102 with four waves, 31
+// with one).  Beyond a chunk a workgroup of 1024 threads fills a compute unit (74 registers each), of 512 threads two or
+// three fit: more than 256 histories take those (288 / 512 of 8192 tokens: 8.9, 10.6 us in two launches, 10.0, 11.5 with 1024
+// threads, 6.9, 8.5 with 512), but for the many serial measurements of the context policy in long ones (512 of 24576 / 32768
+// Zipf ranks: 24.7, 30.3 us with 1024, 23.4, 32.4 with 512).
+static int scan_short_threads(int B, int64_t stride, int nslots, int policy) {
+    if (stride <= 1024) return 64;
+    if (nslots == 1) return SCAN_THREADS;
+    return B > 256 && !(policy == CS_POLICY_CONTEXT && nslots > 6) ? 512 : 1024;
+}
 
 // keys: device scratch of B * nslots int64 (every slot is written by k_scan before k_gather reads
 // it, so it needs no clearing), not used unless cs_scan_needs_keys.  The caller says where it lives: a cache handle's
@@ -245,9 +259,10 @@ int cs_scan_launch(const int32_t* d_hist, int64_t stride, const int32_t* d_len, 
             else start(std::integral_constant<int, CS_POLICY_CONTEXT>{}, threads_tag);
         };
         const int ps = cs_prof_begin(CS_PROF_SCAN, s);
-        // (one wave covers 1024 tokens: 65000 histories of 512, 104 us before, 102 with four waves, 31 with one)
-        if (stride <= 1024) by_policy(std::integral_constant<int, 64>{});
-        else if (nslots == 1) by_policy(std::integral_constant<int, SCAN_THREADS>{});
+        const int threads = scan_short_threads(B, stride, nslots, policy);
+        if (threads == 64) by_policy(std::integral_constant<int, 64>{});
+        else if (threads == SCAN_THREADS) by_policy(std::integral_constant<int, SCAN_THREADS>{});
+        else if (threads == 512) by_policy(std::integral_constant<int, 512>{});
         else by_policy(std::integral_constant<int, 1024>{});
         cs_prof_end(ps, s);
         return cs_launch_ok("k_scan_short");

@@ -102,6 +102,21 @@ def test_many_short_histories(streams):
     _check_batch([rng.integers(0, 9, n).astype(np.int32) for n in rng.integers(1, 4200, streams)], 3, 4, "rightmost", stride=4200)
 
 
+@pytest.mark.parametrize("streams,n,policy,threads", [
+    (256, 4100, "rightmost", 1024), (257, 4100, "rightmost", 512), (300, 8193, "first", 512), (512, 12290, "context", 512),
+    (260, 24577, "context", 1024), (260, 24577, "rightmost", 512)])
+def test_workgroups_of_several_chunks(kernels_of, streams, n, policy, threads):
+    """Histories of several chunks in one launch: a round of the chip takes workgroups of 1024 threads, more histories
+    those of 512, which fit a compute unit twice; lengths around the strides, few different tokens."""
+    rng = np.random.default_rng(streams + n)
+    hs = [rng.integers(0, 40, n - (b * 37) % 300).astype(np.int32) for b in range(streams)]
+    stride = (n + 3) // 4 * 4
+    _check_batch(hs, 4, 10, policy, stride=stride)
+    d_hist, d_len = _batch(hs, stride)
+    names = kernels_of(lambda: cs.cs_find_match_batch_dev(d_hist, d_len, 4, 10, policy))
+    assert len(names) == 1 and f"ELi{threads}E" in names[0], names
+
+
 def test_degenerate_histories():
     same = np.full(9000, 5, dtype=np.int32)
     period = np.tile(np.array([1, 2, 3], dtype=np.int32), 3000)
