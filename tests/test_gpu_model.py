@@ -936,8 +936,8 @@ def test_decode_batch_equals_single_stream_decodes_and_oracle():
 
 
 def test_prefill_batch_and_decode_batch_bf16():
-    """Lock-step prompt ingestion of four ragged streams (the longest needs three passes) leaves
-    the oracle's cache rows; the batched decode follows the oracle under the margin rule."""
+    """Batched ingestion of four ragged prompts (one pass over the rows of all) leaves the oracle's
+    cache rows; the batched decode follows the oracle under the margin rule."""
     shape = MINI128
     B, k, new = 4, 10, 32
     w = synth.model_weights(shape, 8128, threads=4)
@@ -995,6 +995,38 @@ def test_prefill_batch_passes_across_prompts(shape, plain, block_rows):
                     _cache_rows_close(k_rows[:, :n - 1], okv.k[layer, :, :n - 1], tol)
                     _cache_rows_close(v_rows[:, :n - 1], okv.v[layer, :, :n - 1], tol)
                 assert not k_rows[:, n - 1:].any() and not v_rows[:, n - 1:].any()
+    kv.destroy()
+    model.destroy()
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_prefill_batch_in_large_tiles(hd):
+    """Two passes of 1824 and 1812 rows of four ragged prompts, each more than three 64-row tiles per compute unit, so that
+    the attention takes 256-row tiles by every stream's own first row and count, the second pass over the rows of the
+    first: cache rows of two layers and the logits of every prompt's next token."""
+    shape = ModelShape(f"large-tiles-{hd}", 2, 256, 32, 8, hd, 256, 512, 10000.0, 1e-5, "bf16")
+    lens, block_rows = [1500, 40, 900, 1200], 2000
+    assert shape.n_kv_heads * (shape.n_heads // shape.n_kv_heads) * 1812 // 64 > 768
+    w = synth.model_weights(shape, 8132, threads=4)
+    model = cs.Model(w, max_batch=len(lens), max_k=1, prompt_block_rows=block_rows)
+    prompts = _ragged_prompts(shape.vocab, lens, 5203)
+    kv = cs.KV(model, len(lens), max(lens) + 1)
+    cs.cs_prefill_batch(model, kv, prompts)
+    caches = []
+    for b, n in enumerate(lens):
+        assert kv.len(b) == n - 1
+        okv = orc.KVCache(shape, n + 1)
+        orc.prefill(w, okv, prompts[b], chunk=256)
+        for layer in range(shape.n_layers):
+            k_rows, v_rows = kv.read(layer, b, 0, n - 1)
+            _cache_rows_close(k_rows, okv.k[layer, :, :n - 1], 2e-2)
+            _cache_rows_close(v_rows, okv.v[layer, :, :n - 1], 2e-2)
+        caches.append(okv)
+    none = torch.zeros(len(lens), dtype=torch.int32, device=DEV)
+    _, _, logits = cs.cs_verify(model, kv, t32([p[-1] for p in prompts]), None, none, 0, want_logits=True)
+    for b, okv in enumerate(caches):
+        _, _, ologits = orc.verify(w, okv, prompts[b][-1], [])
+        assert np.abs(logits[b].cpu().numpy() - ologits).max() <= tol_for(shape), b
     kv.destroy()
     model.destroy()
 

@@ -321,22 +321,6 @@ def test_attention_prompt_block(k_ramp):
     assert worst < 1e-2, worst
 
 
-@pytest.mark.parametrize("H,KVH,hd,lens,rows,k_ramp", [
-    (28, 4, 128, [0], 7, None), (28, 4, 128, [0, 700], 65, (0.05, 6.0)), (28, 4, 128, [300, 0, 17], 257, None),
-    (8, 8, 64, [0, 33, 400], 49, None), (8, 8, 64, [31, 600], 257, (6.0, 0.05)), (64, 8, 128, [250, 0], 17, None),
-    (6, 2, 64, [100, 0, 3, 64], 128, None), (6, 2, 64, [0] * 30, 256, None), (28, 4, 128, [0, 1] * 5, 257, None)])
-def test_attention_unsplit_short_contexts(H, KVH, hd, lens, rows, k_ramp):
-    """Wide blocks over short contexts, which the prompt kernel takes without splitting the tokens: 64-row tiles (most)
-    and 256-row tiles (the last two), one, three, seven and eight query heads per KV head, 2 to 60 (stream, KV head)
-    pairs, ragged last tiles, poisoned rows past the block."""
-    shape = ModelShape("brief", 1, 256, H, KVH, hd, 256, 512, 10000.0, 1e-5, "bf16")
-    m = cs.Model(synth.model_weights(shape, 97, threads=8), max_batch=len(lens), max_k=256)
-    sample = [(b, h) for b in sorted({0, len(lens) // 2, len(lens) - 1}) for h in (0, H // 2, H - 1)]
-    worst = _attention_case(m, shape, lens, rows, sample, seed=80 + rows, poison=True, k_ramp=k_ramp)
-    m.destroy()
-    assert worst < 1e-2, worst
-
-
 def _attention_kernels(kernels_of, m, shape, lens, rows):
     """The attention kernels of a block behind caches of these lengths."""
     kv = cs.KV(m, len(lens), max(lens) + rows)
@@ -348,10 +332,47 @@ def _attention_kernels(kernels_of, m, shape, lens, rows):
     return [n for n in names if "k_attn" in n]
 
 
+def _prompt_tile(hd, rows):
+    """What the name of the prompt kernel with tiles of this many query rows has in it."""
+    return f"k_attn_prefillILi{hd}ELi{1 if rows == 64 else 2}ELi{4 if rows == 64 else 8}E"
+
+
+@pytest.mark.parametrize("H,KVH,hd,lens,rows,k_ramp,tile", [
+    (28, 4, 128, [0], 7, None, 64), (28, 4, 128, [0, 600], 65, (0.05, 6.0), 64), (28, 4, 128, [300, 0, 17], 257, None, 64),
+    (8, 8, 64, [0, 33, 400], 49, None, 64), (8, 8, 64, [31, 500], 257, (6.0, 0.05), 64), (64, 8, 128, [250, 0], 17, None, 64),
+    (6, 2, 64, [100, 0, 3, 64], 128, None, 64), (6, 2, 64, [0] * 34, 256, None, 256), (28, 4, 128, [0, 1] * 5, 257, None, 256)])
+def test_attention_unsplit_short_contexts(kernels_of, H, KVH, hd, lens, rows, k_ramp, tile):
+    """Wide blocks over short contexts, which the prompt kernel takes without splitting the tokens: 64-row tiles (most)
+    and 256-row tiles (the last two), one, three, seven and eight query heads per KV head, 4 to 68 (stream, KV head)
+    pairs, ragged last tiles, poisoned rows past the block."""
+    shape = ModelShape("brief", 1, 256, H, KVH, hd, 256, 512, 10000.0, 1e-5, "bf16")
+    m = cs.Model(synth.model_weights(shape, 97, threads=8), max_batch=len(lens), max_k=256)
+    sample = [(b, h) for b in sorted({0, len(lens) // 2, len(lens) - 1}) for h in (0, H // 2, H - 1)]
+    worst = _attention_case(m, shape, lens, rows, sample, seed=80 + rows, poison=True, k_ramp=k_ramp)
+    assert _prompt_tile(hd, tile) in _attention_kernels(kernels_of, m, shape, lens, rows)[0]
+    m.destroy()
+    assert worst < 1e-2, worst
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("k_ramp", [None, (0.05, 6.0), (6.0, 0.05)])
+def test_attention_prompt_block_in_large_tiles(kernels_of, hd, k_ramp):
+    """The 256-row tiles of eight waves that large prompts take, over empty, short and long ragged caches, growing and
+    shrinking keys, rows past the block poisoned: 640 tiles of 64 rows would be more than two per compute unit."""
+    shape = ModelShape("large-tiles", 1, 256, 32, 8, hd, 256, 512, 10000.0, 1e-5, "bf16")
+    lens = [0, 700, 2049, 33, 4097]
+    m = cs.Model(synth.model_weights(shape, 95, threads=8), max_batch=5, max_k=255)
+    sample = [(0, 0), (0, 31), (1, 13), (2, 5), (3, 22), (4, 9), (4, 30)]
+    worst = _attention_case(m, shape, lens, 256, sample, seed=22, poison=True, k_ramp=k_ramp)
+    assert _prompt_tile(hd, 256) in _attention_kernels(kernels_of, m, shape, lens, 256)[0]
+    m.destroy()
+    assert worst < 1e-2, worst
+
+
 @pytest.mark.parametrize("H,KVH,hd,lens,rows,kernel", [
     (28, 4, 128, [6000, 5999, 3000, 1], 80, "k_attn_lds"), (40, 8, 128, [3000, 2999], 128, "k_attn_lds"),
     (32, 8, 64, [700], 16, "k_attn_lds"), (32, 8, 128, [3000, 700], 128, "k_attn_lds"),
-    (32, 8, 64, [400], 16, "k_attn_prefillILi64ELi1ELi4E"), (28, 4, 128, [500, 0, 499, 3], 80, "k_attn_prefillILi128ELi1ELi4E")])
+    (32, 8, 64, [400], 16, _prompt_tile(64, 64)), (28, 4, 128, [500, 0, 499, 3], 80, _prompt_tile(128, 64))])
 def test_attention_long_contexts_are_split_over_the_tokens(kernels_of, H, KVH, hd, lens, rows, kernel):
     """Wide blocks of few tiles behind a long context go to the kernel that splits the tokens, whatever the head group;
     behind a short one they do not."""
