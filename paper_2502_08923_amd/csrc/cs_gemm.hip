@@ -977,8 +977,9 @@ static int launch_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
     if (waves == 5) start_mfma<MT, NT, 5>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
-    else if (waves == 2) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
-    else start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
+    else if (waves == 4) start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
+    else if constexpr (NT <= 6) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);   // (see mfma_plan)
+    else CS_REQUIRE(false, CS_E_STATE, "two consumer waves take at most six row tiles");
     cs_prof_end(pg, s);
     return cs_launch_ok("k_gemm_mfma");
 }
