@@ -147,10 +147,14 @@ def _check(rc: int):
         raise CopySpecError(int(rc), load_library().cs_last_error().decode())
 
 
+# The handle of the current stream without a Stream object, which costs 2 us more per call; not a public name of torch,
+# so it may be missing.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int:
     if stream is None:
-        # the raw handle: a Stream object for every call costs 2 us more
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _raw_stream(torch.cuda.current_device()) if _raw_stream else torch.cuda.current_stream().cuda_stream
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 

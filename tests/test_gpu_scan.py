@@ -154,6 +154,16 @@ def test_empty_batch_and_bad_arguments():
         cs.cs_find_match_ex([1, 2, 3], 3, 10, policy=7)
 
 
+def test_current_stream_without_the_raw_handle(monkeypatch):
+    """The stream that a call goes to is the current one, also where torch has no accessor for its raw handle."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert cs._stream(None) == side.cuda_stream
+        monkeypatch.setattr(cs, "_raw_stream", None)
+        assert cs._stream(None) == side.cuda_stream
+    assert cs._stream(None) == torch.cuda.current_stream().cuda_stream != side.cuda_stream
+
+
 def test_deterministic_repeat():
     hs = [synth.history_cfg2(s)["tokens"] for s in range(8)]
     d_hist, d_len = _batch(hs, 32768)
