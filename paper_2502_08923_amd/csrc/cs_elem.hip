@@ -351,8 +351,9 @@ __global__ __launch_bounds__(AM_THREADS) void k_argmax_partial(const float* __re
 // (a stream whose emission budget `room` is used up is skipped, see below)
 // next = a_tau; the KV length grows by tau+1 (App. B.2: truncation past the accepted rows);
 // the accepted drafts and the free token are appended to the history (App. B.3 step 2d).
-// The 16 waves share the rows (11 rows of 1002 pairs: 14.4 us with four waves, 9.3 with 16); a wave reduces the nch partial pairs of a row (up to one per
-// 128 vocabulary entries when the lm_head produced them itself) with four loads in flight per lane.
+// The 16 waves share the rows (11 rows of 1002 pairs: 14.4 us with four waves, 9.3 with 16); a wave reduces the nch partial
+// pairs of a row (up to one per 64 vocabulary entries when the lm_head produced them itself) with four loads in flight
+// per lane.
 #define ACC_THREADS 1024
 __global__ __launch_bounds__(ACC_THREADS) void k_accept(const int32_t* __restrict__ part, int nch, int k,
                                                         const int32_t* __restrict__ draft,
