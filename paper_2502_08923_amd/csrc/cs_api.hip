@@ -672,7 +672,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int r
         if (few) {
             CS_TRY(cs_gemm_norm_launch(m, L.norm1, nss, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, &np, s));
         } else {
-            CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, nqkv, true, s));
+            CS_TRY(cs_addnorm_launch(m, m->part, np_prev, L.norm1, m->xn, R, s));
             CS_TRY(cs_gemm_launch(m, m->xn, L.wqkv, m->part, R, nqkv, d, CS_GEMM_STORE, 1, &np, s));
         }
         if (fuse_rope) {
@@ -688,7 +688,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int r
             continue;
         }
         CS_TRY(cs_gemm_launch(m, m->xn, L.wo, m->part, R, d, nq, CS_GEMM_STORE, 1, &np, s));
-        CS_TRY(cs_addnorm_launch(m, m->part, np, L.norm2, m->xn, R, 2 * c.d_ff, false, s));
+        CS_TRY(cs_addnorm_launch(m, m->part, np, L.norm2, m->xn, R, s));
         if (m->fast) {
             CS_TRY(cs_gemm_launch(m, m->xn, L.wgu, nullptr, R, 2 * c.d_ff, d, CS_GEMM_SWIGLU, 0,
                                   nullptr, s));
@@ -699,7 +699,7 @@ static int forward_layers(cs_model* m, cs_kv* kv, const cs_block_src& src, int r
         CS_TRY(cs_gemm_launch(m, m->act, L.wd, m->part, R, d, c.d_ff, CS_GEMM_STORE, 1, &np_prev, s));
     }
     // the final norm feeds the lm_head (callers that only fill the cache never read it)
-    return cs_addnorm_launch(m, m->part, np_prev, m->final_norm, m->xn, R, c.vocab, false, s);
+    return cs_addnorm_launch(m, m->part, np_prev, m->final_norm, m->xn, R, s);
 }
 
 // the block tokens are in m->tok
@@ -1250,19 +1250,15 @@ extern "C" int cs_op_gemm(cs_model* m, int32_t dtype, const void* X, const void*
     if (dtype == CS_F32) return cs_gemm_plain_launch(CS_F32, (const float*)X, W, Y, R, N, K, s);
     CS_REQUIRE(dtype == CS_BF16, CS_E_ARG, "cs_op_gemm: bad dtype");
     CS_REQUIRE(m->fast, CS_E_STATE, "cs_op_gemm(bf16) needs a model that runs the bf16 kernels");
-    // the tuned kernel reads W in its tiled fp16 layout and X as fp16: convert into temporaries
+    // the tuned kernels read W and X as fp16 in their tiled layouts: convert into temporaries
     void* wt = nullptr;
     const size_t x_bytes = cs_xt_bytes(R, K);
     CS_HIP(hipMalloc(&wt, (size_t)N * K * 2 + 2 * x_bytes));
     void* xt = (char*)wt + (size_t)N * K * 2;
     int rc = cs_tile_weights_launch(W, nullptr, N, K, 0, N, 0, wt, nullptr, s);
     if (rc == CS_OK) rc = cs_convert_launch(X, CS_T_BF16, xt, CS_T_F16, (int64_t)R * K, s);
-    X = xt;
-    if (rc == CS_OK && cs_gemm_x_tiled(R, N, K, (size_t)R * N <= m->part_floats)) {   // the many-row kernel reads fragment order
-        void* xt2 = (char*)xt + x_bytes;
-        rc = cs_tile_x_launch(xt, xt2, R, K, s);
-        X = xt2;
-    }
+    X = (char*)xt + x_bytes;
+    if (rc == CS_OK) rc = cs_tile_x_launch(xt, (char*)xt + x_bytes, R, K, s);
     int np = 1;
     if (rc == CS_OK) {
         if ((size_t)R * N > m->part_floats) {   // too large for the workspace: no K split

@@ -267,7 +267,6 @@ __device__ __forceinline__ float fa_row4_max(float x) {
 static_assert(FA_QROWS == CS_ATTN_GROUP, "the host counts query groups in these rows");
 #define FA_RESCALE_LOG2 8.0f
 #define FA_OPAD 4          // LDS row padding (floats) of the in-workgroup merge buffers
-#define FA_BUFFER_WORD3 0x00027000   // buffer resource word 3: raw 32-bit data, range checked in bytes
 
 // attention output element: float16 outputs feed the output projection and are saturated
 __device__ __forceinline__ void fa_store_out(f16_t* p, int64_t i, float v, bool& hit) { p[i] = cs_f16_sat(v, hit); }
@@ -369,10 +368,10 @@ __global__ __launch_bounds__(256) void k_attn_mfma(const bf16_t* __restrict__ q,
     const int v_blocks = max(1, (n_range + CS_VBLK - 1) / CS_VBLK);
     static_assert((MT - 1) * 16 * CS_VBLK < HD * CS_VBLK, "scalar offsets of a V block stay inside it");
     const auto krsrc = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)((FUSE ? fr.kc_w : kc) + (head0 * cap + w_begin) * HD), 0, n_range * HD * 2, FA_BUFFER_WORD3);
+        (void*)((FUSE ? fr.kc_w : kc) + (head0 * cap + w_begin) * HD), 0, n_range * HD * 2, CS_BUFFER_WORD3);
     const auto vrsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)((FUSE ? fr.vc_w : vc) + head0 * HD * cap + cs_v_index(w_begin, 0, HD)), 0,
-        v_blocks * CS_VBLK * HD * 2, FA_BUFFER_WORD3);
+        v_blocks * CS_VBLK * HD * 2, CS_BUFFER_WORD3);
     constexpr unsigned NOWHERE = 0x80000000u;
     // K tile a, MFMA row m=c  <->  token t0 + 8*(c/4) + 4a + c%4
     const unsigned klane = ((8 * (c >> 2) + (c & 3)) * HD + g * 8) * 2;
@@ -1526,7 +1525,7 @@ __global__ __launch_bounds__(FA_MERGE_THREADS) void k_attn_merge(const float* __
     }
     const float inv = 1.0f / den;
     const int r = row0 + i;
-    // tiled: the output projection runs the many-row GEMM, which reads fragment order
+    // tiled: the output projection reads fragment order
     const int col = (kvh * G + gq) * HD + d;
     const int64_t off = tiled ? cs_xt_index(r, col, H * HD) : (int64_t)r * H * HD + col;
     bool hit = false;
@@ -1649,10 +1648,7 @@ int cs_attention_launch(const cs_model* m, cs_kv* kv, int layer, int rows, int64
     const int QR = G * widest;
     const int nqg = (int)cs_ceil_div(QR, FA_QROWS);
     const int64_t n_tok_ub = len_ub + widest;
-    // layout of the merged output: fragment order if the output projection (d_model outputs)
-    // of these rows runs the many-row GEMM or the one for few rows
-    const int R = rg ? rg->R : B * rows;
-    const int tiled = for_o_proj && (cs_gemm_few_rows(m, R) || cs_gemm_x_tiled(R, c.d_model, H * hd, true)) ? 1 : 0;
+    const int tiled = for_o_proj ? 1 : 0;      // the output projection reads fragment order
     const bf16_t* kc = (const bf16_t*)kv->k + layer * per_layer;
     const bf16_t* vc = (const bf16_t*)kv->v + layer * per_layer;
     CS_REQUIRE(!qkv_part || nqg == 1, CS_E_STATE, "fused rotary embedding needs a narrow block");

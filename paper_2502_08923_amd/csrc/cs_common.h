@@ -170,10 +170,9 @@ struct cs_ragged {
 int cs_block_start_launch(const cs_model* m, const cs_block_src& src, const int32_t* kv_len, int B, int rows,
                           const cs_ragged* rg, hipStream_t s);
 // x[r] += sum of nparts partial tiles (part[p][r][:]) and, if xn_out, xn_out[r] = rmsnorm(x[r])*gain
-// (next_N, next_split: output width of the GEMM that reads xn_out and whether it may split K; they decide
-// the layout of xn_out)
+// (float16 xn_out: in fragment order, see cs_xt_index)
 int cs_addnorm_launch(const cs_model* m, const float* part, int nparts,
-                      const float* gain, void* xn_out, int R, int next_N, bool next_split, hipStream_t s);
+                      const float* gain, void* xn_out, int R, hipStream_t s);
 int cs_rope_append_launch(const cs_model* m, cs_kv* kv, int layer, const float* qkv, int nparts,
                           int rows, const cs_ragged* rg, hipStream_t s);
 int cs_swiglu_launch(const cs_model* m, int R, hipStream_t s);
@@ -209,14 +208,12 @@ int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const voi
                         int* nparts_out, hipStream_t s);
 int cs_gemm_residual_launch(const cs_model* m, const void* X, const void* W, int R, int N, int K, int* nss, hipStream_t s);
 
-// The many-row GEMM kernel reads its activations in MFMA fragment order as well:
+// The tuned GEMM kernels read their activations in MFMA fragment order as well:
 // X_t[r/16][k/32][lane = r%16 + 16*((k%32)/8)][k%8] (K = row length, row tiles padded to 16
 // rows), so that one direct-to-LDS request is 1 KB of contiguous memory, like a request for W.
-// cs_gemm_x_tiled says whether the GEMM of R rows by N outputs over K inputs, with or without leave to
-// split K (as in cs_gemm_launch), runs that kernel; the producer
-// of its X (norm, attention merge, SwiGLU epilogue) then writes this layout.  Four consecutive
-// k (k % 4 == 0) stay contiguous.
-bool cs_gemm_x_tiled(int R, int N, int K, bool may_split);
+// Whoever produces an X (norm, attention, SwiGLU epilogue) writes this layout.  Four consecutive
+// k (k % 4 == 0) stay contiguous.  Rows of 16-row tiles also spread a K chunk over all channels of the L2: with
+// row-major X and a power-of-two K the rows of a chunk met in one or two of them (see k_gemm_mfma).
 __host__ __device__ __forceinline__ int64_t cs_xt_index(int r, int k, int K) {
     return ((int64_t)(r >> 4) * (K >> 5) + (k >> 5)) * 512 + (((r & 15) + 16 * ((k & 31) >> 3)) << 3) + (k & 7);
 }
@@ -257,14 +254,23 @@ int cs_convert_launch(const void* src, int src_type, void* dst, int dst_type, in
 int cs_fill_i32_launch(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 
 // ---- device helpers -----------------------------------------------------------------
+// A buffer of `bytes` bytes at a uniform address.  A load at an offset outside it returns zeros and costs no memory
+// traffic, and unlike a branch around the load it leaves the compiler's load counts exact.
+#define CS_BUFFER_WORD3 0x00027000      // buffer resource word 3: raw 32-bit data, range checked in bytes
+#define CS_BUFFER_OUT 0xfffffff0u       // an offset outside every buffer of less than 4 GiB
+__device__ __forceinline__ auto cs_rsrc(const void* p, unsigned bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, CS_BUFFER_WORD3);
+}
+
 // request 16 bytes per lane from (uniform base + per-lane byte offset) into LDS at lds_addr + 16*lane.
 // M0 carries the LDS address.  The compiler reserves M0 and only ever sets it immediately before
 // an instruction of its own that reads it, so overwriting it here is safe; it still warns about
-// any reserved register in a clobber list, which is silenced for this one statement.
+// any reserved register in a clobber list, which is silenced for this one statement.  (One wait state has to lie
+// between a write of M0 and a load that takes its LDS address from it.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void cs_load_to_lds(unsigned voff, const void* sbase, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr) : "m0");
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr) : "m0");
 }
 #pragma clang diagnostic pop
 

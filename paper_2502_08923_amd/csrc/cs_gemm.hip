@@ -5,7 +5,7 @@
 // HBM once.  The tuned kernel therefore treats W as the operand that must never be
 // re-read: each consumer wave loads its W tiles straight from global memory into MFMA
 // A-operand registers (W is pre-tiled so that a wave load is 1 KB contiguous), while the
-// small X block is staged through LDS by producer waves and shared by the consumers.
+// small X block (in the same order) is brought into LDS by producer waves and shared by the consumers.
 // Operands are float16 (weights converted exactly from bfloat16 when the model is created,
 // activations rounded to float16 by their producers); v_mfma_f32_16x16x32_f16 accumulates
 // in float32.  Small-N projections are split along K across workgroups; the float32 partial
@@ -231,35 +231,53 @@ static int launch_plain(int dtype, const float* X, const void* W, float* Y, int 
 // -------------------------------------------------------------------------------------
 #define GEMM_KC 128                       // K elements per pipeline stage
 #define GEMM_LDS_ROW (GEMM_KC * 2 + 16)   // bytes per X row in LDS (padded)
+#define GEMM_STAGES 4                     // X chunks in LDS
 #define GEMM_RING_TILES 8                 // W tile-chunks (4 KB each) in flight per consumer wave
 
 // The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 2 or 5, see mfma_plan) stream W:
 // each owns MT 16-row tiles, keeps 8/MT K-chunks of them (32 KB) in flight in registers and multiplies.
-// Two more waves (producers) stage the X block of every chunk (half of its rows each)
-// through registers into a double-buffered LDS tile.  The hardware counts outstanding loads per wave and retires
+// Two more waves (producers) bring the X block of every chunk into a ring of four LDS stages, direct-to-LDS, three
+// chunks ahead.  The hardware counts outstanding loads per wave and retires
 // them in order, so a wave that waits for a near X load would also drain its far W loads;
-// giving X its own wave keeps the W stream deep.  One barrier per chunk hands the LDS
-// buffers over.
+// giving X its own waves keeps the W stream deep.  One barrier per chunk hands the LDS
+// stages over.
+// What bounds it at 88 rows is the weights from HBM, and in launches of few chunks the time to the first X (6 us while
+// 256 workgroups start their W streams; a load waits behind those requested before it).  Against X row-major through
+// registers into two buffers, fragments read one multiply ahead and surplus chunks loaded again, cold weights, us:
+// 8B q/k/v 15.4 -> 13.5, down 26.6 -> 24.1, gate/up 44.3 -> 41.4 (5.7 TB/s); 1B q/k/v 9.3 -> 7.2, gate/up 18.4 -> 16.0,
+// down 13.0 -> 11.9.
 // MT: 16-row W tiles per consumer wave.  NT: 16-row X tiles per workgroup.
 // grid.x: (W row tile of 16*MT*CW, X row block of 16*NT) pairs, see the mapping below;
 // grid.y: K splits.
-// act_tiled by mode: SWIGLU - the output goes out in fragment order; ARGMAX - tiles per row of the
-// pair buffer.
+// X and the SwiGLU output are in fragment order (cs_xt_index); am_tiles: pairs per row of the argmax epilogue.
 // XN: X is not given; the producers normalise the float32 residual stream themselves (few rows, see cs_norm_in).
+
+// acc += a * b.  PINNED: the sum stays where it is (left to itself the compiler writes it elsewhere and spills at the
+// register limit).  The compiler does not see the statement as a matrix instruction: multiplies into the same
+// accumulator have to lie at least two apart, and before anything else reads one the last has to end (10 wait states).
+template <bool PINNED>
+__device__ __forceinline__ void gemm_mfma(f32x4& acc, f16x8 a, f16x8 b) {
+    if constexpr (PINNED) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+    else acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
+}
+
 #define GEMM_STORE_STREAM 3   // CS_GEMM_STORE whose partial tiles leave through streaming stores
 template <int MT, int NT, int MODE, int CW, bool XN = false>
 __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __restrict__ X,
                                                             const f16_t* __restrict__ W,
                                                             float* __restrict__ Y,
                                                             f16_t* __restrict__ act, int R, int N,
-                                                            int K, int Ks, int RB, int act_tiled,
+                                                            int K, int Ks, int RB, int am_tiles,
                                                             cs_norm_in nrm) {
-    __shared__ __attribute__((aligned(16))) unsigned char xs[2][16 * NT * GEMM_LDS_ROW];
+    // X chunks: 16-row tiles in fragment order, a ring of GEMM_STAGES; XN: padded rows, two buffers
+    constexpr int STAGE = XN ? 16 * NT * GEMM_LDS_ROW : NT * 4096;
+    __shared__ __attribute__((aligned(16))) unsigned char xs[(XN ? 2 : GEMM_STAGES) * STAGE];
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
     const int k_begin = blockIdx.y * Ks;
     const int k_end = min(K, k_begin + Ks);
     const int nchunks = (k_end - k_begin) / GEMM_KC;
+    const int steps = max(nchunks, GEMM_RING_TILES / MT);  // chunks that producers and consumers hand over
     // Workgroup -> (W tile, X row block).  Consecutive workgroup ids go to different XCDs
     // (8 of them, each with its own L2), so the RB row blocks that share one W tile are given
     // ids 8 apart: they run on the same XCD at about the same time and all but the first read
@@ -308,8 +326,11 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
             const float* grow = nrm.gain + k_begin + seg * 8;
             f32x4 xr[2][ROWS4][2], gr[2][2];
             const int last = nchunks - 1;
+            // chunk indices are clamped instead of guarded: a surplus load re-reads the last chunk and a surplus store
+            // lands in the buffer nobody reads any more, so the loop body is branch-free and the compiler's load
+            // counters stay exact (through buffers of no bytes, as W: 1B gate/up 13.7 -> 14.3 us)
             auto load_x = [&](int slot, int c) {
-                c = c < last ? c : last;               // clamped, see below
+                c = c < last ? c : last;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     gr[slot][h] = *reinterpret_cast<const f32x4*>(grow + c * GEMM_KC + 4 * h);
@@ -335,14 +356,14 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
                     f16x8 o;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) o[e] = cs_f16_sat(xr[slot][i][e >> 2][e & 3] * scale[i] * gr[slot][e >> 2][e & 3], hit);
-                    *reinterpret_cast<f16x8*>(&xs[buf][dst0 + i * 4 * GEMM_LDS_ROW]) = o;
+                    *reinterpret_cast<f16x8*>(&xs[buf * STAGE + dst0 + i * 4 * GEMM_LDS_ROW]) = o;
                 }
             };
             store_x(0, 0);
             load_x(0, 2);
             __syncthreads();
             int c = 0;
-            for (; c + 1 < nchunks; c += 2) {          // as below
+            for (; c + 1 < steps; c += 2) {            // chunk c+1 lives in slot 1, chunk c+2 in slot 0
                 store_x(1, 1);
                 load_x(1, c + 3);
                 __syncthreads();
@@ -350,55 +371,46 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
                 load_x(0, c + 4);
                 __syncthreads();
             }
-            if (c < nchunks) __syncthreads();
+            if (c < steps) __syncthreads();
             cs_range_report(nrm.flags, hit, CS_RANGE_NORM);
             return;
         }
     }
     if (!XN && wave >= CW) {
         // ---------------- producers: X chunks -> LDS ----------------
-        // lane -> 16-byte segment (lane & 15) of rows row0 + 4*i, i < ROWS4; the two producer
-        // waves split the 16*NT rows in halves
-        constexpr int ROWS4 = 2 * NT;
-        const int seg = lane & 15, row0 = (lane >> 4) + (wave - CW) * 8 * NT;
-        const f16_t* xbase = X + (int64_t)(r_base + row0) * K + k_begin + seg * 8;
-        const int64_t xstep = (int64_t)4 * K;
-        const int rows_left = R - r_base - row0;          // row 4*i is valid iff 4*i < rows_left
-        const int dst0 = row0 * GEMM_LDS_ROW + seg * 16;
-        f16x8 xr[2][ROWS4];
-        // chunk indices are clamped instead of guarded: a surplus load re-reads the last chunk
-        // and a surplus store lands in the buffer nobody reads any more, so the loop body is
-        // branch-free and the compiler's load counters stay exact
-        const int last = nchunks - 1;
-        auto load_x = [&](f16x8* dst, int c) {
-            c = c < last ? c : last;
+        // Chunk c + 3 is requested while chunk c is multiplied, by direct-to-LDS loads: every request is one 1 KB
+        // fragment block, the two waves take every second one.  They issue no other loads, so the counts are exact.
+        // (A stage is free again when its chunk's barrier is behind: the fragments read from it have been multiplied.)
+        const int p = __builtin_amdgcn_readfirstlane(wave) - CW;
+        const int rt_tiles = (R + 15) >> 4;
+        const f16_t* xt[NT];
 #pragma unroll
-            for (int i = 0; i < ROWS4; ++i)
-                dst[i] = (4 * i < rows_left)
-                             ? *reinterpret_cast<const f16x8*>(xbase + i * xstep + c * GEMM_KC)
-                             : (f16x8){0, 0, 0, 0, 0, 0, 0, 0};
-        };
-        auto store_x = [&](const f16x8* src, int buf) {
+        for (int nt = 0; nt < NT; ++nt)                      // (tiles past R: the last one again)
+            xt[nt] = X + ((int64_t)min((r_base >> 4) + nt, rt_tiles - 1) * (K >> 5) + (k_begin >> 5)) * 512;
+        const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)xs;
+        const unsigned lane16 = lane * 16;
+        auto issue = [&](int c) {
+            const unsigned dst = lds0 + (c & (GEMM_STAGES - 1)) * STAGE;
+            const int cc = min(c, nchunks - 1);              // (a surplus chunk meets zeros of W)
 #pragma unroll
-            for (int i = 0; i < ROWS4; ++i)
-                *reinterpret_cast<f16x8*>(&xs[buf][dst0 + i * 4 * GEMM_LDS_ROW]) = src[i];
+            for (int i = 0; i < 2 * NT; ++i) {
+                const int s = 2 * (i & 1) + p;
+                cs_load_to_lds(lane16, xt[i >> 1] + (cc * 4 + s) * 512, dst + ((i >> 1) * 4 + s) * 1024);
+            }
         };
-        load_x(xr[0], 0);
-        load_x(xr[1], 1);
-        store_x(xr[0], 0);
-        load_x(xr[0], 2);
-        __syncthreads();
+        static_assert(GEMM_STAGES == 4 && 6 * NT <= 63, "three chunks in flight");
+        issue(0);
+        issue(1);
+        issue(2);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * NT) : "memory");
         int c = 0;
-        for (; c + 1 < nchunks; c += 2) {
-            // chunk c+1 lives in xr[1], chunk c+2 in xr[0]
-            store_x(xr[1], 1);
-            load_x(xr[1], c + 3);
-            __syncthreads();
-            store_x(xr[0], 0);
-            load_x(xr[0], c + 4);
-            __syncthreads();
+        for (; c + 3 < steps; ++c) {                         // chunk c is multiplied, chunk c + 1 has to be there next
+            issue(c + 3);
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * NT) : "memory");
         }
-        if (c < nchunks) __syncthreads();
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NT) : "memory");
+        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");
         if (MODE == CS_GEMM_ARGMAX) {                      // the two barriers of the consumers' epilogue
             __syncthreads();
             __syncthreads();
@@ -415,15 +427,16 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
     // contiguous slab of N*256 bytes, which spreads evenly over the HBM channels (a row-major
     // W with its power-of-two row pitch makes concurrent workgroups hit the same channels).
     // (row tiles past N are clamped; their results are never stored)
-    const f16_t* wtile[MT];
+    unsigned wtile[MT];                                           // byte offsets within a slab
     const int n_tiles = N >> 4;
     const int64_t chunk_stride = (int64_t)n_tiles * 4 * 512;     // elements per K chunk slab
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         int t = (n_wave >> 4) + mt;
         t = t < n_tiles ? t : n_tiles - 1;
-        wtile[mt] = W + (k_begin / GEMM_KC) * chunk_stride + (int64_t)t * 4 * 512 + lane * 8;
+        wtile[mt] = (unsigned)t * 4096 + lane * 16;
     }
+    const f16_t* __restrict__ wsplit = W + (k_begin / GEMM_KC) * chunk_stride;
     f32x4 acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -432,50 +445,71 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
 
     constexpr int GEMM_DEPTH = GEMM_RING_TILES / MT;            // K chunks in flight
     f16x8 a[GEMM_DEPTH][MT][4];
-    const int last = nchunks - 1;
-    auto load_w = [&](f16x8 (*dst)[4], int c) {
-        c = c < last ? c : last;               // clamped, see the producer
+    auto w_rsrc = [&](int c) { return cs_rsrc(wsplit + c * chunk_stride, c < nchunks ? (unsigned)n_tiles * 4096u : 0u); };
+    auto load_w = [&](f16x8 (*dst)[4], auto rsrc, int mt, int s0, int s1) {
+        unsigned off = wtile[mt];
+        asm volatile("" : "+v"(off));                          // (one register: the additions below stay in the loads)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                dst[mt][s] = *reinterpret_cast<const f16x8*>(wtile[mt] + c * chunk_stride + s * 512);
+        for (int s = s0; s < s1; ++s) dst[mt][s] = __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + s * 1024, 0, 0));
     };
-    auto compute = [&](f16x8 (*src)[4], int buf) {
-        const unsigned char* xb = xs[buf];
+    // The X fragments of a chunk are read AHEAD of their multiplies: a consumer has a SIMD to itself (nearly), so a read
+    // that is waited for at once costs its whole latency, which is three multiplies.  From three row tiles on the order is
+    // pinned and a k-step of the ring is requested anew right after its last multiply (8B down, 88 rows: 24.1 us, 27.5 with
+    // all requests behind the chunk); fewer rows leave it to the compiler (one stream's 1B gate/up 13.8, pinned 14.5).
+    constexpr int NF = 4 * NT, AHEAD = NF < 6 ? NF : 6;
+    auto compute = [&](f16x8 (*src)[4], int buf, int c_next) {
+        const unsigned char* xb = xs + (XN ? (buf & 1) * STAGE + lrow * GEMM_LDS_ROW + g * 16 : buf * STAGE + lane * 16);
+        auto frag = [&](int f) {
+            return *reinterpret_cast<const f16x8*>(xb + (XN ? (f % NT) * 16 * GEMM_LDS_ROW + (f / NT) * 64 : ((f % NT) * 4 + f / NT) * 1024));
+        };
+        const auto rsrc = w_rsrc(c_next);                      // (past the last chunk: no memory traffic, see cs_rsrc)
+        f16x8 b[AHEAD];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int f = 0; f < AHEAD; ++f) b[f] = frag(f);
+        if constexpr (NT >= 3) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const f16x8 bfrag = *reinterpret_cast<const f16x8*>(
-                    xb + (nt * 16 + lrow) * GEMM_LDS_ROW + s * 64 + g * 16);
+        for (int f = 0; f < NF; ++f) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(src[mt][s], bfrag, acc[mt][nt], 0, 0, 0);
-            }
+            for (int mt = 0; mt < MT; ++mt)
+                gemm_mfma<(NT >= 3)>(acc[mt][f % NT], src[mt][f / NT], b[f % AHEAD]);
+            if (f + AHEAD < NF) b[f % AHEAD] = frag(f + AHEAD);
+            if (NT >= 3 && f % NT == NT - 1)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) load_w(src, rsrc, mt, f / NT, f / NT + 1);
+            if constexpr (NT >= 3) __builtin_amdgcn_sched_barrier(0);
         }
+        if (NT < 3)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) load_w(src, rsrc, mt, 0, 4);
     };
 #pragma unroll
-    for (int u = 0; u < GEMM_DEPTH; ++u) load_w(a[u], u);
+    for (int u = 0; u < GEMM_DEPTH; ++u) {
+        const auto rsrc = w_rsrc(u);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) load_w(a[u], rsrc, mt, 0, 4);
+    }
     if constexpr (XN) sq_reduce();
     __syncthreads();
+    // Branch-free rings of DEPTH chunks, at least one (surplus chunks are zeros): with a way round the loop the
+    // compiler copied the ring from one set of registers into another, which waits for every load in it.
     int c = 0;
-    for (; c + GEMM_DEPTH <= nchunks; c += GEMM_DEPTH) {      // branch-free groups of DEPTH chunks
+    do {
 #pragma unroll
         for (int u = 0; u < GEMM_DEPTH; ++u) {
-            compute(a[u], u & 1);
-            load_w(a[u], c + u + GEMM_DEPTH);
+            compute(a[u], u, c + u + GEMM_DEPTH);
             __syncthreads();
         }
-    }
+        c += GEMM_DEPTH;
+    } while (c + GEMM_DEPTH <= nchunks);
 #pragma unroll
     for (int u = 0; u < GEMM_DEPTH - 1; ++u) {                // remainder, data already in a[u]
         if (c + u < nchunks) {
-            compute(a[u], u & 1);
+            compute(a[u], u, nchunks);
             __syncthreads();
         }
     }
 
+    if constexpr (NT >= 3) asm volatile("s_nop 15" ::: "memory");     // (see gemm_mfma)
     // epilogue.  acc[mt][nt][j] = Y[row r_base + nt*16 + lrow][col n_wave + mt*16 + 4g + j]
     if (MODE == CS_GEMM_STORE || MODE == GEMM_STORE_STREAM) {
         float* __restrict__ y = Y + (int64_t)blockIdx.y * R * N;
@@ -520,11 +554,11 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
         // Per row, the largest of this workgroup's 16*MT*CW columns and its column (the lowest on
         // ties): over the lane's own columns in increasing order, over the four lanes that share
         // a row, then over the waves through LDS (the X buffers are free).  Y carries the
-        // pair buffer [R][tiles][2], act_tiled the number of tiles per row.
+        // pair buffer [R][tiles][2], am_tiles the number of tiles per row.
         int32_t* __restrict__ am = reinterpret_cast<int32_t*>(Y);
-        const int nch = act_tiled;
-        float* rv = reinterpret_cast<float*>(&xs[0][0]);                 // [CW waves][16*NT rows]
-        int* ri = reinterpret_cast<int*>(&xs[0][0]) + CW * 16 * NT;
+        const int nch = am_tiles;
+        float* rv = reinterpret_cast<float*>(xs);                 // [CW waves][16*NT rows]
+        int* ri = reinterpret_cast<int*>(xs) + CW * 16 * NT;
         __syncthreads();                                    // every wave is past its last X fragment
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -581,8 +615,7 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
                     const float gt = acc[2 * mp][nt][j], up = acc[2 * mp + 1][nt][j];
                     o[j] = cs_f16_sat(gt / (1.0f + __expf(-gt)) * up, hit);
                 }
-                // act_tiled: the down projection runs the many-row GEMM (fragment order)
-                *reinterpret_cast<f16x4*>(act + (act_tiled ? cs_xt_index(r, f, F) : (int64_t)r * F + f)) = o;
+                *reinterpret_cast<f16x4*>(act + cs_xt_index(r, f, F)) = o;        // fragment order
             }
         }
         cs_range_report(reinterpret_cast<int32_t*>(Y), hit, CS_RANGE_FFN);
@@ -629,7 +662,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
                                                          const f16_t* __restrict__ W,
                                                          float* __restrict__ Y,
                                                          f16_t* __restrict__ act, int R, int N, int K,
-                                                         int Ks, int RB, int act_tiled) {
+                                                         int Ks, int RB, int am_tiles) {
     constexpr int NT0 = (XT + 1) / 2, NT1 = XT / 2;   // X tiles of a wave in wave row 0 / 1
     constexpr int NBLK = 16 + XT;                     // 1 KB blocks per stage: 16 W tiles, then X tiles
     constexpr int XLD = (XT + 7) / 8;                 // X loads per wave per stage (the last may be partial)
@@ -799,7 +832,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
         } else if (MODE == CS_GEMM_ARGMAX) {
             // as in k_gemm_mfma: the largest of the workgroup's 256 columns per row, lowest column on ties
             int32_t* __restrict__ am = reinterpret_cast<int32_t*>(Y);
-            const int nch = act_tiled;
+            const int nch = am_tiles;
             float* rv = reinterpret_cast<float*>(lds);                        // [4 column waves][16*XT rows]
             int* ri = reinterpret_cast<int*>(lds) + 4 * 16 * XT;
             __syncthreads();                                    // every wave is past its last fragment
@@ -855,7 +888,7 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
                         const float gt = acc[2 * mp][nt][j], up = acc[2 * mp + 1][nt][j];
                         o[j] = cs_f16_sat(gt / (1.0f + __expf(-gt)) * up, hit);
                     }
-                    *reinterpret_cast<f16x4*>(act + (act_tiled ? cs_xt_index(r, f, F) : (int64_t)r * F + f)) = o;
+                    *reinterpret_cast<f16x4*>(act + cs_xt_index(r, f, F)) = o;
                 }
             }
             cs_range_report(reinterpret_cast<int32_t*>(Y), hit, CS_RANGE_FFN);
@@ -872,15 +905,15 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
 
 template <int XT>
 static int launch_tile(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int R, int N, int K, int mode,
-                       int ksplit, int act_tiled, hipStream_t s) {
+                       int ksplit, int am_tiles, hipStream_t s) {
     CS_REQUIRE(((int64_t)R + 15) * K < ((int64_t)1 << 31), CS_E_UNSUPPORTED, "R*K too large for the many-row GEMM");
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
     const int RB = (int)cs_ceil_div(R, 16 * XT);
     dim3 grid((unsigned)(cs_round_up(cs_ceil_div(N, TG_WROWS), 8) * RB), (unsigned)cs_ceil_div(K, Ks));
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
-    if (mode == CS_GEMM_STORE) k_gemm_dma<XT, CS_GEMM_STORE><<<grid, TG_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
-    else if (mode == CS_GEMM_ARGMAX) k_gemm_dma<XT, CS_GEMM_ARGMAX><<<grid, TG_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
-    else k_gemm_dma<XT, CS_GEMM_SWIGLU><<<grid, TG_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled);
+    if (mode == CS_GEMM_STORE) k_gemm_dma<XT, CS_GEMM_STORE><<<grid, TG_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles);
+    else if (mode == CS_GEMM_ARGMAX) k_gemm_dma<XT, CS_GEMM_ARGMAX><<<grid, TG_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles);
+    else k_gemm_dma<XT, CS_GEMM_SWIGLU><<<grid, TG_THREADS, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles);
     cs_prof_end(pg, s);
     return cs_launch_ok("k_gemm_dma");
 }
@@ -938,7 +971,7 @@ static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
 
 template <int MT, int NT, int CW>
 static void start_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int R, int N, int K, int mode, int Ks,
-                       int act_tiled, hipStream_t s) {
+                       int am_tiles, hipStream_t s) {
     const int RB = (int)cs_ceil_div(R, 16 * NT);
     constexpr int threads = 64 * (CW + 2);
     dim3 grid((unsigned)(cs_round_up(cs_ceil_div(N, 16 * MT * CW), 8) * RB), (unsigned)cs_ceil_div(K, Ks));
@@ -946,13 +979,13 @@ static void start_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     // 168: -0.9 %, 264: -0.3 %); with few rows the readers find them in the caches and a plain
     // store wins (48 rows +0.4 %, one stream of 11 rows +2.5 to +3.6 %).
     if (mode == CS_GEMM_STORE && R >= 64)
-        k_gemm_mfma<MT, NT, GEMM_STORE_STREAM, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
+        k_gemm_mfma<MT, NT, GEMM_STORE_STREAM, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles, cs_norm_in{});
     else if (mode == CS_GEMM_STORE)
-        k_gemm_mfma<MT, NT, CS_GEMM_STORE, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
+        k_gemm_mfma<MT, NT, CS_GEMM_STORE, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles, cs_norm_in{});
     else if (mode == CS_GEMM_ARGMAX)
-        k_gemm_mfma<MT, NT, CS_GEMM_ARGMAX, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
+        k_gemm_mfma<MT, NT, CS_GEMM_ARGMAX, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles, cs_norm_in{});
     else if constexpr (MT % 2 == 0)
-        k_gemm_mfma<MT, NT, CS_GEMM_SWIGLU, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, act_tiled, cs_norm_in{});
+        k_gemm_mfma<MT, NT, CS_GEMM_SWIGLU, CW><<<grid, threads, 0, s>>>(X, W, Y, act, R, N, K, Ks, RB, am_tiles, cs_norm_in{});
 }
 
 // few rows, normalised by the producers
@@ -964,7 +997,7 @@ static void start_norm(const cs_norm_in& nrm, const f16_t* W, float* Y, f16_t* a
         if (mode == CS_GEMM_STORE)
             k_gemm_mfma<2, 1, CS_GEMM_STORE, CW, true><<<grid, 64 * (CW + 2), 0, s>>>(nullptr, W, Y, act, R, N, K, Ks, 1, 0, nrm);
         else
-            k_gemm_mfma<2, 1, CS_GEMM_SWIGLU, CW, true><<<grid, 64 * (CW + 2), 0, s>>>(nullptr, W, Y, act, R, N, K, Ks, 1, 1, nrm);
+            k_gemm_mfma<2, 1, CS_GEMM_SWIGLU, CW, true><<<grid, 64 * (CW + 2), 0, s>>>(nullptr, W, Y, act, R, N, K, Ks, 1, 0, nrm);
     };
     if (waves == 5) start(std::integral_constant<int, 5>{});
     else if (waves == 2) start(std::integral_constant<int, 2>{});
@@ -973,12 +1006,12 @@ static void start_norm(const cs_norm_in& nrm, const f16_t* W, float* Y, f16_t* a
 
 template <int MT, int NT>
 static int launch_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int R, int N, int K,
-                       int mode, int ksplit, int waves, int act_tiled, hipStream_t s) {
+                       int mode, int ksplit, int waves, int am_tiles, hipStream_t s) {
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
-    if (waves == 5) start_mfma<MT, NT, 5>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
-    else if (waves == 4) start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);
-    else if constexpr (NT <= 6) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, act_tiled, s);   // (see mfma_plan)
+    if (waves == 5) start_mfma<MT, NT, 5>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);
+    else if (waves == 4) start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);
+    else if constexpr (NT <= 6) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);   // (see mfma_plan)
     else CS_REQUIRE(false, CS_E_STATE, "two consumer waves take at most six row tiles");
     cs_prof_end(pg, s);
     return cs_launch_ok("k_gemm_mfma");
@@ -1102,8 +1135,6 @@ static mfma_shape gemm_plan(int R, int N, int K, bool may_split) {
     return R > 128 && tile_fits && tile_us < mfma_us(R, N, K, p) ? t : p;
 }
 
-bool cs_gemm_x_tiled(int R, int N, int K, bool may_split) { return gemm_plan(R, N, K, may_split).waves == 0; }
-
 int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, int R, int N, int K,
                    int mode, int allow_split, int* nparts_out, hipStream_t s) {
     if (nparts_out) *nparts_out = 1;
@@ -1118,8 +1149,7 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     const bool may_split = allow_split && mode == CS_GEMM_STORE;
     const mfma_shape plan = gemm_plan(R, N, K, may_split);
     const bool tile = plan.waves == 0;
-    // the SwiGLU epilogue writes the input of the down projection (d_model outputs, same rows)
-    int act_tiled = mode == CS_GEMM_SWIGLU && cs_gemm_x_tiled(R, m->cfg.d_model, m->cfg.d_ff, true) ? 1 : 0;
+    int am_tiles = 0;                         // pairs per row of the argmax epilogue
     if (mode == CS_GEMM_ARGMAX) {
         // one (value, column) pair per row and workgroup column tile, in place of Y
         CS_REQUIRE(!allow_split && nparts_out, CS_E_STATE, "argmax epilogue: no K split, tile count wanted");
@@ -1134,38 +1164,38 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     if (ksplit > 1) CS_REQUIRE(allow_split, CS_E_STATE, "K split without a partial-tile buffer");
     const int Ks = (int)cs_round_up(cs_ceil_div(K, ksplit), GEMM_KC);
     const int nparts = (int)cs_ceil_div(K, Ks);
-    if (mode == CS_GEMM_ARGMAX) act_tiled = (int)cs_ceil_div(N, tile ? TG_WROWS : 32 * waves);
-    if (nparts_out) *nparts_out = mode == CS_GEMM_ARGMAX ? act_tiled : nparts;
+    if (mode == CS_GEMM_ARGMAX) am_tiles = (int)cs_ceil_div(N, tile ? TG_WROWS : 32 * waves);
+    if (nparts_out) *nparts_out = mode == CS_GEMM_ARGMAX ? am_tiles : nparts;
     const int rt = (int)cs_ceil_div(rt_total, r_blocks);
     const f16_t* x = (const f16_t*)X;
     const f16_t* w = (const f16_t*)W;
     f16_t* act = (f16_t*)m->act;
     if (tile) {
         switch (rt) {                                // 16-row X tiles per workgroup
-            case 7: return launch_tile<7>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 8: return launch_tile<8>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 9: return launch_tile<9>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 10: return launch_tile<10>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 11: return launch_tile<11>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 12: return launch_tile<12>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 13: return launch_tile<13>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 14: return launch_tile<14>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 15: return launch_tile<15>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 16: return launch_tile<16>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 17: return launch_tile<17>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            case 18: return launch_tile<18>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
-            default: return launch_tile<TG_XT_MIN>(x, w, Y, act, R, N, K, mode, nparts, act_tiled, s);
+            case 7: return launch_tile<7>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 8: return launch_tile<8>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 9: return launch_tile<9>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 10: return launch_tile<10>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 11: return launch_tile<11>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 12: return launch_tile<12>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 13: return launch_tile<13>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 14: return launch_tile<14>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 15: return launch_tile<15>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 16: return launch_tile<16>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 17: return launch_tile<17>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            case 18: return launch_tile<18>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
+            default: return launch_tile<TG_XT_MIN>(x, w, Y, act, R, N, K, mode, nparts, am_tiles, s);
         }
     }
     switch (rt) {
-        case 1: return launch_mfma<2, 1>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        case 2: return launch_mfma<2, 2>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        case 3: return launch_mfma<2, 3>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        case 4: return launch_mfma<2, 4>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        case 5: return launch_mfma<2, 5>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        case 6: return launch_mfma<2, 6>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        case 7: return launch_mfma<2, 7>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
-        default: return launch_mfma<2, 8>(x, w, Y, act, R, N, K, mode, nparts, waves, act_tiled, s);
+        case 1: return launch_mfma<2, 1>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        case 2: return launch_mfma<2, 2>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        case 3: return launch_mfma<2, 3>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        case 4: return launch_mfma<2, 4>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        case 5: return launch_mfma<2, 5>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        case 6: return launch_mfma<2, 6>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        case 7: return launch_mfma<2, 7>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
+        default: return launch_mfma<2, 8>(x, w, Y, act, R, N, K, mode, nparts, waves, am_tiles, s);
     }
 }
 

@@ -133,6 +133,14 @@ def test_gemm_five_wave_tiles_over_long_rows(host_model, R, N, K):
     _gemm_case(host_model, N, K, R)
 
 
+@pytest.mark.parametrize("chunks", [1, 2, 3, 5, 6, 7, 9])
+@pytest.mark.parametrize("R", [1, 16, 33, 81, 96, 112, 128])
+def test_gemm_chunk_counts_of_the_ring(host_model, R, chunks):
+    """The weight-streaming kernel over 128 * chunks of K: less than its ring of four chunks, whole rings and every
+    remainder, for row tiles below and above the count from which the multiply order is pinned."""
+    _gemm_case(host_model, 1040, 128 * chunks, R)
+
+
 def test_gemm_tiny_weights_are_not_flushed(host_model):
     """The tuned projections multiply in float16 (weights converted from bfloat16, exactly for
     |w| >= 2^-17).  Weights in float16's subnormal range must still contribute."""
