@@ -1135,6 +1135,8 @@ static mfma_shape gemm_plan(int R, int N, int K, bool may_split) {
     return R > 128 && tile_fits && tile_us < mfma_us(R, N, K, p) ? t : p;
 }
 
+bool cs_gemm_x_tiled(int R, int N, int K, bool may_split) { return gemm_plan(R, N, K, may_split).waves == 0; }
+
 int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, int R, int N, int K,
                    int mode, int allow_split, int* nparts_out, hipStream_t s) {
     if (nparts_out) *nparts_out = 1;
