@@ -268,12 +268,18 @@ __device__ __forceinline__ auto cs_rsrc(const void* p, unsigned bytes) {
 // request 16 bytes per lane from (uniform base + per-lane byte offset) into LDS at lds_addr + 16*lane.
 // M0 carries the LDS address.  The compiler reserves M0 and only ever sets it immediately before
 // an instruction of its own that reads it, so overwriting it here is safe; it still warns about
-// any reserved register in a clobber list, which is silenced for this one statement.  (One wait state has to lie
+// any reserved register in a clobber list, which is silenced here.  (One wait state has to lie
 // between a write of M0 and a load that takes its LDS address from it.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void cs_load_to_lds(unsigned voff, const void* sbase, unsigned lds_addr) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "s"(lds_addr) : "m0");
+}
+// The same unless `on` is 0 (uniform).  One statement: a branch that the compiler sees in a loop splits the live ranges
+// of its accumulators.
+__device__ __forceinline__ void cs_load_to_lds_if(int on, unsigned voff, const void* sbase, unsigned lds_addr) {
+    asm volatile("s_cmp_eq_u32 %3, 0\n\ts_cbranch_scc1 .Lno%=\n\ts_mov_b32 m0, %2\n\ts_nop 0\n"
+                 "\tglobal_load_lds_dwordx4 %0, %1\n.Lno%=:" ::"v"(voff), "s"(sbase), "s"(lds_addr), "s"(on) : "m0", "scc");
 }
 #pragma clang diagnostic pop
 

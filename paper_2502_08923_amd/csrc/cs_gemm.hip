@@ -625,21 +625,25 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
 // -------------------------------------------------------------------------------------
 // tuned kernel for many rows (e.g. batch 16 x (k = 32) + 1 = 528 rows)
 //
-// With hundreds of block rows the projections are bound by the matrix cores and by the
-// bandwidth between L2 and the compute units, so the tile is chosen for operand reuse: a
-// workgroup of eight waves (4 x 2, two per SIMD so one wave's waits hide behind the other's
-// MFMAs) owns a 256 (W rows) x 32*NT (X rows) output tile, each wave 64 x 16*NT.  Both
+// With hundreds of block rows the projections are bound by the matrix cores, and those by power: the loop below runs
+// its multiplies at 1.4 to 1.65 GHz where constant operands leave the clock at 2.4 (a loop of nothing but multiplies of random
+// registers: 1.9 GHz, 1.88 PFLOP/s; with 32x32x16 instructions 1.63).  So the tile is chosen for operand reuse: a
+// workgroup of eight waves (4 x 2, two per SIMD) owns a 256 (W rows) x 32*NT (X rows) output tile, each wave 64 x 16*NT.  Both
 // operands go through LDS, every element fetched from L2 once per workgroup.  LDS holds them
 // in MFMA fragment order (1 KB blocks of 16 rows x 32 k, lane l's 16 bytes at offset 16*l), so
 // fragment reads are conflict-free without padding; the pre-tiled W is already stored that
 // way in memory.  The operands never pass through registers on their way in: every wave
 // issues 16-byte direct-to-LDS loads (lane l's 16 bytes land at the wave-uniform LDS address
-// in M0 plus 16*l, so one load fills one fragment block; X is stored in the same order by
-// whoever produces it, see cs_gemm_x_tiled).  K advances 32 at a time through a ring of four
-// LDS stages.  Chunk c+3 is requested
-// while chunk c is multiplied; one barrier per chunk publishes chunk c+1 and frees the stage
-// of chunk c-1, and the first fragments of chunk c+1 are read before that chunk's barrier so
-// the matrix cores do not drain at the hand-over.
+// in M0 plus 16*l, so one load fills one fragment block; X is stored in the same order, see
+// cs_xt_index).  K advances 32 at a time through a ring of four LDS stages.
+// The two waves of a SIMD, one of each wave row, take turns: while one multiplies a chunk out of its registers, the
+// other reads its fragments of the next and requests its share of the chunk three further on; a barrier, and they change
+// places.  With both in phase, fragments read a few multiplies ahead and one barrier per chunk, the reads of all eight
+// waves met at the chunk's start: 1303 cycles a chunk at 17 X tiles, 841 at ten, now 1170 and 761 (1088 and 640 of them
+// multiplies).  Gate/up of the 8B shape at 2048 rows 390 -> 372 us (1.29 PFLOP/s), at 528 100.3 -> 98.3, at 300 68.1 -> 66.2; by
+// X tiles 6, 7, 8, 10, 16, 17 over 690 launches 0.93, 0.95, 0.96, 0.96, 0.96, 0.97 of the time.  (One barrier per chunk with the
+// wave rows half a chunk apart: 850 us where in phase took 807; four waves of 128 x 128, a third fewer LDS
+// reads: the cycles it loses are what the clock gains, 841; two chunks per phase: 78 where one took 72.)
 //
 // The loads and the waits on them are written as inline assembly: the compiler's own
 // bookkeeping would make every LDS read wait for all outstanding direct-to-LDS loads.  This
@@ -649,7 +653,7 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
 #define TD_KC 32
 #define TG_THREADS 512
 #define TG_WROWS 256
-#define TG_XT_MIN 6        // fewest X tiles of a workgroup (a wave reads its X fragments three tiles ahead)
+#define TG_XT_MIN 6        // fewest X tiles of a workgroup (three per wave)
 #define TG_PANEL 4          // row blocks a compute die walks per W tile, see the mapping in the kernel
 
 
@@ -713,6 +717,8 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
     const f16_t* xbase = X + (int64_t)(k_begin / TD_KC) * 512;
     const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)lds;
 
+    int extra = __builtin_amdgcn_readfirstlane(wave < XT % 8 ? 1 : 0);   // requests one X block more than the others
+    asm volatile("" : "+s"(extra));                  // stays a scalar register
     // request number `idx` (0, 1: W blocks; 2..: X blocks) of chunk c into stage sb
     constexpr int NL = 2 + XLD;                       // requests per wave and chunk (the last may be void)
     auto issue_one = [&](int sb, int c, int idx) {
@@ -722,9 +728,9 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
             cs_load_to_lds(lane16, wc + (int64_t)tw[idx] * 2048, dst + 8 * idx * 1024);
         } else {
             const int i = idx - 2;
-            const f16_t* xc = xbase + (int64_t)c * 512;
-            if (8 * i + 7 < XT || wave + 8 * i < XT)
-                cs_load_to_lds(lane16, xc + tx[i] * x_pitch, dst + (16 + 8 * i) * 1024);
+            const f16_t* xc = xbase + (int64_t)c * 512 + tx[i] * x_pitch;
+            if (8 * i + 7 < XT) cs_load_to_lds(lane16, xc, dst + (16 + 8 * i) * 1024);
+            else cs_load_to_lds_if(extra, lane16, xc, dst + (16 + 8 * i) * 1024);
         }
     };
     auto issue = [&](int sb, int c) {
@@ -737,84 +743,89 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
     auto b_frag = [&](int sb, int nt) { return *reinterpret_cast<const f16x8*>(b_base + sb * STAGE + nt * 1024); };
     const int n_wave = w_tile * TG_WROWS + wn * 64;
 
-    // wait until at most `n` chunks of this wave's requests are outstanding, then meet the other waves.
-    // (A plain s_barrier: the workgroup fence of __syncthreads would drain every load in flight.)  With XT
-    // no multiple of 8 the first XT % 8 waves request one block more per chunk and count their own number:
-    // with the smaller count of the others they waited for part of the newest chunk, and everybody with
-    // them.  (One asm statement: a branch the compiler sees splits the accumulators' live ranges.)
-    int extra = __builtin_amdgcn_readfirstlane(wave < XT % 8 ? 1 : 0);
-    asm volatile("" : "+s"(extra));                  // stays a scalar register
-#define TD_SYNC(n)                                                                                    \
+    // TD_WAIT: until at most `n` chunks of this wave's requests are outstanding.  With XT no multiple of 8 the first
+    // XT % 8 waves request one block more per chunk and count their own number.  (One asm statement: a branch the compiler
+    // sees splits the accumulators' live ranges.)  TD_MEET is a plain s_barrier: the workgroup fence of
+    // __syncthreads would drain every load in flight; nothing moves across it.
+#define TD_WAIT(n)                                                                                    \
     do {                                                                                              \
-        if constexpr (XT % 8 == 0)                                                                    \
-            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((n) * LDMIN) : "memory");           \
+        if constexpr (XT % 8 == 0 || (n) == 0)                                                        \
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((n) * LDMIN) : "memory");                        \
         else                                                                                          \
             asm volatile("s_cmp_eq_u32 %0, 0\n\ts_cbranch_scc1 .Lfew%=\n\ts_waitcnt vmcnt(%1)\n"      \
-                         "\ts_branch .Lmet%=\n.Lfew%=:\n\ts_waitcnt vmcnt(%2)\n.Lmet%=:\n\ts_barrier" \
+                         "\ts_branch .Lmet%=\n.Lfew%=:\n\ts_waitcnt vmcnt(%2)\n.Lmet%=:"             \
                          ::"s"(extra), "n"((n) * (LDMIN + 1)), "n"((n) * LDMIN) : "memory", "scc");   \
+    } while (0)
+#define TD_MEET()                                                                                     \
+    do {                                                                                              \
+        __builtin_amdgcn_sched_barrier(0);                                                            \
+        asm volatile("s_barrier" ::: "memory");                                                       \
+        __builtin_amdgcn_sched_barrier(0);                                                            \
+    } while (0)
+    // the next chunk has landed, as far as this wave requested it; of those behind it two may be outstanding
+#define TD_LANDED(left)                                                                               \
+    do {                                                                                              \
+        if constexpr ((left) == 3) TD_WAIT(2);                                                        \
+        else if constexpr ((left) == 2) TD_WAIT(1);                                                   \
+        else if constexpr ((left) == 1) TD_WAIT(0);                                                   \
     } while (0)
 
     // Everything a wave does with its NT X tiles: the multiply loop and the epilogue.  Both wave rows
     // run it with their own NT; the requests, the waits and the barriers are the same in both, so
     // the two instantiations stay in step.
-    auto body = [&](auto nt_tag) {
+    auto body = [&](auto nt_tag, auto row_tag) {
         constexpr int NT = decltype(nt_tag)::value;
+        constexpr bool SECOND = decltype(row_tag)::value == 1;
         const int xt0 = wm * NT0;                        // first X tile of this wave within the block
         f32x4 acc[4][NT];
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-        f16x8 a[4], bq[4];
+        f16x8 a[4], b[NT];
 
         issue(0, 0);
         issue(1, 1);
         issue(2, 2);
-        TD_SYNC(2);                                                // chunk 0 has landed everywhere
+        TD_WAIT(2);                                                // chunk 0 has landed
+        TD_MEET();
+        if constexpr (SECOND) TD_MEET();                           // from here on half a chunk behind
+        // One chunk, two phases.  LEFT: chunks behind it, 3 for three or more.  The first wave row reads chunk c in phase
+        // 2c and multiplies it in 2c + 1, the second a phase later each.  Chunk c + 3 takes the stage of chunk c - 1, last
+        // read in phase 2c - 1 (and waited for before its barrier); chunk c + 1 is first read in phase 2c + 2, so
+        // both wave rows wait for their requests of it at the end of phase 2c + 1.
+        auto chunk = [&](int u, int c, auto left_tag) {
+            constexpr int LEFT = decltype(left_tag)::value;
+            // read and request; the other wave row multiplies
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt) a[mt] = a_frag(0, mt);
-        bq[0] = b_frag(0, 0);
-        bq[1] = b_frag(0, 1);
-        bq[2] = b_frag(0, 2);
-
-        // four chunks, one per stage.  TAIL marks the last trip, where nothing more is requested.
-        auto trip = [&](int c0, auto tailc) {
-            constexpr bool TAIL = decltype(tailc)::value;
+            for (int mt = 0; mt < 4; ++mt) a[mt] = a_frag(u, mt);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                // chunk c+1 (requested two iterations ago) must be in LDS before its first fragments
-                // are read at the end of this iteration; only chunk c+2 may still be in flight
-                if (TAIL && u >= 2) TD_SYNC(0);
-                else TD_SYNC(1);
-                // chunk c+3 goes to the stage of chunk c-1, free since the barrier.  Its requests are
-                // spread over the iteration, one after every few MFMA groups: a wave issues in order,
-                // so a burst of requests that the memory pipeline takes one at a time would hold
-                // back the MFMAs behind it, in all eight waves at once right after the barrier.
-                const bool req = !TAIL || u == 0;
-                const bool more = !TAIL || u < 3;
-                int next_req = 0;
+            for (int nt = 0; nt < NT; ++nt) b[nt] = b_frag(u, nt);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (LEFT == 3) issue((u + 3) & 3, c + 3);
+            __builtin_amdgcn_s_waitcnt(0xC07F);                    // the fragments are here (lgkmcnt 0, no other count)
+            if constexpr (SECOND) TD_LANDED(LEFT);
+            TD_MEET();
+            // multiply; the other wave row reads
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    if (req && next_req < NL && nt == (next_req * NT) / NL) {
-                        issue_one((u + 3) & 3, c0 + u + 3, next_req);
-                        ++next_req;
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                    const int q = u * NT + nt;                        // position in the B fragment stream
-                    if (nt + 3 < NT) bq[(q + 3) & 3] = b_frag(u, nt + 3);              // three tiles ahead
-                    else if (more) bq[(q + 3) & 3] = b_frag((u + 1) & 3, nt + 3 - NT);
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) {
-                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], bq[q & 3], acc[mt][nt], 0, 0, 0);
-                        // an A fragment is replaced by the next chunk's right after its last use
-                        if (nt == NT - 1 && more) a[mt] = a_frag((u + 1) & 3, mt);
-                    }
-                }
-            }
+                for (int mt = 0; mt < 4; ++mt)
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (!SECOND) TD_LANDED(LEFT);
+            TD_MEET();
         };
+        constexpr std::integral_constant<int, 3> more{};
         int c0 = 0;
-        for (; c0 + 4 < nchunks; c0 += 4) trip(c0, std::false_type{});
-        trip(c0, std::true_type{});
+        for (; c0 + 4 < nchunks; c0 += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) chunk(u, c0 + u, more);
+        chunk(0, c0, more);
+        chunk(1, c0 + 1, std::integral_constant<int, 2>{});
+        chunk(2, c0 + 2, std::integral_constant<int, 1>{});
+        chunk(3, c0 + 3, std::integral_constant<int, 0>{});
+        if constexpr (!SECOND) TD_MEET();
 
         // epilogue: acc[mt][nt][j] = Y[r_base + (xt0 + nt)*16 + lrow][n_wave + mt*16 + 4g + j]
         if (MODE == CS_GEMM_STORE) {
@@ -894,13 +905,11 @@ __global__ __launch_bounds__(TG_THREADS) void k_gemm_dma(const f16_t* __restrict
             cs_range_report(reinterpret_cast<int32_t*>(Y), hit, CS_RANGE_FFN);
         }
     };
-    if constexpr (NT0 == NT1) {
-        body(std::integral_constant<int, NT0>{});
-    } else {
-        if (wm == 0) body(std::integral_constant<int, NT0>{});
-        else body(std::integral_constant<int, NT1>{});
-    }
-#undef TD_SYNC
+    if (wm == 0) body(std::integral_constant<int, NT0>{}, std::integral_constant<int, 0>{});
+    else body(std::integral_constant<int, NT1>{}, std::integral_constant<int, 1>{});
+#undef TD_WAIT
+#undef TD_MEET
+#undef TD_LANDED
 }
 
 template <int XT>
@@ -937,7 +946,7 @@ static double gemm_either(double compute, double weights) {
 // Estimated time of a launch, us, and of reading its partial tiles in the kernel behind it (4.9 TB/s).  Both formulas are
 // fitted to 4600 launches with cold weights (1B, 8B and Qwen2.5-7B projections, 22 to 1000 rows; root mean square error 4.7 and
 // 2.2 %).  Per 128 of K a workgroup of the weight-streaming kernel takes 0.47 us + 0.068 per X tile (five consumer waves share four
-// SIMDs, two have W for half as many rows), one of the many-row kernel 0.69 us + 0.13 per X tile, behind 1.4 and 3.4 us
+// SIMDs, two have W for half as many rows), one of the many-row kernel 0.58 us + 0.13 per X tile, behind 1.4 and 3.4 us
 // until the first chunk is there.
 static double mfma_us(int R, int N, int K, const gemm_shape& p, bool may_split) {
     const int64_t rt = cs_ceil_div(R, 16), nt = cs_ceil_div(rt, p.r_blocks);
@@ -953,7 +962,7 @@ static double tile_us(int R, int N, int K, const gemm_shape& p, bool may_split) 
     const int64_t xt = cs_ceil_div(rt, p.r_blocks) < TG_XT_MIN ? TG_XT_MIN : cs_ceil_div(rt, p.r_blocks);
     const int64_t per_xcd = cs_ceil_div(cs_ceil_div(N, TG_WROWS), 8) * cs_ceil_div(rt, xt) * p.ksplit;
     const double parts = may_split ? 1e-6 * p.ksplit * R * N : 0.;
-    const double us = gemm_rounds(per_xcd, 0.75) * (3.4 + cs_ceil_div(K / GEMM_KC, p.ksplit) * (0.69 + 0.13 * xt)) + 0.46 * parts;
+    const double us = gemm_rounds(per_xcd, 0.75) * (3.4 + cs_ceil_div(K / GEMM_KC, p.ksplit) * (0.58 + 0.13 * xt)) + 0.46 * parts;
     return 3.6 + gemm_either(us, 2e-6 * N * K / 5.3) + 0.82 * parts;
 }
 
