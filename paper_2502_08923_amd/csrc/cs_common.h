@@ -215,8 +215,10 @@ int cs_gemm_residual_launch(const cs_model* m, const void* X, const void* W, int
 // k (k % 4 == 0) stay contiguous.  Rows of 16-row tiles also spread a K chunk over all channels of the L2: with
 // row-major X and a power-of-two K the rows of a chunk met in one or two of them (see k_gemm_mfma).
 // cs_gemm_x_tiled says whether the GEMM of R rows by N outputs over K inputs, with or without leave to split K (as in
-// cs_gemm_launch), runs the many-row kernel.
+// cs_gemm_launch), runs the many-row kernel; cs_gemm_shape gives its consumer waves (0: the many-row kernel), 16-row X tiles
+// per workgroup and K splits where the workspace holds them.  (Both are asked by tests only.)
 bool cs_gemm_x_tiled(int R, int N, int K, bool may_split);
+void cs_gemm_shape(int R, int N, int K, bool may_split, int* shape);
 __host__ __device__ __forceinline__ int64_t cs_xt_index(int r, int k, int K) {
     return ((int64_t)(r >> 4) * (K >> 5) + (k >> 5)) * 512 + (((r & 15) + 16 * ((k & 31) >> 3)) << 3) + (k & 7);
 }

@@ -234,7 +234,7 @@ static int launch_plain(int dtype, const float* X, const void* W, float* Y, int 
 #define GEMM_STAGES 4                     // X chunks in LDS
 #define GEMM_RING_TILES 8                 // W tile-chunks (4 KB each) in flight per consumer wave
 
-// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 2 or 5, see gemm_plan) stream W:
+// The workgroup is specialised by wave.  Waves 0..CW-1 (consumers; 4, or 2 or 5, see mfma_plan) stream W:
 // each owns MT 16-row tiles, keeps 8/MT K-chunks of them (32 KB) in flight in registers and multiplies.
 // Two more waves (producers) bring the X block of every chunk into a ring of four LDS stages, direct-to-LDS, three
 // chunks ahead.  The hardware counts outstanding loads per wave and retires
@@ -927,81 +927,54 @@ static int launch_tile(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     return cs_launch_ok("k_gemm_dma");
 }
 
-// Launch shape of a projection (waves 0: the many-row kernel, 256 W rows x up to 288 block rows per workgroup).
-struct gemm_shape { int r_blocks, ksplit, waves; };
+// Launch shape of the weight-streaming kernel.
+struct mfma_shape { int r_blocks, ksplit, waves; };
 
-// `per_xcd` workgroups of one compute die on its 32 compute units, in rounds; a round that fills a part f takes
-// part + (1 - part) f of a full one (less contention).
-static double gemm_rounds(int64_t per_xcd, double part) {
-    const double f = (per_xcd % 32) / 32.;
-    return (double)(per_xcd / 32) + (f > 0. ? part + (1. - part) * f : 0.);
+// Estimated time of a launch, us.  A workgroup fills a compute unit and takes 30 us per 4096 of K while it
+// is bound by its weights, 6.1 us per X tile from five tiles on (8B width, 224 workgroups: 4, 6, 7, 8 X tiles
+// 30, 37, 43 to 48, 49 to 55 us); five consumer waves share four SIMDs, 1.35 of the time for 1.25 of the
+// rows; a partial tile is written and read once more at about 4.9 TB/s (an unsplit output is charged nothing here
+// and once in tile_plan: with both charged alike, and the rate fitted anew, 21 of 284 whole calls of 97 to 1024
+// rows and prompts up to 4096 got faster and 53 slower, 1 to 6 % each).
+static double mfma_us(int R, int N, int K, const mfma_shape& p) {
+    const int nt = (int)cs_ceil_div(cs_ceil_div(R, 16), p.r_blocks);
+    const int64_t wgs = cs_ceil_div(N, 32 * p.waves) * p.r_blocks * p.ksplit;
+    const double per = (6.1 * nt > 30. ? 6.1 * nt : 30.) * (p.waves == 5 ? 1.35 : 1.);
+    return cs_ceil_div(wgs, 256) * per * K / p.ksplit / 4096. + (p.ksplit > 1 ? p.ksplit * 8e-6 * R * N / 4.9 : 0.);
 }
 
-// A launch takes about the larger of what its workgroups take and what its weights take from HBM.
-static double gemm_either(double compute, double weights) {
-    const double a = compute * compute, b = weights * weights;
-    return sqrt(sqrt(a * a + b * b));
-}
-
-// Estimated time of a launch, us, and of reading its partial tiles in the kernel behind it (4.9 TB/s).  Both formulas are
-// fitted to 4600 launches with cold weights (1B, 8B and Qwen2.5-7B projections, 22 to 1000 rows; root mean square error 4.7 and
-// 2.2 %).  Per 128 of K a workgroup of the weight-streaming kernel takes 0.47 us + 0.068 per X tile (five consumer waves share four
-// SIMDs, two have W for half as many rows), one of the many-row kernel 0.58 us + 0.13 per X tile, behind 1.4 and 3.4 us
-// until the first chunk is there.
-static double mfma_us(int R, int N, int K, const gemm_shape& p, bool may_split) {
-    const int64_t rt = cs_ceil_div(R, 16), nt = cs_ceil_div(rt, p.r_blocks);
-    const int64_t per_xcd = cs_ceil_div(cs_ceil_div(N, 32 * p.waves), 8) * cs_ceil_div(rt, nt) * p.ksplit;
-    const double chunk = (0.47 + 0.068 * nt) * (p.waves == 5 ? 1.4 : p.waves == 2 ? 0.62 : 1.);
-    const double parts = may_split ? 1e-6 * p.ksplit * R * N : 0.;
-    const double us = gemm_rounds(per_xcd, 0.8) * (1.4 + cs_ceil_div(K / GEMM_KC, p.ksplit) * chunk) + 0.55 * parts;
-    return 2.1 + gemm_either(us, 2e-6 * N * K / 5.5) + 0.82 * parts;
-}
-
-static double tile_us(int R, int N, int K, const gemm_shape& p, bool may_split) {
-    const int64_t rt = cs_ceil_div(R, 16);
-    const int64_t xt = cs_ceil_div(rt, p.r_blocks) < TG_XT_MIN ? TG_XT_MIN : cs_ceil_div(rt, p.r_blocks);
-    const int64_t per_xcd = cs_ceil_div(cs_ceil_div(N, TG_WROWS), 8) * cs_ceil_div(rt, xt) * p.ksplit;
-    const double parts = may_split ? 1e-6 * p.ksplit * R * N : 0.;
-    const double us = gemm_rounds(per_xcd, 0.75) * (3.4 + cs_ceil_div(K / GEMM_KC, p.ksplit) * (0.58 + 0.13 * xt)) + 0.46 * parts;
-    return 3.6 + gemm_either(us, 2e-6 * N * K / 5.3) + 0.82 * parts;
-}
-
-// Which kernel a projection of R rows takes, with how many row blocks, K splits and consumer waves: the least estimated
-// time.  Over those 276 (matrix, rows) pairs the choice is 0.7 % slower than the best launch measured; with one row
-// block up to 96 rows, and the many-row kernel for all above 288, it was 5.9 % (88 rows: 8B o in two row blocks of four K
-// splits 14.2 -> 11.9 us, 1B q/k/v 8.2 -> 7.1, down 15.5 -> 12.7; 300 rows: o 24.7 -> 19.3, q/k/v 30.8 -> 27.2, 1B
-// down 25.6 -> 20.0; 528 rows: Qwen2.5-7B q/k/v 33.5 -> 27.2).  What the estimates do not see: up to 128 rows the many-row kernel
-// loses unless its 256-row W tiles alone fill most of the chip; with that many (the lm_head) it wins from 97 rows on (128 rows of
-// the 8B lm_head 178 against 196 us, 105 rows of Qwen2.5-7B's 212 against 205).  Two consumer waves for a projection
-// that may not split K and has tiles of 128 W rows for half of the chip at most (1B gate/up, 16 to 88 rows 13 to 16 us; with
-// twice as many tiles they lose: 8B gate/up, 88 rows 42 -> 54), five where 128-row tiles need a nearly empty second round
-// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 88 rows 61 -> 48 us).
-static gemm_shape gemm_plan(int R, int N, int K, bool may_split) {
-    const int rt = (int)cs_ceil_div(R, 16);
+// Up to 96 rows: one row block, and K splits until about 3/4 of the compute units have a workgroup (measured
+// at the 8B shapes, more splits cost more in partial-tile traffic and fixed per-workgroup latency than they
+// gain: q/k/v 4, o 8, down 8).  More rows: row blocks of up to 128 rows and K splits by estimated time (100
+// rows: gate/up 60 -> 48 us in one block instead of two; 256 rows: q/k/v, gate/up, down 40, 109, 58 ->
+// 28, 97, 46 us in two instead of three; the 1B shape keeps two blocks of 64, which fill the chip, 18 us
+// against 23).  Five consumer waves where tiles of 128 W rows need a second, nearly empty round of the chip
+// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 80 -> 56 us), not for the few
+// chunks of a K split (1B q/k/v at 200 rows: 19 us against 12).  Two consumer waves where a projection that may not
+// split K has tiles of 128 W rows for half of the chip at most (1B gate/up, 16384 rows: 16, 48, 88 rows 16.2, 18.8,
+// 23.5 -> 13.5, 15.9, 19.9 us); with twice as many tiles as compute units they lose (8B gate/up, 88 rows: 46 -> 53).
+static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
+    const int rt_total = (int)cs_ceil_div(R, 16);
     const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
-    const bool tall = cs_ceil_div(N, TG_WROWS) >= 192;
-    const bool tile_fits = ((int64_t)R + 15) * K < ((int64_t)1 << 31);      // (launch_tile refuses more)
-    gemm_shape best = {1, 1, 4};
-    double best_us = -1.;
-    auto consider = [&](const gemm_shape& p, double us) {
-        if (best_us < 0. || us < best_us) { best_us = us; best = p; }
-    };
-    for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2) {
-        if (!(tall && R > 96 && tile_fits)) {
-            const int rb_max = (int)cs_ceil_div(rt, 4) > 3 ? (int)cs_ceil_div(rt, 4) : rt < 3 ? rt : 3;
-            for (int rb = (int)cs_ceil_div(rt, 8); rb <= rb_max; ++rb) {
-                const gemm_shape four = {rb, ks, 4}, five = {rb, ks, 5}, two = {rb, ks, 2};
-                consider(four, mfma_us(R, N, K, four, may_split));
-                if (ks == 1) consider(five, mfma_us(R, N, K, five, may_split));
-                if (!may_split && rb == 1 && rt <= 6 && cs_ceil_div(N, 64) <= 256) consider(two, mfma_us(R, N, K, two, may_split));
-            }
-        }
-        if (tile_fits && (R > 128 || (tall && R > 80)))
-            for (int rb = (int)cs_ceil_div(rt, 18); rb <= (int)cs_ceil_div(rt, TG_XT_MIN); ++rb) {
-                const gemm_shape p = {rb, ks, 0};
-                consider(p, tile_us(R, N, K, p, may_split));
-            }
+    mfma_shape best = {1, 1, 4};
+    if (rt_total <= 6) {
+        const int n_tiles = (int)cs_ceil_div(N, 128);
+        while (n_tiles * best.ksplit < 192 && best.ksplit * 2 <= max_split) best.ksplit *= 2;
+        if (best.ksplit > 1) return best;
+        mfma_shape five = best;
+        five.waves = 5;
+        if (mfma_us(R, N, K, five) < mfma_us(R, N, K, best)) return five;
+        if (!may_split && cs_ceil_div(N, 64) <= 256) best.waves = 2;
+        return best;
     }
+    double best_us = -1.;
+    for (int rb = (int)cs_ceil_div(rt_total, 8); rb <= (int)cs_ceil_div(rt_total, 4); ++rb)
+        for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2)
+            for (int waves = 4; waves <= (ks == 1 ? 5 : 4); ++waves) {
+                const mfma_shape p = {rb, ks, waves};
+                const double us = mfma_us(R, N, K, p);
+                if (best_us < 0. || us < best_us) { best_us = us; best = p; }
+            }
     return best;
 }
 
@@ -1047,7 +1020,7 @@ static int launch_mfma(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
     const int pg = cs_prof_begin(CS_PROF_GEMM, s);
     if (waves == 5) start_mfma<MT, NT, 5>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);
     else if (waves == 4) start_mfma<MT, NT, 4>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);
-    else if constexpr (NT <= 6) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);   // (see gemm_plan)
+    else if constexpr (NT <= 6) start_mfma<MT, NT, 2>(X, W, Y, act, R, N, K, mode, Ks, am_tiles, s);   // (see mfma_plan)
     else CS_REQUIRE(false, CS_E_STATE, "two consumer waves take at most six row tiles");
     cs_prof_end(pg, s);
     return cs_launch_ok("k_gemm_mfma");
@@ -1124,7 +1097,70 @@ int cs_tile_x_launch(const void* src, void* dst, int R, int K, hipStream_t s) {
     return cs_launch_ok("k_tile_x");
 }
 
+// Row blocks and K splits of a many-row GEMM: the pair with the least estimated time.  A workgroup
+// with rt X tiles takes 4.5 us * (6.7 + rt) per 4096 of K on a full chip (fitted to q/k/v, o, gate/up
+// and down at 300, 528, 1023 and 4095 rows: the requests and the barrier of a chunk cost what 6.7
+// tiles cost to multiply, so a tile shorter by a ninth pays only where it does not add a round of the
+// chip); a round that fills a part f of the chip takes 0.65 + 0.35 f of a full one (less contention);
+// every partial tile is written and read once more at about 4.9 TB/s.
+// 4095 rows, 8B width, against the fewest row blocks (15 x 288 rows): gate/up 771 -> 695 us,
+// q/k/v 209 -> 169, o 113 -> 104, down 368 -> 339 us; 528 rows: o 31 -> 27 us with half the partial tiles.
+// (returns the time; a launch of its own costs about 4 us on top)
+static double tile_plan(int R, int N, int K, bool may_split, int* r_blocks, int* ksplit) {
+    const int rt_total = (int)cs_ceil_div(R, 16);
+    const int per_xcd = (int)cs_ceil_div(cs_ceil_div(N, TG_WROWS), 8);   // W tiles of one die
+    const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
+    const int rb_min = (int)cs_ceil_div(rt_total, 18), rb_max = (int)cs_ceil_div(rt_total, TG_XT_MIN);
+    double best = -1.;
+    for (int rb = rb_min; rb <= rb_max; ++rb) {
+        const int rt = (int)cs_ceil_div(rt_total, rb) < TG_XT_MIN ? TG_XT_MIN : (int)cs_ceil_div(rt_total, rb);
+        for (int ks = 1; ks <= max_split && ks <= 16; ks *= 2) {
+            const int wgs = per_xcd * (int)cs_ceil_div(rt_total, rt) * ks;   // on 32 compute units
+            const double part = (wgs % 32) / 32., rounds = wgs / 32 + (part > 0. ? 0.65 + 0.35 * part : 0.);
+            const double us = rounds * 4.5 * (6.7 + rt) * K / ks / 4096. + (may_split ? ks * 8e-6 * R * N / 4.9 : 0.);
+            if (best < 0. || us < best) {
+                best = us;
+                *r_blocks = rb;
+                *ksplit = ks;
+            }
+        }
+    }
+    return best + 4.;
+}
+
+// Which kernel a projection of R rows takes, and its launch shape (waves 0: the many-row kernel, 256 W rows
+// x up to 288 block rows per workgroup).  Measured at the 8B, Qwen2.5-7B and 1B widths: from 97 rows on the
+// many-row kernel wins where its 256-row W tiles alone fill most of the chip (lm_head), from 289 on
+// everywhere, between 129 and 288 rows where the two estimates say so (250 rows, 8B: gate/up 89 -> 68,
+// down 43 -> 38 us; 1B gate/up stays, 27 against 29 us), up to 128 rows nowhere else (128 rows, 8B
+// gate/up: 55 against 65 us).
+// The K splits are part of the result: each float32 sum is a chain of K / splits products, and fewer, longer chains round
+// worse.  Estimates fitted anew to both kernels choose fewer of them (8B q/k/v at 300 rows one instead of four, at 528
+// one instead of two; o at 88, 300 and 528 rows 4, 2, 1 instead of 8, 4, 4) and are up to 5 us a launch faster, but the
+// largest error against float64 grew with the chains (q/k/v at 300 rows 1.9e-7 -> 4.0e-7 of the largest output).
+static mfma_shape gemm_plan(int R, int N, int K, bool may_split) {
+    mfma_shape t = {1, 1, 0};
+    if (R <= 96) return mfma_plan(R, N, K, may_split);
+    const double tile_us = tile_plan(R, N, K, may_split, &t.r_blocks, &t.ksplit);
+    const bool tile_fits = ((int64_t)R + 15) * K < ((int64_t)1 << 31);      // (launch_tile refuses more)
+    if (tile_fits && (R > 288 || cs_ceil_div(N, TG_WROWS) >= 192)) return t;
+    const mfma_shape p = mfma_plan(R, N, K, may_split);
+    return R > 128 && tile_fits && tile_us < mfma_us(R, N, K, p) ? t : p;
+}
+
+// 16-row X tiles of a workgroup
+static int gemm_row_tiles(int R, const mfma_shape& p) {
+    const int rt = (int)cs_ceil_div(cs_ceil_div(R, 16), p.r_blocks);
+    return p.waves == 0 && rt < TG_XT_MIN ? TG_XT_MIN : rt;
+}
+
 bool cs_gemm_x_tiled(int R, int N, int K, bool may_split) { return gemm_plan(R, N, K, may_split).waves == 0; }
+void cs_gemm_shape(int R, int N, int K, bool may_split, int* shape) {
+    const mfma_shape p = gemm_plan(R, N, K, may_split);
+    shape[0] = p.waves;
+    shape[1] = gemm_row_tiles(R, p);
+    shape[2] = p.ksplit;
+}
 
 int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, int R, int N, int K,
                    int mode, int allow_split, int* nparts_out, hipStream_t s) {
@@ -1136,9 +1172,9 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     // Shape of the launch.
     // Weight-streaming kernel: a workgroup takes up to 128 block rows; more rows are split into
     // equal row blocks whose workgroups share each W tile through one XCD's L2 (see the mapping
-    // in the kernel and gemm_plan).
+    // in the kernel and mfma_plan).
     const bool may_split = allow_split && mode == CS_GEMM_STORE;
-    const gemm_shape plan = gemm_plan(R, N, K, may_split);
+    const mfma_shape plan = gemm_plan(R, N, K, may_split);
     const bool tile = plan.waves == 0;
     int am_tiles = 0;                         // pairs per row of the argmax epilogue
     if (mode == CS_GEMM_ARGMAX) {
@@ -1147,8 +1183,7 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
         Y = reinterpret_cast<float*>(m->am_val_idx);
     }
     if (mode == CS_GEMM_SWIGLU) Y = reinterpret_cast<float*>(m->range_flags);   // see the epilogue
-    const int rt_total = (int)cs_ceil_div(R, 16);
-    const int r_blocks = plan.r_blocks, waves = plan.waves;
+    const int waves = plan.waves;
     int ksplit = plan.ksplit;
     // the partial tiles must fit the workspace
     while (ksplit > 1 && (size_t)ksplit * R * N > m->part_floats) ksplit /= 2;
@@ -1157,7 +1192,7 @@ int cs_gemm_launch(const cs_model* m, const void* X, const void* W, float* Y, in
     const int nparts = (int)cs_ceil_div(K, Ks);
     if (mode == CS_GEMM_ARGMAX) am_tiles = (int)cs_ceil_div(N, tile ? TG_WROWS : 32 * waves);
     if (nparts_out) *nparts_out = mode == CS_GEMM_ARGMAX ? am_tiles : nparts;
-    const int rt = (int)cs_ceil_div(rt_total, r_blocks);
+    const int rt = gemm_row_tiles(R, plan);
     const f16_t* x = (const f16_t*)X;
     const f16_t* w = (const f16_t*)W;
     f16_t* act = (f16_t*)m->act;
@@ -1294,7 +1329,7 @@ int cs_gemm_norm_launch(const cs_model* m, const float* gain, int nss, const voi
     }
     CS_REQUIRE(mfma_shape_ok(N, K) && (mode == CS_GEMM_STORE || N % 32 == 0), CS_E_UNSUPPORTED,
                "bf16 GEMM needs N %% 16 == 0 and K %% 128 == 0 (N=%d K=%d)", N, K);
-    gemm_shape plan = gemm_plan(R, N, K, mode == CS_GEMM_STORE);
+    mfma_shape plan = mfma_plan(R, N, K, mode == CS_GEMM_STORE);
     while (plan.ksplit > 1 && (size_t)plan.ksplit * R * N > m->part_floats) plan.ksplit /= 2;
     const int Ks = (int)cs_round_up(cs_ceil_div(K, plan.ksplit), GEMM_KC);
     if (nparts_out) *nparts_out = (int)cs_ceil_div(K, Ks);

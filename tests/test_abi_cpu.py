@@ -79,3 +79,26 @@ def test_rows_too_long_for_the_many_row_gemm_go_to_the_other_kernel(lib, R, N, K
     tiled.restype = ctypes.c_bool
     assert (R + 15) * K >= 2**31
     assert not tiled(R, N, K, True) and not tiled(R, N, K, False)
+
+
+@pytest.mark.parametrize("N,K,splits", [
+    (6144, 4096, {88: 4, 264: 1, 300: 4, 528: 2, 1000: 2, 4095: 1}), (4096, 4096, {88: 8, 105: 4, 300: 4, 528: 4, 1000: 2, 2048: 2}),
+    (4096, 14336, {88: 8, 200: 8, 300: 8, 528: 8, 1000: 4}), (3072, 2048, {88: 4, 300: 4, 528: 2, 1000: 2}),
+    (2048, 2048, {88: 4, 300: 4, 528: 4, 2048: 2}), (2048, 8192, {88: 16, 105: 8, 300: 8, 528: 8, 1000: 4, 2048: 4}),
+    (4608, 3584, {105: 4, 300: 4, 528: 2, 1000: 2}), (3584, 3584, {88: 4, 300: 4, 528: 4, 1000: 2}), (3584, 18944, {88: 8, 200: 16, 528: 8})])
+def test_k_splits_of_the_projections(lib, N, K, splits):
+    """Every output of a projection is the sum of K / splits products in a chain, then of the splits: the rounding error
+    grows with the chain, so a launch shape with fewer splits is another result and a worse one (8B q/k/v at 300 rows
+    unsplit: twice the largest error against float64)."""
+    shape = (ctypes.c_int * 3)()
+    for R, want in splits.items():
+        lib._Z13cs_gemm_shapeiiibPi(R, N, K, True, shape)
+        assert shape[2] == want, (R, list(shape))
+
+
+@pytest.mark.parametrize("R", [289, 528, 2048])
+def test_rows_too_long_for_the_many_row_gemm_are_still_taken(lib, R):
+    """The other kernel takes them, and the lm_head's as well."""
+    K = 16_000_000
+    lib._Z15cs_gemm_x_tilediiib.restype = ctypes.c_bool
+    assert not lib._Z15cs_gemm_x_tilediiib(R, 1152, K, True) and not lib._Z15cs_gemm_x_tilediiib(R, 128256, K, False)
