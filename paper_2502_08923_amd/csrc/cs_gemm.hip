@@ -391,26 +391,34 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
         const unsigned lane16 = lane * 16;
         auto issue = [&](int c) {
             const unsigned dst = lds0 + (c & (GEMM_STAGES - 1)) * STAGE;
-            const int cc = min(c, nchunks - 1);              // (a surplus chunk meets zeros of W)
 #pragma unroll
             for (int i = 0; i < 2 * NT; ++i) {
                 const int s = 2 * (i & 1) + p;
-                cs_load_to_lds(lane16, xt[i >> 1] + (cc * 4 + s) * 512, dst + ((i >> 1) * 4 + s) * 1024);
+                cs_load_to_lds(lane16, xt[i >> 1] + (c * 4 + s) * 512, dst + ((i >> 1) * 4 + s) * 1024);
             }
         };
-        static_assert(GEMM_STAGES == 4 && 6 * NT <= 63, "three chunks in flight");
-        issue(0);
-        issue(1);
-        issue(2);
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * NT) : "memory");
-        int c = 0;
-        for (; c + 3 < steps; ++c) {                         // chunk c is multiplied, chunk c + 1 has to be there next
-            issue(c + 3);
+        static_assert(GEMM_STAGES == 4 && GEMM_STAGES == GEMM_RING_TILES / MT && 6 * NT <= 63, "three chunks in flight");
+        if (nchunks >= GEMM_STAGES) {
+            issue(0);
+            issue(1);
+            issue(2);
             asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * NT) : "memory");
+            for (int c = 0; c + 3 < nchunks; ++c) {          // chunk c is multiplied, chunk c + 1 has to be there next
+                issue(c + 3);
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(4 * NT) : "memory");
+            }
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NT) : "memory");
+            asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+            asm volatile("s_barrier" ::: "memory");
+        } else {
+            // Less than a ring: the consumers multiply the surplus chunks too, zeros of W by zeros of X (an infinity
+            // of X times the zeros of W would be a NaN).
+            for (int c = 0; c < nchunks; ++c) issue(c);
+            for (int i = nchunks * STAGE + p * 1024 + lane16; i < GEMM_STAGES * STAGE; i += 2048)
+                *reinterpret_cast<f16x8*>(xs + i) = (f16x8){0, 0, 0, 0, 0, 0, 0, 0};
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            for (int c = 0; c < GEMM_STAGES; ++c) asm volatile("s_barrier" ::: "memory");
         }
-        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NT) : "memory");
-        asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
-        asm volatile("s_barrier" ::: "memory");
         if (MODE == CS_GEMM_ARGMAX) {                      // the two barriers of the consumers' epilogue
             __syncthreads();
             __syncthreads();
@@ -490,7 +498,7 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
     }
     if constexpr (XN) sq_reduce();
     __syncthreads();
-    // Branch-free rings of DEPTH chunks, at least one (surplus chunks are zeros): with a way round the loop the
+    // Branch-free rings of DEPTH chunks, at least one (surplus chunks are zeros on both sides; XN: of W, its X is saturated): with a way round the loop the
     // compiler copied the ring from one set of registers into another, which waits for every load in it.
     int c = 0;
     do {

@@ -141,6 +141,21 @@ def test_gemm_chunk_counts_of_the_ring(host_model, R, chunks):
     _gemm_case(host_model, 1040, 128 * chunks, R)
 
 
+@pytest.mark.parametrize("K", [128, 256, 384, 512, 640])
+@pytest.mark.parametrize("R", [1, 33, 88, 128])
+def test_gemm_input_beyond_float16(host_model, R, K):
+    """An X beyond float16 is an infinity to the multiplies: its row of Y is infinite with the sign of each weight (the
+    others stay finite), also where K is shorter than the ring of four chunks."""
+    N, at, row = 1040, K - 3, R // 2
+    rng = np.random.default_rng(R + K)
+    x = rng.standard_normal((R, K)).astype(np.float32)
+    x[row, at] = 1e5
+    w = (rng.integers(1, 8, (N, K)) * 0.125 * rng.choice([-1.0, 1.0], (N, K))).astype(np.float32)
+    Y = cs.cs_op_gemm(host_model, bf16_dev(synth.f32_to_bf16_bits(x)), bf16_dev(synth.f32_to_bf16_bits(w))).cpu().numpy()
+    assert np.array_equal(Y[row], np.copysign(np.inf, w[:, at]))
+    assert np.isfinite(np.delete(Y, row, axis=0)).all()
+
+
 def test_gemm_tiny_weights_are_not_flushed(host_model):
     """The tuned projections multiply in float16 (weights converted from bfloat16, exactly for
     |w| >= 2^-17).  Weights in float16's subnormal range must still contribute."""
