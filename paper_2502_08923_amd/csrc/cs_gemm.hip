@@ -252,15 +252,6 @@ static int launch_plain(int dtype, const float* X, const void* W, float* Y, int 
 // X and the SwiGLU output are in fragment order (cs_xt_index); am_tiles: pairs per row of the argmax epilogue.
 // XN: X is not given; the producers normalise the float32 residual stream themselves (few rows, see cs_norm_in).
 
-// acc += a * b.  PINNED: the sum stays where it is (left to itself the compiler writes it elsewhere and spills at the
-// register limit).  The compiler does not see the statement as a matrix instruction: multiplies into the same
-// accumulator have to lie at least two apart, and before anything else reads one the last has to end (10 wait states).
-template <bool PINNED>
-__device__ __forceinline__ void gemm_mfma(f32x4& acc, f16x8 a, f16x8 b) {
-    if constexpr (PINNED) asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
-    else acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, acc, 0, 0, 0);
-}
-
 #define GEMM_STORE_STREAM 3   // CS_GEMM_STORE whose partial tiles leave through streaming stores
 template <int MT, int NT, int MODE, int CW, bool XN = false>
 __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __restrict__ X,
@@ -479,7 +470,7 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
         for (int f = 0; f < NF; ++f) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
-                gemm_mfma<(NT >= 3)>(acc[mt][f % NT], src[mt][f / NT], b[f % AHEAD]);
+                acc[mt][f % NT] = __builtin_amdgcn_mfma_f32_16x16x32_f16(src[mt][f / NT], b[f % AHEAD], acc[mt][f % NT], 0, 0, 0);
             if (f + AHEAD < NF) b[f % AHEAD] = frag(f + AHEAD);
             if (NT >= 3 && f % NT == NT - 1)
 #pragma unroll
@@ -517,7 +508,6 @@ __global__ __launch_bounds__(64 * (CW + 2)) void k_gemm_mfma(const f16_t* __rest
         }
     }
 
-    if constexpr (NT >= 3) asm volatile("s_nop 15" ::: "memory");     // (see gemm_mfma)
     // epilogue.  acc[mt][nt][j] = Y[row r_base + nt*16 + lrow][col n_wave + mt*16 + 4g + j]
     if (MODE == CS_GEMM_STORE || MODE == GEMM_STORE_STREAM) {
         float* __restrict__ y = Y + (int64_t)blockIdx.y * R * N;

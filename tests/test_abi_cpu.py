@@ -102,3 +102,12 @@ def test_rows_too_long_for_the_many_row_gemm_are_still_taken(lib, R):
     K = 16_000_000
     lib._Z15cs_gemm_x_tilediiib.restype = ctypes.c_bool
     assert not lib._Z15cs_gemm_x_tilediiib(R, 1152, K, True) and not lib._Z15cs_gemm_x_tilediiib(R, 128256, K, False)
+
+
+def test_matrix_instructions_are_the_compilers():
+    """A multiply written as inline assembly is no matrix instruction to the compiler: it then places neither the wait
+    states that an operand's last writer needs before it nor those that a reader of its sums needs behind it."""
+    csrc = os.path.join(ROOT, "paper_2502_08923_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        for line in open(os.path.join(csrc, f)):
+            assert not ("asm" in line and "v_mfma" in line), (f, line)
