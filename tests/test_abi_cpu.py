@@ -1,6 +1,7 @@
 """CPU-only checks of the boundary: the shared library loads and exports every entry point
 that include/copyspec.h declares, and the binding's struct layouts match the header."""
 import ctypes
+import itertools
 import os
 import re
 
@@ -111,3 +112,35 @@ def test_matrix_instructions_are_the_compilers():
     for f in sorted(os.listdir(csrc)):
         for line in open(os.path.join(csrc, f)):
             assert not ("asm" in line and "v_mfma" in line), (f, line)
+
+
+def test_projection_tests_reach_every_kernel(lib):
+    """The launch shapes of the projection tests' matrices, which a change of the launch rules may move: every row-tile count
+    of the many-row kernel (6 to 18) and of the weight-streaming one (1 to 8), the latter over less than a ring of
+    four K chunks, whole rings and every remainder; its tiles of five consumer waves with 6 to 8."""
+    import test_gpu_ops as ops
+    reached = {}
+    shape = (ctypes.c_int * 3)()
+    for test in (ops.test_gemm_bf16_full_shapes, ops.test_gemm_row_sweep, ops.test_gemm_prompt_rows, ops.test_gemm_row_tile_counts_between,
+                 ops.test_gemm_wide_blocks_and_five_wave_tiles, ops.test_gemm_five_wave_tiles_over_long_rows,
+                 ops.test_gemm_chunk_counts_of_the_ring, ops.test_gemm_chunk_counts_in_one_row_block):
+        wide = {ops.test_gemm_chunk_counts_of_the_ring: 1040, ops.test_gemm_chunk_counts_in_one_row_block: 28688}.get(test)
+        marks = [(m.args[0].split(","), m.args[1]) for m in test.pytestmark if m.name == "parametrize"]
+        for values in itertools.product(*(m[1] for m in marks)):
+            case = {} if test is not ops.test_gemm_row_tile_counts_between else {"N": 49168, "K": 512}
+            for (names, _), v in zip(marks, values):
+                case.update(zip(names, v if len(names) > 1 else [v]))
+            if wide:
+                case.update(N=wide, K=128 * case["chunks"])
+            R, N, K = case["R"], case["N"], case["K"]
+            lib._Z13cs_gemm_shapeiiibPi(R, N, K, True, shape)
+            per_split = -(-K // shape[2] // 128)
+            while K > 0:
+                reached.setdefault((shape[0], shape[1]), set()).add(min(per_split, K // 128))
+                K -= 128 * per_split
+    assert {t for w, t in reached if w == 0} == set(range(6, 19))
+    for waves, tiles in [(4, t) for t in range(1, 9)] + [(5, 6), (5, 7), (5, 8)]:
+        chunks = reached[waves, tiles]
+        assert any(c < 4 for c in chunks) and any(c > 4 for c in chunks), (waves, tiles, chunks)
+        if waves == 4:
+            assert {1, 2, 3} <= chunks and {c % 4 for c in chunks if c >= 4} == {0, 1, 2, 3}, (tiles, chunks)

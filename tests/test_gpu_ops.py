@@ -137,8 +137,16 @@ def test_gemm_five_wave_tiles_over_long_rows(host_model, R, N, K):
 @pytest.mark.parametrize("R", [1, 16, 33, 81, 96, 112, 128])
 def test_gemm_chunk_counts_of_the_ring(host_model, R, chunks):
     """The weight-streaming kernel over 128 * chunks of K: less than its ring of four chunks, whole rings and every
-    remainder, for row tiles below and above the count from which the multiply order is pinned."""
+    remainder, for row tiles below and above the count from which the multiply order is pinned (1, 1, 3, 6, 6 and, in two
+    row blocks, 4 and 4)."""
     _gemm_case(host_model, 1040, 128 * chunks, R)
+
+
+@pytest.mark.parametrize("chunks", [1, 2, 3, 4, 5, 6, 7])
+@pytest.mark.parametrize("R", [32, 80, 105, 128])
+def test_gemm_chunk_counts_in_one_row_block(host_model, R, chunks):
+    """The same with 2, 5, 7 and 8 row tiles: 225 tiles of 128 W rows fill the chip in one row block."""
+    _gemm_case(host_model, 28688, 128 * chunks, R)
 
 
 @pytest.mark.parametrize("K", [128, 256, 384, 512, 640])
