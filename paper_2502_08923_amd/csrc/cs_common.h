@@ -262,7 +262,6 @@ int cs_fill_i32_launch(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 // A buffer of `bytes` bytes at a uniform address.  A load at an offset outside it returns zeros and costs no memory
 // traffic, and unlike a branch around the load it leaves the compiler's load counts exact.
 #define CS_BUFFER_WORD3 0x00027000      // buffer resource word 3: raw 32-bit data, range checked in bytes
-#define CS_BUFFER_OUT 0xfffffff0u       // an offset outside every buffer of less than 4 GiB
 __device__ __forceinline__ auto cs_rsrc(const void* p, unsigned bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, CS_BUFFER_WORD3);
 }

@@ -929,11 +929,13 @@ static int launch_tile(const f16_t* X, const f16_t* W, float* Y, f16_t* act, int
 struct mfma_shape { int r_blocks, ksplit, waves; };
 
 // Estimated time of a launch, us.  A workgroup fills a compute unit and takes 30 us per 4096 of K while it
-// is bound by its weights, 6.1 us per X tile from five tiles on (8B width, 224 workgroups: 4, 6, 7, 8 X tiles
-// 30, 37, 43 to 48, 49 to 55 us); five consumer waves share four SIMDs, 1.35 of the time for 1.25 of the
-// rows; a partial tile is written and read once more at about 4.9 TB/s (an unsplit output is charged nothing here
+// is bound by its weights, 6.1 us per X tile from five tiles on; five consumer waves share four SIMDs, 1.35 of the time for
+// 1.25 of the rows; a partial tile is written and read once more at about 4.9 TB/s (an unsplit output is charged nothing here
 // and once in tile_plan: with both charged alike, and the rate fitted anew, 21 of 284 whole calls of 97 to 1024
 // rows and prompts up to 4096 got faster and 53 slower, 1 to 6 % each).
+// The constants of both estimates are of the kernels as they were when X came row-major and the many-row kernel's waves
+// worked in phase (224 workgroups at the 8B width, 4, 6, 7, 8 X tiles: 30, 37, 43 to 48, 49 to 55 us; cold weights and the
+// present kernel 39, 43, 45, 47).  They stay because they decide the K splits, and those the results (see gemm_plan).
 static double mfma_us(int R, int N, int K, const mfma_shape& p) {
     const int nt = (int)cs_ceil_div(cs_ceil_div(R, 16), p.r_blocks);
     const int64_t wgs = cs_ceil_div(N, 32 * p.waves) * p.r_blocks * p.ksplit;
@@ -941,16 +943,15 @@ static double mfma_us(int R, int N, int K, const mfma_shape& p) {
     return cs_ceil_div(wgs, 256) * per * K / p.ksplit / 4096. + (p.ksplit > 1 ? p.ksplit * 8e-6 * R * N / 4.9 : 0.);
 }
 
-// Up to 96 rows: one row block, and K splits until about 3/4 of the compute units have a workgroup (measured
-// at the 8B shapes, more splits cost more in partial-tile traffic and fixed per-workgroup latency than they
-// gain: q/k/v 4, o 8, down 8).  More rows: row blocks of up to 128 rows and K splits by estimated time (100
-// rows: gate/up 60 -> 48 us in one block instead of two; 256 rows: q/k/v, gate/up, down 40, 109, 58 ->
-// 28, 97, 46 us in two instead of three; the 1B shape keeps two blocks of 64, which fill the chip, 18 us
+// Up to 96 rows: one row block, and K splits until about 3/4 of the compute units have a workgroup (8B shapes, 88 rows: q/k/v
+// with 2, 4, 8 splits 19.0, 14.4, 19.1 us, o with 4 and 8 12.8 and 12.0, down with 4, 8, 16 31.0, 24.7, 29.7).  More rows: row
+// blocks of up to 128 rows and K splits by estimated time (100 rows: gate/up 60 us in two blocks, 44 in one; 256 rows: q/k/v,
+// gate/up, down 33, 94, 54 us in three blocks, 22, 79, 37 in two; the 1B shape keeps two blocks of 64, which fill the chip, 18 us
 // against 23).  Five consumer waves where tiles of 128 W rows need a second, nearly empty round of the chip
-// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 80 -> 56 us), not for the few
-// chunks of a K split (1B q/k/v at 200 rows: 19 us against 12).  Two consumer waves where a projection that may not
-// split K has tiles of 128 W rows for half of the chip at most (1B gate/up, 16384 rows: 16, 48, 88 rows 16.2, 18.8,
-// 23.5 -> 13.5, 15.9, 19.9 us); with twice as many tiles as compute units they lose (8B gate/up, 88 rows: 46 -> 53).
+// (Qwen2.5-7B gate/up, 37888 rows: 296 tiles, 237 of 160 rows; 105 rows 72 -> 50 us), not for the few
+// chunks of a K split (1B q/k/v at 200 rows: unsplit with five 22 us against 8).  Two consumer waves where a projection that may
+// not split K has tiles of 128 W rows for half of the chip at most (1B gate/up, 16384 rows: 16, 48, 88 rows 13.9, 16.0,
+// 19.5 -> 11.9, 13.5, 16.9 us); with twice as many tiles as compute units they lose (8B gate/up, 88 rows: 42 -> 54).
 static mfma_shape mfma_plan(int R, int N, int K, bool may_split) {
     const int rt_total = (int)cs_ceil_div(R, 16);
     const int max_split = may_split && K / (4 * GEMM_KC) > 0 ? K / (4 * GEMM_KC) : 1;
@@ -1096,13 +1097,12 @@ int cs_tile_x_launch(const void* src, void* dst, int R, int K, hipStream_t s) {
 }
 
 // Row blocks and K splits of a many-row GEMM: the pair with the least estimated time.  A workgroup
-// with rt X tiles takes 4.5 us * (6.7 + rt) per 4096 of K on a full chip (fitted to q/k/v, o, gate/up
-// and down at 300, 528, 1023 and 4095 rows: the requests and the barrier of a chunk cost what 6.7
-// tiles cost to multiply, so a tile shorter by a ninth pays only where it does not add a round of the
-// chip); a round that fills a part f of the chip takes 0.65 + 0.35 f of a full one (less contention);
+// with rt X tiles takes 4.5 us * (6.7 + rt) per 4096 of K on a full chip (the requests and the barriers of a chunk cost
+// what 6.7 tiles cost to multiply, so a tile shorter by a ninth pays only where it does not add a round of the chip; see
+// mfma_us on the constants); a round that fills a part f of the chip takes 0.65 + 0.35 f of a full one (less contention);
 // every partial tile is written and read once more at about 4.9 TB/s.
-// 4095 rows, 8B width, against the fewest row blocks (15 x 288 rows): gate/up 771 -> 695 us,
-// q/k/v 209 -> 169, o 113 -> 104, down 368 -> 339 us; 528 rows: o 31 -> 27 us with half the partial tiles.
+// 4095 rows, 8B width, against the fewest row blocks (15 x 288 rows): gate/up 756 -> 686 us,
+// q/k/v 200 -> 166, o 111 -> 106, down 355 -> 340 us; 528 rows: o 32 -> 27 us with half the partial tiles.
 // (returns the time; a launch of its own costs about 4 us on top)
 static double tile_plan(int R, int N, int K, bool may_split, int* r_blocks, int* ksplit) {
     const int rt_total = (int)cs_ceil_div(R, 16);
@@ -1127,15 +1127,15 @@ static double tile_plan(int R, int N, int K, bool may_split, int* r_blocks, int*
 }
 
 // Which kernel a projection of R rows takes, and its launch shape (waves 0: the many-row kernel, 256 W rows
-// x up to 288 block rows per workgroup).  Measured at the 8B, Qwen2.5-7B and 1B widths: from 97 rows on the
-// many-row kernel wins where its 256-row W tiles alone fill most of the chip (lm_head), from 289 on
-// everywhere, between 129 and 288 rows where the two estimates say so (250 rows, 8B: gate/up 89 -> 68,
-// down 43 -> 38 us; 1B gate/up stays, 27 against 29 us), up to 128 rows nowhere else (128 rows, 8B
-// gate/up: 55 against 65 us).
+// x up to 288 block rows per workgroup): from 97 rows on the many-row kernel where its 256-row W tiles alone fill most of
+// the chip (lm_head; 128 rows of the 8B one 196 -> 178 us), from 289 on everywhere, between 129 and 288 rows where the two estimates say so (250 rows: 8B gate/up
+// 79 -> 63 us; 1B gate/up stays, 24 us in two row blocks against 28 in three), up to 128 rows nowhere else (128 rows, 8B
+// gate/up: 47 against 63 us).
 // The K splits are part of the result: each float32 sum is a chain of K / splits products, and fewer, longer chains round
-// worse.  Estimates fitted anew to both kernels choose fewer of them (8B q/k/v at 300 rows one instead of four, at 528
-// one instead of two; o at 88, 300 and 528 rows 4, 2, 1 instead of 8, 4, 4) and are up to 5 us a launch faster, but the
-// largest error against float64 grew with the chains (q/k/v at 300 rows 1.9e-7 -> 4.0e-7 of the largest output).
+// worse.  Estimates fitted to both kernels as they are now, whatever the splits, took half as many or fewer at 8B o
+// (88 rows 12.0 -> 10.8 us, 300 rows 20.3 -> 17.7, 528 rows 27.4 -> 27.5) and q/k/v (300 rows 25.1 -> 26.3) and at the
+// 1B shape (eight batched prompts 4 % faster), and doubled the error of some of them against float64 (o at 528 rows
+// 1.9e-7 -> 4.0e-7).  Not kept.
 static mfma_shape gemm_plan(int R, int N, int K, bool may_split) {
     mfma_shape t = {1, 1, 0};
     if (R <= 96) return mfma_plan(R, N, K, may_split);
